@@ -110,6 +110,66 @@ ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, co
   return pl;
 }
 
+// The fp32 contraction's launch: tile side, groups of four waves per tile, and for the sum over all tokens the number of
+// token chunks, by the smallest modelled time
+//   max( lone * steps_max + fixed,                                   the longest workgroup's walk, alone on its unit
+//        (max(work, adds) + epilogues) / 256 units ) + (split) beta pass
+// with `steps` the groups * 16 token steps of a workgroup, work = sum of steps * busy, adds = chunks * outputs * 3 ps (fp32
+// atomics drain while others multiply).  Per shape, measured: `lone` the time of a step where a workgroup has its compute
+// unit to itself, `busy` a step's share of a full unit, `epilogue` what a workgroup costs besides its steps:
+//   128, 1 group   1536x1536, 16 sequences of 256 .. 1024: 276 us (64, 1 group: 340; 64, 4 groups: 602)
+//   64, 1 group    768x768, 8 sequences of 30 .. 200: 18.5 us (128: 22.6; 64, 2 groups: 22.7)
+//   64, 2 groups   1024x256, 8 sequences of 400 .. 1500: 45 us (64, 1 group: 48; 128: 80)
+//   64, 4 groups   256x1280, 2 sequences, 3159 tokens: 41 us (64, 1 group: 66; 128: 123)
+SplitContractionPlan plan_split_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
+                                            bool per_sequence) {
+  struct Shape { int tile, groups; double lone, busy, epilogue, fixed; };
+  static const Shape shapes[] = {{128, 1, 1.1e-6, 0.785e-6, 3.9e-6, 5.0e-6},
+                                 {64, 1, 0.58e-6, 0.24e-6, 1.25e-6, 4.5e-6},
+                                 {64, 2, 0.87e-6, 0.56e-6, 1.5e-6, 5.5e-6},
+                                 {64, 4, 1.6e-6, 1.7e-6, 2.5e-6, 7.0e-6}};
+  constexpr double kBeta = 6.0e-6, kAdd = 3.0e-12, kUnits = 256.0;
+  constexpr int kBlock = 16;
+  SplitContractionPlan pl{128, 1, 1, n_tokens > 0 ? n_tokens : 1};
+  // 16-token blocks in all and of the longest sequence (every sequence ends in a block of its own)
+  long long blocks = 0, longest = 0;
+  for (int i = 0; i < n_seq; ++i) {
+    const long long len = off_host ? off_host[i + 1] - off_host[i] : n_tokens / n_seq;
+    blocks += (len + kBlock - 1) / kBlock;
+    if (len > longest) longest = len;
+  }
+  const double outputs = (double)rows * d_in;
+  double best = 0.0;
+  bool first = true;
+  for (const Shape& sh : shapes) {
+    const double tiles = (double)((rows + sh.tile - 1) / sh.tile) * ((d_in + sh.tile - 1) / sh.tile);
+    const int step = sh.groups * kBlock;
+    for (int w = 1; w <= (per_sequence ? 1 : 64); ++w) {
+      if (w > 1 && n_tokens / w < step) break;
+      const double items = per_sequence ? n_seq : w;
+      const double steps = (double)blocks / sh.groups / items;
+      const double steps_max = per_sequence ? (double)((longest + step - 1) / step) : steps;
+      double work = tiles * items * steps * sh.busy;
+      const double adds = w > 1 ? w * outputs * kAdd * kUnits : 0.0;
+      if (adds > work) work = adds;
+      const double full = (work + tiles * items * sh.epilogue) / kUnits, alone = steps_max * sh.lone + sh.fixed;
+      const double t = (full > alone ? full : alone) + (w > 1 ? kBeta : 0.0);
+      if (first || t < best) {
+        best = t;
+        first = false;
+        pl.tile = sh.tile;
+        pl.groups = sh.groups;
+        pl.n_chunks = w;
+      }
+    }
+  }
+  if (pl.n_chunks > 1) {
+    pl.chunk_tokens = ((n_tokens + pl.n_chunks - 1) / pl.n_chunks + kBlock - 1) / kBlock * kBlock;
+    pl.n_chunks = (n_tokens + pl.chunk_tokens - 1) / pl.chunk_tokens;
+  }
+  return pl;
+}
+
 int stash_tile_order_ok(int d_out, int d_in, int n_tokens, int n_seq, const int32_t* off_host) {
   // multiples of the larger tile, so that a band of output rows may pick either tile size
   if (d_out % 256 || d_in % 256) return 0;

@@ -57,6 +57,16 @@ struct ContractionPlan {
 ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
                                  bool per_sequence);
 hipError_t launch_seq_grad(const SeqGradArgs& a, hipStream_t s);
+// Launch plan of the fp32 contraction (host arithmetic only).
+struct SplitContractionPlan {
+  int tile;                    // 128 or 64
+  int groups;                  // groups of four waves per tile, which take its token blocks in turn: 1 (128), 1, 2 or 4 (64)
+  int n_chunks, chunk_tokens;  // sum-over-all-tokens mode: token chunks (1: no split)
+};
+SplitContractionPlan plan_split_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
+                                            bool per_sequence);
+// o[i] = beta * o[i] (0 for beta = 0, whatever o held), ahead of an atomic accumulation.
+hipError_t launch_apply_beta(float* o, long long n, float beta, hipStream_t s);
 // bf16 only, c == nullptr only: the direct-to-LDS streaming kernel (launch_seq_grad routes to it).
 hipError_t launch_seq_grad_stream(const SeqGradArgs& a, hipStream_t s);
 // Schedule probe: the plain sum over all tokens (c == nullptr, not per sequence) on the 256x256 tile with four or

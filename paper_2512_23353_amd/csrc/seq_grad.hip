@@ -6,222 +6,413 @@
 // scale_i * seq_logprob_grad`) when t runs over all tokens.  (bf16 inputs, the
 // benchmark's case, take the streaming kernel in seq_grad_stream.hip.)
 //
-// Both operands are token-major: the reduction index is the slow index of X and
-// of Delta.  Tiles are staged in LDS as [token][feature], exactly as they lie in
-// HBM (coalesced 16-byte loads along the feature axis).  The fp32 MFMA takes one
-// value per lane, so a plain 32-bit LDS read already has the register layout.
+// What bounds it: the matrix cores.  The fp32 MFMA is a sixteenth of the bf16 MFMA's rate, so every fp32 value
+// enters as the sum of three bf16 values, x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m
+// (8 + 8 + 8 significant bits: exact for every fp32 value of normal size), and a product is formed from the
+// six partial products hh, hm, mh, mm, hl, lh.  The three left out are below 2^-25 of the product, under half an ulp
+// of the fp32 product itself; and six accumulations per sixteen tokens round the fp32 accumulator less often than
+// one per two tokens did.  Against
+// 64-bit sums over 34 layers of 32 .. 2048 by 32 .. 4096 the error of dW is 0.52 of the plain fp32 MFMA form's and that
+// of K 0.79 (geometric means).  1536x1536, 16 sequences, 10^4 tokens: 276 us per-sequence (182 TFLOP/s of fp32 products,
+// 1.1 PFLOP/s of bf16 at the clock the power limit leaves) against 609 us (78 TFLOP/s) for 64x64 fp32 MFMA tiles.
 //
-// Work item = (sequence range, 2-D tile of the [d_out, d_in] output).  The
-// K-loop walks the tokens of the range sequence by sequence, BK rows at a time;
-// the last block of a sequence is zero-filled, so ragged lengths need no
-// host-side padding.
+// A tile whose result is not finite (an infinity or NaN among the inputs, a value that bf16 rounds to infinity) or
+// so small that the low parts may have been subnormal is formed again with fp32 MFMAs straight from global memory.
+//
+// Both operands are token-major: the reduction index is the slow index of X and of Delta.  A thread loads two
+// features of eight consecutive tokens, splits them in registers and stores 16 bytes (one feature, eight tokens)
+// per part to LDS, which is the bf16 MFMA's operand layout: the multiplying waves read their fragments with plain
+// 16-byte reads.  Two LDS stages of sixteen tokens (24 KiB each), one barrier per stage.
+//
+// Work item = (sequence, 128x128 tile of the [d_out, d_in] output) or (token chunk, tile); four waves, 64x64 each.
+// The walk over the tokens goes sequence by sequence, sixteen rows at a time; the last block of a sequence is
+// zero-filled, so ragged lengths need no host-side padding.
 #include "common.h"
 #include "kernels.h"
 
 namespace isopo {
 namespace {
 
+constexpr int kBK = 16;                              // tokens per stage
+constexpr int kParts = 3;                            // bf16 parts of an fp32 value
+constexpr int kUnit = 16;                            // bytes: eight tokens of one feature and part
+// one part of a stage, [operand][token half][feature], and the two stages of a group of four waves
+constexpr int plane_bytes(int bt) { return 2 * 2 * bt * kUnit; }
+constexpr int group_lds(int bt) { return 2 * kParts * plane_bytes(bt); }
+// fp32 sums below this may have lost subnormal low parts (a part is at most 2^-16 of its value): formed again in fp32
+constexpr unsigned kTinyBits = 0x12800000u;          // 2^-90
+
 struct SeqGradParams {
-  const void* X;
-  const void* Delta;
+  const float* X;
+  const float* Delta;
   const int32_t* off;
   const float* c;
-  void* out;
-  int d_in, d_out, n_seq;
+  float* out;
+  int d_in, d_out, n_seq, n_tokens;
   int row0, row_end;
   int out_row0;
   long long out_seq_stride;
   float beta;
-  int tiles_m, tiles_n;
-  unsigned n_blocks;
+  int tiles_n, tiles;
+  int chunk_tokens;                                  // sum over all tokens: tokens per chunk
+  int atomic;                                        // ... whose partial tiles are added to `out`
+  int longest_first;                                 // per sequence: item i is the i-th longest sequence (n_seq <= 64)
 };
 
-template <int BM, int BN, int BK, int PAD, bool WEIGHTED>
-__global__ __launch_bounds__(256) void seq_grad_kernel(SeqGradParams p) {
-  typedef float T;
-  constexpr int kVec = 4;                        // elements per 16-byte vector
-  constexpr int WM = BM / 2, WN = BN / 2;        // 2x2 waves
-  constexpr int FM = WM / 32, FN = WN / 32;      // 32x32 MFMA blocks per wave
-  constexpr int PA = BM + PAD, PB = BN + PAD;    // LDS row pitch in elements
-  constexpr int VA = BM / kVec, VB = BN / kVec;  // 16-byte vectors per tile row
-  constexpr int RA = 256 / VA, RB = 256 / VB;    // tile rows covered per pass of the workgroup
-  constexpr int NA = BK / RA, NB = BK / RB;      // passes
-  static_assert(256 % VA == 0 && 256 % VB == 0 && BK % RA == 0 && BK % RB == 0, "tile shape");
+// The features' 16-byte units of a stage swap places in pairs in half of all groups of eight, so that the writes of two
+// neighbouring features per lane (32 bytes apart from lane to lane) cover all banks, and the reads of 32
+// consecutive features still do.
+__device__ __forceinline__ int unit_pos(int f) { return f ^ (((f >> 3) ^ (f >> 4)) & 1); }
 
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  T* As = reinterpret_cast<T*>(smem);            // [2][BK][PA]
-  T* Bs = As + 2 * BK * PA;                      // [2][BK][PB]
+// Two fp32 values -> their three bf16 parts, packed low half first.
+__device__ __forceinline__ unsigned pack_bf16(float x0, float x1) {
+  unsigned r;                                        // the compiler converts each half by itself and packs them after
+  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(x0), "v"(x1));
+  return r;
+}
+__device__ __forceinline__ void split2(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
+  h = pack_bf16(x0, x1);
+  x0 -= __builtin_bit_cast(float, h << 16);
+  x1 -= __builtin_bit_cast(float, h & 0xffff0000u);
+  m = pack_bf16(x0, x1);
+  x0 -= __builtin_bit_cast(float, m << 16);
+  x1 -= __builtin_bit_cast(float, m & 0xffff0000u);
+  l = pack_bf16(x0, x1);
+}
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-
-  const unsigned work = xcd_contiguous(blockIdx.x, p.n_blocks);
-  const int tiles = p.tiles_m * p.tiles_n;
-  const int item = work / tiles, tile = work % tiles;
-  const int tile_m = tile / p.tiles_n, tile_n = tile % p.tiles_n;
-  const int seq_begin = WEIGHTED ? 0 : item;
-  const int seq_end = WEIGHTED ? p.n_seq : item + 1;
-  const int m0 = p.row0 + tile_m * BM;           // first output row (index into d_out)
-  const int n0 = tile_n * BN;                    // first output column (index into d_in)
-
-  const T* __restrict__ Xg = static_cast<const T*>(p.X);
-  const T* __restrict__ Dg = static_cast<const T*>(p.Delta);
-
-  const int a_cv = tid % VA, a_r = tid / VA;
-  const int b_cv = tid % VB, b_r = tid / VB;
-  const bool a_ok = (m0 + a_cv * kVec) < p.row_end;
-  const bool b_ok = (n0 + b_cv * kVec) < p.d_in;
-  const T* a_src = Dg + m0 + a_cv * kVec;
-  const T* b_src = Xg + n0 + b_cv * kVec;
-
-  uint4 ra[NA], rb[NB];
-  auto gload = [&](int t, int t_end) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int tt = t + a_r + i * RA;
-      ra[i] = (a_ok && tt < t_end) ? *reinterpret_cast<const uint4*>(a_src + (size_t)tt * p.d_out)
-                                   : make_uint4(0, 0, 0, 0);
+// The token ranges a work item walks: one sequence, or the parts of the sequences inside a chunk of tokens with
+// their coefficients (one range for the whole chunk where nothing is weighted).
+template <bool WEIGHTED>
+struct TokenWalk {
+  const SeqGradParams& p;
+  int seq, t, t_end, chunk_end;
+  float scale = 1.f;
+  __device__ __forceinline__ TokenWalk(const SeqGradParams& prm, int item) : p(prm) {
+    if constexpr (!WEIGHTED) {
+      t = p.off[item];
+      t_end = p.off[item + 1];
+    } else {
+      t = item * p.chunk_tokens;
+      chunk_end = p.n_tokens - t < p.chunk_tokens ? p.n_tokens : t + p.chunk_tokens;
+      if (!p.c) {
+        t_end = chunk_end;
+      } else {
+        int lo = 0, hi = p.n_seq;                    // largest seq with off[seq] <= t
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (p.off[mid] <= t) lo = mid; else hi = mid;
+        }
+        seq = lo;
+        enter();
+      }
     }
+  }
+  __device__ __forceinline__ void enter() {
+    const int e = p.off[seq + 1];
+    t_end = e < chunk_end ? e : chunk_end;
+    scale = p.c[seq];
+  }
+  // The next block of at most `step` tokens: [b0, b1) with its coefficient.  Uniform over the workgroup.
+  __device__ __forceinline__ bool next(int step, int& b0, int& b1, float& s) {
+    if constexpr (WEIGHTED) {
+      if (p.c)
+        while (t >= t_end && t < chunk_end) { ++seq; enter(); }
+    }
+    if (t >= t_end) return false;
+    b0 = t;
+    b1 = t_end - t < step ? t_end : t + step;
+    s = scale;
+    t = b1;
+    return true;
+  }
+};
+
+// The sequence with `rank` longer ones (ties by index), n_seq <= 64: every wave finds it by itself, lane = sequence.
+__device__ __forceinline__ int sequence_by_length(const int32_t* off, int n_seq, int rank, int lane) {
+  const int len = lane < n_seq ? off[lane + 1] - off[lane] : -1;
+  int longer = 0;
+  for (int j = 0; j < n_seq; ++j) {
+    const int lj = __builtin_amdgcn_readlane(len, j);
+    longer += lj > len || (lj == len && j < lane) ? 1 : 0;
+  }
+  return __ffsll((long long)__ballot(lane < n_seq && longer == rank)) - 1;
+}
+
+// WT: side of a wave's square of outputs (64 or 32); a tile is 2 WT on a side.  KG groups of four waves share a
+// tile: group g takes every KG-th block of tokens, the groups' sums meet in LDS.
+template <int WT, int KG, bool WEIGHTED>
+__global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void seq_grad_kernel(SeqGradParams p) {
+  constexpr int BT = 2 * WT, NB = WT / 32;           // NB x NB MFMA blocks of 32x32 per wave
+  constexpr int FPL = BT / 64;                       // features a lane stages
+  constexpr int PLANE = plane_bytes(BT), STAGE = kParts * PLANE;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int lane = threadIdx.x & 63, wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = wave_id >> 2, wave = wave_id & 3;
+  const int wm = wave >> 1, wn = wave & 1;
+  unsigned char* lds = smem + group * group_lds(BT);
+
+  // XCD x walks the x-th eighth of every item's tiles
+  int item = blockIdx.x / p.tiles;
+  const int tile = (int)xcd_contiguous(blockIdx.x % p.tiles, p.tiles);
+  if (!WEIGHTED && p.longest_first) item = sequence_by_length(p.off, p.n_seq, item, lane);
+  const int m0 = p.row0 + (tile / p.tiles_n) * BT;   // first output row (index into d_out)
+  const int n0 = (tile % p.tiles_n) * BT;            // first output column (index into d_in)
+
+  // staging: waves 0, 1 take Delta, waves 2, 3 X; even waves tokens 0..7 of a block, odd waves 8..15; lane l the
+  // features FPL l ..
+  const bool is_x = wave >= 2;
+  const int half = wave & 1;
+  const int pitch = is_x ? p.d_in : p.d_out;
+  const int f0 = is_x ? n0 : m0, f_end = is_x ? p.d_in : p.row_end;
+  const float* src = (is_x ? p.X : p.Delta) + f0;
+  const int f_bytes = (f_end - f0 < BT ? f_end - f0 : BT) * 4;
+  float r[2][8][FPL];                                // two stages in flight
+  // one buffer descriptor per token row, empty for a row past the block's end: what lies outside arrives as zeros,
+  // without a branch between the loads and the MFMAs they are meant to run under
+  auto gload = [&](float (&d)[8][FPL], int b0, int b1) {
+    const float* rowp = src + (size_t)(b0 + 8 * half) * pitch;
+    const int rows = b1 - b0 - 8 * half;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int tt = t + b_r + i * RB;
-      rb[i] = (b_ok && tt < t_end) ? *reinterpret_cast<const uint4*>(b_src + (size_t)tt * p.d_in)
-                                   : make_uint4(0, 0, 0, 0);
+    for (int i = 0; i < 8; ++i) {
+      const __amdgpu_buffer_rsrc_t row =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(rowp), 0, i < rows ? f_bytes : 0, 0x00020000);
+      if constexpr (FPL == 2) {
+        const float2 v = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(row, lane * 8, 0, 0));
+        d[i][0] = v.x; d[i][1] = v.y;
+      } else {
+        d[i][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(row, lane * 4, 0, 0));
+      }
+      rowp += pitch;
     }
   };
-  auto sstore = [&](int buf, float scale) {
+  unsigned char* const dst = lds + ((is_x ? 2 : 0) + half) * BT * kUnit;
+  auto sstore = [&](float (&d)[8][FPL], int buf, float scale) {
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      uint4 v = ra[i];
+    for (int f = 0; f < FPL; ++f) {
       if constexpr (WEIGHTED) {
-        float4 f = __builtin_bit_cast(float4, v);
-        f.x *= scale; f.y *= scale; f.z *= scale; f.w *= scale;
-        v = __builtin_bit_cast(uint4, f);
+        if (!is_x) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) d[i][f] *= scale;
+        }
       }
-      *reinterpret_cast<uint4*>(As + (buf * BK + a_r + i * RA) * PA + a_cv * kVec) = v;
+      unsigned h[4], m[4], l[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) split2(d[2 * q][f], d[2 * q + 1][f], h[q], m[q], l[q]);
+      unsigned char* const o = dst + unit_pos(FPL * lane + f) * kUnit + buf * STAGE;
+      *reinterpret_cast<uint4*>(o) = make_uint4(h[0], h[1], h[2], h[3]);
+      *reinterpret_cast<uint4*>(o + PLANE) = make_uint4(m[0], m[1], m[2], m[3]);
+      *reinterpret_cast<uint4*>(o + 2 * PLANE) = make_uint4(l[0], l[1], l[2], l[3]);
     }
+  };
+
+  f32x16 acc[NB][NB];
+  auto clear = [&]() {
 #pragma unroll
     for (int i = 0; i < NB; ++i)
-      *reinterpret_cast<uint4*>(Bs + (buf * BK + b_r + i * RB) * PB + b_cv * kVec) = rb[i];
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   };
+  clear();
 
-  f32x16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
+  const int mw = m0 + wm * WT, nw = n0 + wn * WT;
+  const bool live = mw < p.row_end && nw < p.d_in;   // edge tiles: this wave has outputs
+  const unsigned char* const at = lds + (lane >> 5) * BT * kUnit + unit_pos(wm * WT + (lane & 31)) * kUnit;
+  const unsigned char* const bt = lds + (2 + (lane >> 5)) * BT * kUnit + unit_pos(wn * WT + (lane & 31)) * kUnit;
   auto compute = [&](int buf) {
-    const T* at = As + buf * BK * PA + wm * WM;
-    const T* bt = Bs + buf * BK * PB + wn * WN;
+    // small products first: lh, hl, mm, mh, hm, hh
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+    bf16x8 a[NB][kParts], b[NB][kParts];
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      float af[FM], bf[FN];
-      const int kr = kk + (lane >> 5), col = lane & 31;
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-      for (int i = 0; i < FM; ++i) af[i] = at[kr * PA + i * 32 + col];
+      for (int s = 0; s < kParts; ++s) {
+        a[i][s] = *reinterpret_cast<const bf16x8*>(at + buf * STAGE + s * PLANE + i * 32 * kUnit);
+        b[i][s] = *reinterpret_cast<const bf16x8*>(bt + buf * STAGE + s * PLANE + i * 32 * kUnit);
+      }
 #pragma unroll
-      for (int j = 0; j < FN; ++j) bf[j] = bt[kr * PB + j * 32 + col];
+    for (int s = 0; s < 6; ++s)
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
+      for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
-    }
+        for (int j = 0; j < NB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][pa[s]], b[j][pb[s]], acc[i][j], 0, 0, 0);
   };
 
-  // Walk the token blocks of sequences [seq_begin, seq_end).  Uniform over the workgroup.
-  int seq = seq_begin - 1, t = 0, t_end = 0;
-  float scale = 1.f;
-  auto next_block = [&](int& bt0, int& bt1, float& bs) -> bool {
-    while (t >= t_end) {
-      if (++seq >= seq_end) return false;
-      t = p.off[seq];
-      t_end = p.off[seq + 1];
-      if constexpr (WEIGHTED) scale = p.c ? p.c[seq] : 1.f;
-    }
-    bt0 = t;
-    bt1 = t_end;
-    bs = scale;
-    t += BK;
-    return true;
-  };
-
-  int bt0, bt1;
-  float bs;
-  bool have = next_block(bt0, bt1, bs);
-  if (have) {
-    gload(bt0, bt1);
-    sstore(0, bs);
+  {
+    TokenWalk<WEIGHTED> walk(p, item);
+    // A step is KG blocks of tokens, one per group; a group without one in the last step loads zeros.  Step s is
+    // multiplied from LDS while step s + 1 is in registers and step s + 2 on its way there.
+    auto fetch = [&](float (&d)[8][FPL], float& scale) -> bool {
+      int b0 = 0, b1 = 0;
+      bool any = false;
+#pragma unroll
+      for (int g = 0; g < KG; ++g) {
+        int q0 = 0, q1 = 0;
+        float qs = 1.f;
+        const bool got = walk.next(kBK, q0, q1, qs);
+        if (g == 0) any = got;
+        if (g == group && got) { b0 = q0; b1 = q1; scale = qs; }
+      }
+      gload(d, b0, b1);
+      return any;
+    };
+    float s0 = 1.f, s1 = 1.f;
+    bool have0 = fetch(r[0], s0), have1 = fetch(r[1], s1);
+    if (have0) sstore(r[0], 0, s0);
     __syncthreads();
-    int cur = 0;
-    while (true) {
-      const bool more = next_block(bt0, bt1, bs);
-      if (more) gload(bt0, bt1);
-      compute(cur);
-      if (more) sstore(cur ^ 1, bs);
+    while (have0) {
+      const bool have2 = fetch(r[0], s0);
+      if (live) compute(0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (have1) sstore(r[1], 1, s1);
       __syncthreads();
-      if (!more) break;
-      cur ^= 1;
+      if (!have1) break;
+      have1 = fetch(r[1], s1);
+      if (live) compute(1);
+      __builtin_amdgcn_sched_barrier(0);
+      if (have2) sstore(r[0], 0, s0);
+      __syncthreads();
+      have0 = have2;
     }
   }
 
-  // Epilogue.  Lane l holds column (l%32) and rows acc_row(v, l) of each block.
-  const int col_in_blk = lane & 31;
+  if constexpr (KG > 1) {
+    // the groups' sums, added in group order (every stage has been read: the loop ends with a barrier)
+    float* red = reinterpret_cast<float*>(smem);     // [group - 1][value][thread of the group]
+    const int tg = wave * 64 + lane;
+    if (group > 0) {
 #pragma unroll
-  for (int i = 0; i < FM; ++i) {
+      for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int n = n0 + wn * WN + j * 32 + col_in_blk;
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) red[((group - 1) * NB * NB * 16 + (i * NB + j) * 16 + v) * 256 + tg] = acc[i][j][v];
+    }
+    __syncthreads();
+    if (group > 0) return;
+#pragma unroll
+    for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][j][v] += red[(g * NB * NB * 16 + (i * NB + j) * 16 + v) * 256 + tg];
+          __builtin_amdgcn_sched_barrier(0);         // sixteen reads in flight, not all at once: no spills
+        }
+  }
+  if (!live) return;
+
+  // Lane l holds column l%32 and rows acc_row(v, l) of each block.
+  const int col = lane & 31;
+  unsigned top = 0;                                  // largest magnitude among the stored values, as bits
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const unsigned bits = __builtin_bit_cast(unsigned, (float)acc[i][j][v]) & 0x7fffffffu;
+        const bool stored = nw + j * 32 + col < p.d_in && mw + i * 32 + acc_row(v, lane) < p.row_end;
+        top = stored && bits > top ? bits : top;
+      }
+  if (__ballot(top >= 0x7f800000u) || (__ballot(top >= kTinyBits) == 0 && __ballot(top != 0))) {
+    // once more with fp32 MFMAs, the operands straight from global memory: one token per lane half
+    clear();
+    TokenWalk<WEIGHTED> walk(p, item);
+    int b0, b1;
+    float bs;
+    const int kr = lane >> 5;
+    while (walk.next(2, b0, b1, bs)) {
+      const bool tok = b0 + kr < b1;
+      const size_t t = tok ? b0 + kr : b0;
+      float a[NB], b[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int m = mw + i * 32 + col, n = nw + i * 32 + col;
+        a[i] = tok && m < p.row_end ? p.Delta[t * p.d_out + m] * bs : 0.f;
+        b[i] = tok && n < p.d_in ? p.X[t * p.d_in + n] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+  }
+
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int n = nw + j * 32 + col;
       if (n >= p.d_in) continue;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int m = m0 + wm * WM + i * 32 + acc_row(v, lane);
+        const int m = mw + i * 32 + acc_row(v, lane);
         if (m >= p.row_end) continue;
         const size_t idx = (size_t)(m - p.out_row0) * p.d_in + n;
         if constexpr (WEIGHTED) {
-          float* o = static_cast<float*>(p.out) + idx;
-          *o = (p.beta != 0.f ? p.beta * *o : 0.f) + acc[i][j][v];
+          float* o = p.out + idx;
+          if (p.atomic) atomicAdd(o, acc[i][j][v]);
+          else *o = (p.beta != 0.f ? p.beta * *o : 0.f) + acc[i][j][v];
         } else {
-          static_cast<float*>(p.out)[(size_t)item * p.out_seq_stride + idx] = acc[i][j][v];
+          p.out[(size_t)item * p.out_seq_stride + idx] = acc[i][j][v];
         }
       }
     }
   }
 }
 
-template <int BM, int BN, int BK, int PAD, bool WEIGHTED>
-hipError_t launch_cfg(const SeqGradArgs& a, hipStream_t s) {
-  SeqGradParams p;
-  p.X = a.X; p.Delta = a.Delta; p.off = a.off; p.c = a.c; p.out = a.out;
-  p.d_in = a.d_in; p.d_out = a.d_out; p.n_seq = a.n_seq;
-  p.row0 = a.row0; p.row_end = a.row0 + a.rows; p.out_row0 = a.out_row0;
-  p.out_seq_stride = a.out_seq_stride; p.beta = a.beta;
-  p.tiles_m = (a.rows + BM - 1) / BM;
-  p.tiles_n = (a.d_in + BN - 1) / BN;
-  const long long items = WEIGHTED ? 1 : a.n_seq;
-  const long long blocks = items * p.tiles_m * p.tiles_n;
+template <int WT, int KG, bool WEIGHTED>
+hipError_t launch_cfg(SeqGradParams p, int rows, long long items, hipStream_t s) {
+  constexpr int BT = 2 * WT;
+  p.tiles_n = (p.d_in + BT - 1) / BT;
+  const long long tiles = (long long)((rows + BT - 1) / BT) * p.tiles_n, blocks = items * tiles;
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  p.n_blocks = (unsigned)blocks;
-  constexpr size_t smem = 2ull * BK * ((BM + PAD) + (BN + PAD)) * sizeof(float);
-  auto kern = seq_grad_kernel<BM, BN, BK, PAD, WEIGHTED>;
+  p.tiles = (int)tiles;
+  p.longest_first = !WEIGHTED && p.n_seq > 1 && p.n_seq <= 64 && blocks > 768;
+  constexpr size_t smem = (size_t)KG * group_lds(BT);
+  static_assert(smem >= (size_t)(KG - 1) * WT * WT * 4 * sizeof(float), "the groups' sums meet in LDS");
+  auto kern = seq_grad_kernel<WT, KG, WEIGHTED>;
   // once per process and instantiation (static initialisation is thread-safe); a failure is returned by every call
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(p.n_blocks), dim3(256), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256 * KG), smem, s, p);
   return hipGetLastError();
+}
+
+template <bool WEIGHTED>
+hipError_t launch_plan(const SeqGradParams& p, const SplitContractionPlan& pl, int rows, long long items, hipStream_t s) {
+  if (pl.tile == 128) return launch_cfg<64, 1, WEIGHTED>(p, rows, items, s);
+  if (pl.groups == 1) return launch_cfg<32, 1, WEIGHTED>(p, rows, items, s);
+  return pl.groups == 2 ? launch_cfg<32, 2, WEIGHTED>(p, rows, items, s) : launch_cfg<32, 4, WEIGHTED>(p, rows, items, s);
 }
 
 }  // namespace
 
 hipError_t launch_seq_grad(const SeqGradArgs& a, hipStream_t s) {
   if (a.bf16) return launch_seq_grad_stream(a, s);
-  if (a.per_sequence) return launch_cfg<64, 64, 16, 4, false>(a, s);
-  return launch_cfg<64, 64, 16, 4, true>(a, s);
+  SeqGradParams p;
+  p.X = static_cast<const float*>(a.X); p.Delta = static_cast<const float*>(a.Delta); p.off = a.off; p.c = a.c;
+  p.out = static_cast<float*>(a.out);
+  p.d_in = a.d_in; p.d_out = a.d_out; p.n_seq = a.n_seq; p.n_tokens = a.n_tokens;
+  p.row0 = a.row0; p.row_end = a.row0 + a.rows; p.out_row0 = a.out_row0;
+  p.out_seq_stride = a.out_seq_stride; p.beta = a.beta;
+  p.chunk_tokens = 1;
+  p.atomic = 0;
+  const SplitContractionPlan pl = plan_split_contraction(a.rows, a.d_in, a.n_tokens, a.n_seq, a.off_host, a.per_sequence);
+  if (a.per_sequence) return launch_plan<false>(p, pl, a.rows, a.n_seq, s);
+  p.chunk_tokens = pl.chunk_tokens;
+  if (pl.n_chunks > 1) {
+    p.atomic = 1;
+    const hipError_t e = launch_apply_beta(p.out + (size_t)(a.row0 - a.out_row0) * a.d_in, (long long)a.rows * a.d_in, a.beta, s);
+    if (e != hipSuccess) return e;
+  }
+  return launch_plan<true>(p, pl, a.rows, pl.n_chunks, s);
 }
 
 }  // namespace isopo

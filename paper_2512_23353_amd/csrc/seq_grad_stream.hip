@@ -867,7 +867,8 @@ hipError_t launch_stream(const SeqGradArgs& a, const ContractionPlan& pl, hipStr
     // the band of output rows this launch owns is contiguous in dW
     float* band = static_cast<float*>(a.out) + (size_t)(a.row0 - a.out_row0) * a.d_in;
     const long long n = (long long)a.rows * a.d_in;
-    hipLaunchKernelGGL(apply_beta_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s, band, n, a.beta);
+    const hipError_t e = launch_apply_beta(band, n, a.beta, s);
+    if (e != hipSuccess) return e;
   }
   if constexpr (PERSIST) {
     hipLaunchKernelGGL(queue_zero_kernel, dim3(1), dim3(64), 0, s, queue);
@@ -879,6 +880,11 @@ hipError_t launch_stream(const SeqGradArgs& a, const ContractionPlan& pl, hipStr
 }
 
 }  // namespace
+
+hipError_t launch_apply_beta(float* o, long long n, float beta, hipStream_t s) {
+  hipLaunchKernelGGL(apply_beta_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s, o, n, beta);
+  return hipGetLastError();
+}
 
 // bf16: the per-sequence stash, the plain sum over all tokens, or (c != nullptr) the weighted sum.
 hipError_t launch_seq_grad_stream(const SeqGradArgs& a, hipStream_t s) {

@@ -1,0 +1,87 @@
+"""The fp32 contraction (three bf16 parts per value on the matrix cores) against 64-bit sums, at the edges of its tiles,
+token blocks, groups and chunks, and on the values its parts do not cover."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_23353_amd import isopo
+from paper_2512_23353_amd import workloads as wl
+
+from helpers import to_device
+
+pytestmark = pytest.mark.gpu
+
+# d_in, d_out, lengths: (tile, groups) the plan is meant to take in per-sequence mode
+SHAPES = [
+    (4, 4, [1]), (64, 64, [16, 0, 15, 17]), (68, 132, [33, 1, 64]),          # few short items
+    (128, 260, [700, 31, 0, 1201]),                                          # few items, long walks: groups
+    (36, 1028, [90] * 27),                                                   # narrow: 64-wide tiles
+    (260, 516, list(range(1, 140, 2))),                                      # more than 64 sequences
+    (640, 1284, [150, 90, 1, 47, 0, 128, 200, 16] * 4),                      # 128-wide tiles, longest sequence first
+]
+
+
+def _reference(prob, c=None):
+    X, D = prob.X.double().numpy(), prob.Delta.double().numpy()
+    off = prob.seq_offsets
+    G = [D[off[i]:off[i + 1]].T @ X[off[i]:off[i + 1]] for i in range(prob.n_seq)]
+    M = [np.abs(D[off[i]:off[i + 1]]).T @ np.abs(X[off[i]:off[i + 1]]) for i in range(prob.n_seq)]
+    if c is None:
+        return np.stack(G), np.stack(M)
+    return sum(ci * g for ci, g in zip(c, G)), sum(abs(ci) * g for ci, g in zip(c, M))
+
+
+def _bound(n_terms):
+    """fp32: every product is right to 2^-23 of itself and every one of at most six sums per sixteen tokens (and one per
+    chunk or group, at most 64 + 4) rounds the running sum, itself at most the sum of magnitudes, by 2^-23 at most."""
+    return (2 + 6 * -(-n_terms // 16) + 68) * 2.0 ** -23
+
+
+@pytest.mark.parametrize("case", range(len(SHAPES)))
+def test_f32_contraction_edges(gpu_device, case):
+    d_in, d_out, lengths = SHAPES[case]
+    prob = wl.custom_layer(d_in, d_out, lengths, dtype="f32", seed=400 + case, sigma_delta=1e-2, rho=0.3)
+    layer, _ = to_device(prob, gpu_device)
+    G, M = _reference(prob)
+    stash = torch.full((prob.n_seq, d_out, d_in), float("nan"), device=gpu_device)
+    got = isopo.seq_grads(layer, stash).double().cpu().numpy()
+    assert (np.abs(got - G) <= _bound(max(lengths)) * M).all()
+    c = np.random.default_rng(case).standard_normal(prob.n_seq).astype(np.float32)
+    c_dev = torch.from_numpy(c).to(gpu_device)
+    for coef, cc in ((c_dev, c), (None, np.ones_like(c))):
+        want, mag = _reference(prob, cc.astype(np.float64))
+        bound = _bound(sum(lengths) + 16 * len(lengths)) * mag
+        dW = isopo.weighted_grad(layer, coef).double().cpu().numpy()
+        assert (np.abs(dW - want) <= bound).all()
+        old = torch.ones((d_out, d_in), device=gpu_device)
+        dW = isopo.weighted_grad(layer, coef, None, 0.5, old).double().cpu().numpy()
+        assert (np.abs(dW - want - 0.5) <= bound + 2.0 ** -23 * (64 + 4) * (0.5 + mag)).all()
+
+
+@pytest.mark.parametrize("dims", [(64, 96), (640, 1284)])
+@pytest.mark.parametrize("what", ["tiny", "huge", "inf", "nan"])
+def test_f32_contraction_outside_the_parts_range(gpu_device, dims, what):
+    """Values whose bf16 parts would be subnormal or infinite: as exact as ever, and infinities and NaN stay in the
+    rows and columns they belong to."""
+    d_in, d_out = dims
+    prob = wl.custom_layer(d_in, d_out, [40, 90, 3, 17] * 4, dtype="f32", seed=77, sigma_delta=1.0)
+    X, D = prob.X, prob.Delta
+    if what == "tiny":
+        D *= 2.0 ** -112
+    elif what == "huge":
+        X *= 2.0 ** -20
+        D[45, 3] = 3.4e38                                  # rounds to infinity in bf16
+    else:
+        D[45, 3] = float(what)
+    layer, _ = to_device(prob, gpu_device)
+    with np.errstate(all="ignore"):
+        G, M = _reference(prob)
+    got = isopo.seq_grads(layer).double().cpu().numpy()
+    if what in ("tiny", "huge"):
+        # the plain fp32 form rounds once per two tokens; 2^-149: the products' own underflow
+        assert (np.abs(got - G) <= (2 + 90) * 2.0 ** -23 * M + 90 * 2.0 ** -149).all()
+        return
+    fin = np.isfinite(G)
+    assert not fin[1, 3].any() and fin.sum() == fin.size - d_in
+    assert np.array_equal(np.isnan(got), np.isnan(G)) and np.array_equal(np.isinf(got), np.isinf(G))
+    assert (np.abs(got - G)[fin] <= (2 + 90) * 2.0 ** -23 * M[fin]).all()
