@@ -262,6 +262,7 @@ isopo_status isopo_layer_gram(const isopo_layer* layer, isopo_gram_path path, fl
                                                          : align_up(stash_bytes(layer, (int)chunk_rows))));
   if (reinterpret_cast<char*>(partials) + pbytes > ws + ws_bytes) return ISOPO_ERR_WORKSPACE_TOO_SMALL;
 
+  const int slots = stash_gram_slots(layer->n_seq, bf16, (long long)chunk_rows * layer->d_in);
   for (int r0 = 0; r0 < layer->d_out; r0 += (int)chunk_rows) {
     const int rows = (layer->d_out - r0) < (int)chunk_rows ? (layer->d_out - r0) : (int)chunk_rows;
     SeqGradArgs a;
@@ -277,10 +278,10 @@ isopo_status isopo_layer_gram(const isopo_layer* layer, isopo_gram_path path, fl
     g.stash = ws; g.seq_stride = seq_stride;
     g.p0 = whole ? (long long)r0 * layer->d_in : 0;
     g.p1 = g.p0 + (long long)rows * layer->d_in;
-    g.n_seq = layer->n_seq; g.bf16 = bf16; g.first = (r0 == 0); g.partials = partials;
+    g.n_seq = layer->n_seq; g.bf16 = bf16; g.first = (r0 == 0); g.slots = slots; g.partials = partials;
     if (launch_stash_gram(g, s) != hipSuccess) return ISOPO_ERR_HIP;
   }
-  return launch_stash_gram_finish(partials, bf16, layer->n_seq, K, s) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
+  return launch_stash_gram_finish(partials, bf16, slots, layer->n_seq, K, s) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
 }
 
 isopo_status isopo_seq_grads(const isopo_layer* layer, void* stash, void* stream) {
@@ -320,7 +321,8 @@ isopo_status isopo_seq_grads_stash(const isopo_layer* layer, void* stash, isopo_
 
 size_t isopo_stash_gram_workspace(int32_t n_seq) {
   if (n_seq <= 0) return 0;
-  return align_up(stash_gram_partial_bytes(n_seq, true));
+  const size_t bf16 = stash_gram_partial_bytes(n_seq, true), f32 = stash_gram_partial_bytes(n_seq, false);
+  return align_up(bf16 > f32 ? bf16 : f32);
 }
 
 isopo_status isopo_stash_gram(const void* stash, isopo_dtype dtype, int32_t n_seq, int64_t n_elem, float* K,
@@ -334,9 +336,10 @@ isopo_status isopo_stash_gram(const void* stash, isopo_dtype dtype, int32_t n_se
   hipStream_t s = static_cast<hipStream_t>(stream);
   StashGramArgs g;
   g.stash = stash; g.seq_stride = n_elem; g.p0 = 0; g.p1 = n_elem; g.n_seq = n_seq;
-  g.bf16 = dtype == ISOPO_BF16; g.first = true; g.partials = static_cast<float*>(workspace);
+  g.bf16 = dtype == ISOPO_BF16; g.first = true; g.slots = stash_gram_slots(n_seq, g.bf16, n_elem);
+  g.partials = static_cast<float*>(workspace);
   if (launch_stash_gram(g, s) != hipSuccess) return ISOPO_ERR_HIP;
-  return launch_stash_gram_finish(g.partials, g.bf16, n_seq, K, s) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
+  return launch_stash_gram_finish(g.partials, g.bf16, g.slots, n_seq, K, s) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
 }
 
 size_t isopo_transform_workspace(int32_t n_seq, int32_t batch) {

@@ -81,9 +81,11 @@ struct StashGramArgs {
   int n_seq;
   bool bf16;
   bool first;                // overwrite the partial slots instead of adding to them
-  float* partials;           // [stash_gram_slots()][stash_gram_slot_floats(n_seq)]
+  int slots;                 // stash_gram_slots of the first chunk's element count; the same for all chunks
+  float* partials;           // [slots][stash_gram_slot_floats(n_seq, bf16)]
 };
-int stash_gram_slots();
+// partial slots a reduction over n_elem elements of each sequence uses
+int stash_gram_slots(int n_seq, bool bf16, long long n_elem);
 // bytes of partial-sum scratch the Gram reduction needs (0 = shape not covered)
 size_t stash_gram_partial_bytes(int n_seq, bool bf16);
 // n_seq > 128 (bf16): 128x128 super-block pairs
@@ -91,12 +93,12 @@ int stash_gram_large_slots(int n_seq);
 size_t stash_gram_large_slot_floats(int n_seq);
 hipError_t launch_stash_gram_large(const StashGramArgs& a, hipStream_t s);
 hipError_t launch_stash_gram_large_finish(const float* partials, int n_seq, float* K, hipStream_t s);
-size_t stash_gram_slot_floats(int n_seq);
+size_t stash_gram_slot_floats(int n_seq, bool bf16);
 hipError_t launch_stash_gram(const StashGramArgs& a, hipStream_t s);
 // K[i][j] = K[j][i] = sum over slots (fixed order) of the (i<=j) entry.
-hipError_t launch_stash_gram_finish(const float* partials, bool bf16, int n_seq, float* K, hipStream_t s);
-// bf16 stash: row-contiguous DMA into an LDS ring (launch_stash_gram routes to it); uses fewer slots.
-int stash_gram_stream_slots();
+hipError_t launch_stash_gram_finish(const float* partials, bool bf16, int slots, int n_seq, float* K, hipStream_t s);
+// n_seq <= 128: row-contiguous DMA into an LDS ring (launch_stash_gram routes to it).
+int stash_gram_stream_slots(int n_seq, bool bf16, long long n_elem);
 hipError_t launch_stash_gram_stream(const StashGramArgs& a, hipStream_t s);
 
 // dW[p] = beta*dW[p] + sum_i c[i] * stash[i][p],  p in [0, n_elem).  dW fp32, or bf16 (dw_bf16; bf16 stash only:

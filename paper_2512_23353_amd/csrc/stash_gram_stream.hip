@@ -1,4 +1,4 @@
-// Gram matrix of a bf16 stash, streaming variants (n_seq <= 128 first; larger batches further down):
+// Gram matrix of a stash, streaming variants (n_seq <= 128, bf16 and fp32, first; larger bf16 batches further down):
 //     K_ij = sum_p S[i][p] * S[j][p]        (interacting listing:
 //                                            ntk[i, j] = sum(seq_grads[i] * seq_grads[j]))
 // One pass over the stash, bound by HBM.  The stash rows are 10^7..10^8 elements
@@ -10,13 +10,20 @@
 // share of the stage's 16-element steps with ds_read_b128 (16-byte column index
 // XOR-swizzled with the row, so the row-per-lane reads do not pile on one bank)
 // and issues mfma(a_i, a_j) for every row-block pair i <= j; the A and B
-// fragments of K = S S^T are the same registers.
+// fragments of K = S S^T are the same registers.  Up to 16 sequences the stage holds 16 rows and the products are
+// 16x16: 32 rows would stage every byte twice (16 sequences of 1536x1536 in bf16, 75 MB: 17.8 us with 32 rows, 15.7 us
+// with 16).  fp32 stashes take fp32 MFMAs, one per element of a lane's 16-byte vector; the accumulators are emptied into
+// a second set of registers every few stages, so that no chain of matrix-core sums is longer than 64 (which of four
+// waves multiplied 1/4096 or 1/1024 of the elements then does not show in K's error).  16 sequences of
+// 1536x1536 in fp32, 151 MB: 31 us (4.9 TB/s; fragment-shaped loads by 1024 workgroups: 71 us); 40 of 300x1220, 59 MB: 22 us (40 us).
 //
 // Deterministic: fixed p -> workgroup -> wave assignment, waves added in order
 // through LDS into the workgroup's partial slot, slots added in a fixed tree by
 // the finishing kernel.
 #include "common.h"
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace isopo {
 namespace {
@@ -34,7 +41,7 @@ __host__ __device__ constexpr int tri(int nb) { return nb * (nb + 1) / 2; }
 __host__ __device__ constexpr int pair_index(int bi, int bj, int nb) { return bi * nb - bi * (bi - 1) / 2 + (bj - bi); }
 
 struct Params {
-  const u16* stash;
+  const void* stash;
   long long seq_stride, p0, p1;
   int n_seq, first;
   float* partials;
@@ -54,17 +61,22 @@ __device__ __forceinline__ void load_lds16_nt(const void* gptr, unsigned lds_add
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(lds_addr), "v"(gptr) : "memory");
 }
 
-// NB   32-row blocks that carry sequences (pairs are formed among these)
-// NBL  row blocks of the LDS layout: 1, 2 or 4 (NBL >= NB); stage = 32*NBL rows x KW elements
-template <int NB, int NBL>
-__global__ __launch_bounds__(256) void stash_gram_stream_kernel(Params p) {
-  constexpr int ROWS = 32 * NBL;
-  constexpr int RB = kStageBytes / ROWS;           // bytes per row and stage: 1024, 512, 256
-  constexpr int KW = RB / 2;                        // elements per row and stage
-  constexpr int VPR = RB / 16;                      // 16-byte vectors per row: 64, 32, 16
-  constexpr int RPL = 1024 / RB;                    // rows per 1 KiB wave-load: 1, 2, 4
+// MB   side of an MFMA block, 32 or 16 (fp32, and n_seq <= 16)
+// NB   MB-row blocks that carry sequences (pairs are formed among these)
+// NBL  row blocks of the LDS layout: 1, 2, 4 or 8 (NBL >= NB); stage = MB*NBL rows x KW elements
+template <bool BF16, int MB, int NB, int NBL>
+__global__ __launch_bounds__(256, 1) void stash_gram_stream_kernel(Params p) {
+  constexpr int ES = BF16 ? 2 : 4, EPV = 16 / ES;   // bytes per element, elements per 16-byte vector
+  constexpr int ROWS = MB * NBL;
+  constexpr int RB = kStageBytes / ROWS;            // bytes per row and stage: 2048 (MB 16), 1024, 512, 256
+  constexpr int KW = RB / ES;                       // elements per row and stage
+  constexpr int VPR = RB / 16;                      // 16-byte vectors per row: 128, 64, 32, 16
   constexpr int LPW = kStageBytes / 1024 / 4;       // wave-loads per wave and stage: 8
-  constexpr int STEPS = KW / 16 / 4;                // 16-element steps per wave and stage: 8, 4, 2
+  constexpr int LV = 64 / MB;                       // vectors of a row that one step's lanes hold: 2 or 4
+  constexpr int STEPS = VPR / LV / 4;               // steps per wave and stage: 8, 8, 4, 2
+  constexpr int AV = MB * MB / 64;                  // accumulator registers per block: 16 or 4
+  constexpr int FLUSH = BF16 ? 1 : 64 / (STEPS * EPV);   // fp32: stages per chain of 64 sums
+  typedef typename std::conditional<MB == 32, f32x16, f32x4>::type acc_t;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const unsigned smem_base = (unsigned)(size_t)(lds_void_ptr)smem;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -75,16 +87,16 @@ __global__ __launch_bounds__(256) void stash_gram_stream_kernel(Params p) {
   const long long my_first = blockIdx.x;
   const long long my_count = my_first < n_super ? (n_super - my_first + gridDim.x - 1) / gridDim.x : 0;
 
-  // DMA addressing: wave-load q of this wave covers rows (wave*LPW + q)*RPL .. +RPL-1
+  // DMA addressing: wave-load q of this wave covers bytes (wave*LPW + q) * 1024 .. of the stage
   const char* src[LPW];
   int vec_off[LPW];
 #pragma unroll
   for (int q = 0; q < LPW; ++q) {
-    const int row = (wave * LPW + q) * RPL + lane / VPR;
-    const int pos = lane % VPR;
+    const int slot = (wave * LPW + q) * 64 + lane;
+    const int row = slot / VPR, pos = slot % VPR;
     const int g = pos ^ (row & (VPR - 1) & 31);                 // global vector this LDS slot holds
     const int r = row < p.n_seq ? row : p.n_seq - 1;            // padded rows re-read a real row; their K entries are dropped
-    src[q] = reinterpret_cast<const char*>(p.stash + (size_t)r * p.seq_stride + p.p0);
+    src[q] = static_cast<const char*>(p.stash) + ((size_t)r * p.seq_stride + p.p0) * ES;
     vec_off[q] = g * 16;
   }
   auto issue = [&](long long k) {     // k-th super step of this workgroup -> ring stage k % kStages
@@ -93,22 +105,25 @@ __global__ __launch_bounds__(256) void stash_gram_stream_kernel(Params p) {
     const unsigned stage = smem_base + (unsigned)(k % kStages) * kStageBytes;
 #pragma unroll
     for (int q = 0; q < LPW; ++q) {
-      long long byte = e0 * 2 + vec_off[q];
-      const long long last = (n_elems - 8) * 2;
+      long long byte = e0 * ES + vec_off[q];
+      const long long last = (n_elems - EPV) * ES;
       if (byte > last) byte = last;                               // tail: stays inside the row, zeroed at read time
       if (k >= my_count) byte = 0;                                // look-ahead past the end: harmless re-read
       load_lds16_nt(src[q] + byte, stage + (unsigned)(wave_s * LPW + q) * 1024);
     }
   };
 
-  f32x16 acc[tri(NB)];
+  acc_t acc[tri(NB)], sum[BF16 ? 1 : tri(NB)];
 #pragma unroll
   for (int q = 0; q < tri(NB); ++q)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
+    for (int v = 0; v < AV; ++v) {
+      acc[q][v] = 0.f;
+      if constexpr (!BF16) sum[q][v] = 0.f;
+    }
 
-  // fragment addressing: lane (row = lane&31, half = lane>>5) of row block b, step s of this wave
-  const int frow = lane & 31, half = lane >> 5;
+  // fragment addressing: lane (row = lane % MB, quarter = lane / MB) of row block b, step s of this wave
+  const int frow = lane % MB, part = lane / MB;
 
 #pragma unroll
   for (int s = 0; s < kStages - 1; ++s) issue(s);
@@ -123,24 +138,50 @@ __global__ __launch_bounds__(256) void stash_gram_stream_kernel(Params p) {
     const long long valid = n_elems - u * KW;                    // elements of this stage inside [p0, p1)
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
-      const int step = wave * STEPS + s;                         // 16-element step within the stage
-      const int vec = step * 2 + half;                           // 16-byte vector within the row
+      const int vec = (wave * STEPS + s) * LV + part;            // 16-byte vector within the row
       v4u frag[NB];
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        const int row = b * 32 + frow;
+        const int row = b * MB + frow;
         const unsigned a = sb + (unsigned)row * RB + (unsigned)((vec ^ (row & (VPR - 1) & 31)) * 16);
         frag[b] = *(lds_v4u_ptr)(a);
-        if (valid < KW && (long long)vec * 8 >= valid) frag[b] = v4u{0u, 0u, 0u, 0u};
+        if (valid < KW && (long long)vec * EPV >= valid) frag[b] = v4u{0u, 0u, 0u, 0u};
       }
 #pragma unroll
-      for (int bi = 0; bi < NB; ++bi)
+      for (int e = 0; e < (BF16 ? 1 : 4); ++e)
 #pragma unroll
-        for (int bj = bi; bj < NB; ++bj)
-          acc[pair_index(bi, bj, NB)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8, frag[bi]), __builtin_bit_cast(bf16x8, frag[bj]), acc[pair_index(bi, bj, NB)],
-              0, 0, 0);
+        for (int bi = 0; bi < NB; ++bi)
+#pragma unroll
+          for (int bj = bi; bj < NB; ++bj) {
+            acc_t& a = acc[pair_index(bi, bj, NB)];
+            if constexpr (BF16 && MB == 32)
+              a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, frag[bi]),
+                                                          __builtin_bit_cast(bf16x8, frag[bj]), a, 0, 0, 0);
+            else if constexpr (BF16)
+              a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, frag[bi]),
+                                                          __builtin_bit_cast(bf16x8, frag[bj]), a, 0, 0, 0);
+            else if constexpr (MB == 32)
+              a = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(f32x4, frag[bi])[e],
+                                                       __builtin_bit_cast(f32x4, frag[bj])[e], a, 0, 0, 0);
+            else
+              a = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4, frag[bi])[e],
+                                                       __builtin_bit_cast(f32x4, frag[bj])[e], a, 0, 0, 0);
+          }
     }
+    if constexpr (!BF16) {
+      if (k % FLUSH == FLUSH - 1) {
+#pragma unroll
+        for (int q = 0; q < tri(NB); ++q)
+#pragma unroll
+          for (int v = 0; v < AV; ++v) { sum[q][v] += acc[q][v]; acc[q][v] = 0.f; }
+      }
+    }
+  }
+  if constexpr (!BF16) {
+#pragma unroll
+    for (int q = 0; q < tri(NB); ++q)
+#pragma unroll
+      for (int v = 0; v < AV; ++v) acc[q][v] += sum[q][v];
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);      // drain the look-ahead loads before LDS is reused / released
   __builtin_amdgcn_s_barrier();
@@ -152,28 +193,53 @@ __global__ __launch_bounds__(256) void stash_gram_stream_kernel(Params p) {
 #pragma unroll
       for (int q = 0; q < tri(NB); ++q)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float* o = red + (q * 16 + v) * 64 + lane;
+        for (int v = 0; v < AV; ++v) {
+          float* o = red + (q * AV + v) * 64 + lane;
           *o = (w == 0 ? 0.f : *o) + acc[q][v];
         }
     }
     __syncthreads();
   }
   float* out = p.partials + (long long)blockIdx.x * p.slot_floats;
-  for (int e = threadIdx.x; e < tri(NB) * 1024; e += 256) out[e] = (p.first ? 0.f : out[e]) + red[e];
+  for (int e = threadIdx.x; e < tri(NB) * AV * 64; e += 256) out[e] = (p.first ? 0.f : out[e]) + red[e];
 }
 
-template <int NB, int NBL>
-hipError_t launch(const Params& p, hipStream_t s) {
+template <bool BF16, int MB, int NB, int NBL>
+hipError_t launch(const Params& p, int blocks, hipStream_t s) {
   constexpr size_t smem = (size_t)kStages * kStageBytes;
-  static_assert((size_t)tri(NB) * 4096 <= smem, "reduction scratch fits the ring");
-  auto kern = stash_gram_stream_kernel<NB, NBL>;
+  static_assert((size_t)tri(NB) * MB * MB * 4 <= smem, "reduction scratch fits the ring");
+  auto kern = stash_gram_stream_kernel<BF16, MB, NB, NBL>;
   // once per process (static initialisation is thread-safe); a failure is returned by every call
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(kBlocks), dim3(256), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), smem, s, p);
   return hipGetLastError();
+}
+
+// fp32: 16x16 blocks throughout.  The fp32 MFMA's rate is the same for either shape, and of 32x32 blocks more lies below
+// the diagonal or past the last sequence (40 sequences: 6 of 16x16 against 3 of 32x32, half the MFMA cycles).
+hipError_t launch_f32(const Params& p, int blocks, hipStream_t s) {
+  switch ((p.n_seq + 15) / 16) {
+    case 1: return launch<false, 16, 1, 1>(p, blocks, s);
+    case 2: return launch<false, 16, 2, 2>(p, blocks, s);
+    case 3: return launch<false, 16, 3, 4>(p, blocks, s);
+    case 4: return launch<false, 16, 4, 4>(p, blocks, s);
+    case 5: return launch<false, 16, 5, 8>(p, blocks, s);
+    case 6: return launch<false, 16, 6, 8>(p, blocks, s);
+    case 7: return launch<false, 16, 7, 8>(p, blocks, s);
+    default: return launch<false, 16, 8, 8>(p, blocks, s);
+  }
+}
+
+hipError_t launch_bf16(const Params& p, int blocks, hipStream_t s) {
+  if (p.n_seq <= 16) return launch<true, 16, 1, 1>(p, blocks, s);
+  switch ((p.n_seq + 31) / 32) {
+    case 1: return launch<true, 32, 1, 1>(p, blocks, s);
+    case 2: return launch<true, 32, 2, 2>(p, blocks, s);
+    case 3: return launch<true, 32, 3, 4>(p, blocks, s);
+    default: return launch<true, 32, 4, 4>(p, blocks, s);
+  }
 }
 
 
@@ -464,6 +530,7 @@ __global__ __launch_bounds__(1024) void stash_gram_large_finish_kernel(const flo
   if (bi > bj || bi * 32 >= n_seq || bj * 32 >= n_seq) return;
   const long long e = ((long long)blk * 16 + v) * 64 + lane;
   float s = 0.f;
+#pragma unroll 8
   for (int w = wave; w < n_slots; w += 16) s += partials[(long long)w * slot_floats + e];
   red[wave][lane] = s;
   __syncthreads();
@@ -493,7 +560,13 @@ hipError_t launch_pair(const LargeParams& p, int gx, int n_pairs, hipStream_t s)
 
 }  // namespace
 
-int stash_gram_stream_slots() { return kBlocks; }
+// One workgroup per compute unit, fewer where the stash has fewer stages than that: a short stash's finish pass then
+// adds only slots that hold something.
+int stash_gram_stream_slots(int n_seq, bool bf16, long long n_elem) {
+  const int rows = n_seq <= 16 ? 16 : (n_seq <= 32 ? 32 : (n_seq <= 64 ? 64 : 128));
+  const long long kw = kStageBytes / rows / (bf16 ? 2 : 4), stages = (n_elem + kw - 1) / kw;
+  return stages < kBlocks ? (int)(stages > 0 ? stages : 1) : kBlocks;
+}
 
 // Large batches (n_seq > 128).
 int stash_gram_large_slots(int n_seq) {
@@ -536,18 +609,12 @@ hipError_t launch_stash_gram_large_finish(const float* partials, int n_seq, floa
 }
 
 hipError_t launch_stash_gram_stream(const StashGramArgs& a, hipStream_t s) {
-  const int nb = (a.n_seq + 31) / 32;
-  if (nb > 4 || !a.bf16 || a.n_seq < 1) return hipErrorInvalidValue;
+  if (a.n_seq < 1 || a.n_seq > 128) return hipErrorInvalidValue;
   Params p;
-  p.stash = static_cast<const u16*>(a.stash); p.seq_stride = a.seq_stride; p.p0 = a.p0; p.p1 = a.p1;
+  p.stash = a.stash; p.seq_stride = a.seq_stride; p.p0 = a.p0; p.p1 = a.p1;
   p.n_seq = a.n_seq; p.first = a.first ? 1 : 0; p.partials = a.partials;
-  p.slot_floats = (long long)stash_gram_slot_floats(a.n_seq);
-  switch (nb) {
-    case 1: return launch<1, 1>(p, s);
-    case 2: return launch<2, 2>(p, s);
-    case 3: return launch<3, 4>(p, s);
-    default: return launch<4, 4>(p, s);
-  }
+  p.slot_floats = (long long)stash_gram_slot_floats(a.n_seq, a.bf16);
+  return a.bf16 ? launch_bf16(p, a.slots, s) : launch_f32(p, a.slots, s);
 }
 
 }  // namespace isopo
