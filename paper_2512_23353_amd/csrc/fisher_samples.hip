@@ -162,6 +162,46 @@ __device__ __forceinline__ void product_pass(const void* M, int d, const int32_t
   __builtin_amdgcn_s_barrier();          // the ring is reused by the next pass
 }
 
+// Block b of H = P o Q over the 32 tokens from tw on (live: at least one exists): the sample norms it holds and the
+// segment sums.  Lane holds sample column (lane & 31) of the block and token rows acc_row(v, lane).
+__device__ __forceinline__ void block_sums(const Params& p, const f32x16& P, const f32x16& Q, int b, int tw, int lane,
+                                           int r_first, int r_last, int ncol, double* __restrict__ S64,
+                                           double* __restrict__ den) {
+  const int j = b * 32 + (lane & 31);
+  // ||g^(j)||^2 = ||g0_j||^2 ||a0_j||^2 (eq. (two)) is the product's own entry at the sampled row:
+  // P[idx_j][j] = g0_j . g0_j and Q[idx_j][j] = a0_j . a0_j; exactly one lane of the grid holds it
+  if (j < p.n_samples) {
+    const int tj = min(max(p.idx[j], 0), p.n_tokens - 1);
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (tw + acc_row(v, lane) == tj) den[j] = (double)P[v] * (double)Q[v];
+  }
+  if (r_first == r_last) {
+    double s = 0.0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (tw + acc_row(v, lane) < p.n_tokens) s += (double)P[v] * (double)Q[v];
+    s += __shfl_xor(s, 32, kWave);
+    if (lane < 32 && j < p.n_samples) atomicAdd(&S64[(size_t)r_first * ncol + j], s);
+  } else {
+    double run = 0.0;
+    int run_r = -1;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int t = tw + acc_row(v, lane);
+      if (t >= p.n_tokens) continue;
+      const int r = p.tok_seq[t];
+      if (r != run_r) {
+        if (run_r >= 0 && j < p.n_samples) atomicAdd(&S64[(size_t)run_r * ncol + j], run);
+        run_r = r;
+        run = 0.0;
+      }
+      run += (double)P[v] * (double)Q[v];
+    }
+    if (run_r >= 0 && j < p.n_samples) atomicAdd(&S64[(size_t)run_r * ncol + j], run);
+  }
+}
+
 template <int NBS, bool BF16>
 __global__ __launch_bounds__(256) void fisher_samples_kernel(Params p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -178,7 +218,6 @@ __global__ __launch_bounds__(256) void fisher_samples_kernel(Params p) {
     for (int v = 0; v < 16; ++v) Q[b][v] = 0.f;
   product_pass<NBS, BF16>(g.X, g.d_in, p.idx, p.n_samples, p.n_tokens, t0, smem_base, lane, wave, Q);
 
-  // lane holds sample column (lane & 31) of each block and token rows acc_row(v, lane) of the wave's 32 tokens
   const int tw = t0 + wave * 32;
   const bool live = tw < p.n_tokens;                  // wave-uniform; idle waves still join every pass's barriers
   const int t_last = min(tw + 31, p.n_tokens - 1);
@@ -192,44 +231,139 @@ __global__ __launch_bounds__(256) void fisher_samples_kernel(Params p) {
       for (int v = 0; v < 16; ++v) P[b][v] = 0.f;
     product_pass<NBS, BF16>(g.Delta[l], g.d_out[l], p.idx, p.n_samples, p.n_tokens, t0, smem_base, lane, wave, P);
     if (!live) continue;
-    double* S64 = g.S64 + (size_t)l * p.n_seq * ncol;
-    double* den = g.den + (size_t)l * p.n_samples;
 #pragma unroll
-    for (int b = 0; b < NBS; ++b) {
-      const int j = b * 32 + (lane & 31);
-      // ||g^(j)||^2 = ||g0_j||^2 ||a0_j||^2 (eq. (two)) is the product's own entry at the sampled row:
-      // P[idx_j][j] = g0_j . g0_j and Q[idx_j][j] = a0_j . a0_j; exactly one lane of the grid holds it
-      if (j < p.n_samples) {
-        const int tj = min(max(p.idx[j], 0), p.n_tokens - 1);
+    for (int b = 0; b < NBS; ++b)
+      block_sums(p, P[b], Q[b], b, tw, lane, r_first, r_last, ncol, g.S64 + (size_t)l * p.n_seq * ncol,
+                 g.den + (size_t)l * p.n_samples);
+  }
+}
+
+// ---- few token tiles: 32 tokens per workgroup ---------------------------------------------------------
+// With one workgroup per 128 tokens a short microbatch leaves most of the chip idle while every workgroup walks all
+// features at the latency of one 128-byte stage after the other (about 1 us each).  Here a workgroup takes 32 tokens, a
+// stage is 512 (up to 64 samples) or 256 bytes per row, and the eight waves split a stage's columns; their sums meet in
+// LDS at the end of each product.  768 -> 3072 in fp32, 4600 tokens: the call's three
+// launches take 45 us, 124 with 128-token workgroups; 4096 -> 14336 in bf16, 2000 tokens: 54 against 170 us.
+constexpr int kNarrowWaves = 8;              // a workgroup's DMA rate follows the waves that issue (four: 54 us, below)
+template <int NBS>
+struct NarrowShape {
+  static constexpr int kRows = 32 + 32 * NBS;                    // token rows, then sample rows
+  static constexpr int kRowLen = NBS <= 2 ? 512 : 256;           // bytes per row and stage
+  static constexpr int kRing = NBS == 2 ? 3 : 4;
+  static constexpr int kStageLen = kRows * kRowLen;
+  static constexpr int kLds = kRing * kStageLen;
+  static_assert(kLds <= 160 * 1024, "the ring fits the LDS");
+};
+
+// sum (of the wave's own block b = wave, if wave < NBS) = 32 tokens x 32 samples of T S_b^T over d features
+template <int NBS, bool BF16>
+__device__ __forceinline__ void narrow_pass(const void* M, int d, const int32_t* __restrict__ idx, int n_samples,
+                                            int n_tokens, int t0, unsigned char* smem, int lane, int wave, f32x16& sum) {
+  typedef NarrowShape<NBS> Sh;
+  constexpr int kEs = BF16 ? 2 : 4, kV = 16 / kEs;
+  constexpr int VPR = Sh::kRowLen / 16, KW = Sh::kRowLen / kEs;
+  constexpr int LPW = Sh::kStageLen / 1024 / kNarrowWaves;       // wave-loads per wave and stage
+  constexpr int STEPS = VPR / 2 / kNarrowWaves;                          // two-vector steps per wave and stage
+  static_assert(Sh::kStageLen % (1024 * kNarrowWaves) == 0 && STEPS >= 1 && (32 * Sh::kRowLen) % 1024 == 0, "wave-loads hold whole kinds of rows");
+  const unsigned smem_base = (unsigned)(size_t)(lds_void_ptr)smem;
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const int n_super = (d + KW - 1) / KW;
+  const char* src[LPW];
+  int vec_off[LPW];
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (tw + acc_row(v, lane) == tj) den[j] = (double)P[b][v] * (double)Q[b][v];
-      }
-      if (r_first == r_last) {
-        double s = 0.0;
+  for (int q = 0; q < LPW; ++q) {
+    const int slot = (wave * LPW + q) * 64 + lane;
+    const int row = slot / VPR, pos = slot % VPR;
+    long long grow;
+    if (row < 32) grow = min(t0 + row, n_tokens - 1);
+    else grow = min(max(idx[row - 32 < n_samples ? row - 32 : 0], 0), n_tokens - 1);
+    src[q] = static_cast<const char*>(M) + (size_t)grow * d * kEs;
+    vec_off[q] = (pos ^ (row & (VPR - 1))) * 16;
+  }
+  auto issue = [&](int k) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (tw + acc_row(v, lane) < p.n_tokens) s += (double)P[b][v] * (double)Q[b][v];
-        s += __shfl_xor(s, 32, kWave);
-        if (lane < 32 && j < p.n_samples) atomicAdd(&S64[(size_t)r_first * ncol + j], s);
-      } else {
-        double run = 0.0;
-        int run_r = -1;
+    for (int q = 0; q < LPW; ++q) {
+      long long byte = (long long)k * Sh::kRowLen + vec_off[q];
+      const long long last = ((long long)d - kV) * kEs;
+      if (byte > last) byte = last;          // tail and look-ahead past the end: stays inside the row
+      const int load = wave_s * LPW + q;
+      const unsigned dst = smem_base + (unsigned)(k % Sh::kRing) * Sh::kStageLen + (unsigned)load * 1024;
+      if (load * 1024 < 32 * Sh::kRowLen) load_lds16_nt(src[q] + byte, dst);
+      else load_lds16(src[q] + byte, dst);
+    }
+  };
+  f32x16 acc[NBS];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int t = tw + acc_row(v, lane);
-          if (t >= p.n_tokens) continue;
-          const int r = p.tok_seq[t];
-          if (r != run_r) {
-            if (run_r >= 0 && j < p.n_samples) atomicAdd(&S64[(size_t)run_r * ncol + j], run);
-            run_r = r;
-            run = 0.0;
-          }
-          run += (double)P[b][v] * (double)Q[b][v];
+  for (int b = 0; b < NBS; ++b)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+#pragma unroll
+  for (int s = 0; s < Sh::kRing - 1; ++s) issue(s);
+  const int frow = lane & 31, half = lane >> 5;
+  constexpr int kPending = (Sh::kRing - 2) * LPW;
+  for (int k = 0; k < n_super; ++k) {
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (kPending & 15) | ((kPending >> 4) << 14));
+    __builtin_amdgcn_s_barrier();
+    issue(k + Sh::kRing - 1);
+    const unsigned sb = smem_base + (unsigned)(k % Sh::kRing) * Sh::kStageLen;
+    const int valid = d - k * KW;
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+      const int vec = (wave * STEPS + st) * 2 + half;
+      v4u fa = *(lds_v4u_ptr)(sb + (unsigned)frow * Sh::kRowLen + (unsigned)((vec ^ (frow & (VPR - 1))) * 16));
+      if (valid < KW && vec * kV >= valid) fa = v4u{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int b = 0; b < NBS; ++b) {
+        const int rb = 32 + b * 32 + frow;
+        v4u fb = *(lds_v4u_ptr)(sb + (unsigned)rb * Sh::kRowLen + (unsigned)((vec ^ (rb & (VPR - 1))) * 16));
+        if (valid < KW && vec * kV >= valid) fb = v4u{0u, 0u, 0u, 0u};
+        if constexpr (BF16) {
+          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa), __builtin_bit_cast(bf16x8, fb),
+                                                           acc[b], 0, 0, 0);
+        } else {
+          const f32x4 xa = __builtin_bit_cast(f32x4, fa), xb = __builtin_bit_cast(f32x4, fb);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[e], xb[e], acc[b], 0, 0, 0);
         }
-        if (run_r >= 0 && j < p.n_samples) atomicAdd(&S64[(size_t)run_r * ncol + j], run);
       }
     }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0f70);        // the look-ahead loads have landed: the ring can be written
+  __syncthreads();
+  float* red = reinterpret_cast<float*>(smem);                   // [wave][block][value][lane]
+#pragma unroll
+  for (int b = 0; b < NBS; ++b)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) red[((wave * NBS + b) * 16 + v) * 64 + lane] = acc[b][v];
+  __syncthreads();
+  if (wave < NBS) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      float x = 0.f;
+#pragma unroll
+      for (int w = 0; w < kNarrowWaves; ++w) x += red[((w * NBS + wave) * 16 + v) * 64 + lane];
+      sum[v] = x;
+    }
+  }
+  __syncthreads();                           // the ring is reused by the next pass
+}
+
+template <int NBS, bool BF16>
+__global__ __launch_bounds__(64 * kNarrowWaves) void fisher_samples_narrow_kernel(Params p) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  static_assert(kNarrowWaves * NBS * 4096 <= NarrowShape<NBS>::kLds, "the waves' sums meet in the ring");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int t0 = blockIdx.x * 32;                    // below n_tokens: at least one token
+  const GroupParams& g = p.group[blockIdx.y];
+  f32x16 Q, P;
+  narrow_pass<NBS, BF16>(g.X, g.d_in, p.idx, p.n_samples, p.n_tokens, t0, smem, lane, wave, Q);
+  const int r_first = p.tok_seq[t0], r_last = p.tok_seq[min(t0 + 31, p.n_tokens - 1)];
+  const int ncol = 32 * NBS;
+  for (int l = 0; l < g.n_layers; ++l) {
+    narrow_pass<NBS, BF16>(g.Delta[l], g.d_out[l], p.idx, p.n_samples, p.n_tokens, t0, smem, lane, wave, P);
+    if (wave < NBS)
+      block_sums(p, P, Q, wave, t0, lane, r_first, r_last, ncol, g.S64 + (size_t)l * p.n_seq * ncol,
+                 g.den + (size_t)l * p.n_samples);
   }
 }
 
@@ -294,14 +428,21 @@ __global__ __launch_bounds__(256) void fisher_samples_finish_kernel(const double
 }
 
 template <int NBS, bool BF16>
-hipError_t launch_main(const Params& p, int n_groups, hipStream_t s) {
+hipError_t launch_main(const Params& p, int n_groups, bool narrow, hipStream_t s) {
   constexpr size_t smem = (size_t)kStages * (kTok + 32 * NBS) * kRowBytes;
-  auto kern = fisher_samples_kernel<NBS, BF16>;
+  constexpr size_t smem_narrow = NarrowShape<NBS>::kLds;
+  auto kern = narrow ? fisher_samples_narrow_kernel<NBS, BF16> : fisher_samples_kernel<NBS, BF16>;
   // once per process (static initialisation is thread-safe); a failure is returned by every call
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(fisher_samples_kernel<NBS, BF16>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  static const hipError_t attr_narrow =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(fisher_samples_narrow_kernel<NBS, BF16>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_narrow);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3((p.n_tokens + kTok - 1) / kTok, n_groups), dim3(256), smem, s, p);
+  if (attr_narrow != hipSuccess) return attr_narrow;
+  const int tok = narrow ? 32 : kTok;
+  hipLaunchKernelGGL(kern, dim3((p.n_tokens + tok - 1) / tok, n_groups), dim3(narrow ? 64 * kNarrowWaves : 256),
+                     narrow ? smem_narrow : smem, s, p);
   return hipGetLastError();
 }
 
@@ -394,20 +535,23 @@ hipError_t launch_fisher_samples(const FisherSamplesArgs& a, hipStream_t s) {
       p.group[j - 1] = t;
     }
 
+  // up to two rounds of 32-token workgroups: 125 tiles of 1536 -> 8960 in bf16 77 us against 104, 110 of 512 -> 512 in fp32
+  // 39 against 44; from there on the wide form's full chip wins (157 tiles: 113 either way, 188: 110 against 105)
+  const bool narrow = token_tiles * n_launch_groups <= 128;
   const long long ns = (long long)n_layers * a.n_seq * ncol;
   if (a.n_tokens > 0) {
     const long long items = ns > a.n_tokens ? ns : (long long)a.n_tokens;
     hipLaunchKernelGGL(prep_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, p, ns);
     hipError_t e;
     switch (nbs * 2 + (a.bf16 ? 1 : 0)) {
-      case 2: e = launch_main<1, false>(p, n_launch_groups, s); break;
-      case 3: e = launch_main<1, true>(p, n_launch_groups, s); break;
-      case 4: e = launch_main<2, false>(p, n_launch_groups, s); break;
-      case 5: e = launch_main<2, true>(p, n_launch_groups, s); break;
-      case 6: e = launch_main<3, false>(p, n_launch_groups, s); break;
-      case 7: e = launch_main<3, true>(p, n_launch_groups, s); break;
-      case 8: e = launch_main<4, false>(p, n_launch_groups, s); break;
-      default: e = launch_main<4, true>(p, n_launch_groups, s); break;
+      case 2: e = launch_main<1, false>(p, n_launch_groups, narrow, s); break;
+      case 3: e = launch_main<1, true>(p, n_launch_groups, narrow, s); break;
+      case 4: e = launch_main<2, false>(p, n_launch_groups, narrow, s); break;
+      case 5: e = launch_main<2, true>(p, n_launch_groups, narrow, s); break;
+      case 6: e = launch_main<3, false>(p, n_launch_groups, narrow, s); break;
+      case 7: e = launch_main<3, true>(p, n_launch_groups, narrow, s); break;
+      case 8: e = launch_main<4, false>(p, n_launch_groups, narrow, s); break;
+      default: e = launch_main<4, true>(p, n_launch_groups, narrow, s); break;
     }
     if (e != hipSuccess) return e;
   } else {

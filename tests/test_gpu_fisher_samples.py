@@ -246,3 +246,36 @@ def test_bad_arguments(gpu_device):
         isopo.fisher_samples(layer, idx[:8], A, lam=-1.0)
     with pytest.raises(isopo.IsopoError):
         isopo.fisher_samples(layer, idx[:8], A, workspace=torch.empty(256, dtype=torch.uint8, device=gpu_device))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_tokens,n_samples,dims", [
+    (1, 1, (8, 8)), (31, 31, (72, 200)), (33, 33, (256, 264)), (129, 64, (520, 8)), (300, 65, (64, 136)),
+    (500, 97, (136, 72)), (700, 128, (264, 520)),                      # 32 tokens per workgroup: every number of sample blocks
+    (16384, 40, (40, 24)), (16385, 40, (40, 24)), (16500, 128, (24, 40))])   # 128 tiles, and past them 128 tokens per workgroup
+def test_both_workgroup_shapes(gpu_device, dtype, n_tokens, n_samples, dims):
+    """F^2 against 64 bits at the edges of the 32- and 128-token workgroups.  P and Q are sums of d exact (bf16) or 2^-24
+    products in fp32, so H = P Q is right to (d_in + d_out + 4) 2^-23 of its magnitudes; the segment sums run in 64 bits."""
+    n_seq = min(7, n_tokens)
+    cuts = np.sort(np.random.default_rng(n_tokens).integers(0, n_tokens + 1, n_seq - 1))
+    lengths = np.diff(np.concatenate([[0], cuts, [n_tokens]]))
+    prob = wl.custom_layer(dims[0], dims[1], lengths, dtype=dtype, seed=n_tokens + n_samples, sigma_delta=1e-2, rho=0.4)
+    layer, A = to_device(prob, gpu_device)
+    idx = np.random.default_rng(1).permutation(n_tokens)[:n_samples].astype(np.int32)
+    c, f2 = isopo.fisher_samples(layer, torch.from_numpy(idx).to(gpu_device), A, 1e-2, isopo.REG_REL_TRACE)
+    X, D = prob.X.double().numpy(), prob.Delta.double().numpy()
+    g0, a0 = D[idx], X[idx]
+    H = (D @ g0.T) * (X @ a0.T)
+    M = (np.abs(D) @ np.abs(g0).T) * (np.abs(X) @ np.abs(a0).T)
+    den = ((g0 ** 2).sum(1) * (a0 ** 2).sum(1)).sum()
+    off = prob.seq_offsets
+    S = np.stack([H[off[i]:off[i + 1]].sum(0) for i in range(n_seq)])
+    eS = np.stack([M[off[i]:off[i + 1]].sum(0) for i in range(n_seq)]) * (sum(dims) + 4) * 2.0 ** -23
+    want = (S ** 2).sum(1) / den
+    # |S + e|^2 - |S|^2 <= 2 |S| e + e^2; den itself and the fp32 result are right to (d + 4) 2^-23
+    bound = ((2 * np.abs(S) * eS + eS ** 2).sum(1)) / den + want * (sum(dims) + 6) * 2.0 ** -23
+    got = f2.double().cpu().numpy()
+    assert (np.abs(got - want) <= bound).all()
+    c_want = prob.A / np.sqrt(got + 1e-2 * got.mean())
+    live = got > 0
+    assert np.abs(c.cpu().numpy()[live] / c_want[live] - 1).max() <= 1e-5 if (prob.A[live] != 0).all() else True
