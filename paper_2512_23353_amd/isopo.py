@@ -169,7 +169,8 @@ def _check(status: int, where: str) -> None:
 
 def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current stream's handle without the Python Stream object around it (0.3 against 3 us, three times a step)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -321,7 +322,7 @@ def transform(K: torch.Tensor, A: torch.Tensor, variant="fisher", lam: float = 0
     if c is None:
         c = torch.empty_like(A)
     if info is None:
-        info = torch.zeros(batch, dtype=torch.int32, device=K.device)
+        info = torch.empty(batch, dtype=torch.int32, device=K.device)      # written by every launch: no fill
     need = transform_workspace(m, batch)
     if workspace is None and need:
         workspace = alloc_workspace(need, K.device)
@@ -362,7 +363,7 @@ def transform_ema(K: torch.Tensor, A: torch.Tensor, variant, factor: float, ema_
     if c is None:
         c = torch.empty_like(A)
     if info is None:
-        info = torch.zeros(batch, dtype=torch.int32, device=K.device)
+        info = torch.empty(batch, dtype=torch.int32, device=K.device)      # written by every launch: no fill
     need = transform_workspace(m, batch)
     if workspace is None and need:
         workspace = alloc_workspace(need, K.device)
@@ -473,7 +474,7 @@ def ntk_eigh(K: torch.Tensor, workspace: Optional[torch.Tensor] = None, stream=N
     lead = (batch,) if K.dim() == 3 else ()
     D = torch.empty(lead + (m,), dtype=torch.float64, device=K.device)
     U = torch.empty(lead + (m, m), dtype=torch.float64, device=K.device)
-    info = torch.zeros(batch, dtype=torch.int32, device=K.device)
+    info = torch.empty(batch, dtype=torch.int32, device=K.device)
     if workspace is None:
         workspace = alloc_workspace(load().isopo_ntk_eigh_workspace(m, batch), K.device)
     _check(load().isopo_ntk_eigh(K.data_ptr(), m, batch, D.data_ptr(), U.data_ptr(), info.data_ptr(),
@@ -495,7 +496,7 @@ def transform_eigh(D: torch.Tensor, U: torch.Tensor, A: torch.Tensor, lambdas, r
     if c is None:
         c = torch.empty(lead + (len(lam), m), dtype=torch.float32, device=D.device)
     if info is None:
-        info = torch.zeros(batch, dtype=torch.int32, device=D.device)
+        info = torch.empty(batch, dtype=torch.int32, device=D.device)
     arr = (ctypes.c_float * max(len(lam), 1))(*lam)
     _check(load().isopo_transform_eigh(D.data_ptr(), U.data_ptr(), m, batch, A.data_ptr(), arr, len(lam),
                                        int(reg_mode), _ptr(ema_state), float(ema_decay), c.data_ptr(),
@@ -621,6 +622,7 @@ def layer_step(layer: Layer, A: torch.Tensor, variant="interacting", lam: float 
     chosen, full, _ = gram_plan(layer, path)
     if workspace is None:
         workspace = alloc_workspace(full, layer.device)
+    stream = _stream(stream)
     keep = chosen == "materialised" and workspace.numel() >= full
     K, workspace = layer_gram(layer, path, workspace=workspace, keep_stash=KEEP_FAST if keep else 0, stream=stream)
     c, info = transform(K, A, variant, lam, reg_mode, stream=stream)
