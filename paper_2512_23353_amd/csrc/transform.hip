@@ -16,8 +16,8 @@
 // workgroup per problem works in fp64: a
 // right-looking Cholesky factorisation in panels and two triangular solves.  The
 // matrix lives in LDS (m <= 128) or in a caller-provided global scratch (larger
-// m); the panel being factored is in LDS, column-major, and each thread holds one
-// of its rows in registers (one barrier per column); A rides along as one more
+// m); the panel being factored is in LDS, column-major, and one wave factors its
+// first 64 rows in registers (no barrier per column); A rides along as one more
 // row of the matrix, which makes the forward solve part of the factorisation, and
 // the backward solve runs panel by panel as well.  The result is the unique
 // solution; the eigendecomposition the interacting listing uses reaches the same
@@ -42,11 +42,10 @@ __device__ double block_sum(double x, double* red /* [kThreads/64] */) {
   return s;
 }
 
-// A value every lane holds alike, moved to scalar registers (the column entries all rows are updated with:
-// thirty-one doubles next to a 32-double row would not fit the vector registers of a 1024-thread workgroup).
-__device__ __forceinline__ double uniform_value(double x) {
-  const int lo = __builtin_amdgcn_readfirstlane(__double2loint(x));
-  const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(x));
+// The value lane `src` (the same for all lanes) holds.
+__device__ __forceinline__ double lane_value(double x, int src) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(x), src);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), src);
   return __hiloint2double(hi, lo);
 }
 
@@ -55,134 +54,151 @@ __device__ __forceinline__ double uniform_value(double x) {
 __device__ __forceinline__ int panel_pos(int lr) { return lr + (lr >> 5); }
 __host__ __device__ constexpr int panel_stride(int m) { return ((m + 1) + ((m + 1) >> 5) + 1 + 3) & ~3; }
 
+// Doubles ahead of the matrix and the panel in LDS: the pivots' inverse roots and a copy of the panel's diagonal block.
+__host__ __device__ constexpr int transform_panel(int m) { return m > kTransformLdsMax && m <= kTransformWidePanelMax ? 32 : 16; }
+__host__ __device__ constexpr int transform_front(int m) { return m + transform_panel(m) * (transform_panel(m) + 1); }
+
 // (K + reg I) c = A: M [m + 1, m] fp64 in LDS or global memory (row m holds A, then y), the panel of NB columns
-// in LDS as PT[column][row - k0] with row stride RS.  kThreads threads; c is left in cs.
+// in LDS as PT[column][row - k0] with row stride RS.  c is left in cs.
 //
-// Panel step: thread t holds the panel rows t and t + kThreads (R = 2: only a 1025-row panel has the second;
-// the launch gives smaller problems enough threads for R = 1) in registers.  Per column kk: every row's entry
-// goes to LDS, one barrier, then each thread reads the pivot and the entries (q, kk) of the rows q > kk (the
-// same addresses for all lanes) and eliminates column kk from its rows with the unscaled entries,
-// row[q] -= row[kk] * (q, kk) / pivot; its own entry of L is row[kk] / sqrt(pivot).
-// The upper triangle of the diagonal block is carried along and never read.  The trailing matrix (rows up to
-// and including the row of A) then takes the rank-NB update in 4 x 4 register blocks whose factors come from
-// the panel in LDS.
-template <int kThreads, int NB, int R>
+// Panel step: every wave holds the NB rows of the panel's diagonal block and 64 - NB rows below it, one per lane, in
+// registers, and factors the NB columns by itself (the diagonal block again in every wave): the pivot and a column's entries
+// of the diagonal block's rows come from their lanes (v_readlane), so that a column is one reciprocal square root and a
+// chain of multiply-adds, without an LDS round trip or a barrier (one of each per column, and a 64-bit division and
+// square root in every thread, made a column 0.8 us).  Sequences,
+// us before and now: 16, 11.4 and 8.3; 32, 23 and 14; 64, 49 and 26; 128, 112 and 60; 256, 328 and 226; 1024, 8980 and
+// 6270 (of which launch and regulariser 6).  The upper triangle of the diagonal block is carried
+// along and never read.  The trailing matrix (rows up to and including the row of A) then takes the rank-NB update in TB x TB
+// register blocks whose factors come from the panel in LDS: 4 x 4 where the matrix is in global memory, 2 x 2 where it
+// is in LDS and 4 x 4 blocks would leave most threads without one.
+template <int kThreads, int NB, int TB>
 __device__ bool cholesky_solve(const float* __restrict__ K, const float* __restrict__ A, int m, double reg,
-                               double* __restrict__ M, double* cs /* LDS [m] */, double* PT /* LDS */, int* fail_col) {
-  const int tid = threadIdx.x;
+                               double* __restrict__ M, double* cs /* LDS [m] */, double* inv_diag /* LDS [m] */,
+                               double* PT /* LDS */, int* fail /* LDS */, int* fail_col) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int RS = panel_stride(m);
+  double* const diag = inv_diag + m;                     // [NB][NB + 1]
   // the whole square, so that every later read is of a defined value; the upper triangle never enters a result
-  for (int e = tid; e < m * m; e += kThreads) {
-    const int r = e / m, q = e - r * m;
-    M[e] = (double)K[e] + (r == q ? reg : 0.0);
+  // (a wave per row, four rows of loads in flight)
+  for (int q = lane; q < m; q += kWave) {
+#pragma unroll 4
+    for (int r = tid / kWave; r < m; r += kThreads / kWave)
+      M[(size_t)r * m + q] = (double)K[(size_t)r * m + q] + (r == q ? reg : 0.0);
   }
   for (int i = tid; i < m; i += kThreads) M[(size_t)m * m + i] = (double)A[i];
+  if (tid == 0) *fail = -1;
   __syncthreads();
 
   for (int k0 = 0; k0 < m; k0 += NB) {
     const int nbk = m - k0 < NB ? m - k0 : NB;
     const int nrows = m + 1 - k0;                        // rows k0 .. m
-    // panel -> LDS (a wave reads NB-element pieces of rows)
+    // panel -> LDS (a wave reads NB-element pieces of rows), its diagonal block a second time
+#pragma unroll 4
     for (int e = tid; e < nrows * NB; e += kThreads) {
       const int lr = e / NB, kk = e % NB;
-      if (kk < nbk) PT[kk * RS + panel_pos(lr)] = M[(size_t)(k0 + lr) * m + k0 + kk];
+      if (kk < nbk) {
+        const double x = M[(size_t)(k0 + lr) * m + k0 + kk];
+        PT[kk * RS + panel_pos(lr)] = x;
+        if (lr < NB) diag[kk * (NB + 1) + lr] = x;
+      }
     }
     __syncthreads();
-    // the thread's rows (R = 2 only where m + 1 > kThreads) in registers; waves without a row only keep the barriers
-    const bool wave_has_rows = (tid & ~(kWave - 1)) < nrows;
-    double row[R][NB];
+    // lanes < NB: the diagonal block's rows, the others NB + base + lane - NB.  Rows and columns from nbk on are the
+    // identity's, so that the columns are one straight run of code; what the row of A makes of them is never read.  A pivot
+    // that is not positive leaves NaN or infinity in all that follows; the first one is found at the end.
+    constexpr int kRowsPerWave = kWave - NB, kRowsPerPass = kRowsPerWave * (kThreads / kWave);
+    for (int base = (tid / kWave) * kRowsPerWave; base == 0 || base < nrows - NB; base += kRowsPerPass) {
+      const int lr = lane < NB ? lane : base + lane;
+      const bool has = lr < nrows;
+      double row[NB], pivot = 1.0, inv = 0.0;
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int lr = tid + i * kThreads;
-#pragma unroll
-      for (int q = 0; q < NB; ++q) row[i][q] = (lr < nrows && q < nbk) ? PT[q * RS + panel_pos(lr)] : 0.0;
-    }
-    bool failed = false;                                           // uniform
-#pragma unroll
-    for (int kk = 0; kk < NB; ++kk) {
-      if (kk >= nbk || failed) continue;                           // no break: the loop has to unroll for row[][] to stay in registers
-      // column kk as the columns before it left it: every row's entry goes to the column's own place in LDS
-#pragma unroll
-      for (int i = 0; i < R; ++i) {
-        const int lr = tid + i * kThreads;
-        if (lr < nrows) PT[kk * RS + panel_pos(lr)] = row[i][kk];
+      for (int q = 0; q < NB; ++q) {
+        row[q] = lane == q ? 1.0 : 0.0;
+        if (has && q < nbk) row[q] = lane < NB ? diag[q * (NB + 1) + lane] : PT[q * RS + panel_pos(lr)];
       }
-      __syncthreads();
-      const double d = uniform_value(PT[kk * RS + panel_pos(kk)]);
-      if (!(d > 0.0)) { *fail_col = k0 + kk; failed = true; continue; }      // every thread reads the same value
-      if (!wave_has_rows) continue;
-      const double rsq = 1.0 / sqrt(d), rd = rsq * rsq;
-      double f[R];
 #pragma unroll
-      for (int i = 0; i < R; ++i) {
-        f[i] = row[i][kk] * rd;
-        row[i][kk] *= rsq;                                         // the entry of L; the pivot's own row: d / sqrt(d)
+      for (int kk = 0; kk < NB; ++kk) {
+        if (lane == kk) { pivot = row[kk]; inv = rsqrt(row[kk]); }
+        row[kk] *= lane_value(inv, kk);                  // the entry of L; the pivot's own lane: d / sqrt(d)
+#pragma unroll
+        for (int q = kk + 1; q < NB; ++q) row[q] -= row[kk] * lane_value(row[kk], q);
+        __builtin_amdgcn_sched_barrier(0);               // entries of later columns fetched ahead would not fit the registers
       }
-      // eight columns at a time, so that only eight of the column's entries are held at once
+      if (has && (lane >= NB || base == 0)) {
 #pragma unroll
-      for (int q0 = kk + 1; q0 < NB; q0 += 8) {
-        double b[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (q0 + j < NB) b[j] = uniform_value(PT[kk * RS + panel_pos(q0 + j)]);   // entry (q, kk); for q >= nbk a row below the block: unused
-#pragma unroll
-        for (int i = 0; i < R; ++i)
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            if (q0 + j < NB) row[i][q0 + j] -= f[i] * b[j];
-        __builtin_amdgcn_sched_barrier(0);
+        for (int q = 0; q < NB; ++q)
+          if (q < nbk) PT[q * RS + panel_pos(lr)] = row[q];
       }
-    }
-    if (failed) return false;
-    __syncthreads();                                               // the last column has been read
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int lr = tid + i * kThreads;
-#pragma unroll
-      for (int q = 0; q < NB; ++q)
-        if (lr < nrows && q < nbk) PT[q * RS + panel_pos(lr)] = row[i][q];
+      if (base == 0) {
+        if (lane < nbk) inv_diag[k0 + lane] = inv;
+        const unsigned long long bad = __ballot(lane < nbk && !(pivot > 0.0));
+        if (bad && lane == 0) *fail = k0 + __ffsll((long long)bad) - 1;
+      }
     }
     __syncthreads();
+    if (*fail >= 0) { *fail_col = *fail; return false; }           // every thread reads the same value
     for (int e = tid; e < nrows * NB; e += kThreads) {
       const int lr = e / NB, kk = e % NB;
       if (kk < nbk) M[(size_t)(k0 + lr) * m + k0 + kk] = PT[kk * RS + panel_pos(lr)];
     }
     // trailing update: rows t0 .. m (the row of A included), columns t0 .. min(row, m - 1)
     const int t0 = k0 + nbk;
-    const int nbr = (m + 1 - t0 + 3) >> 2, nbq = (m - t0 + 3) >> 2;
-    for (int e = tid; e < nbr * nbq; e += kThreads) {
-      const int br = e / nbq, bq = e - br * nbq;
-      if (bq > br) continue;
-      const int r0 = t0 + 4 * br, q0 = t0 + 4 * bq;
-      int lr[4], lq[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        lr[i] = panel_pos((r0 + i <= m ? r0 + i : m) - k0);
-        lq[i] = panel_pos((q0 + i < m ? q0 + i : m - 1) - k0);
+    const int nbr = (m + 1 - t0 + TB - 1) / TB, nbq = (m - t0 + TB - 1) / TB;
+    // the blocks on and below the diagonal, row by row (nbr is nbq, or nbq + 1 where the row of A opens a block row)
+    const int below = nbq * (nbq + 1) / 2, blocks = below + (nbr - nbq) * nbq;
+    for (int e = tid; e < blocks; e += kThreads) {
+      int br, bq;
+      if (e < below) {
+        br = (int)((sqrtf(8.f * (float)e + 1.f) - 1.f) * 0.5f);
+        if (br * (br + 1) / 2 > e) --br;
+        if ((br + 1) * (br + 2) / 2 <= e) ++br;
+        bq = e - br * (br + 1) / 2;
+      } else {
+        br = nbq;
+        bq = e - below;
       }
-      double acc[4][4] = {};
-      for (int kk = 0; kk < nbk; ++kk) {
-        double a[4], b[4];
+      const int r0 = t0 + TB * br, q0 = t0 + TB * bq;
+      // the block's entries are fetched together, ahead of the products (one after the other, a fetch and a store each,
+      // was most of a panel's time where the matrix is in global memory)
+      int lr[TB], lq[TB];
+      double cur[TB][TB];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { a[i] = PT[kk * RS + lr[i]]; b[i] = PT[kk * RS + lq[i]]; }
+      for (int i = 0; i < TB; ++i) {
+        const int r = r0 + i <= m ? r0 + i : m, q = q0 + i < m ? q0 + i : m - 1;
+        lr[i] = panel_pos(r - k0);
+        lq[i] = panel_pos(q - k0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < TB; ++j) cur[i][j] = M[(size_t)r * m + (q0 + j < m ? q0 + j : m - 1)];
+      }
+      auto products = [&](int kk) {
+        double a[TB], b[TB];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
+        for (int i = 0; i < TB; ++i) { a[i] = PT[kk * RS + lr[i]]; b[i] = PT[kk * RS + lq[i]]; }
+#pragma unroll
+        for (int i = 0; i < TB; ++i)
+#pragma unroll
+          for (int j = 0; j < TB; ++j) cur[i][j] -= a[i] * b[j];
+      };
+      if (nbk == NB) {                                   // always, but for a last panel, which has only the row of A below it
+#pragma unroll TB == 2 ? 16 : 4
+        for (int kk = 0; kk < NB; ++kk) products(kk);
+      } else {
+        for (int kk = 0; kk < nbk; ++kk) products(kk);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < TB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < TB; ++j) {
           const int r = r0 + i, q = q0 + j;
-          if (r <= m && q < m && (q <= r)) M[(size_t)r * m + q] -= acc[i][j];
+          if (r <= m && q < m && q <= r) M[(size_t)r * m + q] = cur[i][j];
         }
     }
     __syncthreads();
   }
 
   // backward: L^T c = y (y is row m of M), last panel first.  The sums over the rows below a panel are split
-  // over kThreads / NB row groups and met in LDS; wave 0 then solves the panel's triangle, lane = column.
+  // over kThreads / NB row groups and met in LDS; wave 0 then solves the panel's triangle, lane = column, with the
+  // triangle's rows in registers.
   constexpr int RG = kThreads / NB;
   double* red = PT;                                       // [RG][NB + 1]
   double* tri = PT + RG * (NB + 1);                       // [NB][NB + 1]: the panel's diagonal block of L
@@ -192,35 +208,36 @@ __device__ bool cholesky_solve(const float* __restrict__ K, const float* __restr
     const int t0 = k0 + nbk;
     double acc = 0.0;
     if (kk < nbk)
+#pragma unroll 4
       for (int r = t0 + rg; r < m; r += RG) acc += M[(size_t)r * m + k0 + kk] * cs[r];
     red[rg * (NB + 1) + kk] = acc;
     for (int e = tid; e < NB * NB; e += kThreads) {
       const int r = e / NB, q = e % NB;
-      if (r < nbk && q <= r) tri[r * (NB + 1) + q] = M[(size_t)(k0 + r) * m + k0 + q];
+      tri[r * (NB + 1) + q] = r < nbk && q < r ? M[(size_t)(k0 + r) * m + k0 + q] : 0.0;
     }
     __syncthreads();
     if (tid < kWave) {
-      const int lane = tid;
-      double v = 0.0;
-      if (lane < nbk) {
+      const bool has = lane < nbk;
+      double t[NB], v = 0.0;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) t[j] = tri[j * (NB + 1) + (lane < NB ? lane : 0)];
+      if (has) {
         double sum = 0.0;
+#pragma unroll 8
         for (int g = 0; g < RG; ++g) sum += red[g * (NB + 1) + lane];
         v = M[(size_t)m * m + k0 + lane] - sum;
       }
-      double cv = 0.0;
-      for (int j = nbk - 1; j >= 0; --j) {
-        const double cj = __shfl(v, j, kWave) / tri[j * (NB + 1) + j];
-        if (lane == j) cv = cj;
-        if (lane < j) v -= tri[j * (NB + 1) + lane] * cj;
-      }
-      if (lane < nbk) cs[k0 + lane] = cv;
+      const double inv = has ? inv_diag[k0 + lane] : 0.0;
+#pragma unroll
+      for (int j = NB - 1; j >= 0; --j) v -= t[j] * lane_value(v * inv, j);     // rows from nbk on: zeros
+      if (has) cs[k0 + lane] = v * inv;
     }
     __syncthreads();
   }
   return true;
 }
 
-template <int kThreads>
+template <int kThreads, bool GLOBAL>
 __global__ __launch_bounds__(kThreads) void transform_kernel(const float* __restrict__ Kb, const float* __restrict__ Ab,
                                                              int m, int variant, int reg_mode, float lambda,
                                                              float* __restrict__ cb, int32_t* __restrict__ info,
@@ -235,14 +252,16 @@ __global__ __launch_bounds__(kThreads) void transform_kernel(const float* __rest
 
   // FISHER: the norms first; the relative regulariser is measured against their mean
   __shared__ double f2s[ISOPO_MAX_SEQ_TRANSFORM];
+  __shared__ int fail;
   if (variant == 0) {
-    for (int i = tid; i < m; i += kThreads) {
+    for (int i = tid / kWave; i < m; i += kThreads / kWave) {             // a wave per row
       double s = 0.0;
-      for (int j = 0; j < m; ++j) {
+      for (int j = tid % kWave; j < m; j += kWave) {
         const double k = (double)K[(size_t)i * m + j];
         s += k * k;
       }
-      f2s[i] = s / (double)m;
+      s = wave_sum(s);
+      if (tid % kWave == 0) f2s[i] = s / (double)m;
     }
     __syncthreads();
   }
@@ -276,44 +295,45 @@ __global__ __launch_bounds__(kThreads) void transform_kernel(const float* __rest
     return;
   }
 
-  if (gws) {
-    if constexpr (kThreads == 1024) {
+  {
+    if constexpr (GLOBAL) {
       double* Mg = gws + (size_t)prob * ((size_t)m * m + m);
-      double* PT = reinterpret_cast<double*>(smem);
+      double* inv_diag = reinterpret_cast<double*>(smem);
+      double* PT = inv_diag + transform_front(m);
       int fail_col = 0;
-      const bool ok = m <= kTransformWidePanelMax ? cholesky_solve<1024, 32, 1>(K, A, m, reg, Mg, f2s, PT, &fail_col)
-                                                  : cholesky_solve<1024, 16, 2>(K, A, m, reg, Mg, f2s, PT, &fail_col);
+      const bool ok = m <= kTransformWidePanelMax ? cholesky_solve<kThreads, 32, 4>(K, A, m, reg, Mg, f2s, inv_diag, PT, &fail, &fail_col)
+                                                  : cholesky_solve<kThreads, 16, 4>(K, A, m, reg, Mg, f2s, inv_diag, PT, &fail, &fail_col);
+      for (int i = tid; i < m; i += kThreads) c[i] = ok ? (float)f2s[i] : __builtin_nanf("");
+      if (info && tid == 0) info[prob] = ok ? 0 : fail_col + 1;
+    } else {
+      // the matrix in LDS as well, panels of 16 columns
+      double* inv_diag = reinterpret_cast<double*>(smem);
+      double* Ml = inv_diag + transform_front(m);
+      int fail_col = 0;
+      const bool ok = cholesky_solve<kThreads, 16, 2>(K, A, m, reg, Ml, f2s, inv_diag, Ml + (size_t)(m + 1) * m, &fail, &fail_col);
       for (int i = tid; i < m; i += kThreads) c[i] = ok ? (float)f2s[i] : __builtin_nanf("");
       if (info && tid == 0) info[prob] = ok ? 0 : fail_col + 1;
     }
-    return;
   }
-
-  // the matrix in LDS as well, panels of 16 columns
-  double* Ml = reinterpret_cast<double*>(smem);
-  int fail_col = 0;
-  const bool ok = cholesky_solve<kThreads, 16, 1>(K, A, m, reg, Ml, f2s, Ml + (size_t)(m + 1) * m, &fail_col);
-  for (int i = tid; i < m; i += kThreads) c[i] = ok ? (float)f2s[i] : __builtin_nanf("");
-  if (info && tid == 0) info[prob] = ok ? 0 : fail_col + 1;
 }
 
 }  // namespace
 
 // Dynamic LDS of the INTERACTING transform: the panel (32 columns up to kTransformWidePanelMax sequences in
 // global scratch, else 16) or what the backward solve keeps there instead (at most 1024 / 16 + 16 rows of 17),
-// and up to kTransformLdsMax sequences the matrix with the row of A in front of it.
+// up to kTransformLdsMax sequences the matrix with the row of A in front of it, and what stands ahead of both.
 constexpr size_t transform_lds_bytes(int m) {
   const bool lds = m <= kTransformLdsMax;
-  const int nb = (!lds && m <= kTransformWidePanelMax) ? 32 : 16;
+  const int nb = transform_panel(m);
   size_t panel = (size_t)nb * panel_stride(m);
   const size_t backward = nb == 32 ? (size_t)(32 + 32) * 33 : (size_t)(64 + 16) * 17;
   if (panel < backward) panel = backward;
-  return ((lds ? (size_t)(m + 1) * m : 0) + panel) * sizeof(double);
+  return (transform_front(m) + (lds ? (size_t)(m + 1) * m : 0) + panel) * sizeof(double);
 }
 
-template <int THREADS>
+template <int THREADS, bool GLOBAL>
 hipError_t launch_transform_t(const TransformArgs& a, size_t smem, double* gws, hipStream_t s) {
-  auto kern = transform_kernel<THREADS>;
+  auto kern = transform_kernel<THREADS, GLOBAL>;
   // once per process and instantiation (static initialisation is thread-safe); a failure is returned by every call
   constexpr int max_smem = (int)transform_lds_bytes(kTransformLdsMax) > (int)transform_lds_bytes(kTransformWidePanelMax)
                                ? (int)transform_lds_bytes(kTransformLdsMax) : (int)transform_lds_bytes(kTransformWidePanelMax);
@@ -330,10 +350,13 @@ hipError_t launch_transform(const TransformArgs& a, hipStream_t s) {
   const bool lds = a.n_seq <= kTransformLdsMax;
   const size_t smem = a.variant == 1 ? transform_lds_bytes(a.n_seq) : 0;
   double* gws = (a.variant == 1 && !lds) ? a.workspace : nullptr;
-  // the trailing update of column k has (m-k)^2/2 independent elements: more threads for larger problems
-  if (a.n_seq <= 48) return launch_transform_t<256>(a, smem, gws, s);
-  if (a.n_seq <= 96) return launch_transform_t<512>(a, smem, gws, s);
-  return launch_transform_t<1024>(a, smem, gws, s);
+  // the matrix in global memory: 512 threads have the registers for panels of 32 columns (256 sequences: 229 us against 309
+  // with 1024, 328 before), 1024 the loads in flight for the larger ones (1024 sequences: 6.0 ms against 6.8 and 9.0)
+  if (!lds) return a.variant == 1 && a.n_seq <= kTransformWidePanelMax ? launch_transform_t<512, true>(a, smem, gws, s)
+                                                                       : launch_transform_t<1024, true>(a, smem, gws, s);
+  // more threads for the larger problems' trailing updates
+  if (a.n_seq <= 48) return launch_transform_t<256, false>(a, smem, gws, s);
+  return launch_transform_t<512, false>(a, smem, gws, s);
 }
 
 }  // namespace isopo

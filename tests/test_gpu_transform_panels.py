@@ -1,0 +1,30 @@
+"""The Cholesky transform at the edges of what one wave holds of a panel (48 or 32 rows below its diagonal block), of one
+pass of the workgroup's waves over the rows, and of the last, partial panel: against a 64-bit solve."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_23353_amd import isopo
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m", [3, 16, 17, 47, 48, 49, 63, 64, 65, 111, 113, 127, 128, 161, 257, 287, 289, 385, 511, 513, 783, 785])
+def test_transform_panel_edges(gpu_device, m):
+    rng = np.random.default_rng(m)
+    J = rng.standard_normal((2, m, m + 8))
+    K = np.einsum("bij,bkj->bik", J, J).astype(np.float32)
+    K = (K + K.transpose(0, 2, 1)) / 2
+    A = rng.standard_normal((2, m)).astype(np.float32)
+    bad = m - 1 - m // 3                                  # in the second problem this pivot is exactly -2
+    K[1, bad, :] = 0
+    K[1, :, bad] = 0
+    K[1, bad, bad] = -2 - 0.25
+    c, info = isopo.transform(torch.from_numpy(K).to(gpu_device), torch.from_numpy(A).to(gpu_device), "interacting", 0.25)
+    c, info = c.cpu().numpy().astype(np.float64), info.cpu().tolist()
+    assert info == [0, bad + 1] and np.isnan(c[1]).all()
+    M = K[0].astype(np.float64) + 0.25 * np.eye(m)
+    want = np.linalg.solve(M, A[0].astype(np.float64))
+    # backward stable in 64 bits (residual below m^2 2^-53 of |M||c|), c rounded to fp32 once
+    cond = np.linalg.cond(M)
+    assert np.linalg.norm(c[0] - want) <= (2.0 ** -24 + cond * m * m * 2.0 ** -53) * np.linalg.norm(want)
