@@ -270,7 +270,7 @@ def eigh_case(dev) -> dict:
         t_sweep = med(lambda: isopo.transform_eigh(D, U, A, lambdas, isopo.REG_REL_TRACE))
         t_chol = med(lambda: [isopo.transform(K, A, "interacting", lam, isopo.REG_REL_TRACE, workspace=tws) for lam in lambdas])
         out["sizes"][str(m)] = {"eigh_ms": t_eigh, "sweep_of_3_from_eigh_ms": t_sweep, "three_cholesky_transforms_ms": t_chol,
-                                "route": "jacobi" if m <= 94 else "tridiagonal + QL", "info": int(info.item())}
+                                "route": "tridiagonal + divide and conquer", "info": int(info.item())}
     return out
 
 

@@ -4,25 +4,14 @@
 // One decomposition serves any number of regularisers, so a sweep over lambda
 // costs one factorisation instead of one Cholesky per value.  K is m x m with
 // m the number of sequences (tens to a few hundred), so one workgroup per problem
-// (a block's projections go in one launch) runs a cyclic two-sided Jacobi iteration
-// in fp64: each round applies m/2 disjoint
-// plane rotations (round-robin pairing), first to the rows, then to the columns
-// of the work matrix and to the accumulated eigenvector matrix, both in LDS.
-// Problems too large for that (95 sequences and more) take the classical dense
-// route further down: Householder tridiagonalisation and implicit QL.
+// (a block's projections go in one launch) runs the classical dense route in fp64:
+// Householder tridiagonalisation, then divide and conquer on the tridiagonal matrix.
 // Eigenvalues come out ascending, eigenvectors as columns.
 #include "common.h"
 #include "kernels.h"
 
 namespace isopo {
 namespace {
-
-constexpr int kMaxPairs = kEighMaxSeq / 2;
-constexpr int kMaxSweeps = 40;
-constexpr double kOffTol = 1e-14;      // stop when ||off(A)||_F <= kOffTol * ||A||_F
-// Sizes from which the tridiagonal route below replaces the Jacobi iteration: where the Jacobi iteration's two
-// matrices no longer both fit LDS (measured: Jacobi 2.1 ms against 2.4 ms at 80, 4.1 against 3.3 ms at 96).
-constexpr int kEighTridiagonalFrom = 95;
 
 template <int THREADS>
 __device__ double block_sum(double x, double* red) {
@@ -36,165 +25,186 @@ __device__ double block_sum(double x, double* red) {
   return s;
 }
 
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void jacobi_eigh_kernel(const float* __restrict__ Kb, int m,
-                                                              double* __restrict__ Db, double* __restrict__ Ub,
-                                                              int32_t* __restrict__ infob, double* __restrict__ gAb,
-                                                              double* __restrict__ gVb, size_t ws_stride) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  __shared__ double rot_c[kMaxPairs], rot_s[kMaxPairs];
-  __shared__ short rot_p[kMaxPairs], rot_q[kMaxPairs];
-  __shared__ double red[THREADS / 64];
-  __shared__ short rank_of[kEighMaxSeq];
-  const int tid = threadIdx.x;
-  const size_t prob = blockIdx.x;        // one problem per workgroup
-  const float* K = Kb + prob * m * m;
-  double* D = Db + prob * m;
-  double* U = Ub + prob * m * m;
-  int32_t* info = infob ? infob + prob : nullptr;
-  double* gA = gAb ? gAb + prob * ws_stride : nullptr;
-  double* gV = gVb ? gVb + prob * ws_stride : nullptr;
-  const int n = (m + 1) & ~1;            // even: an odd m gets one idle index
-  const int ld = n + 1;                  // odd pitch: column walks spread over the LDS banks
-  // work matrix and eigenvectors: each in LDS when the caller passes no global buffer for it
-  double* Aw = gA ? gA : reinterpret_cast<double*>(smem_raw);
-  double* V = gV ? gV : reinterpret_cast<double*>(smem_raw) + (gA ? 0 : (size_t)n * ld);
-  const int half = n / 2;
+// K = H T H^T with H a product of n - 2 reflectors H_k = I - tau_k v_k v_k^T and T tridiagonal; T = Q^T diag(D) Q by
+// Cuppen's divide and conquer with Gu and Eisenstat's stable eigenvectors (SIAM J. Matrix Anal. Appl. 16, 1995);
+// U = H Q^T.
+// One workgroup per problem, fp64 throughout: bound by the latency of its dependent steps and, with sixteen waves on four
+// vector units, by what each of them issues, so that sums run over sixteen lanes where sixteen rows wait side by side.
+// 16 / 32 / 64 / 128 / 256 / 512 / 1024 sequences: 0.06 / 0.11 / 0.24 / 0.84 / 5.7 / 45 / 380 ms, where a Jacobi iteration (two
+// barriers per round of n/2 rotations, up to 94 sequences) and implicit QL (a sequential chain of about 25 dependent
+// operations per plane rotation) took 0.09 / 0.26 / 1.19 / 5.5 / 22 / 100 / 630; errors of D, U^T U and U D U^T 2e-16 .. 1e-14
+// of the largest eigenvalue, a fifth of the Jacobi iteration's.  At 64 sequences half of the time is the reduction.
+// K is scaled by a power of two so that its largest entry lies in [1, 2) (exact; D is scaled back at the end).
+//   A (n x n, kept bit-symmetric; LDS up to 128 sequences, else U's own memory): rows k+1.. of the trailing block are
+//     updated as A -= v w^T + w v^T; row k then holds v_k for the back-transformation
+//   Qt (n x n, two of them; LDS up to 64 sequences, else global scratch): row i is eigenvector i of the blocks solved so
+//     far; a merge writes the other one
+//
+// The tree's leaves are single indices (every off-diagonal entry is torn out as |e| (1, s)(1, s)^T), the first level's pairs
+// are solved directly.  All merges of a level are alike and run in step, an index's block given by its position: at the level with nb blocks, block s holds
+// indices [s n / nb, (s + 1) n / nb).  A merge of blocks with eigenvalues d and coupling vector z (the last row of
+// the left, s times the first row of the right eigenvectors, over sqrt 2; rho = 2 |e|):
+//   rank      d sorted within the block, one thread per index
+//   deflation components with negligible rho |z|, and pairs close enough that a rotation clears one; the scan is sequential,
+//             so it only runs in blocks where some neighbouring pair or component calls for it
+//   roots     of 1 + rho sum z_i^2 / (d_i - x), sixteen lanes per root, as an offset from the nearer pole: the rational
+//             interpolation through both neighbouring poles, kept inside a bracket that every step narrows
+//   zh        the vector for which the computed roots are exact (products of differences): the eigenvectors formed from
+//             it are orthogonal to rounding however close the roots are
+//   vectors   columns zh_i / (d_i - x_j), normalised, times the old eigenvectors; a wave per four new vectors
+constexpr int kMaxRootIterations = 100;
+constexpr double kUlp = 1.1102230246251565e-16;      // 2^-53
 
-  for (int e = tid; e < n * n; e += THREADS) {
-    const int i = e / n, j = e % n;
-    double v = 0.0;
-    if (i < m && j < m) v = 0.5 * ((double)K[(size_t)i * m + j] + (double)K[(size_t)j * m + i]);
-    Aw[(size_t)i * ld + j] = v;
-    V[(size_t)i * ld + j] = i == j ? 1.0 : 0.0;
-  }
-  __syncthreads();
-
-  int status = 1;                        // 1: not converged within kMaxSweeps
-  for (int sweep = 0; sweep <= kMaxSweeps; ++sweep) {
-    double off = 0.0, dia = 0.0;
-    for (int e = tid; e < n * n; e += THREADS) {
-      const int i = e / n, j = e % n;
-      const double v = Aw[(size_t)i * ld + j];
-      if (i == j) dia += v * v; else off += v * v;
-    }
-    off = block_sum<THREADS>(off, red);
-    dia = block_sum<THREADS>(dia, red);
-    if (off <= kOffTol * kOffTol * (off + dia)) { status = 0; break; }     // uniform: same sums in every thread
-    if (sweep == kMaxSweeps) break;
-    for (int round = 0; round < n - 1; ++round) {
-      if (tid < half) {
-        // round-robin pairing of n players: index n-1 stays, the others rotate
-        int p, q;
-        if (tid == 0) { p = n - 1; q = round; }
-        else { p = (round + tid) % (n - 1); q = (round - tid + (n - 1)) % (n - 1); }
-        double c = 1.0, s = 0.0;
-        if (p < m && q < m) {
-          const double apq = Aw[(size_t)p * ld + q];
-          if (apq != 0.0) {
-            const double tau = (Aw[(size_t)q * ld + q] - Aw[(size_t)p * ld + p]) / (2.0 * apq);
-            const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            c = 1.0 / sqrt(1.0 + t * t);
-            s = t * c;
-          }
-        }
-        rot_c[tid] = c; rot_s[tid] = s; rot_p[tid] = (short)p; rot_q[tid] = (short)q;
-      }
-      __syncthreads();
-      // A <- J^T A J, one 2x2 block per item: rows (p1, q1) of pair P, columns (p2, q2) of pair R.  The
-      // block's new value depends on the block alone, and blocks are disjoint, so read-modify-write in place.
-      for (int e = tid; e < half * half; e += THREADS) {
-        const int P = e / half, R = e % half;
-        const double c1 = rot_c[P], s1 = rot_s[P], c2 = rot_c[R], s2 = rot_s[R];
-        const int p1 = rot_p[P], q1 = rot_q[P], p2 = rot_p[R], q2 = rot_q[R];
-        const double a_pp = Aw[(size_t)p1 * ld + p2], a_pq = Aw[(size_t)p1 * ld + q2];
-        const double a_qp = Aw[(size_t)q1 * ld + p2], a_qq = Aw[(size_t)q1 * ld + q2];
-        const double r_pp = c1 * a_pp - s1 * a_qp, r_pq = c1 * a_pq - s1 * a_qq;     // rows: J_P^T B
-        const double r_qp = s1 * a_pp + c1 * a_qp, r_qq = s1 * a_pq + c1 * a_qq;
-        Aw[(size_t)p1 * ld + p2] = c2 * r_pp - s2 * r_pq;                             // columns: (.) J_R
-        Aw[(size_t)p1 * ld + q2] = s2 * r_pp + c2 * r_pq;
-        Aw[(size_t)q1 * ld + p2] = c2 * r_qp - s2 * r_qq;
-        Aw[(size_t)q1 * ld + q2] = s2 * r_qp + c2 * r_qq;
-      }
-      for (int e = tid; e < half * n; e += THREADS) {            // V <- V J, columns p and q of row k
-        const int R = e % half, k = e / half;
-        const double c = rot_c[R], s = rot_s[R];
-        const int p = rot_p[R], q = rot_q[R];
-        const double vp = V[(size_t)k * ld + p], vq = V[(size_t)k * ld + q];
-        V[(size_t)k * ld + p] = c * vp - s * vq;
-        V[(size_t)k * ld + q] = s * vp + c * vq;
-      }
-      __syncthreads();
-    }
-  }
-
-  // ascending order by rank (ties broken by index), eigenvectors as columns of U
-  for (int i = tid; i < m; i += THREADS) {
-    const double di = Aw[(size_t)i * ld + i];
-    int rank = 0;
-    for (int j = 0; j < m; ++j) {
-      const double dj = Aw[(size_t)j * ld + j];
-      rank += (dj < di || (dj == di && j < i)) ? 1 : 0;
-    }
-    D[rank] = di;
-    rank_of[i] = (short)rank;
-  }
-  __syncthreads();
-  for (int e = tid; e < m * m; e += THREADS) {
-    const int k = e / m, i = e % m;
-    U[(size_t)k * m + rank_of[i]] = V[(size_t)k * ld + i];
-  }
-  if (info && tid == 0) *info = status;
+// Sums over the 16 lanes of a row, in all of them, and over the wave, in all lanes: lane permutations inside the vector
+// unit instead of LDS round trips.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, false);
+  return x + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_sum(double x) {
+  x = dpp_add<0xB1, 0xf>(x);                         // lanes xor 1
+  x = dpp_add<0x4E, 0xf>(x);                         // lanes xor 2
+  x = dpp_add<0x141, 0xf>(x);                        // mirrored within eight
+  return dpp_add<0x140, 0xf>(x);                     // mirrored within sixteen
+}
+__device__ __forceinline__ double quad_sum(double x) { return dpp_add<0x4E, 0xf>(dpp_add<0xB1, 0xf>(x)); }
+__device__ __forceinline__ int row_count(int x) {    // the same for counts
+  x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);
+  return x + __builtin_amdgcn_update_dpp(0, x, 0x140, 0xf, 0xf, false);
+}
+__device__ __forceinline__ double row_product(double x) {
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) x *= __shfl_xor(x, o, 64);
+  return x;
+}
+__device__ __forceinline__ double lane_value(double x, int src) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(x), src);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), src);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_total(double x) {
+  x = row_sum(x);
+  x = dpp_add<0x142, 0xa>(x);                        // rows 1 and 3 += the row before
+  x = dpp_add<0x143, 0xc>(x);                        // rows 2 and 3 += rows 0 and 1
+  return lane_value(x, 63);
 }
 
-// ---- larger problems: Householder tridiagonalisation, then implicit QL on the tridiagonal matrix -----
-// Once its matrices no longer fit LDS the Jacobi iteration streams them through one compute unit in each
-// of its ~10 n rounds (9.3 ms at n = 128, 84 ms at n = 256).  The classical dense route needs one
-// O(n^3) reduction instead: K = Q T Q^T with Q a product of n - 2 reflectors H_k = I - tau_k v_k v_k^T and T
-// tridiagonal, then T = Z diag(D) Z^T by implicit QL steps with Wilkinson's shift, whose plane rotations
-// are applied to the columns of Q as they are generated, so that U = Q Z comes out in place.  One workgroup
-// per problem, fp64 throughout.  K is scaled by a power of two so that its largest entry lies in [1, 2)
-// (exact; D is scaled back at the end).
-//   work matrix A (n x n, global scratch, kept bit-symmetric): rows k+1.. of the trailing block are updated
-//     as A -= v w^T + w v^T; row k then holds v_k for the accumulation of Q
-//   Zt (n x n, global scratch) holds Q^T, later (Q Z)^T: a rotation of columns i, i+1 of Z is a rotation of rows
-//     i, i+1 of Zt, which thread k applies to element k of both rows (coalesced)
-constexpr int kMaxQlIterations = 60;       // per eigenvalue
+// 1/x and sqrt(x) to a unit or so in the last place (x of normal size), without the full division's and root's long
+// dependent chains.
+__device__ __forceinline__ double quick_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ __forceinline__ double quick_sqrt(double x) { return x > 0.0 ? x * rsqrt(x) : 0.0; }
 
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void tridiag_eigh_kernel(const float* __restrict__ Kb, int m,
-                                                               double* __restrict__ Db, double* __restrict__ Ub,
-                                                               int32_t* __restrict__ infob, double* __restrict__ wsb,
-                                                               size_t ws_stride) {
-  __shared__ double d[kEighMaxSeq], e[kEighMaxSeq], tau[kEighMaxSeq], v[kEighMaxSeq], w[kEighMaxSeq];
-  __shared__ double rc[kEighMaxSeq], rs[kEighMaxSeq];
+// Root j of 1 + rho sum_i z_i^2 / (d_i - x) over the k poles d (ascending, distinct), as d[org] + tau; LPR lanes (4 or 16,
+// lane `sub` of them): the interpolation is repeated in every one of them, so few lanes where there are few poles.
+template <int LPR>
+__device__ __forceinline__ void secular_root(const double* d, const double* z, int k, double rho, int j, int sub, int& org,
+                                             double& tau) {
+  auto lanes_sum = [](double x) { return LPR == 4 ? quad_sum(x) : row_sum(x); };
+  const bool last = j == k - 1;
+  double zz = 0.0;
+  if (last) {
+    for (int i = sub; i < k; i += LPR) zz += z[i] * z[i];
+    zz = lanes_sum(zz);
+  }
+  const double gap = last ? rho * zz : d[j + 1] - d[j];
+  // which half of the interval
+  double mid = 0.0;
+  for (int i = sub; i < k; i += LPR) mid += z[i] * z[i] * quick_rcp((d[i] - d[j]) - 0.5 * gap);
+  mid = 1.0 + rho * lanes_sum(mid);
+  double lo, hi;
+  org = j;
+  if (mid >= 0.0) { lo = 0.0; hi = 0.5 * gap; }
+  else if (last) { lo = 0.5 * gap; hi = gap * (1.0 + 8.0 * kUlp); }
+  else { org = j + 1; lo = -0.5 * gap; hi = 0.0; }
+  tau = 0.5 * (lo + hi);
+  const double near = 4.0 * kUlp * quick_sqrt((double)k);
+  const double dorg = d[org], dj = d[j] - dorg, dj1 = last ? 0.0 : d[j + 1] - dorg;
+  for (int it = 0; it < kMaxRootIterations; ++it) {
+    double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;         // poles up to j, and after it
+    for (int i = sub; i < k; i += LPR) {
+      const double inv = quick_rcp((d[i] - dorg) - tau), r = rho * z[i] * z[i] * inv, dr = r * inv;
+      if (i <= j) { psi += r; dpsi += dr; }
+      else { phi += r; dphi += dr; }
+    }
+    psi = lanes_sum(psi); dpsi = lanes_sum(dpsi); phi = lanes_sum(phi); dphi = lanes_sum(dphi);
+    const double w = 1.0 + psi + phi;
+    if (fabs(w) <= near * (1.0 + fabs(psi) + fabs(phi))) break;
+    if (w < 0.0) lo = tau; else hi = tau;
+    const double dp = dj - tau;
+    double eta;
+    if (last) {
+      eta = dp + dpsi * dp * dp * quick_rcp(w - dpsi * dp);      // one pole and a constant
+    } else {
+      const double dq = dj1 - tau;
+      const double c = w - dpsi * dp - dphi * dq, b = (dp + dq) * w - dp * dq * (dpsi + dphi), a = w * dp * dq;
+      const double s = quick_sqrt(b * b - 4.0 * a * c);
+      eta = b > 0.0 ? 2.0 * a * quick_rcp(b + s) : (b - s) * quick_rcp(2.0 * c);
+    }
+    double next = tau + eta;
+    if (!(next > lo && next < hi)) next = 0.5 * (lo + hi);       // also where the interpolation gave no number
+    if (next == tau || next == lo || next == hi) break;          // the bracket's ends are never taken: one may be a pole
+    tau = next;
+  }
+}
+
+// Row pitch of a matrix in LDS: an odd multiple of sixteen doubles, so that the four rows a wave works on at a time lie in
+// different banks, where that fits.
+__host__ __device__ constexpr int eigh_pitch(int m) {
+  const int p = (m + 15) / 16 * 16, odd = p % 32 ? p : p + 16;
+  return (m <= 64 || m * odd <= 128 * 128) ? odd : m;
+}
+
+template <int THREADS, int MAXN, bool LDS, bool QLDS>
+__global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __restrict__ Kb, int m,
+                                                              double* __restrict__ Db, double* __restrict__ Ub,
+                                                              int32_t* __restrict__ infob, double* __restrict__ wsb,
+                                                              size_t ws_stride) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  __shared__ double d[MAXN], e[MAXN], htau[MAXN], v[2 * MAXN], w[MAXN];      // v: this column's and the next one's
+  __shared__ double ds[MAXN], zs[MAXN], dk[MAXN], zk[MAXN], zh[MAXN], rtau[MAXN];
+  __shared__ short perm[MAXN], list[MAXN], org[MAXN], rot_a[MAXN], rot_b[MAXN];
+  __shared__ short n_live[MAXN], n_rot[MAXN], scan[MAXN];       // per block, at its first index
   __shared__ double red[THREADS / 64];
-  __shared__ short rank_of[kEighMaxSeq];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ int bad;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = tid & 15;
   constexpr int WAVES = THREADS / 64;
   const size_t prob = blockIdx.x;        // one problem per workgroup
   const float* K = Kb + prob * m * m;
   double* D = Db + prob * m;
   double* U = Ub + prob * m * m;
   int32_t* info = infob ? infob + prob : nullptr;
-  double* A = wsb + prob * ws_stride;
-  double* Zt = A + (size_t)m * m;
   const int n = m;
+  const int lda = LDS ? eigh_pitch(m) : m, ldq = QLDS ? lda : m;
+  double* A = LDS ? reinterpret_cast<double*>(smem_raw) : U;
+  double* Qt = QLDS ? A + (size_t)m * lda : wsb + prob * ws_stride;
+  double* Qnext = Qt + (size_t)m * ldq;
+  const int group = tid >> 4;            // sixteen lanes, which work on a row of a matrix together
+  constexpr int GROUPS = THREADS / 16;
 
-  // symmetrised, scaled copy; Zt = I
+  // symmetrised, scaled copy
   double amax = 0.0;
-  for (int el = tid; el < n * n; el += THREADS) {
-    const int i = el / n, j = el % n;
-    const double a = 0.5 * ((double)K[(size_t)i * n + j] + (double)K[(size_t)j * n + i]);
-    A[el] = a;
-    Zt[el] = i == j ? 1.0 : 0.0;
-    const double aa = fabs(a);
-    amax = aa > amax ? aa : amax;        // a NaN never wins; it surfaces as "not converged" below
-  }
+  for (int j = lane; j < n; j += 64)
+#pragma unroll 4
+    for (int i = wave; i < n; i += WAVES) {
+      const double a = 0.5 * ((double)K[(size_t)i * n + j] + (double)K[(size_t)j * n + i]);
+      A[(size_t)i * lda + j] = a;
+      Qt[(size_t)i * ldq + j] = i == j ? 1.0 : 0.0;
+      Qnext[(size_t)i * ldq + j] = 0.0;  // elements outside a vector's block are never written
+      const double aa = fabs(a);
+      amax = aa > amax ? aa : amax;      // a NaN never wins; it surfaces as "not converged" below
+    }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) { const double t = __shfl_xor(amax, o); amax = t > amax ? t : amax; }
-  __syncthreads();
   if (lane == 0) red[wave] = amax;
+  if (tid == 0) bad = 0;
   __syncthreads();
   amax = 0.0;
 #pragma unroll
@@ -202,269 +212,412 @@ __global__ __launch_bounds__(THREADS) void tridiag_eigh_kernel(const float* __re
   int expo = 0;
   if (amax > 0.0 && amax < 1.7e308) (void)frexp(amax, &expo);
   const double down = scalbn(1.0, 1 - expo), up = scalbn(1.0, expo - 1);
-  __syncthreads();
-  for (int el = tid; el < n * n; el += THREADS) A[el] *= down;
+  for (int i = wave; i < n; i += WAVES)
+    for (int j = lane; j < n; j += 64) A[(size_t)i * lda + j] *= down;      // the elements this thread wrote
   __syncthreads();
 
-  // ---- tridiagonalisation: three barriers per column ----
+  // ---- tridiagonalisation: two barriers per column, sixteen lanes per row ----
+  // The reflector of column k from row k of the (symmetric) matrix, by the sixteen lanes that hold the row (lane `sub` its
+  // elements k + sub + 16 t): sig the sum of squares behind element k + 1, x0 that element, diag element k.
+  auto reflector = [&](int k, double sig, double x0, double diag) {
+    double* vk = v + (k & 1) * MAXN;
+    if (sub == 0) d[k] = diag;
+    if (sig == 0.0) {                                         // column already reduced
+      if (sub == 0) { e[k] = x0; htau[k] = 0.0; }
+      return;
+    }
+    const double nrm = quick_sqrt(x0 * x0 + sig);
+    const double alpha = x0 > 0.0 ? -nrm : nrm;
+    const double v0 = x0 - alpha;
+    if (sub == 0) { e[k] = alpha; htau[k] = 2.0 * quick_rcp(v0 * v0 + sig); }
+    for (int j = k + sub; j < n; j += 16) {
+      if (j == k) continue;
+      double* a = A + (size_t)k * lda + j;                    // kept there for the back-transformation
+      const double vj = j == k + 1 ? v0 : *a;
+      vk[j] = vj;
+      *a = vj;
+    }
+  };
+  if (group == 0 && n > 2) {
+    double sig = 0.0, x0 = 0.0, diag = 0.0;
+    for (int j = sub; j < n; j += 16) {
+      const double x = A[j];
+      if (j == 0) diag = x;
+      else if (j == 1) x0 = x;
+      else sig += x * x;
+    }
+    reflector(0, row_sum(sig), __shfl(x0, 1, 16), diag);
+  }
+  __syncthreads();
   for (int k = 0; k + 2 < n; ++k) {
-    // trailing block: indices k+1 .. n-1; row k holds the column to reduce (the matrix is symmetric)
-    if (wave == 0) {                                          // the reflector, by one wave
-      double* rowk = A + (size_t)k * n;
-      double sig = 0.0;
-      for (int j = k + 2 + lane; j < n; j += 64) { const double x = rowk[j]; sig += x * x; }
-      sig = wave_sum(sig);
-      const double x0 = rowk[k + 1];
-      if (lane == 0) d[k] = rowk[k];
-      if (sig == 0.0) {                                       // column already reduced
-        if (lane == 0) { e[k] = x0; tau[k] = 0.0; }
-      } else {
-        const double nrm = sqrt(x0 * x0 + sig);
-        const double alpha = x0 > 0.0 ? -nrm : nrm;
-        const double v0 = x0 - alpha;
-        if (lane == 0) { e[k] = alpha; tau[k] = 2.0 / (v0 * v0 + sig); }
-        for (int j = k + 1 + lane; j < n; j += 64) {
-          const double vj = j == k + 1 ? v0 : rowk[j];
-          v[j] = vj;
-          rowk[j] = vj;                                       // kept for the accumulation of Q
-        }
+    const double tk = htau[k];
+    const double* vk = v + (k & 1) * MAXN;
+    if (tk != 0.0) {                                          // uniform
+      // p = tau A22 v
+      for (int i = k + 1 + group; i < n; i += GROUPS) {
+        const double* row = A + (size_t)i * lda;
+        double acc = 0.0;
+#pragma unroll 4
+        for (int j = k + 1 + sub; j < n; j += 16) acc += row[j] * vk[j];
+        acc = row_sum(acc);
+        if (sub == 0) w[i] = tk * acc;
       }
     }
     __syncthreads();
-    const double tk = tau[k];
-    if (tk == 0.0) continue;                                  // uniform
-    // p = tau A22 v: a wave takes four rows at a time (four independent streams of loads), lanes along the row
-    for (int i0 = k + 1 + wave; i0 < n; i0 += 4 * WAVES) {
-      double acc[4] = {0.0, 0.0, 0.0, 0.0};
-      const double* row[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) row[q] = A + (size_t)(i0 + q * WAVES < n ? i0 + q * WAVES : n - 1) * n;
-      for (int j = k + 1 + lane; j < n; j += 64) {
-        const double vj = v[j];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] += row[q][j] * vj;
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const double a = wave_sum(acc[q]);
-        if (lane == 0 && i0 + q * WAVES < n) w[i0 + q * WAVES] = tk * a;
-      }
-    }
-    __syncthreads();
-    // every wave forms p.v by itself (the same sum in the same order: the same bits), then
+    // every sixteen lanes form p.v by themselves (the same sum in the same order: the same bits), then
     // A22 -= v w^T + w v^T with w = p - (tau/2)(p.v) v formed where it is used; the two products are added
     // before they are subtracted, so (i, j) and (j, i) get the same bits
-    double pv = 0.0;
-    for (int j = k + 1 + lane; j < n; j += 64) pv += w[j] * v[j];
-    const double kk = 0.5 * tk * wave_sum(pv);
-    for (int i0 = k + 1 + wave; i0 < n; i0 += 4 * WAVES) {
-      double* row[4];
-      double vi[4], wi[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = i0 + q * WAVES < n ? i0 + q * WAVES : n - 1;
-        row[q] = A + (size_t)i * n; vi[q] = v[i]; wi[q] = __dsub_rn(w[i], __dmul_rn(kk, v[i]));
-      }
-      for (int j = k + 1 + lane; j < n; j += 64) {
-        const double vj = v[j], wj = __dsub_rn(w[j], __dmul_rn(kk, vj));
-        double a[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) a[q] = row[q][j];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const double p1 = __dmul_rn(vi[q], wj), p2 = __dmul_rn(wi[q], vj);
-          if (i0 + q * WAVES < n) row[q][j] = __dsub_rn(a[q], __dadd_rn(p1, p2));
+    double kk = 0.0;
+    if (tk != 0.0) {
+#pragma unroll 4
+      for (int j = k + 1 + sub; j < n; j += 16) kk += w[j] * vk[j];
+      kk = 0.5 * tk * row_sum(kk);
+    }
+    for (int i = k + 1 + group; i < n; i += GROUPS) {
+      const bool next_row = i == k + 1;                       // whose lanes form the next reflector
+      if (tk == 0.0 && !next_row) continue;
+      const double vi = tk != 0.0 ? vk[i] : 0.0, wi = tk != 0.0 ? __dsub_rn(w[i], __dmul_rn(kk, vi)) : 0.0;
+      double* row = A + (size_t)i * lda;
+      double sig = 0.0, x0 = 0.0, diag = 0.0;
+#pragma unroll 4
+      for (int j = k + 1 + sub; j < n; j += 16) {
+        double x = row[j];
+        if (tk != 0.0) {
+          const double vj = vk[j], wj = __dsub_rn(w[j], __dmul_rn(kk, vj));
+          const double p1 = __dmul_rn(vi, wj), p2 = __dmul_rn(wi, vj);
+          x = __dsub_rn(x, __dadd_rn(p1, p2));
+          row[j] = x;
         }
+        if (j == i) diag = x;
+        else if (j == i + 1) x0 = x;
+        else sig += x * x;                                    // of use in the next row only
       }
+      if (next_row && k + 3 < n) reflector(k + 1, row_sum(sig), __shfl(x0, 1, 16), diag);
     }
     __syncthreads();
   }
   if (tid == 0) {
-    if (n >= 2) { d[n - 2] = A[(size_t)(n - 2) * n + n - 2]; e[n - 2] = A[(size_t)(n - 2) * n + n - 1]; }
-    d[n - 1] = A[(size_t)(n - 1) * n + n - 1];
-    e[n - 1] = 0.0;
+    if (n >= 2) { d[n - 2] = A[(size_t)(n - 2) * lda + n - 2]; e[n - 2] = A[(size_t)(n - 2) * lda + n - 1]; }
+    d[n - 1] = A[(size_t)(n - 1) * lda + n - 1];
   }
   __syncthreads();
-
-  // ---- Zt = Q^T = H_{n-3} ... H_0, accumulated from the last reflector: Zt <- Zt H_k ----
-  // One barrier per reflector: v_k sits in one of two LDS buffers (v, w) while the next one is fetched into the other.
-  {
-    int kq = n - 3;
-    while (kq >= 0 && tau[kq] == 0.0) --kq;                   // uniform
-    if (kq >= 0)
-      for (int j = kq + 1 + tid; j < n; j += THREADS) v[j] = A[(size_t)kq * n + j];
-    __syncthreads();
-    for (int par = 0; kq >= 0; par ^= 1) {
-      const int k = kq;
-      const double tk = tau[k];
-      const double* vk = par ? w : v;
-      double* vnext = par ? v : w;
-      kq = k - 1;
-      while (kq >= 0 && tau[kq] == 0.0) --kq;                 // the next reflector that does anything (uniform)
-      if (kq >= 0)
-        for (int j = kq + 1 + tid; j < n; j += THREADS) vnext[j] = A[(size_t)kq * n + j];
-      for (int i0 = k + 1 + wave; i0 < n; i0 += 4 * WAVES) {
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        double* row[4];
+  double size = 0.0;                                          // of the tridiagonal matrix: largest sum of a row's magnitudes
+#pragma unroll 4
+  for (int i = lane; i < n; i += 64) {
+    const double x = fabs(d[i]) + (i + 1 < n ? fabs(e[i]) : 0.0) + (i > 0 ? fabs(e[i - 1]) : 0.0);
+    if (!(x < 1.7e308)) bad = 1;                              // NaN or infinity among the entries of K
+    size = fmax(size, x);
+  }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) row[q] = Zt + (size_t)(i0 + q * WAVES < n ? i0 + q * WAVES : n - 1) * n;
-        for (int j = k + 1 + lane; j < n; j += 64) {
-          const double vj = vk[j];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[q] += row[q][j] * vj;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] = tk * wave_sum(acc[q]);
-        for (int j = k + 1 + lane; j < n; j += 64) {
-          const double vj = vk[j];
-          double a[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) a[q] = row[q][j];
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (i0 + q * WAVES < n) row[q][j] = a[q] - acc[q] * vj;
-        }
-      }
-      __syncthreads();
-    }
+  for (int o = 32; o > 0; o >>= 1) size = fmax(size, __shfl_xor(size, o));
+  const double tol = 8.0 * kUlp * size;                       // what the merges may neglect
+  __syncthreads();
+  if (bad) {                                                  // uniform
+    for (int i = tid; i < n; i += THREADS) D[i] = __builtin_nan("");
+    for (int el = tid; el < n * n; el += THREADS) U[el] = __builtin_nan("");
+    if (info && tid == 0) *info = 1;
+    return;
   }
 
-  // ---- implicit QL with Wilkinson's shift ----
-  // The last wave generates the plane rotations of a QL step (a sequential recurrence over the tridiagonal
-  // matrix alone) while threads k < n apply the previous step's rotations to Zt: two rotation buffers in
-  // LDS (the second one reuses v and w), one barrier per step.  All 64 lanes of the generating wave compute
-  // the same values, so that its control flow is scalar; the entries of d and e a step walks over are read
-  // 64 at a time, one per lane, and handed to the recurrence by v_readlane: no LDS round trip on the
-  // dependent chain.
-  __shared__ int meta[2][4];               // {0: rotations of rows lo..hi | 1: finished with status lo, lo, hi}
-  const bool producer = wave == WAVES - 1;
-  int l = 0, iter = 0;                     // producer state (uniform over the wave)
-  double tst = 0.0;                        // largest |d| + |e| seen so far: what "negligible" is measured against
-  auto lane_value = [](double x, int src) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(x), src);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(x), src);
-    return __hiloint2double(hi, lo);
-  };
-  auto produce = [&](int buf) {
-    double* pc = buf ? v : rc;
-    double* ps = buf ? w : rs;
-    for (;;) {
-      if (l >= n) { if (lane == 0) { meta[buf][0] = 1; meta[buf][1] = 0; } return; }
-      const double t = fabs(d[l]) + fabs(e[l]);
-      tst = t > tst ? t : tst;
-      int mm = n - 1;                      // first index >= l whose e is negligible (e[n-1] = 0 counts)
-      for (int base = l; base < n; base += 64) {
-        const int idx = base + lane;
-        const bool stop = idx >= n - 1 || fabs(e[idx < n ? idx : n - 1]) <= 1.1102230246251565e-16 * tst;
-        const unsigned long long hit = __ballot(stop);
-        if (hit) { mm = base + __ffsll((long long)hit) - 1; break; }
+  // ---- divide and conquer ----
+  int levels = 0;
+  while ((1 << levels) < n) ++levels;
+  // Tear the off-diagonal entries between the first level's pairs out, d_i -= |e| on both sides, and solve the pairs (some
+  // are single indices) by one rotation each.
+  const int pairs = 1 << (levels > 0 ? levels - 1 : 0);
+  for (int s = tid; s < pairs; s += THREADS) {
+    const int b0 = (int)((long long)s * n / pairs), b2 = (int)((long long)(s + 1) * n / pairs);
+    if (b0 == b2) continue;
+    double d0 = d[b0] - (b0 > 0 ? fabs(e[b0 - 1]) : 0.0);
+    double d1 = d[b2 - 1];
+    if (b2 < n) { if (b2 - b0 == 1) d0 -= fabs(e[b2 - 1]); else d1 -= fabs(e[b2 - 1]); }
+    if (b2 - b0 == 2) {
+      const double x = e[b0];
+      if (x != 0.0) {
+        // tan of the angle that clears x: the smaller root of t^2 + 2 q t - 1, q = (d1 - d0) / (2 x)
+        const double q = (d1 - d0) / (2.0 * x);
+        const double t = (q >= 0.0 ? 1.0 : -1.0) / (fabs(q) + sqrt(1.0 + q * q));
+        const double c = 1.0 / sqrt(1.0 + t * t), sn = t * c;
+        d0 -= t * x;
+        d1 += t * x;
+        Qt[(size_t)b0 * ldq + b0] = c;        Qt[(size_t)b0 * ldq + b0 + 1] = -sn;
+        Qt[(size_t)(b0 + 1) * ldq + b0] = sn; Qt[(size_t)(b0 + 1) * ldq + b0 + 1] = c;
       }
-      mm = __builtin_amdgcn_readfirstlane(mm);
-      if (mm == l) { ++l; iter = 0; continue; }                              // d[l] is an eigenvalue
-      if (iter++ >= kMaxQlIterations) { if (lane == 0) { meta[buf][0] = 1; meta[buf][1] = 1; } return; }
-      double g = (d[l + 1] - d[l]) / (2.0 * e[l]);
-      const double r0 = sqrt(g * g + 1.0);
-      g = d[mm] - d[l] + e[l] / (g + (g >= 0.0 ? r0 : -r0));
-      double sn = 1.0, cs = 1.0, p = 0.0, dip1 = d[mm];
-      int i = mm - 1;
-      bool under = false;
-      while (i >= l && !under) {
-        const int cnt = __builtin_amdgcn_readfirstlane(i - l + 1 < 64 ? i - l + 1 : 64);
-        const int mine = i - lane >= 0 ? i - lane : 0;
-        const double dl = d[mine], el = e[mine];          // this step writes d and e above index i only
-        for (int q = 0; q < cnt; ++q, --i) {
-          const double ei = lane_value(el, q), di = lane_value(dl, q);
-          const double f = sn * ei, b = cs * ei;
-          const double h = f * f + g * g;
-          if (__builtin_amdgcn_readfirstlane((int)(h == 0.0))) {
-            if (lane == 0) { e[i + 1] = 0.0; d[i + 1] = dip1 - p; e[mm] = 0.0; }
-            under = true;
-            break;
-          }
-          const double inv = rsqrt(h);
-          sn = f * inv; cs = g * inv;
-          const double g2 = dip1 - p;
-          const double r2 = (di - g2) * sn + 2.0 * cs * b;
-          p = sn * r2;
-          g = cs * r2 - b;
-          if (lane == 0) { e[i + 1] = h * inv; d[i + 1] = g2 + p; pc[i] = cs; ps[i] = sn; }
-          dip1 = di;
-        }
-      }
-      if (!under && lane == 0) { d[l] -= p; e[l] = g; e[mm] = 0.0; }
-      const int lo = under ? i + 1 : l, hi = mm - 1;
-      if (hi < lo) continue;
-      if (lane == 0) { meta[buf][0] = 0; meta[buf][1] = lo; meta[buf][2] = hi; }
-      return;
+      d[b0 + 1] = d1;
     }
-  };
-  if (producer) produce(0);
+    d[b0] = d0;
+  }
+  double* const rot_c = v;                                    // the reflectors' vectors are done with
+  double* const rot_s = w;
   __syncthreads();
-  int status = 0;
-  for (int cur = 0;; cur ^= 1) {
-    const int kind = meta[cur][0], lo = meta[cur][1], hi = meta[cur][2];
-    if (kind != 0) { status = lo; break; }                                   // uniform
-    if (producer) produce(cur ^ 1);
-    if (tid < n) {
-      const double* pc = cur ? v : rc;
-      const double* ps = cur ? w : rs;
-      double carry = Zt[(size_t)(hi + 1) * n + tid];
-      for (int i = hi; i >= lo; i -= 8) {
-        double z[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) z[q] = Zt[(size_t)(i - q >= lo ? i - q : lo) * n + tid];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          if (i - q >= lo) {
-            const double cs = pc[i - q], sn = ps[i - q];
-            Zt[(size_t)(i - q + 1) * n + tid] = sn * z[q] + cs * carry;
-            carry = cs * z[q] - sn * carry;
-          }
-        }
+  for (int lev = 1; lev < levels; ++lev) {
+    const int nb = 1 << (levels - lev);                       // blocks before the merges of this level
+    auto block_of = [&](int i, int& b0, int& b1, int& b2) {
+      int s = (int)((long long)i * (nb >> 1) / n);
+      while ((int)((long long)(2 * s + 2) * n / nb) <= i) ++s;
+      while ((int)((long long)(2 * s) * n / nb) > i) --s;
+      b0 = (int)((long long)(2 * s) * n / nb);
+      b1 = (int)((long long)(2 * s + 1) * n / nb);
+      b2 = (int)((long long)(2 * s + 2) * n / nb);
+    };
+    // z, into sorted order; no scan asked for yet
+    for (int i = group; i < n; i += GROUPS) {
+      int b0, b1, b2;
+      block_of(i, b0, b1, b2);
+      const double di = d[i];
+      int rank = 0;
+      for (int j = b0 + sub; j < b2; j += 16) {
+        const double dj = d[j];
+        rank += (dj < di || (dj == di && j < i)) ? 1 : 0;
       }
-      Zt[(size_t)lo * n + tid] = carry;
+      rank = row_count(rank);
+      if (sub == 0) {
+        double z = 0.0;
+        if (b0 < b1 && b1 < b2)
+          z = 0.70710678118654752440 *
+              (i < b1 ? Qt[(size_t)i * ldq + b1 - 1] : (e[b1 - 1] < 0.0 ? -1.0 : 1.0) * Qt[(size_t)i * ldq + b1]);
+        ds[b0 + rank] = di;
+        zs[b0 + rank] = z;
+        perm[b0 + rank] = (short)i;
+        scan[i] = 0;
+        n_rot[i] = 0;
+      }
     }
     __syncthreads();
+    for (int i = tid; i < n; i += THREADS) {                  // i: a sorted position
+      int b0, b1, b2;
+      block_of(i, b0, b1, b2);
+      const double rho = b0 < b1 && b1 < b2 ? 2.0 * fabs(e[b1 - 1]) : 0.0;
+      const double z0 = zs[i];
+      bool want = rho * fabs(z0) <= tol;
+      if (i + 1 < b2) {
+        const double z1 = zs[i + 1];
+        want = want || fabs((ds[i + 1] - ds[i]) * z0 * z1) <= tol * (z0 * z0 + z1 * z1);
+      }
+      if (want) scan[b0] = 1;
+      list[i] = (short)i;                                     // nothing deflated
+      if (i == b0) n_live[b0] = (short)(b2 - b0);
+    }
+    __syncthreads();
+    for (int i = tid; i < n; i += THREADS) {
+      int b0, b1, b2;
+      block_of(i, b0, b1, b2);
+      if (i != b0 || !scan[b0]) continue;
+      const double rho = b0 < b1 && b1 < b2 ? 2.0 * fabs(e[b1 - 1]) : 0.0;
+      int live = 0, gone = 0, turns = 0, pend = -1;
+      double dp = 0.0, zp = 0.0;                              // the pending position's values
+      double dnext = ds[b0], znext = zs[b0];                  // one position ahead
+      for (int r = b0; r < b2; ++r) {
+        const double dr = dnext, zr = znext;
+        if (r + 1 < b2) { dnext = ds[r + 1]; znext = zs[r + 1]; }
+        if (rho * fabs(zr) <= tol) { list[b2 - 1 - gone++] = (short)r; continue; }
+        if (pend >= 0) {
+          const double r2 = zr * zr + zp * zp, t = dr - dp;
+          if (fabs(t * zr * zp) <= tol * r2) {
+            const double h = sqrt(r2), c = zr / h, s = -zp / h;
+            rot_a[b0 + turns] = perm[pend]; rot_b[b0 + turns] = perm[r];
+            rot_c[b0 + turns] = c; rot_s[b0 + turns] = s;
+            ++turns;
+            ds[pend] = dp * c * c + dr * s * s;
+            const double moved = dp * s * s + dr * c * c;
+            ds[r] = moved; zs[r] = h; zs[pend] = 0.0;
+            list[b2 - 1 - gone++] = (short)pend;
+            pend = r; dp = moved; zp = h;
+            continue;
+          }
+          list[b0 + live++] = (short)pend;
+        }
+        pend = r; dp = dr; zp = zr;
+      }
+      if (pend >= 0) list[b0 + live++] = (short)pend;
+      n_live[b0] = (short)live;
+      n_rot[b0] = (short)turns;
+    }
+    __syncthreads();
+    // the rotations, in order, thread = element of the vectors; the poles that are left, side by side
+    for (int i = tid; i < n; i += THREADS) {
+      int b0, b1, b2;
+      block_of(i, b0, b1, b2);
+      for (int t = 0; t < n_rot[b0]; ++t) {
+        double* qa = Qt + (size_t)rot_a[b0 + t] * ldq + i;
+        double* qb = Qt + (size_t)rot_b[b0 + t] * ldq + i;
+        const double c = rot_c[b0 + t], s = rot_s[b0 + t], xa = *qa, xb = *qb;
+        *qa = c * xa + s * xb;
+        *qb = c * xb - s * xa;
+      }
+      dk[i] = ds[list[i]];                                    // deflated ones too, behind the others
+      zk[i] = zs[list[i]];
+    }
+    __syncthreads();
+    constexpr int LPR = MAXN <= 128 ? 4 : 16;
+    for (int i = tid / LPR; i < n; i += THREADS / LPR) {
+      int b0, b1, b2;
+      block_of(i, b0, b1, b2);
+      const int k = n_live[b0], j = i - b0;
+      if (j < k) {
+        int o;
+        double t;
+        secular_root<LPR>(dk + b0, zk + b0, k, 2.0 * fabs(e[b1 - 1]), j, tid % LPR, o, t);
+        if (tid % LPR == 0) { org[i] = (short)o; rtau[i] = t; }
+      }
+    }
+    __syncthreads();
+    for (int i = group; i < n; i += GROUPS) {
+      int b0, b1, b2;
+      block_of(i, b0, b1, b2);
+      const int k = n_live[b0], q = i - b0;
+      if (q >= k) continue;                                   // uniform over the sixteen lanes
+      const double di = dk[i];
+      const double* dd = dk + b0;
+      double p = 1.0;
+      for (int j = sub; j < k; j += 16) {
+        const double diff = (dd[org[b0 + j]] - di) + rtau[b0 + j];           // root j - pole q
+        p *= j == k - 1 ? diff : diff * quick_rcp((j < q ? dd[j] : dd[j + 1]) - di);
+      }
+      p = row_product(p);
+      if (sub == 0) zh[i] = copysign(sqrt(fabs(p)), zk[i]);
+    }
+    __syncthreads();
+    // New vectors, as a product of matrices in 16x16 tiles: rows u_j (zeros outside j's block, the unit vector for a
+    // deflated position) times the old vectors in sorted order.  Lane l supplies row l % 16, column l / 16 of a step of
+    // the left factor, which it forms itself, and row l / 16, column l % 16 of the right one.
+    {
+      typedef double f64x4 __attribute__((ext_vector_type(4)));
+      const int nt = (n + 15) / 16, l16 = lane & 15, l4 = lane >> 4;
+      for (int tt = wave; tt < nt * nt; tt += WAVES) {
+        const int jt = tt / nt * 16, rt = tt % nt * 16;
+        int lo, mid, hi, unused;
+        block_of(jt, lo, mid, unused);
+        block_of(jt + 15 < n ? jt + 15 : n - 1, unused, mid, hi);
+        if (rt + 16 <= lo || rt >= hi) continue;
+        const int j = jt + l16 < n ? jt + l16 : n - 1, r = rt + l16 < n ? rt + l16 : n - 1;
+        int b0, b1, b2;
+        block_of(j, b0, b1, b2);
+        const int k = n_live[b0];
+        const bool live = j - b0 < k;
+        const double dorg = live ? dk[b0 + org[j]] : 0.0, t = live ? rtau[j] : 0.0;
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        double s = 0.0;
+        for (int i0 = lo; i0 < hi; i0 += 4) {
+          const int i = i0 + l4, ic = i < n ? i : n - 1;
+          double u = 0.0;
+          if (live) {
+            if (i >= b0 && i < b0 + k) u = zh[ic] * quick_rcp((dk[ic] - dorg) - t);
+          } else {
+            u = i == j ? 1.0 : 0.0;
+          }
+          s += u * u;
+          const double x = Qt[(size_t)perm[list[ic]] * ldq + r];
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(u, x, acc, 0, 0, 0);
+        }
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        const double norm = rsqrt(s);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {                         // lane holds rows 4 q + l / 16, column l % 16 of the tile
+          const int row = 4 * q + l4;
+          const double scale = __shfl(norm, row, 64);
+          if (jt + row < n && rt + l16 < n) Qnext[(size_t)(jt + row) * ldq + rt + l16] = acc[q] * scale;
+        }
+      }
+      for (int i = tid; i < n; i += THREADS) {
+        int b0, b1, b2;
+        block_of(i, b0, b1, b2);
+        d[i] = i - b0 < n_live[b0] ? dk[b0 + org[i]] + rtau[i] : dk[i];
+      }
+    }
+    __syncthreads();
+    double* const swap = Qt; Qt = Qnext; Qnext = swap;
   }
-  __syncthreads();
 
+  // ---- U = H_0 ... H_{n-3} Q^T: sixteen lanes (a wave, past 256 elements) per vector, its elements in registers ----
+  constexpr int VL = MAXN <= 256 ? 16 : 64, NE = MAXN / VL;
+  const int vl = tid % VL;
+  for (int i = tid / VL; i < n; i += THREADS / VL) {
+    double x[NE], ahead[NE];                                  // ahead: the next reflector's vector, fetched one step early
+#pragma unroll
+    for (int t = 0; t < NE; ++t) x[t] = t * VL + vl < n ? Qt[(size_t)i * ldq + t * VL + vl] : 0.0;
+    auto fetch = [&](int k) {
+#pragma unroll
+      for (int t = 0; t < NE; ++t) {
+        const int r = t * VL + vl;
+        ahead[t] = k >= 0 && r > k && r < n ? A[(size_t)k * lda + r] : 0.0;
+      }
+    };
+    fetch(n - 3);
+    for (int k = n - 3; k >= 0; --k) {
+      const double tk = htau[k];
+      double vk[NE], dot = 0.0;
+#pragma unroll
+      for (int t = 0; t < NE; ++t) vk[t] = ahead[t];
+      fetch(k - 1);
+      if (tk == 0.0) continue;                                // uniform
+#pragma unroll
+      for (int t = 0; t < NE; ++t) dot += vk[t] * x[t];
+      dot = tk * (VL == 16 ? row_sum(dot) : wave_total(dot));
+#pragma unroll
+      for (int t = 0; t < NE; ++t) x[t] -= dot * vk[t];
+    }
+#pragma unroll
+    for (int t = 0; t < NE; ++t)
+      if (t * VL + vl < n) Qt[(size_t)i * ldq + t * VL + vl] = x[t];
+  }
   // ascending order by rank (ties broken by index), eigenvectors as columns of U
   for (int i = tid; i < n; i += THREADS) {
     const double di = d[i];
     int rank = 0;
+#pragma unroll 8
     for (int j = 0; j < n; ++j) {
       const double dj = d[j];
       rank += (dj < di || (dj == di && j < i)) ? 1 : 0;
     }
     D[rank] = di * up;
-    rank_of[i] = (short)rank;
+    perm[rank] = (short)i;
   }
   __syncthreads();
-  for (int el = tid; el < n * n; el += THREADS) {
-    const int i = el / n, k = el % n;
-    U[(size_t)k * n + rank_of[i]] = Zt[(size_t)i * n + k];
+  for (int c = lane; c < n; c += 64) {
+    const double* q = Qt + (size_t)perm[c] * ldq;
+#pragma unroll 4
+    for (int r = wave; r < n; r += WAVES) U[(size_t)r * n + c] = q[r];
   }
-  if (info && tid == 0) *info = status;
+  if (info && tid == 0) *info = bad;
 }
 
-constexpr int kSolveThreads = 256;
+constexpr int kSolveThreads = 1024;
 
-// c[l] = U ((U^T A) / (D + reg_l)) for each regulariser of the sweep.
+// c[l] = U ((U^T A) / (D + reg_l)) for each regulariser of the sweep.  Latency-bound: every pass over U is spread over the
+// waves by rows (a thread that walked a column, and then a row, by itself waited for one load after the other: 48 us at 64
+// sequences and three regularisers, 17 now).
 __global__ __launch_bounds__(kSolveThreads) void eigh_solve_kernel(EighSolveArgs a) {
-  __shared__ double y[kEighMaxSeq];
-  __shared__ double red[kSolveThreads / 64];
+  constexpr int WAVES = kSolveThreads / 64;
+  __shared__ double y[kEighMaxSeq], f[kEighMaxSeq];
+  __shared__ double part[WAVES][64];
+  __shared__ double red[WAVES];
   __shared__ double sh_scale;
-  const int tid = threadIdx.x, m = a.n_seq;
+  __shared__ int bad;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = a.n_seq;
   const size_t prob = blockIdx.x;        // one problem per workgroup
   a.D += prob * m; a.U += prob * m * m; a.A += prob * m; a.c += prob * a.n_lambda * m;
   if (a.ema_state) a.ema_state += prob * 2;
   if (a.info) a.info += prob;
   double tr = 0.0;
-  for (int j = tid; j < m; j += kSolveThreads) {
+  for (int j = tid; j < m; j += kSolveThreads) tr += a.D[j];
+  if (tid == 0) bad = 0;
+  // y = U^T A: a wave takes every sixteenth row, lanes along the row
+  for (int j0 = 0; j0 < m; j0 += 64) {
+    const int j = j0 + lane < m ? j0 + lane : m - 1;
     double s = 0.0;
-    for (int i = 0; i < m; ++i) s += a.U[(size_t)i * m + j] * (double)a.A[i];
-    y[j] = s;
-    tr += a.D[j];
+#pragma unroll 4
+    for (int i = wave; i < m; i += WAVES) s += a.U[(size_t)i * m + j] * (double)a.A[i];
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && j0 + lane < m) {
+      s = 0.0;
+#pragma unroll
+      for (int q = 0; q < WAVES; ++q) s += part[q][lane];
+      y[j] = s;
+    }
+    __syncthreads();
   }
   const double mean_d = block_sum<kSolveThreads>(tr, red) / (double)m;
   if (tid == 0) {
@@ -481,18 +634,29 @@ __global__ __launch_bounds__(kSolveThreads) void eigh_solve_kernel(EighSolveArgs
   }
   __syncthreads();
   const double scale = sh_scale;
-  int bad = 0;
   for (int l = 0; l < a.n_lambda; ++l) {
     const double reg = (double)a.lambdas[l] * scale;
-    for (int i = tid; i < m; i += kSolveThreads) {
-      double s = 0.0;
-      for (int j = 0; j < m; ++j) {
-        const double den = a.D[j] + reg;
-        if (den > 0.0) s += a.U[(size_t)i * m + j] * (y[j] / den);
-        else if (i == 0) ++bad;
-      }
-      a.c[(size_t)l * m + i] = (float)s;
+    for (int j = tid; j < m; j += kSolveThreads) {
+      const double den = a.D[j] + reg;
+      f[j] = den > 0.0 ? y[j] / den : 0.0;
+      if (!(den > 0.0)) atomicAdd(&bad, 1);
     }
+    __syncthreads();
+    // a wave takes four rows at a time
+    for (int i0 = wave * 4; i0 < m; i0 += WAVES * 4) {
+      double s[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int j = lane; j < m; j += 64) {
+        const double fj = f[j];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] += a.U[(size_t)(i0 + q < m ? i0 + q : m - 1) * m + j] * fj;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double t = wave_total(s[q]);
+        if (lane == 0 && i0 + q < m) a.c[(size_t)l * m + i0 + q] = (float)t;
+      }
+    }
+    __syncthreads();
   }
   if (a.info && tid == 0) *a.info = bad;
 }
@@ -504,35 +668,32 @@ size_t eigh_workspace(int m) {
   return 2 * (size_t)n * (n + 1) * sizeof(double);
 }
 
-template <int THREADS>
-hipError_t launch_jacobi(const float* K, int m, int batch, double* D, double* U, int32_t* info, size_t smem,
-                         double* gA, double* gV, size_t ws_stride, hipStream_t s) {
-  auto kern = jacobi_eigh_kernel<THREADS>;
+template <int THREADS, int MAXN, bool LDS, bool QLDS>
+hipError_t launch_divide(const float* K, int m, int batch, double* D, double* U, int32_t* info, double* ws,
+                         size_t ws_stride, hipStream_t s) {
+  auto kern = divide_eigh_kernel<THREADS, MAXN, LDS, QLDS>;
+  constexpr int matrices = LDS ? (QLDS ? 3 : 1) : 0;
+  // eigh_pitch lets no single matrix grow past 128 x 128; 64 x 80 is the largest of three
+  constexpr size_t most = (size_t)(QLDS ? matrices * 64 * 80 : matrices * 128 * 128) * sizeof(double);
   // once per process (static initialisation is thread-safe); a failure is returned by every call
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kEighLdsBytes);
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(batch), dim3(THREADS), smem, s, K, m, D, U, info, gA, gV, ws_stride);
+  hipLaunchKernelGGL(kern, dim3(batch), dim3(THREADS), (size_t)matrices * m * eigh_pitch(m) * sizeof(double), s, K, m, D, U, info, ws,
+                     ws_stride);
   return hipGetLastError();
 }
 
 hipError_t launch_ntk_eigh(const float* K, int m, int batch, double* D, double* U, int32_t* info, void* workspace,
                            hipStream_t s) {
-  const int n = (m + 1) & ~1;
-  const size_t one = (size_t)n * (n + 1) * sizeof(double);
   double* ws = static_cast<double*>(workspace);
-  size_t smem;
-  double *gA = nullptr, *gV = nullptr;
   const size_t ws_stride = eigh_workspace(m) / sizeof(double);      // doubles per problem
-  if (m >= kEighTridiagonalFrom) {
-    hipLaunchKernelGGL(tridiag_eigh_kernel<1024>, dim3(batch), dim3(1024), 0, s, K, m, D, U, info, ws, ws_stride);
-    return hipGetLastError();
-  }
-  if (2 * one <= kEighLdsBytes) smem = 2 * one;                       // both in LDS
-  else if (one <= kEighLdsBytes) { smem = one; gV = ws; }             // work matrix in LDS, eigenvectors in L2
-  else { smem = 0; gA = ws; gV = ws + (size_t)n * (n + 1); }
-  return n <= 32 ? launch_jacobi<256>(K, m, batch, D, U, info, smem, gA, gV, ws_stride, s)
-                 : launch_jacobi<1024>(K, m, batch, D, U, info, smem, gA, gV, ws_stride, s);
+  // where the matrices lie follows from what fits the LDS; 512 threads up to 32 sequences, 1024 above (64: 243 us against 289)
+  if (m <= 32) return launch_divide<512, 64, true, true>(K, m, batch, D, U, info, ws, ws_stride, s);
+  if (m <= 64) return launch_divide<1024, 64, true, true>(K, m, batch, D, U, info, ws, ws_stride, s);
+  if (m <= 128) return launch_divide<1024, 128, true, false>(K, m, batch, D, U, info, ws, ws_stride, s);
+  if (m <= 256) return launch_divide<1024, 256, false, false>(K, m, batch, D, U, info, ws, ws_stride, s);
+  return launch_divide<1024, kEighMaxSeq, false, false>(K, m, batch, D, U, info, ws, ws_stride, s);
 }
 
 hipError_t launch_eigh_solve(const EighSolveArgs& a, hipStream_t s) {

@@ -232,7 +232,6 @@ hipError_t launch_gram_norms(const float* K, int m, float* fisher_sq, float* gra
 
 // Eigendecomposition route of the interacting variant.
 constexpr int kEighMaxSeq = 1024;
-constexpr size_t kEighLdsBytes = 144 * 1024;     // work matrix + eigenvectors in LDS up to this size
 constexpr int kEighMaxLambdas = 16;
 struct EighSolveArgs {
   const double* D;             // [batch][n_seq]

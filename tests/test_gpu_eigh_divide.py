@@ -1,0 +1,67 @@
+"""The eigendecomposition on matrices that exercise the divide and conquer's deflation and its sizes (first-level pairs
+and single indices, where the matrices lie, LDS pitches): eigenvalues, orthogonality and reconstruction to rounding."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_23353_amd import isopo
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrix(kind, m, rng):
+    if kind == "gram":
+        J = rng.standard_normal((m, 2 * m))
+        return J @ J.T
+    if kind == "identity":
+        return np.eye(m)
+    if kind == "low_rank":
+        J = rng.standard_normal((m, max(1, m // 3)))
+        return J @ J.T
+    if kind == "toeplitz":                                # tridiagonal, every coupling alike
+        return 2 * np.eye(m) - np.eye(m, k=1) - np.eye(m, k=-1)
+    if kind == "wilkinson":                               # pairs of eigenvalues that agree to many digits
+        return np.diag(np.abs(np.arange(m) - (m - 1) / 2)) + np.eye(m, k=1) + np.eye(m, k=-1)
+    if kind == "blocks":                                  # equal blocks, weakly coupled: many equal poles
+        b = 2 * np.eye(m) + 0.5 * (np.eye(m, k=1) + np.eye(m, k=-1))
+        cut = np.arange(4, m - 1, 5)
+        b[cut, cut + 1] = b[cut + 1, cut] = 1e-7
+        return b
+    if kind == "graded":
+        s = 10.0 ** -np.linspace(0, 12, m)
+        J = rng.standard_normal((m, 2 * m)) * s[:, None]
+        return J @ J.T
+    if kind == "duplicates":                              # pairs of equal sequences
+        J = rng.standard_normal((m, 2 * m))
+        J[1::2] = J[0:m - m % 2:2]
+        return J @ J.T
+    raise ValueError(kind)
+
+
+@pytest.mark.parametrize("kind", ["gram", "identity", "low_rank", "toeplitz", "wilkinson", "blocks", "graded", "duplicates"])
+@pytest.mark.parametrize("m", [1, 2, 3, 5, 6, 7, 17, 31, 33, 49, 63, 65, 97, 113, 115, 127, 129, 255, 257])
+def test_divide_and_conquer(gpu_device, kind, m):
+    K = _matrix(kind, m, np.random.default_rng(m)).astype(np.float32)
+    K = (K + K.T) / 2
+    D, U, info = isopo.ntk_eigh(torch.from_numpy(np.stack([K, 3 * K])).to(gpu_device))
+    assert info.tolist() == [0, 0]
+    for b, f in enumerate((1.0, 3.0)):
+        Kd = (np.float32(f) * K).astype(np.float64)
+        Dh, Uh = D[b].cpu().numpy(), U[b].cpu().numpy()
+        ref = np.linalg.eigvalsh(Kd)
+        # backward stable: a modest multiple of n rounding errors of the norm
+        tol = 16 * (m + 8) * 2.0 ** -53
+        size = max(np.abs(ref).max(), 1e-300)
+        assert (np.diff(Dh) >= 0).all()
+        assert np.abs(Dh - ref).max() <= tol * size
+        assert np.abs(Uh.T @ Uh - np.eye(m)).max() <= tol
+        assert np.abs((Uh * Dh) @ Uh.T - Kd).max() <= tol * size
+
+
+@pytest.mark.parametrize("m", [3, 40, 150])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_non_finite_entries_are_reported(gpu_device, m, value):
+    K = torch.eye(m, device=gpu_device).repeat(2, 1, 1)
+    K[0, m // 2, 0] = K[0, 0, m // 2] = value
+    D, U, info = isopo.ntk_eigh(K)
+    assert info.tolist() == [1, 0] and torch.isfinite(D[1]).all() and not torch.isfinite(D[0]).any()
