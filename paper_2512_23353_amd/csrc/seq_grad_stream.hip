@@ -74,6 +74,7 @@ struct StreamParams {
   int whole_tiles;                 // sum-over-all-tokens mode: tiles before this one are not split
   int xcd_start[9];                // XCD x takes (item, tile) pairs [xcd_start[x], xcd_start[x+1]), item-major
   unsigned* queue;                 // persistent mode: eight work counters, one per XCD, zero at launch
+  int stream_stores;               // row-major stash: non-temporal stores
 };
 
 // 16 bytes per lane from a buffer straight into LDS: lane l lands at lds_addr + 16*l.
@@ -768,9 +769,12 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
             const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a + 4 * PT));
             const int m = m0 + wm * WM + i * 32 + 16 * rb + l;
             const int n = n0 + wn * WN + jp * 64 + 8 * pc;
-            if (m < p.row_end && n < p.d_in)
-              __builtin_nontemporal_store(__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7),
-                                          (s16x8*)(outp + (size_t)(m - p.out_row0) * p.d_in + n));
+            if (m < p.row_end && n < p.d_in) {
+              const s16x8 piece = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+              s16x8* o = (s16x8*)(outp + (size_t)(m - p.out_row0) * p.d_in + n);
+              if (p.stream_stores) __builtin_nontemporal_store(piece, o);
+              else *o = piece;
+            }
           }
         }
       }
@@ -834,6 +838,12 @@ hipError_t launch_stream(const SeqGradArgs& a, const ContractionPlan& pl, hipStr
                          unsigned* queue = nullptr) {
   StreamParams p;
   p.queue = queue;
+  // The row-major epilogue stores half lines at a time, of rows that start anywhere in a line.  Left to the L2, the halves
+  // meet there; stored non-temporally each goes to memory by itself (2344x2048, 60 sequences of 31 tokens: 482 us
+  // against 164; 1000x2728, 24 of 400: 123 against 96; 1584x4352, 56 of 2350: 1810 against 1731).  Only narrow layers on
+  // long sequences lose more by the stash in their L2 than they gain (176x5632, 34 of 626: 86 against 105; but 200x3000,
+  // 100 of 180: 82 against 65).
+  p.stream_stores = BM == 128 && (long long)a.n_tokens >= 256LL * a.n_seq;
   p.c = a.c;
   p.X = static_cast<const u16*>(a.X); p.Delta = static_cast<const u16*>(a.Delta); p.off = a.off; p.out = a.out;
   p.d_in = a.d_in; p.d_out = a.d_out; p.n_seq = a.n_seq; p.n_tokens = a.n_tokens;
