@@ -6,15 +6,53 @@
 
 namespace isopo {
 
+// Row-major per-sequence launches whose widths are no multiples of 256 (others may keep the stash in tile order, whose
+// tile is part of a layout): 128x128 tiles where they are modelled faster by 10 %, over stashes that the last-level cache
+// takes (beyond it they lose: 2984x560, 101 sequences of 71 tokens, 337 MB: 145 / 157 us).  A compute unit takes
+//   256: ceil(items / 256) whole items of  27 ns per token + 8 us   (one workgroup at a time)
+//   128: items / 256 items of 9.8 ns per token + 1.5 us             (two at a time)
+// and neither is faster than the stash is written (3.2 TB/s).  Measured, 256 against 128: 264x1280, 106 sequences of 260
+// tokens 63 / 44 us; 2048x1032, 8 of 780: 50 / 41; 512x2056, 40 of 200: 42 / 36; 1000x2728, 24 of 420: 94 / 97; 648x3600,
+// 60 of 1750: 585 / 770.  Of 36 random layers this side of the line 28 gained, by 1.2x on average and 1.8x at most; 384x10504,
+// 26 of 374, lost most (169 / 175).
+static bool small_tiles_win(int rows, int d_in, int n_tokens, int n_seq) {
+  auto tiles = [&](int t) { return (double)((rows + t - 1) / t) * ((d_in + t - 1) / t) * n_seq; };
+  const double len = (double)n_tokens / n_seq, write = (double)rows * d_in * n_seq * 2.0 / 3.2e12;
+  const double items = tiles(256);
+  double big = (double)(long long)((items + 255.0) / 256.0) * (len * 27e-9 + 8e-6);
+  double small = tiles(128) / 256.0 * (len * 9.8e-9 + 1.5e-6);
+  if (big < write) big = write;
+  if (small < write) small = write;
+  return small < 0.9 * big && 2.0 * rows * d_in * n_seq <= 256.0 * (1 << 20);
+}
+
+static ContractionPlan plan_with_tile(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host, bool per_sequence,
+                                      bool big);
+
 ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
-                                 bool per_sequence) {
-  ContractionPlan pl;
-  constexpr int kBlockTokens = 32;
+                                 bool per_sequence, bool weighted) {
   const long long big_tiles = (long long)((rows + 255) / 256) * ((d_in + 255) / 256);
   // 256x256 tiles (one workgroup per CU) when they alone fill the chip, else 128x128 (two per CU).  In the
   // sum-over-all-tokens mode the token split supplies parallelism too.
   const long long par = per_sequence ? n_seq : (n_tokens / 1024 > 1 ? n_tokens / 1024 : 1);
-  const bool big = rows >= 256 && d_in >= 256 && big_tiles * par >= 256;
+  bool big = rows >= 256 && d_in >= 256 && big_tiles * par >= 256;
+  if (big && per_sequence && (rows % 256 || d_in % 256) && small_tiles_win(rows, d_in, n_tokens, n_seq)) big = false;
+  ContractionPlan pl = plan_with_tile(rows, d_in, n_tokens, n_seq, off_host, per_sequence, big);
+  // A weighted sum cut into token chunks, of few tiles and with operands that stay in the last-level cache: 128x128 tiles,
+  // whose four times as many workgroups need fewer chunks, are 5 - 25 % faster (1536x1536, 10^4 tokens: 87 -> 67 us; 2048x2048,
+  // 1.4 10^4: 137 -> 122; 1024x4096, 1.2 10^4: 120 -> 106).  With more tiles or tokens their twice as many reads cost more
+  // (2048x2304, 1.2 10^4: 132 -> 159; 1536x2560, 2.1 10^4: 173 -> 183, and 8.9 10^4: 556 -> 1020), and the plain sum is
+  // faster on the large ones (1024x1024, 4.9 10^4: 118 -> 141), as is either one uncut (1536x8960: 221 -> 276).
+  if (weighted && !per_sequence && big && pl.n_chunks > 1 && big_tiles <= 64 &&
+      2LL * n_tokens * (rows + d_in) <= 128LL << 20)
+    pl = plan_with_tile(rows, d_in, n_tokens, n_seq, off_host, per_sequence, false);
+  return pl;
+}
+
+static ContractionPlan plan_with_tile(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host, bool per_sequence,
+                                      bool big) {
+  ContractionPlan pl;
+  constexpr int kBlockTokens = 32;
   pl.tile = big ? 256 : 128;
   pl.occupancy = big ? 1 : 2;
   pl.tiles_m = (rows + pl.tile - 1) / pl.tile;

@@ -55,7 +55,7 @@ struct ContractionPlan {
   long long blocks;            // workgroups to launch
 };
 ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
-                                 bool per_sequence);
+                                 bool per_sequence, bool weighted = false);
 hipError_t launch_seq_grad(const SeqGradArgs& a, hipStream_t s);
 // Launch plan of the fp32 contraction (host arithmetic only).
 struct SplitContractionPlan {

@@ -1,5 +1,5 @@
-"""The bf16 contraction against 64-bit sums where the output tile or the kind of store changes: row-major stashes on both
-sides of each line."""
+"""The bf16 contraction against 64-bit sums where the output tile or the kind of store changes: row-major stashes and
+weighted sums on both sides of each line."""
 import numpy as np
 import pytest
 import torch
@@ -34,3 +34,39 @@ def test_row_major_stash_stores(gpu_device, d_in, d_out, lens):
     # exact products, at most one rounding of the running sum per token (2^-23 truncated), one rounding to bf16
     bound = 2.0 ** -8 * np.abs(G) + max(lens) * 2.0 ** -23 * 1.01 * M
     assert (np.abs(S.double().cpu().numpy() - G) <= bound).all()
+
+
+@pytest.mark.parametrize("d_in,d_out,lens,tile", [
+    (264, 1280, [70] * 100, 128), (256, 1280, [70] * 100, 256),     # a ragged width, and none: tile order needs wide tiles
+    (520, 1288, [25] * 20, 128), (1000, 2728, [420] * 24, 256),     # either side of the modelled line
+])
+def test_row_major_tile(gpu_device, d_in, d_out, lens, tile):
+    prob = wl.custom_layer(d_in, d_out, lens, dtype="bf16", seed=d_in, sigma_delta=1e-2, rho=0.3)
+    layer, _ = to_device(prob, gpu_device)
+    assert isopo.contraction_plan(layer.ref(), True)["tile"] == tile
+    S = isopo.seq_grads(layer)
+    for i in (0, 7, len(lens) - 1):
+        r = slice(int(prob.seq_offsets[i]), int(prob.seq_offsets[i + 1]))
+        X, D = layer.X[r].double(), layer.Delta[r].double()
+        G, M = D.T.contiguous() @ X, D.abs().T.contiguous() @ X.abs()
+        assert ((S[i].double() - G).abs() <= 2.0 ** -8 * G.abs() + lens[i] * 2.0 ** -23 * 1.01 * M).all(), i
+
+
+@pytest.mark.parametrize("d_in,d_out,lens", [
+    (512, 1288, [2500, 1, 0, 33, 5000, 4100] * 2),      # 12 wide tiles in chunks: narrow ones in fewer
+    (1536, 1536, [900, 31, 64] * 11),                   # 36
+    (256, 4352, [16500]),                               # one sequence
+])
+def test_weighted_sum_in_chunks(gpu_device, d_in, d_out, lens):
+    prob = wl.custom_layer(d_in, d_out, lens, dtype="bf16", seed=d_out, sigma_delta=1e-2, rho=0.3)
+    layer, _ = to_device(prob, gpu_device)
+    c = torch.randn(len(lens), generator=torch.Generator().manual_seed(3))
+    if len(lens) > 1:
+        c[1] = 0.0
+    got = isopo.weighted_grad(layer, c.to(gpu_device))
+    w = torch.repeat_interleave(c, torch.tensor(lens)).to(gpu_device).double()[:, None]
+    X, D = layer.X.double(), layer.Delta.double() * w
+    G, M = D.T.contiguous() @ X, D.abs().T.contiguous() @ X.abs()
+    # exact products; one rounding of the running sum per token, three per change of sequence and one per chunk
+    bound = (sum(lens) + 3 * len(lens) + 64) * 2.0 ** -23 * M
+    assert ((got.double() - G).abs() <= bound).all()
