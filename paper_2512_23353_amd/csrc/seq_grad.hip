@@ -8,16 +8,18 @@
 //
 // What bounds it: the matrix cores.  The fp32 MFMA is a sixteenth of the bf16 MFMA's rate, so every fp32 value
 // enters as the sum of three bf16 values, x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m
-// (8 + 8 + 8 significant bits: exact for every fp32 value of normal size), and a product is formed from the
-// six partial products hh, hm, mh, mm, hl, lh.  The three left out are below 2^-25 of the product, under half an ulp
-// of the fp32 product itself; and six accumulations per sixteen tokens round the fp32 accumulator less often than
+// (8 + 8 + 8 significant bits: exact from 2^-110 on, where the last bit of l is the last one bf16 has), and a product is
+// formed from the six partial products hh, hm, mh, mm, hl, lh.  The three left out are at most 2^-24 of the product, half
+// an ulp of the fp32 product itself; and six accumulations per sixteen tokens round the fp32 accumulator less often than
 // one per two tokens did.  Against
 // 64-bit sums over 34 layers of 32 .. 2048 by 32 .. 4096 the error of dW is 0.52 of the plain fp32 MFMA form's and that
 // of K 0.79 (geometric means).  1536x1536, 16 sequences, 10^4 tokens: 276 us per-sequence (182 TFLOP/s of fp32 products,
 // 1.1 PFLOP/s of bf16 at the clock the power limit leaves) against 609 us (78 TFLOP/s) for 64x64 fp32 MFMA tiles.
 //
-// A tile whose result is not finite (an infinity or NaN among the inputs, a value that bf16 rounds to infinity) or
-// so small that the low parts may have been subnormal is formed again with fp32 MFMAs straight from global memory.
+// A tile whose result is not finite (an infinity or NaN among the inputs, a value that bf16 rounds to infinity) or among
+// whose inputs is a nonzero value below 2^-110 (in the weighted sum: a Delta times its coefficient) is formed again with
+// fp32 MFMAs straight from global memory.  The operands are what has to be looked at, not the result: a small one may meet
+// a large one, or stand beside ordinary ones.  Subnormal parts and sums are kept by the bf16 MFMA as by the fp32 one.
 //
 // Both operands are token-major: the reduction index is the slow index of X and of Delta.  A thread loads two
 // features of eight consecutive tokens, splits them in registers and stores 16 bytes (one feature, eight tokens)
@@ -39,8 +41,8 @@ constexpr int kUnit = 16;                            // bytes: eight tokens of o
 // one part of a stage, [operand][token half][feature], and the two stages of a group of four waves
 constexpr int plane_bytes(int bt) { return 2 * 2 * bt * kUnit; }
 constexpr int group_lds(int bt) { return 2 * kParts * plane_bytes(bt); }
-// fp32 sums below this may have lost subnormal low parts (a part is at most 2^-16 of its value): formed again in fp32
-constexpr unsigned kTinyBits = 0x12800000u;          // 2^-90
+// The parts of a nonzero value below 2^-110 may not hold all of it.  As 2 bits - 1, the sign shifted out: zero is the largest.
+constexpr unsigned kLossy = 2u * 0x08800000u - 1u;
 
 struct SeqGradParams {
   const float* X;
@@ -186,6 +188,7 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
     }
   };
   unsigned char* const dst = lds + ((is_x ? 2 : 0) + half) * BT * kUnit;
+  unsigned least = ~0u;                              // of 2 bits - 1 of the values this lane staged
   auto sstore = [&](float (&d)[8][FPL], int buf, float scale) {
 #pragma unroll
     for (int f = 0; f < FPL; ++f) {
@@ -194,6 +197,11 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
 #pragma unroll
           for (int i = 0; i < 8; ++i) d[i][f] *= scale;
         }
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const unsigned b = 2u * __builtin_bit_cast(unsigned, d[i][f]) - 1u;
+        least = b < least ? b : least;
       }
       unsigned h[4], m[4], l[4];
 #pragma unroll
@@ -278,6 +286,8 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
     }
   }
 
+  const bool lossy = __syncthreads_or(least < kLossy);
+
   if constexpr (KG > 1) {
     // the groups' sums, added in group order (every stage has been read: the loop ends with a barrier)
     float* red = reinterpret_cast<float*>(smem);     // [group - 1][value][thread of the group]
@@ -307,7 +317,7 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
 
   // Lane l holds column l%32 and rows acc_row(v, l) of each block.
   const int col = lane & 31;
-  unsigned top = 0;                                  // largest magnitude among the stored values, as bits
+  unsigned top = 0;                                  // largest magnitude, as bits (zero outside the layer)
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -315,10 +325,9 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const unsigned bits = __builtin_bit_cast(unsigned, (float)acc[i][j][v]) & 0x7fffffffu;
-        const bool stored = nw + j * 32 + col < p.d_in && mw + i * 32 + acc_row(v, lane) < p.row_end;
-        top = stored && bits > top ? bits : top;
+        top = bits > top ? bits : top;
       }
-  if (__ballot(top >= 0x7f800000u) || (__ballot(top >= kTinyBits) == 0 && __ballot(top != 0))) {
+  if (lossy || __ballot(top >= 0x7f800000u)) {
     // once more with fp32 MFMAs, the operands straight from global memory: one token per lane half
     clear();
     TokenWalk<WEIGHTED> walk(p, item);

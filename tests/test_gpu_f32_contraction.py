@@ -85,3 +85,41 @@ def test_f32_contraction_outside_the_parts_range(gpu_device, dims, what):
     assert not fin[1, 3].any() and fin.sum() == fin.size - d_in
     assert np.array_equal(np.isnan(got), np.isnan(G)) and np.array_equal(np.isinf(got), np.isinf(G))
     assert (np.abs(got[fin] - G[fin]) <= (2 + 90) * 2.0 ** -23 * M[fin]).all()
+
+
+@pytest.mark.parametrize("dims", [(64, 96), (640, 1284), (128, 260)])
+@pytest.mark.parametrize("what", ["row", "column", "against large", "subnormal", "coefficient", "products"])
+def test_f32_contraction_small_operands(gpu_device, dims, what):
+    """Operands below 2^-110, where fp32 carries more bits than three bf16 parts can, whose products are of ordinary size
+    or stand beside ordinary ones: each output as exact as ever."""
+    d_in, d_out = dims
+    lengths = [40, 90, 3, 17] if dims == (128, 260) else [40, 90, 3, 17] * 4
+    prob = wl.custom_layer(d_in, d_out, lengths, dtype="f32", seed=78, sigma_delta=1.0)
+    X, D = prob.X, prob.Delta
+    c = np.random.default_rng(5).uniform(0.5, 2.0, prob.n_seq).astype(np.float32)
+    if what == "row":
+        D[:, 5] *= 2.0 ** -122
+    elif what == "column":
+        X[:, 7] *= 2.0 ** -122
+    elif what == "against large":
+        D *= 2.0 ** -122
+        X *= 2.0 ** 60
+    elif what == "subnormal":
+        D *= 2.0 ** -138
+        X *= 2.0 ** 90
+    elif what == "coefficient":
+        c *= np.float32(2.0 ** -122)
+        X *= 2.0 ** 60
+    else:                                                  # ordinary operands, products down to where fp32 ends
+        D *= 2.0 ** -80
+        X *= 2.0 ** -62
+    layer, _ = to_device(prob, gpu_device)
+    G, M = _reference(prob)
+    got = isopo.seq_grads(layer).double().cpu().numpy()
+    # 2^-149: sums below fp32's normal range
+    assert (np.abs(got - G) <= (2 + 90) * 2.0 ** -23 * M + 90 * 2.0 ** -149).all()
+    # c times a subnormal Delta is rounded to 2^-149 before it is multiplied
+    want, mag = _reference(prob, c.astype(np.float64))
+    lost = 2.0 ** -149 * (prob.X.double().abs().sum(0).numpy()[None, :] + 6 * len(lengths) * 90)
+    dW = isopo.weighted_grad(layer, torch.from_numpy(c).to(gpu_device)).double().cpu().numpy()
+    assert (np.abs(dW - want) <= _bound(sum(lengths) + 16 * len(lengths)) * mag + lost).all()
