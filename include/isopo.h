@@ -123,8 +123,11 @@ isopo_status isopo_gram_cost_model(const isopo_layer* layer, double* t_ghost, do
  *                      mode with tiles % 8 == 0 gives XCD x the x-th eighth of every sequence's tiles,
  *                      the unsplit unweighted mode has one item
  *   workgroups         grid size of the one-workgroup-per-pair launch (some workgroups may find their XCD's
- *                      range exhausted and exit); isopo_layer_gram and isopo_seq_grads_limited launch at most
- *                      256 (or the budget) persistent workgroups over the same list instead */
+ *                      range exhausted and exit); with the 256 tile isopo_layer_gram and
+ *                      isopo_seq_grads_limited launch at most 256 (or the budget) persistent workgroups over
+ *                      the same list instead.  isopo_seq_grads_limited also takes the 256 tile, over the list
+ *                      that goes with it, on layers large enough for it whose widths are no multiples of 256
+ *                      and for which 128 is reported here */
 typedef struct {
   int32_t tile, workgroups_per_cu, tiles, n_chunks, chunk_tokens;
   int32_t xcd_start[9];
@@ -179,8 +182,10 @@ isopo_status isopo_seq_grads(const isopo_layer* layer, void* stash, void* stream
  * and the other units stay free.  The result is the same stash, bit for bit.
  *   max_workgroups  0: no limit (isopo_seq_grads).  Otherwise 8..256, rounded down to a multiple of 8
  *                   (the workgroups are dealt evenly to the 8 accelerator dies).  Honoured for bf16
- *                   layers large enough for the 256x256 tile with more tiles than the budget; smaller
- *                   problems and fp32 inputs run as isopo_seq_grads does.
+ *                   layers large enough for the 256x256 tile (d_in and d_out of 256 at least and, over
+ *                   all sequences, 256 tiles) with more tiles than the budget, also those that
+ *                   isopo_seq_grads would form in 128x128 tiles; smaller problems and fp32 inputs run as
+ *                   isopo_seq_grads does.
  *   queue_dev       device uint32[8], 4-byte aligned, caller-owned scratch; zeroed and used by the call
  *                   (work counters); must not be shared by launches that may run concurrently */
 isopo_status isopo_seq_grads_limited(const isopo_layer* layer, void* stash, int32_t max_workgroups,

@@ -309,7 +309,7 @@ isopo_status isopo_seq_grads_stash(const isopo_layer* layer, void* stash, isopo_
                               (reinterpret_cast<uintptr_t>(queue_dev) & 3u)))
     return ISOPO_ERR_INVALID_ARG;
   SeqGradArgs a;
-  a.max_workgroups = max_workgroups; a.queue = queue_dev;
+  a.max_workgroups = max_workgroups; a.queue = queue_dev; a.budget = max_workgroups != 0;
   a.X = layer->X; a.Delta = layer->Delta; a.off = layer->seq_offsets_dev; a.off_host = layer->seq_offsets_host; a.c = nullptr;
   a.out = stash; a.d_in = layer->d_in; a.d_out = layer->d_out; a.n_seq = layer->n_seq; a.n_tokens = (int)layer->n_tokens;
   a.row0 = 0; a.rows = layer->d_out; a.out_row0 = 0;

@@ -30,13 +30,14 @@ static ContractionPlan plan_with_tile(int rows, int d_in, int n_tokens, int n_se
                                       bool big);
 
 ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
-                                 bool per_sequence, bool weighted) {
+                                 bool per_sequence, bool weighted, bool budget) {
   const long long big_tiles = (long long)((rows + 255) / 256) * ((d_in + 255) / 256);
   // 256x256 tiles (one workgroup per CU) when they alone fill the chip, else 128x128 (two per CU).  In the
   // sum-over-all-tokens mode the token split supplies parallelism too.
   const long long par = per_sequence ? n_seq : (n_tokens / 1024 > 1 ? n_tokens / 1024 : 1);
   bool big = rows >= 256 && d_in >= 256 && big_tiles * par >= 256;
-  if (big && per_sequence && (rows % 256 || d_in % 256) && small_tiles_win(rows, d_in, n_tokens, n_seq)) big = false;
+  // only the launch over 256x256 tiles keeps a budget of compute units, so a caller who gives one keeps those tiles
+  if (big && per_sequence && !budget && (rows % 256 || d_in % 256) && small_tiles_win(rows, d_in, n_tokens, n_seq)) big = false;
   ContractionPlan pl = plan_with_tile(rows, d_in, n_tokens, n_seq, off_host, per_sequence, big);
   // A weighted sum cut into token chunks, of few tiles and with operands that stay in the last-level cache: 128x128 tiles,
   // whose four times as many workgroups need fewer chunks, are 5 - 25 % faster (1536x1536, 10^4 tokens: 87 -> 67 us; 2048x2048,

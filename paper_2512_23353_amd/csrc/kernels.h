@@ -29,6 +29,7 @@ struct SeqGradArgs {
   // eight device counters the launch zeroes; the other compute units stay free for other streams
   int max_workgroups = 0;
   unsigned* queue = nullptr;
+  bool budget = false;       // that limit is the caller's own: the launch takes a tile that can keep it
   // per_sequence, bf16: store every sequence's gradient in the order the accumulators hold it (see
   // stash_tile_order_ok) instead of row-major
   bool tile_order = false;
@@ -55,7 +56,7 @@ struct ContractionPlan {
   long long blocks;            // workgroups to launch
 };
 ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
-                                 bool per_sequence, bool weighted = false);
+                                 bool per_sequence, bool weighted = false, bool budget = false);
 hipError_t launch_seq_grad(const SeqGradArgs& a, hipStream_t s);
 // Launch plan of the fp32 contraction (host arithmetic only).
 struct SplitContractionPlan {

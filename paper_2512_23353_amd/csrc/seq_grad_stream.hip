@@ -899,7 +899,7 @@ hipError_t launch_apply_beta(float* o, long long n, float beta, hipStream_t s) {
 // bf16: the per-sequence stash, the plain sum over all tokens, or (c != nullptr) the weighted sum.
 hipError_t launch_seq_grad_stream(const SeqGradArgs& a, hipStream_t s) {
   const ContractionPlan pl =
-      plan_contraction(a.rows, a.d_in, a.n_tokens, a.n_seq, a.off_host, a.per_sequence, a.c != nullptr);
+      plan_contraction(a.rows, a.d_in, a.n_tokens, a.n_seq, a.off_host, a.per_sequence, a.c != nullptr, a.budget);
   // a workgroup budget applies to the large tile's per-sequence launches that would not fit it anyway
   if (a.per_sequence && a.tile_order) {
     // the caller has checked stash_tile_order_ok; anything else would scatter the stores

@@ -70,3 +70,19 @@ def test_weighted_sum_in_chunks(gpu_device, d_in, d_out, lens):
     # exact products; one rounding of the running sum per token, three per change of sequence and one per chunk
     bound = (sum(lens) + 3 * len(lens) + 64) * 2.0 ** -23 * M
     assert ((got.double() - G).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("d_in,d_out,lens,budget", [
+    (264, 1280, [260] * 100, 64), (520, 1288, [300] * 60, 8), (1032, 2048, [780, 0, 801, 333] * 2, 224), (1032, 2048, [780] * 8, 256)])
+def test_budget_on_ragged_widths(gpu_device, d_in, d_out, lens, budget):
+    """Row-major layers that take 128-wide tiles without a budget: the budget is honoured all the same (the work counters
+    are used, which only the persistent launch does), and the stash is the unlimited call's bit for bit."""
+    prob = wl.custom_layer(d_in, d_out, lens, dtype="bf16", seed=d_in, sigma_delta=1e-2, rho=0.3)
+    layer, _ = to_device(prob, gpu_device)
+    assert isopo.contraction_plan(layer.ref(), True)["tile"] == 128
+    want = isopo.seq_grads(layer)
+    for kw in ({}, {"layout": isopo.STASH_ROW_MAJOR}):
+        queue = torch.full((8,), 12345, dtype=torch.int32, device=gpu_device)
+        got = isopo.seq_grads(layer, torch.full_like(want, float("nan")), max_workgroups=budget, queue=queue, **kw)
+        assert (queue != 12345).all()
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
