@@ -54,6 +54,10 @@ __device__ double block_sum(double x, double* red) {
 //   vectors   columns zh_i / (d_i - x_j), normalised, times the old eigenvectors; a wave per four new vectors
 constexpr int kMaxRootIterations = 100;
 constexpr double kUlp = 1.1102230246251565e-16;      // 2^-53
+// Sums of squares below this, of a matrix whose largest entry is 1 to 2, count as zero: entries of 2^-450, where K's own
+// reach down to 2^-277.  Where sequences are copies of each other the trailing block can shrink by 10^16 with every few
+// columns, to where squares and their reciprocals leave the range of fp64.
+constexpr double kNoSquare = 0x1p-900;
 
 // Sums over the 16 lanes of a row, in all of them, and over the wave, in all lanes: lane permutations inside the vector
 // unit instead of LDS round trips.
@@ -222,7 +226,7 @@ __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __res
   auto reflector = [&](int k, double sig, double x0, double diag) {
     double* vk = v + (k & 1) * MAXN;
     if (sub == 0) d[k] = diag;
-    if (sig == 0.0) {                                         // column already reduced
+    if (sig < kNoSquare) {                                    // column already reduced
       if (sub == 0) { e[k] = x0; htau[k] = 0.0; }
       return;
     }

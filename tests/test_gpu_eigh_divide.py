@@ -65,3 +65,26 @@ def test_non_finite_entries_are_reported(gpu_device, m, value):
     K[0, m // 2, 0] = K[0, 0, m // 2] = value
     D, U, info = isopo.ntk_eigh(K)
     assert info.tolist() == [1, 0] and torch.isfinite(D[1]).all() and not torch.isfinite(D[0]).any()
+
+
+@pytest.mark.parametrize("m", [24, 40, 64, 90, 100, 128, 200])
+def test_copies_of_sequences(gpu_device, m):
+    """Rank-one matrices of whole numbers, alone and below a block 10^80 times as large: the trailing block of the reduction
+    is rounding, of rank one again, and shrinks by a factor of 10^16 every few columns until squares underflow."""
+    rng = np.random.default_rng(4)
+    K = np.zeros((64, m, m))
+    for k in range(0, 64, 2):
+        a = rng.integers(1, 1 + rng.choice([1, 2, 4, 9]), m) * rng.choice([-1, 1], m)
+        K[k] = np.outer(a, a)
+        K[k + 1, :4, :4] = np.eye(4) * 2.0 ** 126
+        K[k + 1, 4:, 4:] = np.outer(a, a)[4:, 4:] * (rng.integers(1, 50) * 2.0 ** -149)
+    K = K.astype(np.float32)
+    D, U, info = isopo.ntk_eigh(torch.from_numpy(K).to(gpu_device))
+    assert not info.any()
+    D, U, Kd = D.cpu().numpy(), U.cpu().numpy(), K.astype(np.float64)
+    ref = np.linalg.eigvalsh(Kd)
+    tol, size = 16 * (m + 8) * 2.0 ** -53, np.abs(ref).max(axis=1)
+    assert (np.abs(D - ref).max(axis=1) <= tol * size).all()
+    for b in range(len(K)):
+        assert np.abs(U[b].T @ U[b] - np.eye(m)).max() <= tol
+        assert np.abs((U[b] * D[b]) @ U[b].T - Kd[b]).max() <= tol * size[b]
