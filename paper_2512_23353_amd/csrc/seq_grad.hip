@@ -18,7 +18,9 @@
 //
 // A tile whose result is not finite (an infinity or NaN among the inputs, a value that bf16 rounds to infinity) or among
 // whose inputs is a nonzero value below 2^-110 (in the weighted sum: a Delta times its coefficient) is formed again with
-// fp32 MFMAs straight from global memory.  The operands are what has to be looked at, not the result: a small one may meet
+// fp32 MFMAs, the operands staged as they are in the same LDS (both passes of 1536x1536, 16 sequences, 10^4 tokens: 577 us where
+// every tile is formed twice, 273 where none is; from global memory, token by token, it was 835).
+// The operands are what has to be looked at, not the result: a small one may meet
 // a large one, or stand beside ordinary ones.  Subnormal parts and sums are kept by the bf16 MFMA as by the fp32 one.
 //
 // Both operands are token-major: the reduction index is the slow index of X and of Delta.  A thread loads two
@@ -31,6 +33,8 @@
 // zero-filled, so ragged lengths need no host-side padding.
 #include "common.h"
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace isopo {
 namespace {
@@ -187,29 +191,41 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
       rowp += pitch;
     }
   };
-  unsigned char* const dst = lds + ((is_x ? 2 : 0) + half) * BT * kUnit;
   unsigned least = ~0u;                              // of 2 bits - 1 of the values this lane staged
-  auto sstore = [&](float (&d)[8][FPL], int buf, float scale) {
+  // SPLIT: the three parts of each value; else fp32 rows, [operand][token][feature].  `rows`: the tokens the block has (what
+  // lies past them is zero and stays it, whatever the coefficient)
+  auto sstore = [&](auto split, float (&d)[8][FPL], int buf, float scale, int rows) {
+    if constexpr (WEIGHTED) {
+      if (!is_x) {
 #pragma unroll
-    for (int f = 0; f < FPL; ++f) {
-      if constexpr (WEIGHTED) {
-        if (!is_x) {
+        for (int i = 0; i < 8; ++i)
 #pragma unroll
-          for (int i = 0; i < 8; ++i) d[i][f] *= scale;
+          for (int f = 0; f < FPL; ++f) d[i][f] *= split || 8 * half + i < rows ? scale : 0.f;
+      }
+    }
+    if constexpr (split) {
+      unsigned char* const o = lds + buf * STAGE + ((is_x ? 2 : 0) + half) * BT * kUnit;
+#pragma unroll
+      for (int f = 0; f < FPL; ++f) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const unsigned b = 2u * __builtin_bit_cast(unsigned, d[i][f]) - 1u;
+          least = b < least ? b : least;
         }
-      }
+        unsigned h[4], m[4], l[4];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const unsigned b = 2u * __builtin_bit_cast(unsigned, d[i][f]) - 1u;
-        least = b < least ? b : least;
+        for (int q = 0; q < 4; ++q) split2(d[2 * q][f], d[2 * q + 1][f], h[q], m[q], l[q]);
+        unsigned char* const of = o + unit_pos(FPL * lane + f) * kUnit;
+        *reinterpret_cast<uint4*>(of) = make_uint4(h[0], h[1], h[2], h[3]);
+        *reinterpret_cast<uint4*>(of + PLANE) = make_uint4(m[0], m[1], m[2], m[3]);
+        *reinterpret_cast<uint4*>(of + 2 * PLANE) = make_uint4(l[0], l[1], l[2], l[3]);
       }
-      unsigned h[4], m[4], l[4];
+    } else {
+      float* const o = reinterpret_cast<float*>(lds + buf * STAGE) + ((is_x ? kBK : 0) + 8 * half) * BT + FPL * lane;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) split2(d[2 * q][f], d[2 * q + 1][f], h[q], m[q], l[q]);
-      unsigned char* const o = dst + unit_pos(FPL * lane + f) * kUnit + buf * STAGE;
-      *reinterpret_cast<uint4*>(o) = make_uint4(h[0], h[1], h[2], h[3]);
-      *reinterpret_cast<uint4*>(o + PLANE) = make_uint4(m[0], m[1], m[2], m[3]);
-      *reinterpret_cast<uint4*>(o + 2 * PLANE) = make_uint4(l[0], l[1], l[2], l[3]);
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int f = 0; f < FPL; ++f) o[i * BT + f] = d[i][f];
     }
   };
 
@@ -222,37 +238,54 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   };
-  clear();
 
   const int mw = m0 + wm * WT, nw = n0 + wn * WT;
   const bool live = mw < p.row_end && nw < p.d_in;   // edge tiles: this wave has outputs
   const unsigned char* const at = lds + (lane >> 5) * BT * kUnit + unit_pos(wm * WT + (lane & 31)) * kUnit;
   const unsigned char* const bt = lds + (2 + (lane >> 5)) * BT * kUnit + unit_pos(wn * WT + (lane & 31)) * kUnit;
-  auto compute = [&](int buf) {
-    // small products first: lh, hl, mm, mh, hm, hh
-    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
-    bf16x8 a[NB][kParts], b[NB][kParts];
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int s = 0; s < kParts; ++s) {
-        a[i][s] = *reinterpret_cast<const bf16x8*>(at + buf * STAGE + s * PLANE + i * 32 * kUnit);
-        b[i][s] = *reinterpret_cast<const bf16x8*>(bt + buf * STAGE + s * PLANE + i * 32 * kUnit);
-      }
-#pragma unroll
-    for (int s = 0; s < 6; ++s)
+  auto compute = [&](auto split, int buf) {
+    if constexpr (split) {
+      // small products first: lh, hl, mm, mh, hm, hh
+      constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+      bf16x8 a[NB][kParts], b[NB][kParts];
 #pragma unroll
       for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][pa[s]], b[j][pb[s]], acc[i][j], 0, 0, 0);
+        for (int s = 0; s < kParts; ++s) {
+          a[i][s] = *reinterpret_cast<const bf16x8*>(at + buf * STAGE + s * PLANE + i * 32 * kUnit);
+          b[i][s] = *reinterpret_cast<const bf16x8*>(bt + buf * STAGE + s * PLANE + i * 32 * kUnit);
+        }
+#pragma unroll
+      for (int s = 0; s < 6; ++s)
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][pa[s]], b[j][pb[s]], acc[i][j], 0, 0, 0);
+    } else {
+      const float* const rows = reinterpret_cast<const float*>(lds + buf * STAGE) + (lane >> 5) * BT + (lane & 31);
+#pragma unroll
+      for (int t = 0; t < kBK; t += 2) {
+        float a[NB], b[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          a[i] = rows[t * BT + wm * WT + i * 32];
+          b[i] = rows[(kBK + t) * BT + wn * WT + i * 32];
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+    }
   };
 
-  {
+  auto pass = [&](auto split) {
     TokenWalk<WEIGHTED> walk(p, item);
     // A step is KG blocks of tokens, one per group; a group without one in the last step loads zeros.  Step s is
     // multiplied from LDS while step s + 1 is in registers and step s + 2 on its way there.
-    auto fetch = [&](float (&d)[8][FPL], float& scale) -> bool {
+    auto fetch = [&](float (&d)[8][FPL], float& scale, int& rows) -> bool {
       int b0 = 0, b1 = 0;
       bool any = false;
 #pragma unroll
@@ -264,29 +297,43 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
         if (g == group && got) { b0 = q0; b1 = q1; scale = qs; }
       }
       gload(d, b0, b1);
+      rows = b1 - b0;
       return any;
     };
     float s0 = 1.f, s1 = 1.f;
-    bool have0 = fetch(r[0], s0), have1 = fetch(r[1], s1);
-    if (have0) sstore(r[0], 0, s0);
+    int n0, n1;
+    clear();
+    bool have0 = fetch(r[0], s0, n0), have1 = fetch(r[1], s1, n1);
+    if (have0) sstore(split, r[0], 0, s0, n0);
     __syncthreads();
     while (have0) {
-      const bool have2 = fetch(r[0], s0);
-      if (live) compute(0);
+      const bool have2 = fetch(r[0], s0, n0);
+      if (live) compute(split, 0);
       __builtin_amdgcn_sched_barrier(0);
-      if (have1) sstore(r[1], 1, s1);
+      if (have1) sstore(split, r[1], 1, s1, n1);
       __syncthreads();
       if (!have1) break;
-      have1 = fetch(r[1], s1);
-      if (live) compute(1);
+      have1 = fetch(r[1], s1, n1);
+      if (live) compute(split, 1);
       __builtin_amdgcn_sched_barrier(0);
-      if (have2) sstore(r[0], 0, s0);
+      if (have2) sstore(split, r[0], 0, s0, n0);
       __syncthreads();
       have0 = have2;
     }
-  }
+  };
 
-  const bool lossy = __syncthreads_or(least < kLossy);
+  pass(std::true_type{});
+  unsigned top = 0;                                  // largest magnitude, as bits (zero outside the layer)
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const unsigned bits = __builtin_bit_cast(unsigned, (float)acc[i][j][v]) & 0x7fffffffu;
+        top = bits > top ? bits : top;
+      }
+  if (__syncthreads_or(least < kLossy || top >= 0x7f800000u)) pass(std::false_type{});
 
   if constexpr (KG > 1) {
     // the groups' sums, added in group order (every stage has been read: the loop ends with a barrier)
@@ -317,40 +364,6 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
 
   // Lane l holds column l%32 and rows acc_row(v, l) of each block.
   const int col = lane & 31;
-  unsigned top = 0;                                  // largest magnitude, as bits (zero outside the layer)
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const unsigned bits = __builtin_bit_cast(unsigned, (float)acc[i][j][v]) & 0x7fffffffu;
-        top = bits > top ? bits : top;
-      }
-  if (lossy || __ballot(top >= 0x7f800000u)) {
-    // once more with fp32 MFMAs, the operands straight from global memory: one token per lane half
-    clear();
-    TokenWalk<WEIGHTED> walk(p, item);
-    int b0, b1;
-    float bs;
-    const int kr = lane >> 5;
-    while (walk.next(2, b0, b1, bs)) {
-      const bool tok = b0 + kr < b1;
-      const size_t t = tok ? b0 + kr : b0;
-      float a[NB], b[NB];
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int m = mw + i * 32 + col, n = nw + i * 32 + col;
-        a[i] = tok && m < p.row_end ? p.Delta[t * p.d_out + m] * bs : 0.f;
-        b[i] = tok && n < p.d_in ? p.X[t * p.d_in + n] : 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-  }
-
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
 #pragma unroll
