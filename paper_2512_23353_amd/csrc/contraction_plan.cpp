@@ -169,7 +169,7 @@ SplitContractionPlan plan_split_contraction(int rows, int d_in, int n_tokens, in
                                  {64, 4, 1.6e-6, 1.7e-6, 2.5e-6, 7.0e-6}};
   constexpr double kBeta = 6.0e-6, kAdd = 3.0e-12, kUnits = 256.0;
   constexpr int kBlock = 16;
-  SplitContractionPlan pl{128, 1, 1, n_tokens > 0 ? n_tokens : 1};
+  SplitContractionPlan pl{128, 1, 1, n_tokens > 0 ? n_tokens : 1, 0};
   // 16-token blocks in all and of the longest sequence (every sequence ends in a block of its own)
   long long blocks = 0, longest = 0;
   for (int i = 0; i < n_seq; ++i) {
@@ -206,6 +206,14 @@ SplitContractionPlan plan_split_contraction(int rows, int d_in, int n_tokens, in
     pl.chunk_tokens = ((n_tokens + pl.n_chunks - 1) / pl.n_chunks + kBlock - 1) / kBlock * kBlock;
     pl.n_chunks = (n_tokens + pl.chunk_tokens - 1) / pl.chunk_tokens;
   }
+  // Longest first where the launch has more workgroups than are resident at a time (three per compute unit; from one per unit
+  // on it would pay as well) and the longest sequence outlasts the mean by more than it takes every workgroup to find its
+  // sequence (n_seq steps, a lane of a wave per sequence).  804x860, 22 sequences of 195 tokens on average and 370 at most: 58.9
+  // -> 50.5 us; 988x388, 34 of 440 and 895: 118 -> 99; of 33 random layers this side of the line 31 gained, 0.89x on average.
+  // Past it up to half was lost: 1508x152, 62 of 22 and 39: 21.0 -> 33.4; 484x2420, 32 of 90 and 150: 60.9 -> 66.2; 256x284,
+  // 52 of 158 each: 18.5 -> 21.0.
+  const double tiles = (double)((rows + pl.tile - 1) / pl.tile) * ((d_in + pl.tile - 1) / pl.tile);
+  pl.longest_first = per_sequence && n_seq <= 64 && tiles * n_seq > 768.0 && longest - n_tokens / n_seq >= 128;
   return pl;
 }
 

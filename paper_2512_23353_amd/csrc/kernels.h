@@ -63,6 +63,7 @@ struct SplitContractionPlan {
   int tile;                    // 128 or 64
   int groups;                  // groups of four waves per tile, which take its token blocks in turn: 1 (128), 1, 2 or 4 (64)
   int n_chunks, chunk_tokens;  // sum-over-all-tokens mode: token chunks (1: no split)
+  int longest_first;           // per-sequence mode: the longest sequences' tiles are dispatched first
 };
 SplitContractionPlan plan_split_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
                                             bool per_sequence);

@@ -395,7 +395,6 @@ hipError_t launch_cfg(SeqGradParams p, int rows, long long items, hipStream_t s)
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   p.tiles = (int)tiles;
-  p.longest_first = !WEIGHTED && p.n_seq > 1 && p.n_seq <= 64 && blocks > 768;
   constexpr size_t smem = (size_t)KG * group_lds(BT);
   static_assert(smem >= (size_t)(KG - 1) * WT * WT * 4 * sizeof(float), "the groups' sums meet in LDS");
   auto kern = seq_grad_kernel<WT, KG, WEIGHTED>;
@@ -427,6 +426,7 @@ hipError_t launch_seq_grad(const SeqGradArgs& a, hipStream_t s) {
   p.chunk_tokens = 1;
   p.atomic = 0;
   const SplitContractionPlan pl = plan_split_contraction(a.rows, a.d_in, a.n_tokens, a.n_seq, a.off_host, a.per_sequence);
+  p.longest_first = pl.longest_first;
   if (a.per_sequence) return launch_plan<false>(p, pl, a.rows, a.n_seq, s);
   p.chunk_tokens = pl.chunk_tokens;
   if (pl.n_chunks > 1) {

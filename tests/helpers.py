@@ -1,4 +1,6 @@
 """Comparison helpers shared by the GPU parity tests."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -59,3 +61,17 @@ def to_device(prob, device):
     layer = isopo.Layer(X, D, prob.seq_offsets)
     A = torch.from_numpy(prob.A).to(device)
     return layer, A
+
+
+class SplitPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("tile", "groups", "n_chunks", "chunk_tokens", "longest_first")]
+
+
+def split_plan(d_in, d_out, lengths, per_sequence):
+    """Launch plan of the fp32 contraction (host arithmetic; the library's internal C++ function)."""
+    from paper_2512_23353_amd import isopo
+    fn = isopo.load()._ZN5isopo22plan_split_contractionEiiiiPKib
+    fn.restype = SplitPlan
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    return fn(ctypes.c_int(d_out), ctypes.c_int(d_in), ctypes.c_int(int(off[-1])), ctypes.c_int(len(lengths)),
+              off.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), ctypes.c_bool(per_sequence))

@@ -9,6 +9,8 @@ import pytest
 
 from paper_2512_23353_amd import isopo
 
+from helpers import split_plan
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -300,3 +302,12 @@ def test_bench_reads_the_committed_traffic_summary():
     written = float(re.search(r"WRITE_SIZE mean .*-> ([0-9.e]+) B written", text).group(1))
     assert abs(traffic - (read + written)) <= 0.005 * traffic
     assert bench.read_traffic("no_such_kernel") is None
+
+
+def test_fp32_plan_orders_sequences_only_where_it_pays():
+    """Every workgroup of a launch in length order finds its sequence by itself, which short items do not repay."""
+    for d_in, d_out, lengths, want in ((512, 2048, [8] * 48, 0), (1508, 152, [22] * 62, 0), (1508, 152, [22] * 61 + [39], 0),
+                                       (1536, 1536, [640] * 16, 0), (1536, 1536, [256, 1024] * 8, 1),
+                                       (1536, 1536, [10] * 64 + [1024], 0), (64, 64, [10, 1024], 0)):
+        assert split_plan(d_in, d_out, lengths, True).longest_first == want, (d_in, d_out, lengths)
+    assert split_plan(1536, 1536, [256, 1024] * 8, False).longest_first == 0
