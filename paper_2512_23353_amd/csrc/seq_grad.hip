@@ -45,6 +45,10 @@ constexpr int kUnit = 16;                            // bytes: eight tokens of o
 // one part of a stage, [operand][token half][feature], and the two stages of a group of four waves
 constexpr int plane_bytes(int bt) { return 2 * 2 * bt * kUnit; }
 constexpr int group_lds(int bt) { return 2 * kParts * plane_bytes(bt); }
+// Sequences of so few tokens are formed with fp32 MFMAs at once: a single product would be rounded more than once and lack
+// what is left out (off by 1.5e-7 of itself at most, 6e-8 here; of the sum of magnitudes for two tokens 1.6e-7 and 1.1e-7).
+// From three on the parts' sums are the closer ones.
+constexpr int kFewTokens = 2;
 // The parts of a nonzero value below 2^-110 may not hold all of it.  As 2 bits - 1, the sign shifted out: zero is the largest.
 constexpr unsigned kLossy = 2u * 0x08800000u - 1u;
 
@@ -62,6 +66,7 @@ struct SeqGradParams {
   int tiles_n, tiles;
   int chunk_tokens;                                  // sum over all tokens: tokens per chunk
   int atomic;                                        // ... whose partial tiles are added to `out`
+  int few_tokens;                                    // sum over all tokens: kFewTokens or fewer per block of tokens
   int longest_first;                                 // per sequence: item i is the i-th longest sequence (n_seq <= 64)
 };
 
@@ -243,7 +248,7 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
   const bool live = mw < p.row_end && nw < p.d_in;   // edge tiles: this wave has outputs
   const unsigned char* const at = lds + (lane >> 5) * BT * kUnit + unit_pos(wm * WT + (lane & 31)) * kUnit;
   const unsigned char* const bt = lds + (2 + (lane >> 5)) * BT * kUnit + unit_pos(wn * WT + (lane & 31)) * kUnit;
-  auto compute = [&](auto split, int buf) {
+  auto compute = [&](auto split, int buf, int tokens) {
     if constexpr (split) {
       // small products first: lh, hl, mm, mh, hm, hh
       constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
@@ -264,8 +269,7 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][pa[s]], b[j][pb[s]], acc[i][j], 0, 0, 0);
     } else {
       const float* const rows = reinterpret_cast<const float*>(lds + buf * STAGE) + (lane >> 5) * BT + (lane & 31);
-#pragma unroll
-      for (int t = 0; t < kBK; t += 2) {
+      auto two = [&](int t) {
         float a[NB], b[NB];
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
@@ -277,6 +281,11 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
 #pragma unroll
           for (int j = 0; j < NB; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+      };
+      two(0);
+      if (tokens > 2) {
+#pragma unroll
+        for (int t = 2; t < kBK; t += 2) two(t);
       }
     }
   };
@@ -301,39 +310,43 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
       return any;
     };
     float s0 = 1.f, s1 = 1.f;
-    int n0, n1;
+    int n0, n1, in0, in1;                            // tokens of the two steps in registers, and of those in LDS
     clear();
     bool have0 = fetch(r[0], s0, n0), have1 = fetch(r[1], s1, n1);
-    if (have0) sstore(split, r[0], 0, s0, n0);
+    if (have0) { sstore(split, r[0], 0, s0, n0); in0 = n0; }
     __syncthreads();
     while (have0) {
       const bool have2 = fetch(r[0], s0, n0);
-      if (live) compute(split, 0);
+      if (live) compute(split, 0, in0);
       __builtin_amdgcn_sched_barrier(0);
-      if (have1) sstore(split, r[1], 1, s1, n1);
+      if (have1) { sstore(split, r[1], 1, s1, n1); in1 = n1; }
       __syncthreads();
       if (!have1) break;
       have1 = fetch(r[1], s1, n1);
-      if (live) compute(split, 1);
+      if (live) compute(split, 1, in1);
       __builtin_amdgcn_sched_barrier(0);
-      if (have2) sstore(split, r[0], 0, s0, n0);
+      if (have2) { sstore(split, r[0], 0, s0, n0); in0 = n0; }
       __syncthreads();
       have0 = have2;
     }
   };
 
-  pass(std::true_type{});
-  unsigned top = 0;                                  // largest magnitude, as bits (zero outside the layer)
+  bool fp32 = WEIGHTED ? p.few_tokens : p.off[item + 1] - p.off[item] <= kFewTokens;      // uniform
+  if (!fp32) {
+    pass(std::true_type{});
+    unsigned top = 0;                                // largest magnitude, as bits (zero outside the layer)
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const unsigned bits = __builtin_bit_cast(unsigned, (float)acc[i][j][v]) & 0x7fffffffu;
-        top = bits > top ? bits : top;
-      }
-  if (__syncthreads_or(least < kLossy || top >= 0x7f800000u)) pass(std::false_type{});
+        for (int v = 0; v < 16; ++v) {
+          const unsigned bits = __builtin_bit_cast(unsigned, (float)acc[i][j][v]) & 0x7fffffffu;
+          top = bits > top ? bits : top;
+        }
+    fp32 = __syncthreads_or(least < kLossy || top >= 0x7f800000u);
+  }
+  if (fp32) pass(std::false_type{});
 
   if constexpr (KG > 1) {
     // the groups' sums, added in group order (every stage has been read: the loop ends with a barrier)
@@ -425,6 +438,12 @@ hipError_t launch_seq_grad(const SeqGradArgs& a, hipStream_t s) {
   p.out_seq_stride = a.out_seq_stride; p.beta = a.beta;
   p.chunk_tokens = 1;
   p.atomic = 0;
+  long long blocks = (a.n_tokens + kBK - 1) / kBK;   // of tokens; in the weighted sum a sequence ends one
+  if (a.c && a.off_host) {
+    blocks = 0;
+    for (int i = 0; i < a.n_seq; ++i) blocks += (a.off_host[i + 1] - a.off_host[i] + kBK - 1) / kBK;
+  }
+  p.few_tokens = a.n_tokens <= kFewTokens * blocks;
   const SplitContractionPlan pl = plan_split_contraction(a.rows, a.d_in, a.n_tokens, a.n_seq, a.off_host, a.per_sequence);
   p.longest_first = pl.longest_first;
   if (a.per_sequence) return launch_plan<false>(p, pl, a.rows, a.n_seq, s);

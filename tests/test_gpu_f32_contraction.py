@@ -123,3 +123,23 @@ def test_f32_contraction_small_operands(gpu_device, dims, what):
     lost = 2.0 ** -149 * (prob.X.double().abs().sum(0).numpy()[None, :] + 6 * len(lengths) * 90)
     dW = isopo.weighted_grad(layer, torch.from_numpy(c).to(gpu_device)).double().cpu().numpy()
     assert (np.abs(dW - want) <= _bound(sum(lengths) + 16 * len(lengths)) * mag + lost).all()
+
+
+@pytest.mark.parametrize("dims", [(64, 96), (640, 1284)])
+def test_f32_contraction_of_one_and_two_tokens(gpu_device, dims):
+    """One token: every product rounded once.  Two: each product and the sum rounded once at most, 2^-24 each."""
+    lengths = [1, 2, 0, 1, 40, 2] * 4
+    prob = wl.custom_layer(*dims, lengths, dtype="f32", seed=79, sigma_delta=1.0)
+    layer, _ = to_device(prob, gpu_device)
+    G, M = _reference(prob)
+    got = isopo.seq_grads(layer).double().cpu().numpy()
+    for i, n in enumerate(lengths):
+        if n <= 2:
+            assert (np.abs(got[i] - G[i]) <= n * 2.0 ** -24 * M[i]).all(), i
+    one = wl.custom_layer(*dims, [1, 0], dtype="f32", seed=80, sigma_delta=1.0)
+    layer, _ = to_device(one, gpu_device)
+    c = np.array([0.7, 3.0], dtype=np.float32)
+    for coef, cc, roundings in ((None, np.ones(2), 1), (torch.from_numpy(c).to(gpu_device), c.astype(np.float64), 2)):
+        want, mag = _reference(one, cc)
+        dW = isopo.weighted_grad(layer, coef).double().cpu().numpy()
+        assert (np.abs(dW - want) <= roundings * 2.0 ** -24 * (1 + 2.0 ** -23) * mag).all()
