@@ -378,7 +378,8 @@ isopo_status isopo_rescale(const float* fisher_sq, const float* grad_sq, int64_t
  *   K     device fp32 [batch, n_seq, n_seq], symmetric (the mean of K and K^T is decomposed)
  *   D     device fp64 [batch, n_seq], ascending
  *   U     device fp64 [batch, n_seq, n_seq] row-major, eigenvectors as columns: K = U diag(D) U^T
- *   info  optional device int32 [batch]: 0, or 1 where K has NaN or infinite entries (D and U are then NaN)
+ *   info  optional device int32 [batch]: 0 converged, 1 not converged within the iteration limit (100 steps per
+ *         root of the merges' equations), or K has NaN or infinite entries (D and U are then NaN)
  *   workspace  device, isopo_ntk_eigh_workspace(n_seq, batch) bytes, 256-byte aligned (the eigenvector matrices
  *              of problems with more than 64 sequences) */
 size_t isopo_ntk_eigh_workspace(int32_t n_seq, int32_t batch);

@@ -52,7 +52,6 @@ __device__ double block_sum(double x, double* red) {
 //   zh        the vector for which the computed roots are exact (products of differences): the eigenvectors formed from
 //             it are orthogonal to rounding however close the roots are
 //   vectors   columns zh_i / (d_i - x_j), normalised, times the old eigenvectors; a wave per four new vectors
-constexpr int kMaxRootIterations = 100;
 constexpr double kUlp = 1.1102230246251565e-16;      // 2^-53
 // Sums of squares below this, of a matrix whose largest entry is 1 to 2, count as zero: entries of 2^-450, where K's own
 // reach down to 2^-277.  Where sequences are copies of each other the trailing block can shrink by 10^16 with every few
@@ -107,10 +106,11 @@ __device__ __forceinline__ double quick_rcp(double x) {
 __device__ __forceinline__ double quick_sqrt(double x) { return x > 0.0 ? x * rsqrt(x) : 0.0; }
 
 // Root j of 1 + rho sum_i z_i^2 / (d_i - x) over the k poles d (ascending, distinct), as d[org] + tau; LPR lanes (4 or 16,
-// lane `sub` of them): the interpolation is repeated in every one of them, so few lanes where there are few poles.
+// lane `sub` of them): the interpolation is repeated in every one of them, so few lanes where there are few poles.  False
+// where `limit` steps did not get there.
 template <int LPR>
-__device__ __forceinline__ void secular_root(const double* d, const double* z, int k, double rho, int j, int sub, int& org,
-                                             double& tau) {
+__device__ __forceinline__ bool secular_root(const double* d, const double* z, int k, double rho, int j, int sub, int limit,
+                                             int& org, double& tau) {
   auto lanes_sum = [](double x) { return LPR == 4 ? quad_sum(x) : row_sum(x); };
   const bool last = j == k - 1;
   double zz = 0.0;
@@ -131,7 +131,7 @@ __device__ __forceinline__ void secular_root(const double* d, const double* z, i
   tau = 0.5 * (lo + hi);
   const double near = 4.0 * kUlp * quick_sqrt((double)k);
   const double dorg = d[org], dj = d[j] - dorg, dj1 = last ? 0.0 : d[j + 1] - dorg;
-  for (int it = 0; it < kMaxRootIterations; ++it) {
+  for (int it = 0; it < limit; ++it) {
     double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;         // poles up to j, and after it
     for (int i = sub; i < k; i += LPR) {
       const double inv = quick_rcp((d[i] - dorg) - tau), r = rho * z[i] * z[i] * inv, dr = r * inv;
@@ -140,7 +140,7 @@ __device__ __forceinline__ void secular_root(const double* d, const double* z, i
     }
     psi = lanes_sum(psi); dpsi = lanes_sum(dpsi); phi = lanes_sum(phi); dphi = lanes_sum(dphi);
     const double w = 1.0 + psi + phi;
-    if (fabs(w) <= near * (1.0 + fabs(psi) + fabs(phi))) break;
+    if (fabs(w) <= near * (1.0 + fabs(psi) + fabs(phi))) return true;
     if (w < 0.0) lo = tau; else hi = tau;
     const double dp = dj - tau;
     double eta;
@@ -154,9 +154,10 @@ __device__ __forceinline__ void secular_root(const double* d, const double* z, i
     }
     double next = tau + eta;
     if (!(next > lo && next < hi)) next = 0.5 * (lo + hi);       // also where the interpolation gave no number
-    if (next == tau || next == lo || next == hi) break;          // the bracket's ends are never taken: one may be a pole
+    if (next == tau || next == lo || next == hi) return true;    // the bracket's ends are never taken: one may be a pole
     tau = next;
   }
+  return false;
 }
 
 // Row pitch of a matrix in LDS: an odd multiple of sixteen doubles, so that the four rows a wave works on at a time lie in
@@ -170,7 +171,7 @@ template <int THREADS, int MAXN, bool LDS, bool QLDS>
 __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __restrict__ Kb, int m,
                                                               double* __restrict__ Db, double* __restrict__ Ub,
                                                               int32_t* __restrict__ infob, double* __restrict__ wsb,
-                                                              size_t ws_stride) {
+                                                              size_t ws_stride, int root_steps) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   __shared__ double d[MAXN], e[MAXN], htau[MAXN], v[2 * MAXN], w[MAXN];      // v: this column's and the next one's
   __shared__ double ds[MAXN], zs[MAXN], dk[MAXN], zk[MAXN], zh[MAXN], rtau[MAXN];
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __res
       Qt[(size_t)i * ldq + j] = i == j ? 1.0 : 0.0;
       Qnext[(size_t)i * ldq + j] = 0.0;  // elements outside a vector's block are never written
       const double aa = fabs(a);
-      amax = aa > amax ? aa : amax;      // a NaN never wins; it surfaces as "not converged" below
+      amax = aa > amax ? aa : amax;      // a NaN never wins; it is found in the tridiagonal matrix
     }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) { const double t = __shfl_xor(amax, o); amax = t > amax ? t : amax; }
@@ -461,7 +462,7 @@ __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __res
       if (j < k) {
         int o;
         double t;
-        secular_root<LPR>(dk + b0, zk + b0, k, 2.0 * fabs(e[b1 - 1]), j, tid % LPR, o, t);
+        if (!secular_root<LPR>(dk + b0, zk + b0, k, 2.0 * fabs(e[b1 - 1]), j, tid % LPR, root_steps, o, t)) bad = 1;
         if (tid % LPR == 0) { org[i] = (short)o; rtau[i] = t; }
       }
     }
@@ -674,7 +675,7 @@ size_t eigh_workspace(int m) {
 
 template <int THREADS, int MAXN, bool LDS, bool QLDS>
 hipError_t launch_divide(const float* K, int m, int batch, double* D, double* U, int32_t* info, double* ws,
-                         size_t ws_stride, hipStream_t s) {
+                         size_t ws_stride, int root_steps, hipStream_t s) {
   auto kern = divide_eigh_kernel<THREADS, MAXN, LDS, QLDS>;
   constexpr int matrices = LDS ? (QLDS ? 3 : 1) : 0;
   // eigh_pitch lets no single matrix grow past 128 x 128; 64 x 80 is the largest of three
@@ -684,20 +685,20 @@ hipError_t launch_divide(const float* K, int m, int batch, double* D, double* U,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL(kern, dim3(batch), dim3(THREADS), (size_t)matrices * m * eigh_pitch(m) * sizeof(double), s, K, m, D, U, info, ws,
-                     ws_stride);
+                     ws_stride, root_steps);
   return hipGetLastError();
 }
 
 hipError_t launch_ntk_eigh(const float* K, int m, int batch, double* D, double* U, int32_t* info, void* workspace,
-                           hipStream_t s) {
+                           hipStream_t s, int root_steps) {
   double* ws = static_cast<double*>(workspace);
   const size_t ws_stride = eigh_workspace(m) / sizeof(double);      // doubles per problem
   // where the matrices lie follows from what fits the LDS; 512 threads up to 32 sequences, 1024 above (64: 243 us against 289)
-  if (m <= 32) return launch_divide<512, 64, true, true>(K, m, batch, D, U, info, ws, ws_stride, s);
-  if (m <= 64) return launch_divide<1024, 64, true, true>(K, m, batch, D, U, info, ws, ws_stride, s);
-  if (m <= 128) return launch_divide<1024, 128, true, false>(K, m, batch, D, U, info, ws, ws_stride, s);
-  if (m <= 256) return launch_divide<1024, 256, false, false>(K, m, batch, D, U, info, ws, ws_stride, s);
-  return launch_divide<1024, kEighMaxSeq, false, false>(K, m, batch, D, U, info, ws, ws_stride, s);
+  if (m <= 32) return launch_divide<512, 64, true, true>(K, m, batch, D, U, info, ws, ws_stride, root_steps, s);
+  if (m <= 64) return launch_divide<1024, 64, true, true>(K, m, batch, D, U, info, ws, ws_stride, root_steps, s);
+  if (m <= 128) return launch_divide<1024, 128, true, false>(K, m, batch, D, U, info, ws, ws_stride, root_steps, s);
+  if (m <= 256) return launch_divide<1024, 256, false, false>(K, m, batch, D, U, info, ws, ws_stride, root_steps, s);
+  return launch_divide<1024, kEighMaxSeq, false, false>(K, m, batch, D, U, info, ws, ws_stride, root_steps, s);
 }
 
 hipError_t launch_eigh_solve(const EighSolveArgs& a, hipStream_t s) {

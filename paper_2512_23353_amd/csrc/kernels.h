@@ -249,8 +249,10 @@ struct EighSolveArgs {
   int32_t* info;               // [batch]
 };
 size_t eigh_workspace(int m);           // bytes per problem
+// root_steps: steps a root of the merges' secular equations may take before info reports it
+constexpr int kEighRootSteps = 100;
 hipError_t launch_ntk_eigh(const float* K, int m, int batch, double* D, double* U, int32_t* info, void* workspace,
-                           hipStream_t s);
+                           hipStream_t s, int root_steps = kEighRootSteps);
 hipError_t launch_eigh_solve(const EighSolveArgs& a, hipStream_t s);
 
 // Diagnostic: a loop of nothing but bf16 MFMAs (shape 32: 32x32x16, shape 16: 16x16x32) on register operands,

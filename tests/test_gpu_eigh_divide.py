@@ -1,5 +1,7 @@
 """The eigendecomposition on matrices that exercise the divide and conquer's deflation and its sizes (first-level pairs
 and single indices, where the matrices lie, LDS pitches): eigenvalues, orthogonality and reconstruction to rounding."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -88,3 +90,31 @@ def test_copies_of_sequences(gpu_device, m):
     for b in range(len(K)):
         assert np.abs(U[b].T @ U[b] - np.eye(m)).max() <= tol
         assert np.abs((U[b] * D[b]) @ U[b].T - Kd[b]).max() <= tol * size[b]
+
+
+def _eigh_in_steps(K, steps):
+    """isopo_ntk_eigh with its limit on the steps per root as an argument (the library's internal C++ function)."""
+    b, m, _ = K.shape
+    D = torch.empty((b, m), dtype=torch.float64, device=K.device)
+    U = torch.empty((b, m, m), dtype=torch.float64, device=K.device)
+    info = torch.full((b,), -1, dtype=torch.int32, device=K.device)
+    ws = isopo.alloc_workspace(isopo.load().isopo_ntk_eigh_workspace(m, b), K.device)
+    fn = isopo.load()._ZN5isopo15launch_ntk_eighEPKfiiPdS2_PiPvP12ihipStream_ti
+    ptr, num = ctypes.c_void_p, ctypes.c_int
+    assert fn(ptr(K.data_ptr()), num(m), num(b), ptr(D.data_ptr()), ptr(U.data_ptr()), ptr(info.data_ptr()),
+              ptr(ws.data_ptr()), ptr(torch.cuda.current_stream().cuda_stream), num(steps)) == 0
+    return D, U, info.tolist()
+
+
+@pytest.mark.parametrize("m", [3, 20, 64, 100, 130, 300])
+def test_roots_that_do_not_converge_are_reported(gpu_device, m):
+    """One step per root is too few for a Gram matrix and enough for a diagonal one, which has none to find; a tenth of the
+    library's own limit is enough for all."""
+    rng = np.random.default_rng(m)
+    K = np.stack([_matrix("gram", m, rng), np.diag(np.arange(1.0, m + 1)), _matrix("duplicates", m, rng)])
+    K = torch.from_numpy(K.astype(np.float32)).to(gpu_device)
+    assert _eigh_in_steps(K, 1)[2][:2] == [1, 0]
+    D, U, info = _eigh_in_steps(K, 10)
+    assert info == [0, 0, 0]
+    D1, U1, info = isopo.ntk_eigh(K)
+    assert info.tolist() == [0, 0, 0] and torch.equal(D, D1) and torch.equal(U, U1)
