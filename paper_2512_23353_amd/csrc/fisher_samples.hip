@@ -535,9 +535,15 @@ hipError_t launch_fisher_samples(const FisherSamplesArgs& a, hipStream_t s) {
       p.group[j - 1] = t;
     }
 
-  // up to two rounds of 32-token workgroups: 125 tiles of 1536 -> 8960 in bf16 77 us against 104, 110 of 512 -> 512 in fp32
-  // 39 against 44; from there on the wide form's full chip wins (157 tiles: 113 either way, 188: 110 against 105)
-  const bool narrow = token_tiles * n_launch_groups <= 128;
+  // One round of 32-token workgroups: always (59 tiles of 72 -> 112 in fp32, 128 samples, 25 us against 43; the least of 40
+  // layers of 40 .. 64 tiles 16.5 either way).  Two rounds: where a workgroup's walk, token row bytes times blocks of 32 samples,
+  // is long enough to pay for the second (125 tiles of 1536 -> 8960 in bf16 77 us against 104; of 120 layers 6144 bytes: 46
+  // against 54, 4704: 34.3 against 33.2, 3120: 29.7 against 28.0, 688: 25 against 18).  From there on the wide form's full
+  // chip wins (157 tiles: 113 either way, 188: 110 against 105).
+  long long walk = 0;
+  for (int g = 0; g < n_launch_groups; ++g) walk += features(p.group[g]) * (a.bf16 ? 2 : 4) * nbs;
+  const int tiles = token_tiles * n_launch_groups;
+  const bool narrow = tiles <= 64 || (tiles <= 128 && walk >= 5120LL * n_launch_groups);
   const long long ns = (long long)n_layers * a.n_seq * ncol;
   if (a.n_tokens > 0) {
     const long long items = ns > a.n_tokens ? ns : (long long)a.n_tokens;
