@@ -66,6 +66,7 @@ __device__ __forceinline__ void load_lds16_nt(const void* gptr, unsigned lds_add
 // NBL  row blocks of the LDS layout: 1, 2, 4 or 8 (NBL >= NB); stage = MB*NBL rows x KW elements
 template <bool BF16, int MB, int NB, int NBL>
 __global__ __launch_bounds__(256, 1) void stash_gram_stream_kernel(Params p) {
+  static_assert(BF16 || MB == 16, "fp32 products are formed in 16x16 blocks");
   constexpr int ES = BF16 ? 2 : 4, EPV = 16 / ES;   // bytes per element, elements per 16-byte vector
   constexpr int ROWS = MB * NBL;
   constexpr int RB = kStageBytes / ROWS;            // bytes per row and stage: 2048 (MB 16), 1024, 512, 256
@@ -160,9 +161,6 @@ __global__ __launch_bounds__(256, 1) void stash_gram_stream_kernel(Params p) {
             else if constexpr (BF16)
               a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, frag[bi]),
                                                           __builtin_bit_cast(bf16x8, frag[bj]), a, 0, 0, 0);
-            else if constexpr (MB == 32)
-              a = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(f32x4, frag[bi])[e],
-                                                       __builtin_bit_cast(f32x4, frag[bj])[e], a, 0, 0, 0);
             else
               a = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4, frag[bi])[e],
                                                        __builtin_bit_cast(f32x4, frag[bj])[e], a, 0, 0, 0);
