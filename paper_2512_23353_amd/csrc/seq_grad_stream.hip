@@ -840,9 +840,10 @@ hipError_t launch_stream(const SeqGradArgs& a, const ContractionPlan& pl, hipStr
   p.queue = queue;
   // The row-major epilogue stores half lines at a time, of rows that start anywhere in a line.  Left to the L2, the halves
   // meet there; stored non-temporally each goes to memory by itself (2344x2048, 60 sequences of 31 tokens: 482 us
-  // against 164; 1000x2728, 24 of 400: 123 against 96; 1584x4352, 56 of 2350: 1810 against 1731).  Only narrow layers on
+  // against 164; 1000x2728, 24 of 400: 123 against 96; 1584x4352, 56 of 2350: 1810 against 1731).  Narrow layers on
   // long sequences lose more by the stash in their L2 than they gain (176x5632, 34 of 626: 86 against 105; but 200x3000,
-  // 100 of 180: 82 against 65).
+  // 100 of 180: 82 against 65), so launches over 128x128 tiles on sequences of 256 tokens and more keep the non-temporal
+  // stores; among them are the ragged wide layers that small_tiles_win sends here.
   p.stream_stores = BM == 128 && (long long)a.n_tokens >= 256LL * a.n_seq;
   p.c = a.c;
   p.X = static_cast<const u16*>(a.X); p.Delta = static_cast<const u16*>(a.Delta); p.off = a.off; p.out = a.out;
