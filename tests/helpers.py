@@ -75,3 +75,20 @@ def split_plan(d_in, d_out, lengths, per_sequence):
     off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
     return fn(ctypes.c_int(d_out), ctypes.c_int(d_in), ctypes.c_int(int(off[-1])), ctypes.c_int(len(lengths)),
               off.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), ctypes.c_bool(per_sequence))
+
+
+class ContractionPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("tile", "occupancy", "tiles_m", "tiles_n", "n_chunks", "chunk_tokens",
+                                            "whole_tiles")] + [("xcd_start", ctypes.c_int * 9), ("blocks", ctypes.c_longlong)]
+
+
+def bf16_plan(d_in, d_out, lengths, per_sequence, weighted=False, budget=False):
+    """Launch plan of the bf16 contraction, also for the weighted sum and a launch with a budget of compute units, which
+    isopo_contraction_plan does not describe."""
+    from paper_2512_23353_amd import isopo
+    fn = isopo.load()._ZN5isopo16plan_contractionEiiiiPKibbb
+    fn.restype = ContractionPlan
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    return fn(ctypes.c_int(d_out), ctypes.c_int(d_in), ctypes.c_int(int(off[-1])), ctypes.c_int(len(lengths)),
+              off.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), ctypes.c_bool(per_sequence), ctypes.c_bool(weighted),
+              ctypes.c_bool(budget))

@@ -7,7 +7,7 @@ import torch
 from paper_2512_23353_amd import isopo
 from paper_2512_23353_amd import workloads as wl
 
-from helpers import to_device
+from helpers import bf16_plan, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -52,12 +52,15 @@ def test_row_major_tile(gpu_device, d_in, d_out, lens, tile):
         assert ((S[i].double() - G).abs() <= 2.0 ** -8 * G.abs() + lens[i] * 2.0 ** -23 * 1.01 * M).all(), i
 
 
-@pytest.mark.parametrize("d_in,d_out,lens", [
-    (512, 1288, [2500, 1, 0, 33, 5000, 4100] * 2),      # 12 wide tiles in chunks: narrow ones in fewer
-    (1536, 1536, [900, 31, 64] * 11),                   # 36
-    (256, 4352, [16500]),                               # one sequence
+@pytest.mark.parametrize("d_in,d_out,lens,tile", [
+    (512, 1288, [2500, 1, 0, 33, 5000, 4100] * 2, 128),      # 12 wide tiles in chunks: narrow ones in fewer
+    (1536, 1536, [900, 31, 64] * 11, 128),                   # 36
+    (1024, 2816, [16500], 128), (256, 4352, [16500], 256),   # one sequence, either side of what the last-level cache takes
+    (1536, 2560, [7000, 0, 12001, 2500], 256),               # past it as well
 ])
-def test_weighted_sum_in_chunks(gpu_device, d_in, d_out, lens):
+def test_weighted_sum_in_chunks(gpu_device, d_in, d_out, lens, tile):
+    plan = bf16_plan(d_in, d_out, lens, False, weighted=True)
+    assert plan.tile == tile and plan.n_chunks > 1 and bf16_plan(d_in, d_out, lens, False).tile == 256
     prob = wl.custom_layer(d_in, d_out, lens, dtype="bf16", seed=d_out, sigma_delta=1e-2, rho=0.3)
     layer, _ = to_device(prob, gpu_device)
     c = torch.randn(len(lens), generator=torch.Generator().manual_seed(3))
@@ -80,6 +83,7 @@ def test_budget_on_ragged_widths(gpu_device, d_in, d_out, lens, budget):
     prob = wl.custom_layer(d_in, d_out, lens, dtype="bf16", seed=d_in, sigma_delta=1e-2, rho=0.3)
     layer, _ = to_device(prob, gpu_device)
     assert isopo.contraction_plan(layer.ref(), True)["tile"] == 128
+    assert bf16_plan(d_in, d_out, lens, True, budget=True).tile == 256
     want = isopo.seq_grads(layer)
     for kw in ({}, {"layout": isopo.STASH_ROW_MAJOR}):
         queue = torch.full((8,), 12345, dtype=torch.int32, device=gpu_device)

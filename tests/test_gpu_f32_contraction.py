@@ -7,17 +7,22 @@ import torch
 from paper_2512_23353_amd import isopo
 from paper_2512_23353_amd import workloads as wl
 
-from helpers import to_device
+from helpers import split_plan, to_device
 
 pytestmark = pytest.mark.gpu
 
-# d_in, d_out, lengths: (tile, groups) the plan is meant to take in per-sequence mode
+# d_in, d_out, lengths, and what they are here for: (tile, groups) per sequence, (tile, groups, chunked) of the sum
 SHAPES = [
-    (4, 4, [1]), (64, 64, [16, 0, 15, 17]), (68, 132, [33, 1, 64]),          # few short items
-    (128, 260, [700, 31, 0, 1201]),                                          # few items, long walks: groups
-    (36, 1028, [90] * 27),                                                   # narrow: 64-wide tiles
-    (260, 516, list(range(1, 140, 2))),                                      # more than 64 sequences
-    (640, 1284, [150, 90, 1, 47, 0, 128, 200, 16] * 4),                      # 128-wide tiles, longest sequence first
+    (4, 4, [1], (64, 1), (64, 1, False)),
+    (64, 64, [16, 0, 15, 17], (64, 1), (64, 1, False)),                      # few short items
+    (68, 132, [33, 1, 64], (64, 1), (64, 2, False)),
+    (52, 20, [156, 123, 132, 0, 158], (64, 2), (64, 1, True)),
+    (128, 260, [700, 31, 0, 1201], (64, 4), (64, 1, True)),                  # few items, long walks: groups
+    (580, 916, [18, 10, 43, 54, 24, 59, 59, 0, 43], (128, 1), (64, 2, True)),
+    (8, 12, [9000, 0, 17, 21000, 5, 0, 15000], (64, 4), (64, 4, True)),      # more chunks would help
+    (36, 1028, [90] * 27, (64, 1), (64, 1, True)),                           # narrow: 64-wide tiles
+    (260, 516, list(range(1, 140, 2)), (64, 1), (64, 1, True)),              # more than 64 sequences
+    (640, 1284, [150, 90, 1, 47, 0, 128, 300, 16] * 4, (128, 1), (128, 1, True)),  # 128-wide tiles, longest sequence first
 ]
 
 
@@ -39,7 +44,10 @@ def _bound(n_terms):
 
 @pytest.mark.parametrize("case", range(len(SHAPES)))
 def test_f32_contraction_edges(gpu_device, case):
-    d_in, d_out, lengths = SHAPES[case]
+    d_in, d_out, lengths, per_sequence, summed = SHAPES[case]
+    one, plan = split_plan(d_in, d_out, lengths, True), split_plan(d_in, d_out, lengths, False)
+    assert (one.tile, one.groups) == per_sequence and one.longest_first == (d_in == 640)
+    assert (plan.tile, plan.groups, plan.n_chunks > 1) == summed
     prob = wl.custom_layer(d_in, d_out, lengths, dtype="f32", seed=400 + case, sigma_delta=1e-2, rho=0.3)
     layer, _ = to_device(prob, gpu_device)
     G, M = _reference(prob)

@@ -76,9 +76,8 @@ def test_rescaled_layer_update(gpu_device, dtype):
 
 @pytest.mark.parametrize("m", [1, 2, 3, 4, 16, 31, 32, 64, 65, 94, 95, 96, 128, 135, 200, 256, 511, 1024])
 def test_eigh_sizes(gpu_device, m):
-    """Both routes (Jacobi in LDS with 256 or 1024 threads up to 94 sequences, tridiagonalisation
-    and implicit QL in global scratch from 95), odd sizes (one idle index in the Jacobi pairing),
-    the degenerate m = 1 and the library's limit of 1024 sequences."""
+    """Every place the matrices can lie in (all in LDS up to 64 sequences, one up to 128, none above), odd
+    sizes, the degenerate m = 1 and the library's limit of 1024 sequences."""
     rng = np.random.default_rng(1000 + m)
     K = _random_gram(rng, m)
     A = rng.standard_normal(m).astype(np.float32)

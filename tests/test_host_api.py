@@ -9,7 +9,7 @@ import pytest
 
 from paper_2512_23353_amd import isopo
 
-from helpers import split_plan
+from helpers import bf16_plan, split_plan
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -311,3 +311,43 @@ def test_fp32_plan_orders_sequences_only_where_it_pays():
                                        (1536, 1536, [10] * 64 + [1024], 0), (64, 64, [10, 1024], 0)):
         assert split_plan(d_in, d_out, lengths, True).longest_first == want, (d_in, d_out, lengths)
     assert split_plan(1536, 1536, [256, 1024] * 8, False).longest_first == 0
+
+
+def test_fp32_plan_invariants_on_random_shapes():
+    """Whatever the plan, a shape that is built, every token in one chunk, chunks of whole 16-token blocks."""
+    rng = np.random.default_rng(2025)
+    seen = set()
+    for case in range(400):
+        d_in, d_out = (4 * int(np.exp(rng.uniform(0, np.log(1500)))) for _ in range(2))
+        n_seq = int(np.exp(rng.uniform(0, np.log(300))))
+        lengths = rng.integers(0, int(np.exp(rng.uniform(np.log(2), np.log(20000)))), n_seq)
+        if case % 9 == 0:
+            lengths[:] = 0
+        n = int(lengths.sum())
+        for per_sequence in (True, False):
+            plan = split_plan(d_in, d_out, lengths, per_sequence)
+            assert (plan.tile, plan.groups) in ((128, 1), (64, 1), (64, 2), (64, 4))
+            if per_sequence:
+                assert plan.n_chunks == 1
+                assert not plan.longest_first or (n_seq <= 64 and lengths.max() >= 128 + n // n_seq)
+            elif plan.n_chunks > 1:
+                assert plan.chunk_tokens % 16 == 0 and plan.n_chunks <= 64 and not plan.longest_first
+                assert plan.chunk_tokens * (plan.n_chunks - 1) < n <= plan.chunk_tokens * plan.n_chunks
+            else:
+                assert plan.chunk_tokens == max(n, 1)
+            seen.add((per_sequence, plan.tile, plan.groups, plan.n_chunks > 1))
+    assert len(seen) >= 9, seen
+
+
+def test_bf16_plan_of_the_weighted_sum_and_of_a_budget():
+    """What isopo_contraction_plan does not describe: narrow tiles for weighted sums of few tiles that are cut into chunks,
+    and wide ones for a launch with a budget of compute units wherever they fill the chip."""
+    assert [bf16_plan(1536, 1536, [640] * 16, False, weighted=w).tile for w in (False, True)] == [256, 128]
+    assert bf16_plan(4096, 4096, [1000] * 70, False, weighted=True).tile == 256            # not cut
+    assert bf16_plan(1536, 2560, [1000] * 89, False, weighted=True).tile == 256            # operands past the last-level cache
+    assert bf16_plan(2048, 2304, [1000] * 12, False, weighted=True).tile == 256            # 72 tiles
+    for d_in, d_out, lengths in ((264, 1280, [260] * 100), (520, 1288, [300] * 60), (1032, 2048, [780] * 8)):
+        wide, plan = bf16_plan(d_in, d_out, lengths, True, budget=True), bf16_plan(d_in, d_out, lengths, True)
+        assert (wide.tile, plan.tile) == (256, 128)
+        assert wide.xcd_start[8] == wide.tiles_m * wide.tiles_n * len(lengths) or wide.tiles_m * wide.tiles_n % 8 == 0
+    assert bf16_plan(264, 264, [30] * 4, True, budget=True).tile == 128                    # too few tiles either way
