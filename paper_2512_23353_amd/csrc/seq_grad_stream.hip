@@ -74,7 +74,6 @@ struct StreamParams {
   int whole_tiles;                 // sum-over-all-tokens mode: tiles before this one are not split
   int xcd_start[9];                // XCD x takes (item, tile) pairs [xcd_start[x], xcd_start[x+1]), item-major
   unsigned* queue;                 // persistent mode: eight work counters, one per XCD, zero at launch
-  int stream_stores;               // row-major stash: non-temporal stores
 };
 
 // 16 bytes per lane from a buffer straight into LDS: lane l lands at lds_addr + 16*l.
@@ -770,10 +769,12 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
             const int m = m0 + wm * WM + i * 32 + 16 * rb + l;
             const int n = n0 + wn * WN + jp * 64 + 8 * pc;
             if (m < p.row_end && n < p.d_in) {
-              const s16x8 piece = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-              s16x8* o = (s16x8*)(outp + (size_t)(m - p.out_row0) * p.d_in + n);
-              if (p.stream_stores) __builtin_nontemporal_store(piece, o);
-              else *o = piece;
+              // Half a line, of a row that starts anywhere in a line.  Left to the L2 the halves meet there; stored
+              // non-temporally each goes to memory by itself: 2216x632, 83 sequences of 41 tokens: 57 us against 158;
+              // 3256x2560, 28 of 346: 291 against 367; 568x1104, 79 of 213: 46 against 64.  Widths whose rows start at lines
+              // are level on average (256x1536, 85 of 750: 83 against 74; 512x3328, 40 of 24: 40 against 50).
+              *(s16x8*)(outp + (size_t)(m - p.out_row0) * p.d_in + n) =
+                  __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             }
           }
         }
@@ -838,13 +839,6 @@ hipError_t launch_stream(const SeqGradArgs& a, const ContractionPlan& pl, hipStr
                          unsigned* queue = nullptr) {
   StreamParams p;
   p.queue = queue;
-  // The row-major epilogue stores half lines at a time, of rows that start anywhere in a line.  Left to the L2, the halves
-  // meet there; stored non-temporally each goes to memory by itself (2344x2048, 60 sequences of 31 tokens: 482 us
-  // against 164; 1000x2728, 24 of 400: 123 against 96; 1584x4352, 56 of 2350: 1810 against 1731).  Narrow layers on
-  // long sequences lose more by the stash in their L2 than they gain (176x5632, 34 of 626: 86 against 105; but 200x3000,
-  // 100 of 180: 82 against 65), so launches over 128x128 tiles on sequences of 256 tokens and more keep the non-temporal
-  // stores; among them are the ragged wide layers that small_tiles_win sends here.
-  p.stream_stores = BM == 128 && (long long)a.n_tokens >= 256LL * a.n_seq;
   p.c = a.c;
   p.X = static_cast<const u16*>(a.X); p.Delta = static_cast<const u16*>(a.Delta); p.off = a.off; p.out = a.out;
   p.d_in = a.d_in; p.d_out = a.d_out; p.n_seq = a.n_seq; p.n_tokens = a.n_tokens;

@@ -21,9 +21,9 @@ def _sums(prob):
 
 
 @pytest.mark.parametrize("d_in,d_out,lens", [
-    (264, 1280, [300, 256, 511, 0, 260, 400]),   # long on average: non-temporal
-    (264, 1280, [300, 31, 0, 33, 200, 1]),       # short: through the L2
-    (8, 136, [256] * 3), (8, 136, [255] * 3),    # the line itself
+    (264, 1280, [300, 256, 511, 0, 260, 400]),   # long on average
+    (264, 1280, [300, 31, 0, 33, 200, 1]),       # short
+    (8, 136, [256] * 3), (8, 136, [255] * 3),    # one narrow tile
     (520, 1288, [20, 0, 40] * 6),                # wide tiles, ragged both ways
 ])
 def test_row_major_stash_stores(gpu_device, d_in, d_out, lens):
