@@ -11,17 +11,17 @@
 // (8 + 8 + 8 significant bits: exact from 2^-110 on, where the last bit of l is the last one bf16 has), and a product is
 // formed from the six partial products hh, hm, mh, mm, hl, lh.  The three left out are at most 2^-24 of the product, half
 // an ulp of the fp32 product itself; and six accumulations per sixteen tokens round the fp32 accumulator less often than
-// one per two tokens did.  Against
-// 64-bit sums over 34 layers of 32 .. 2048 by 32 .. 4096 the error of dW is 0.52 of the plain fp32 MFMA form's and that
-// of K 0.79 (geometric means).  1536x1536, 16 sequences, 10^4 tokens: 276 us per-sequence (182 TFLOP/s of fp32 products,
-// 1.1 PFLOP/s of bf16 at the clock the power limit leaves) against 609 us (78 TFLOP/s) for 64x64 fp32 MFMA tiles.
+// one per two tokens did.  Against 64-bit sums over 34 layers of 32 .. 2048 by 32 .. 4096 the error of dW is 0.52 of the plain
+// fp32 MFMA form's and that of K, with the Gram pass's own sums, 0.47 (geometric means; neither larger on any layer).
+// 1536x1536, 16 sequences, 10685 tokens: 286 us per-sequence (176 TFLOP/s of fp32 products, 1.06 PFLOP/s of bf16 at the clock
+// the power limit leaves) against 593 us (85 TFLOP/s) for 64x64 fp32 MFMA tiles; the weighted sum 304 against 677.
 //
 // A tile whose result is not finite (an infinity or NaN among the inputs, a value that bf16 rounds to infinity) or among
 // whose inputs is a nonzero value below 2^-110 (in the weighted sum: a Delta times its coefficient) is formed again with
-// fp32 MFMAs, the operands staged as they are in the same LDS (both passes of 1536x1536, 16 sequences, 10^4 tokens: 577 us where
-// every tile is formed twice, 273 where none is; from global memory, token by token, it was 835).
-// The operands are what has to be looked at, not the result: a small one may meet
-// a large one, or stand beside ordinary ones.  Subnormal parts and sums are kept by the bf16 MFMA as by the fp32 one.
+// fp32 MFMAs, the operands staged as they are in the same LDS (1536x1536, 16 sequences, 9499 tokens: 270 us, every tile formed
+// twice 580; the second time from global memory, token by token: 835).  The operands are what has to be looked at, not the
+// result: a small one may meet a large one, or stand beside ordinary ones.  The look costs a fifth of the staging's
+// instructions, under 2 % of a launch.  Subnormal parts and sums are kept by the bf16 MFMA as by the fp32 one.
 //
 // Both operands are token-major: the reduction index is the slow index of X and of Delta.  A thread loads two
 // features of eight consecutive tokens, splits them in registers and stores 16 bytes (one feature, eight tokens)
