@@ -122,12 +122,14 @@ isopo_status isopo_gram_cost_model(const isopo_layer* layer, double* t_ghost, do
  *                      work, XCD x walks [xcd_start[x], xcd_start[x+1]).  All zero: no list - per-sequence
  *                      mode with tiles % 8 == 0 gives XCD x the x-th eighth of every sequence's tiles,
  *                      the unsplit unweighted mode has one item
- *   workgroups         grid size of the one-workgroup-per-pair launch (some workgroups may find their XCD's
- *                      range exhausted and exit); with the 256 tile isopo_layer_gram and
- *                      isopo_seq_grads_limited launch at most 256 (or the budget) persistent workgroups over
- *                      the same list instead.  isopo_seq_grads_limited also takes the 256 tile, over the list
- *                      that goes with it, on layers large enough for it whose widths are no multiples of 256
- *                      and for which 128 is reported here */
+ *   workgroups         grid size of a launch with one workgroup per pair (some workgroups may find their XCD's
+ *                      range exhausted and exit).  Both hold for a sum cut into chunks.  The per-sequence launches, and
+ *                      uncut sums of more than 256 tiles, run at most 256 workgroups (512 with the 128 tile; or the
+ *                      budget of isopo_seq_grads_limited), each with a list of pairs of its own: every sequence's tiles
+ *                      are dealt evenly to the XCDs, the longest sequences' first, and there the fields describe one
+ *                      equal-work cut of the pairs that no launch follows.  isopo_seq_grads_limited also takes the 256
+ *                      tile on layers large enough for it whose widths are no multiples of 256 and for which 128 is
+ *                      reported here */
 typedef struct {
   int32_t tile, workgroups_per_cu, tiles, n_chunks, chunk_tokens;
   int32_t xcd_start[9];
@@ -186,8 +188,8 @@ isopo_status isopo_seq_grads(const isopo_layer* layer, void* stash, void* stream
  *                   all sequences, 256 tiles) with more tiles than the budget, also those that
  *                   isopo_seq_grads would form in 128x128 tiles; smaller problems and fp32 inputs run as
  *                   isopo_seq_grads does.
- *   queue_dev       device uint32[8], 4-byte aligned, caller-owned scratch; zeroed and used by the call
- *                   (work counters); must not be shared by launches that may run concurrently */
+ *   queue_dev       device uint32[8], 4-byte aligned, caller-owned scratch; zeroed by a call that honours the budget;
+ *                   must not be shared by launches that may run concurrently */
 isopo_status isopo_seq_grads_limited(const isopo_layer* layer, void* stash, int32_t max_workgroups,
                                      uint32_t* queue_dev, void* stream);
 

@@ -25,11 +25,10 @@ struct SeqGradArgs {
   float beta;
   bool per_sequence;
   bool bf16;
-  // per_sequence, bf16: at most this many workgroups resident at a time (0: no limit), fed from `queue`,
-  // eight device counters the launch zeroes; the other compute units stay free for other streams
+  // per_sequence, bf16: at most this many workgroups (0: no limit), so that the other compute units stay free for other
+  // streams; the launch takes a tile that can keep the limit.  `queue`: eight device words it clears
   int max_workgroups = 0;
   unsigned* queue = nullptr;
-  bool budget = false;       // that limit is the caller's own: the launch takes a tile that can keep it
   // per_sequence, bf16: store every sequence's gradient in the order the accumulators hold it (see
   // stash_tile_order_ok) instead of row-major
   bool tile_order = false;
@@ -50,10 +49,10 @@ struct ContractionPlan {
   int n_chunks, chunk_tokens;  // sum-over-all-tokens mode: token chunks (1: no split)
   int whole_tiles;             // sum-over-all-tokens mode: tiles [0, whole_tiles) of the tile order are not split
                                // (one workgroup each, all tokens); the chunks apply to the tiles after them
-  int xcd_start[9];            // XCD x walks (item, tile) pairs [xcd_start[x], xcd_start[x+1]) of the item-major
-                               // list (items: sequences or chunks); all zero: the x-th eighth of every item's
-                               // tiles (per-sequence mode), or no items at all (unsplit)
-  long long blocks;            // workgroups to launch
+  int xcd_start[9];            // a split sum's XCD x walks (chunk, tile) pairs [xcd_start[x], xcd_start[x+1]) of the
+                               // chunk-major list.  Per-sequence mode: such a cut of the (sequence, tile) list, or all
+                               // zero; the launch has its own lists (seq_grad_walk.hip)
+  long long blocks;            // workgroups of a launch with one per pair
 };
 ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
                                  bool per_sequence, bool weighted = false, bool budget = false);
@@ -69,7 +68,7 @@ SplitContractionPlan plan_split_contraction(int rows, int d_in, int n_tokens, in
                                             bool per_sequence);
 // o[i] = beta * o[i] (0 for beta = 0, whatever o held), ahead of an atomic accumulation.
 hipError_t launch_apply_beta(float* o, long long n, float beta, hipStream_t s);
-// bf16 only, c == nullptr only: the direct-to-LDS streaming kernel (launch_seq_grad routes to it).
+// bf16 only: the direct-to-LDS streaming kernels (launch_seq_grad routes to them).
 hipError_t launch_seq_grad_stream(const SeqGradArgs& a, hipStream_t s);
 // Schedule probe: the plain sum over all tokens (c == nullptr, not per sequence) on the 256x256 tile with four or
 // eight waves per workgroup; hipErrorInvalidValue where the plan would take the 128x128 tile.

@@ -1,6 +1,7 @@
-// Token-reduction contraction, bf16, streaming variant: the kernel behind the
-// per-sequence gradients G_i = Delta_i^T X_i (`grad_out.T @ act_in` of both hook
-// listings) and behind the unweighted dW = Delta^T X.
+// Token-reduction contraction, bf16, streaming variant, a work item per workgroup: the sums over all tokens,
+// dW = Delta^T X and dW = Delta^T diag(c_tok) X.  (The per-sequence gradients, and the sums of layers with many tiles
+// for few tokens, are formed by the kernel of seq_grad_walk.hip, whose workgroups walk lists of items; launch_seq_grad_stream
+// routes to it.)
 //
 // Design (gfx950):
 //  * Operand tiles go from HBM/L2 straight into LDS with buffer_load ... lds
@@ -14,49 +15,26 @@
 //    NSTAGE-1 blocks are in flight while one is multiplied; one s_barrier per block.
 //  * MFMA fragments need 8 consecutive tokens of one feature per lane; they come
 //    from the LDS transpose read (ds_read_b64_tr_b16).  Rows are not padded:
-//    the 16-byte column index is XOR-swizzled with the token row
-//    (f(r) = 4*(r&3) ^ (r&2)), which makes both the linear DMA writes and the
-//    transpose reads bank-conflict free.
-//  * Two inner loops.  The tile-order stash and the sum over all tokens use the
-//    16x16x32 MFMA (less energy per flop, and the part runs at its power cap): a
-//    token block is one K = 32 step of 64 MFMAs per wave (32 with eight waves per
-//    workgroup, which the sums over all tokens use on the 256x256 tile); the DMA
+//    the 16-byte column index is XOR-swizzled with the token row, which makes both the
+//    linear DMA writes and the transpose reads bank-conflict free.
+//  * The 16x16x32 MFMA, which draws less energy per flop than the 32x32x16 one (the part
+//    runs at its power cap): a token block is one K = 32 step of 64 MFMAs per wave (32 with eight waves per
+//    workgroup, on the 256x256 tile); the DMA
 //    instructions of the block NSTAGE-1 ahead (eight per wave, or four) go out
 //    behind the first half of them, the barrier sits mid-block, the next block's
-//    fragments are read behind the second half.  The row-major stash keeps the 32x32x16 MFMA, whose
-//    accumulator blocks its transposing epilogue is written for: fragments
-//    double-buffered in registers, the reads of the next half block interleaved
-//    one-to-one with the MFMAs of the current one, the DMA instructions between
-//    the MFMAs of the second half block.
-//  * Per-sequence mode: XCD x owns the x-th eighth of the output tiles of every
-//    sequence, so all eight L2s see every sequence (balanced under ragged
-//    lengths) and neighbouring workgroups share operand panels.  When the tile
-//    count is no multiple of eight that would leave XCDs unevenly loaded (or
-//    idle); the host then cuts the sequence-major list of (sequence, tile) pairs
-//    into eight contiguous ranges of equal work (tokens plus a fixed charge per
-//    workgroup) and each XCD walks one.  For a row-major stash the bf16 tile is
-//    transposed through LDS in the epilogue so that every lane stores 16 bytes;
-//    for a stash in tile order (TILED) every lane stores the 16 bytes it holds,
-//    with no LDS round trip at all.
-//  * Sum-over-all-tokens mode with few output tiles (narrow projections, long
-//    microbatches): the token range is split into chunks, a workgroup takes one
-//    (chunk, tile) pair from its XCD's range of the same kind of list, and the
+//    fragments are read behind the second half.
+//  * With few output tiles (narrow projections, long
+//    microbatches) the token range is split into chunks, a workgroup takes one
+//    (chunk, tile) pair from its XCD's range of the chunk-major list of pairs (eight contiguous ranges of equal work), and the
 //    fp32 partial tiles are added to dW with hardware float atomics after a pass
 //    that applies beta.  With more tiles than compute units only the tiles of the
 //    last, partial round of one tile per unit are split; the others stay whole.
-#include "common.h"
-#include "kernels.h"
+#include "seq_grad_stream.h"
 
 #include <type_traits>
 
 namespace isopo {
 namespace {
-
-typedef unsigned short u16;
-typedef s16x4 __attribute__((address_space(3)))* lds_s16x4_ptr;
-typedef void __attribute__((address_space(3)))* lds_void_ptr;
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
 struct StreamParams {
   const u16* X;
@@ -66,146 +44,68 @@ struct StreamParams {
   void* out;
   int d_in, d_out, n_seq, n_tokens;
   int row0, row_end, out_row0;
-  long long out_seq_stride;
   float beta;
-  int tiles_m, tiles_n;
+  TileGrid grid;
   unsigned n_blocks;
-  int n_chunks, chunk_tokens;      // sum-over-all-tokens mode: token chunks (1: no split)
-  int whole_tiles;                 // sum-over-all-tokens mode: tiles before this one are not split
-  int xcd_start[9];                // XCD x takes (item, tile) pairs [xcd_start[x], xcd_start[x+1]), item-major
-  unsigned* queue;                 // persistent mode: eight work counters, one per XCD, zero at launch
+  int n_chunks, chunk_tokens;      // token chunks (1: no split)
+  int whole_tiles;                 // tiles before this one are not split
+  int xcd_start[9];                // XCD x takes (chunk, tile) pairs [xcd_start[x], xcd_start[x+1]), chunk-major
 };
 
-// 16 bytes per lane from a buffer straight into LDS: lane l lands at lds_addr + 16*l.
-// Inline asm, so that the compiler's LDS-DMA tracking does not put a vmcnt(0) before
-// every later LDS read; the kernel orders them itself with s_waitcnt vmcnt(n) + s_barrier.
-__device__ __forceinline__ void load_lds16(v4i rsrc, unsigned lds_addr, unsigned voff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               : : "s"(lds_addr), "v"(voff), "s"(rsrc) : "memory");
-}
-
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// Two fp32 -> one dword of two bf16 (round to nearest even), one v_cvt_pk_bf16_f32.
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
-  f32x2 v = {lo, hi};
-  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
-}
-
-// Accumulator element -> VGPR at the point of use.  Without this the register allocator copies the
-// whole 256-register tile out of the AGPRs before the epilogue and spills.
-__device__ __forceinline__ float acc_read(float a) {
-  float v;
-  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
-  return v;
-}
-
-constexpr int BK = 32;
-
-// Column-blocked tile order: ids run down 8-column strips of the tile grid, so the 32 workgroups an
-// XCD runs at a time cover about 4 tile rows x 8 tile columns (12 operand panels) rather than
-// 2 x 16 (18 panels): fewer L2 misses per flop.
-__device__ __forceinline__ void strip_tile_coords(int tile, int tiles_m, int tiles_n, int& tile_m, int& tile_n) {
-  constexpr int W = 8;
-  const int strip = tile / (tiles_m * W);
-  const int c0 = strip * W;
-  const int w = tiles_n - c0 < W ? tiles_n - c0 : W;     // the last strip may be narrower
-  const int in_strip = tile - strip * tiles_m * W;
-  tile_m = in_strip / w;
-  tile_n = c0 + in_strip % w;
-}
-
-// NW: waves per workgroup.  Four: a 2 x 2 arrangement of BM/2 x BN/2 wave tiles, one wave per SIMD on the
-// 256x256 tile with its accumulators pinned to the AGPRs.  Eight (16x16x32 loop only): 2 x 4, wave tiles of
-// BM/2 x BN/4, two waves per SIMD, 128 accumulators per lane in VGPRs, half the DMA instructions per wave, so
+// NW: waves per workgroup.  Four: a 2 x 2 arrangement of BT/2 x BT/2 wave tiles, one wave per SIMD on the
+// 256x256 tile with its accumulators pinned to the AGPRs.  Eight: 2 x 4, wave tiles of
+// BT/2 x BT/4, two waves per SIMD, 128 accumulators per lane in VGPRs, half the DMA instructions per wave, so
 // that twice as many waves issue operand loads.  On the workload's operands, where the board's power limit sets
-// the rate, the two are within a few per cent of each other: the per-sequence launch is no faster with eight
-// and keeps four; the sums over all tokens are 1 - 5 % faster with eight (more where the launch is not at the
-// power limit) and take eight on the 256x256 tile.
-template <int BM, int BN, int NSTAGE, bool PER_SEQ, bool PERSIST, bool TILED, bool WTD, int NW>
+// the rate, the two are within a few per cent of each other: the sums are 1 - 5 % faster with eight (more where the launch is
+// not at the power limit) and take eight on the 256x256 tile; four serve the 128x128 tile and the schedule probe.
+template <int BT, bool WTD, int NW>
 __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
-  static_assert(PER_SEQ || !TILED, "tile order is a layout of the per-sequence stash");
-  static_assert(!PER_SEQ || !WTD, "the coefficients weight the sum over all tokens");
-  // the 16x16x32 inner loop: the tile-order stash and the sum over all tokens (the row-major stash keeps the
-  // 32x32x16 loop, whose accumulator blocks its transposing epilogue is written for)
-  constexpr bool MF16 = TILED || !PER_SEQ;
-  static_assert(PER_SEQ || !PERSIST, "the persistent mode serves the per-sequence gradients");
-  static_assert(NW == 4 || (NW == 8 && (TILED || !PER_SEQ)), "eight waves: the 16x16x32 loop only");
+  static_assert(NW == 4 || NW == 8, "waves per workgroup");
   constexpr int WNC = NW / 2, NT = 64 * NW;                    // waves along the tile's columns; threads
-  constexpr int WM = BM / 2, WN = BN / WNC, FM = WM / 32, FN = WN / 32;
-  constexpr unsigned PA = BM * 2, PB = BN * 2;                 // LDS row pitch, bytes (no padding: swizzled)
-  constexpr unsigned A_BYTES = BK * PA, B_BYTES = BK * PB, STAGE = A_BYTES + B_BYTES;
-  constexpr int LA = A_BYTES / 1024 / NW, LB = B_BYTES / 1024 / NW;   // 1 KiB wave-loads per wave and tile
-  constexpr int RA = 1024 / PA, RB = 1024 / PB;                // tile rows per wave-load
+  constexpr int WM = BT / 2, WN = BT / WNC;
+  constexpr unsigned P = BT * 2;                               // LDS row pitch, bytes (no padding: swizzled)
+  constexpr unsigned HALF = BK * P, STAGE = 2 * HALF;          // Delta's rows, then X's
+  constexpr int LH = HALF / 1024 / NW, LPT = 2 * LH;           // 1 KiB wave-loads per wave: of an operand, of a block
+  constexpr int RPL = 1024 / P;                                // tile rows per wave-load
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const unsigned smem_base = (unsigned)(size_t)(lds_void_ptr)smem;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WNC, wn = wave % WNC;
 
-  // Persistent mode (per-sequence only): the grid is a chosen number of workgroups, a multiple of eight;
-  // the workgroups of XCD x pull that XCD's work items one at a time from the counter queue[x].  The
-  // launch then occupies that many compute units and no more, and kernels queued on other streams (the
-  // passes over the previous layer's stash) run on the rest.
-  __shared__ int sh_next;
-  for (int round = 0;; ++round) {
-    int e;
-    if constexpr (PERSIST) {
-      if (round > 0) {
-        // nobody still reads the previous item's LDS (epilogue staging) or its sh_next
-        __builtin_amdgcn_s_waitcnt(0xc07f);
-        __builtin_amdgcn_s_barrier();
-      }
-      if (tid == 0) sh_next = (int)atomicAdd(p.queue + (blockIdx.x & 7), 1u);
-      __syncthreads();
-      e = sh_next;
-    } else {
-      e = (int)(blockIdx.x >> 3);
-    }
-    int item, tile;
-    bool split = !PER_SEQ && p.n_chunks > 1;       // this workgroup adds a token chunk's part with atomics
-    if (!PER_SEQ && p.whole_tiles > 0) {
+  {
+    const int e = (int)(blockIdx.x >> 3), tiles = p.grid.m * p.grid.n;
+    int item = 0, tile;
+    bool split = p.n_chunks > 1;                   // this workgroup adds a token chunk's part with atomics
+    if (p.whole_tiles > 0) {
       // Whole tiles first, then the token chunks of the remaining tiles; XCD x takes the x-th eighth of
       // each of the two lists, in id order, so a compute unit gets chunks once its whole tiles are done.
       const int x = blockIdx.x & 7, wq = p.whole_tiles >> 3;
       if (e < wq) {
-        item = 0;
         tile = x * wq + e;
         split = false;
       } else {
-        const int rest = p.tiles_m * p.tiles_n - p.whole_tiles, S = rest * p.n_chunks;
+        const int rest = tiles - p.whole_tiles, S = rest * p.n_chunks;
         const int first = (int)((long long)x * S / 8);
         const int id = first + (e - wq);
-        if (id >= (int)((long long)(x + 1) * S / 8)) break;
+        if (id >= (int)((long long)(x + 1) * S / 8)) return;
         item = id / rest;
         tile = p.whole_tiles + id % rest;
       }
-    } else if (PER_SEQ || split) {
-      const int tiles = p.tiles_m * p.tiles_n;
-      const int x = blockIdx.x & 7;
-      if (p.xcd_start[8] > 0) {
-        // XCD x (= blockIdx % 8) walks a contiguous range of the item-major (item, tile) list; the host cut
-        // the list into eight ranges of equal work
-        const int id = p.xcd_start[x] + e;
-        if (id >= p.xcd_start[x + 1]) break;
-        item = id / tiles;
-        tile = id - item * tiles;
-      } else {
-        // XCD x owns tiles [x*tiles/8, (x+1)*tiles/8) of every sequence (or token chunk)
-        const int s0 = x * tiles / 8, cs = (x + 1) * tiles / 8 - s0;
-        if (cs == 0 || e >= (PER_SEQ ? p.n_seq : p.n_chunks) * cs) break;
-        item = e / cs;
-        tile = s0 + e % cs;
-      }
+    } else if (split) {
+      // XCD x (= blockIdx % 8) walks a contiguous range of the chunk-major (chunk, tile) list; the host cut
+      // the list into eight ranges of equal work
+      const int x = blockIdx.x & 7, id = p.xcd_start[x] + e;
+      if (id >= p.xcd_start[x + 1]) return;
+      item = id / tiles;
+      tile = id - item * tiles;
     } else {
-      item = 0;
       tile = xcd_contiguous(blockIdx.x, p.n_blocks);
     }
     int tile_m, tile_n;
-    strip_tile_coords(tile, p.tiles_m, p.tiles_n, tile_m, tile_n);
-    const int m0 = p.row0 + tile_m * BM, n0 = tile_n * BN;
-    const int t0 = PER_SEQ ? p.off[item] : (split ? item * p.chunk_tokens : 0);
-    const int t1 = PER_SEQ ? p.off[item + 1] : (split ? min(p.n_tokens, t0 + p.chunk_tokens) : p.n_tokens);
+    tile_coords(tile, p.grid, tile_m, tile_n);
+    const int m0 = p.row0 + tile_m * BT, n0 = tile_n * BT;
+    const int t0 = split ? item * p.chunk_tokens : 0;
+    const int t1 = split ? min(p.n_tokens, t0 + p.chunk_tokens) : p.n_tokens;
     const int n_rows = t1 - t0;
     int n_tiles = (n_rows + BK - 1) / BK;
     // Weighted sum over all tokens: the token range is walked segment by segment (a segment: the part of one
@@ -338,44 +238,38 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
       range_open(ld, t0, n_rows);
     }
 
-    // 16-byte column swizzle of token row r.  The 16x16x32 fragments (TILED) are read by lane groups whose
-    // rows lie 8 apart, so that variant also moves rows 8..15 and 24..31 by two columns.
-    auto swz = [](int r) { return ((r & 3) << 2) ^ (r & 2) ^ (MF16 ? ((r >> 3) & 1) << 1 : 0); };
-    unsigned offA[LA], offB[LB];
+    // 16-byte column swizzle of token row r (fragments are read by lane groups whose rows lie 8 apart)
+    auto swz = [](int r) { return ((r & 3) << 2) ^ (r & 2) ^ (((r >> 3) & 1) << 1); };
+    unsigned offA[LH], offB[LH];
 #pragma unroll
-    for (int q = 0; q < LA; ++q) {
-      const int r = (wave * LA + q) * RA + lane / (64 / RA);
-      const int g = (lane % (64 / RA)) ^ swz(r);
+    for (int q = 0; q < LH; ++q) {
+      const int r = (wave * LH + q) * RPL + lane / (64 / RPL);
+      const int g = (lane % (64 / RPL)) ^ swz(r);
       offA[q] = (unsigned)r * rbA + (unsigned)(m0 * 2 + g * 16);
-    }
-#pragma unroll
-    for (int q = 0; q < LB; ++q) {
-      const int r = (wave * LB + q) * RB + lane / (64 / RB);
-      const int g = (lane % (64 / RB)) ^ swz(r);
       offB[q] = (unsigned)r * rbB + (unsigned)(n0 * 2 + g * 16);
     }
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+    auto issue = [&](int q, v4i ra, v4i rb, unsigned stage) {
+      if (q < LH) load_lds16(ra, stage + (unsigned)(wave_s * LH + q) * 1024, offA[q]);
+      else load_lds16(rb, stage + HALF + (unsigned)(wave_s * LH + (q - LH)) * 1024, offB[q - LH]);
+    };
     auto issue_loads = [&](int it) {
       v4i ra, rb;
       next_block(ld, ra, rb);
       if constexpr (WTD) segment_step(ld);
       const unsigned stage = smem_base + ((unsigned)it % NSTAGE) * STAGE;
 #pragma unroll
-      for (int q = 0; q < LA; ++q) load_lds16(ra, stage + (unsigned)(wave_s * LA + q) * 1024, offA[q]);
-#pragma unroll
-      for (int q = 0; q < LB; ++q) load_lds16(rb, stage + A_BYTES + (unsigned)(wave_s * LB + q) * 1024, offB[q]);
+      for (int q = 0; q < LPT; ++q) issue(q, ra, rb, stage);
     };
 
-    if constexpr (MF16) {
-      // ---- stash in tile order, and the sum over all tokens: the 16x16x32 MFMA, which draws less power per flop than the 32x32x16 one
-      // (a loop of either on random operands in registers sustains 2.04 against 1.81 PFLOP/s under the
+    {
+      // ---- the 16x16x32 MFMA, which draws less power per flop than the 32x32x16 one (a loop of either on random operands in registers sustains 2.04 against 1.81 PFLOP/s under the
       // board's power cap).  A token block is one K = 32 step: 8 + 8 fragments (16 features x 32 tokens
       // each), FM16 x FN16 MFMAs row by row.  Behind row i go the next block's B fragment i (into the other
       // of two register sets) and, once the row is done with it, the next block's A fragment i (in place),
       // and a share of the eight DMA instructions of the block AHEAD ahead.  One barrier per block.
       constexpr int FM16 = WM / 16, FN16 = WN / 16, NMF16 = FM16 * FN16;
       static_assert(NMF16 - (FM16 / 2) * FN16 >= FN16 + FM16 / 2, "the second half's MFMAs carry the next block's fragment reads");
-      constexpr int LPT = LA + LB, AHEAD = NSTAGE - 1;
       typedef float f32x4v __attribute__((ext_vector_type(4)));
       unsigned adA[FM16], adB[FN16];
       {
@@ -387,17 +281,17 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
 #pragma unroll
         for (int i = 0; i < FM16; ++i) {
           const int ca = wm * WM + i * 16 + 4 * (l & 3);
-          adA[i] = (unsigned)kr * PA + (unsigned)(((ca >> 3) ^ f) << 4) + (unsigned)((ca & 7) * 2);
+          adA[i] = (unsigned)kr * P + (unsigned)(((ca >> 3) ^ f) << 4) + (unsigned)((ca & 7) * 2);
         }
 #pragma unroll
         for (int j = 0; j < FN16; ++j) {
           const int cb = wn * WN + j * 16 + 4 * (l & 3);
-          adB[j] = A_BYTES + (unsigned)kr * PB + (unsigned)(((cb >> 3) ^ f) << 4) + (unsigned)((cb & 7) * 2);
+          adB[j] = HALF + (unsigned)kr * P + (unsigned)(((cb >> 3) ^ f) << 4) + (unsigned)((cb & 7) * 2);
         }
       }
-      auto frag = [&](unsigned a, unsigned pitch) {
+      auto frag = [&](unsigned a) {
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a + 4 * pitch));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a + 4 * P));
         return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
       };
       f32x4v acc[FM16][FN16];
@@ -414,17 +308,14 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
         __builtin_amdgcn_s_waitcnt(0x0f70 | (((AHEAD - 1) * LPT) & 15) | ((((AHEAD - 1) * LPT) >> 4) << 14));
         __builtin_amdgcn_s_barrier();
 #pragma unroll
-        for (int i = 0; i < FM16; ++i) fa[i] = frag(smem_base + adA[i], PA);
+        for (int i = 0; i < FM16; ++i) fa[i] = frag(smem_base + adA[i]);
 #pragma unroll
-        for (int j = 0; j < FN16; ++j) fb[0][j] = frag(smem_base + adB[j], PB);
+        for (int j = 0; j < FN16; ++j) fb[0][j] = frag(smem_base + adB[j]);
         // The descriptors of the next block's loads are formed a block ahead, behind the barrier, so that this
         // scalar work issues between MFMAs and not ahead of a block's first one.
-        constexpr bool PIPE = true;
-        [[maybe_unused]] v4i ra_n, rb_n;
-        if constexpr (PIPE) {
-          next_block(ld, ra_n, rb_n);
-          if constexpr (WTD) segment_step(ld);
-        }
+        v4i ra_n, rb_n;
+        next_block(ld, ra_n, rb_n);
+        if constexpr (WTD) segment_step(ld);
         // LATE: the two waves of the lower tile half take the other of every two read slots, so that the LDS
         // serves two waves' fragment reads at a time, not four (compile-time, as CUR, so that the bodies stay
         // straight-line code)
@@ -440,8 +331,7 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
           constexpr int SCALE = decltype(scale_c)::value;
           static_assert(SCALE == 0 || NMF16 * 4 <= 128, "the multiplications are written for accumulators in VGPRs");
           const unsigned sn = smem_base + ((unsigned)(it + 1) % NSTAGE) * STAGE;
-          v4i ra, rb;                              // of block it + AHEAD
-          if constexpr (PIPE) { ra = ra_n; rb = rb_n; } else next_block(ld, ra, rb);
+          const v4i ra = ra_n, rb = rb_n;          // of block it + AHEAD
           const unsigned stage = smem_base + ((unsigned)(it + AHEAD) % NSTAGE) * STAGE;
           // When the accumulator tile fills the AGPRs the MFMA is written as asm, so that every accumulator
           // stays where it is (left to itself the register allocator shuttles them through VGPRs).
@@ -471,8 +361,7 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
               for (int q = idx * LPT / HEAD; q < (idx + 1) * LPT / HEAD; ++q) {
                 // builtin MFMAs: the scheduler would move every load to the top of the block, ahead of the MFMAs
                 if constexpr (NMF16 * 4 <= 128) __builtin_amdgcn_sched_barrier(0);
-                if (q < LA) load_lds16(ra, stage + (unsigned)(wave_s * LA + q) * 1024, offA[q]);
-                else load_lds16(rb, stage + A_BYTES + (unsigned)(wave_s * LB + (q - LA)) * 1024, offB[q - LA]);
+                issue(q, ra, rb, stage);
               }
             }
           // block it + 1 has landed (this wave's part; the barrier makes it everyone's)
@@ -480,7 +369,7 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
           __builtin_amdgcn_s_barrier();
           // the descriptors the next block's loads need: scalar work that issues between this half's MFMAs
           // instead of ahead of the next block's first one
-          if constexpr (PIPE) next_block(ld, ra_n, rb_n);
+          next_block(ld, ra_n, rb_n);
           // the other rows: behind their MFMAs the fragments of block it + 1, the B ones into the other register
           // set, the A ones in place: those of the first RB rows at once, the others as their rows end
 #pragma unroll
@@ -495,14 +384,14 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
                   acc[q / FN16][q % FN16] = acc[q / FN16][q % FN16] * r;
               }
               constexpr int PER = REST / (FN16 + RB);                 // MFMAs per fragment slot
-              if (j == (LATE && PER > 1 ? 1 : 0) && i > RB) fa[i - 1] = frag(sn + adA[i - 1], PA);
+              if (j == (LATE && PER > 1 ? 1 : 0) && i > RB) fa[i - 1] = frag(sn + adA[i - 1]);
               if (k % PER == (LATE ? 0 : PER - 1)) {
                 const int f = k / PER;
-                if (f < FN16) fb[NXT][f] = frag(sn + adB[f], PB);
-                else if (f < FN16 + RB) fa[f - FN16] = frag(sn + adA[f - FN16], PA);
+                if (f < FN16) fb[NXT][f] = frag(sn + adB[f]);
+                else if (f < FN16 + RB) fa[f - FN16] = frag(sn + adA[f - FN16]);
               }
             }
-          fa[FM16 - 1] = frag(sn + adA[FM16 - 1], PA);
+          fa[FM16 - 1] = frag(sn + adA[FM16 - 1]);
           // weighted sum: the cursor's branch (taken where a segment ends) closes the block.  Behind the barrier
           // it would cut the block in two there, with the scalar work of the second part standing between the
           // barrier and the MFMAs that follow it.
@@ -551,248 +440,36 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
       auto rd16 = [](float a) {
         if constexpr (NMF16 * 4 > 128) return acc_read(a); else return a;
       };
-      (void)rd16;
-      if constexpr (!PER_SEQ) {
-        // dW: sixteen lanes store (or add) sixteen consecutive floats of a row
-        const int col = lane & 15, rq = lane >> 4;
-#pragma unroll
-        for (int i = 0; i < FM16; ++i)
-#pragma unroll
-          for (int j = 0; j < FN16; ++j) {
-            const int n = n0 + wn * WN + j * 16 + col;
-            if (n >= p.d_in) continue;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const int m = m0 + wm * WM + i * 16 + 4 * rq + v;
-              if (m >= p.row_end) continue;
-              float* o = static_cast<float*>(p.out) + (size_t)(m - p.out_row0) * p.d_in + n;
-              const float val = WTD ? last_c * rd16(acc[i][j][v]) : rd16(acc[i][j][v]);
-              if (split) atomicAdd(o, val);        // beta already applied by the pass before
-              else *o = (p.beta != 0.f ? p.beta * *o : 0.f) + val;
-            }
-          }
-        if constexpr (PERSIST) continue; else break;
-      }
-      // Tile order: two blocks side by side make the lane's 16 bytes; a piece (two blocks, 512 elements) is
-      // one 1 KiB store of the wave.
-      typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-      const int tile_row = (m0 - p.out_row0) / BM;
-      // the wave's quadrant of the tile, and inside each 16-row strip of the quadrant the wave's pieces (all of
-      // them with four waves, the left or the right half with eight)
-      constexpr int QP = (BN / 2) / 32;                        // pieces per strip of a quadrant
-      const int quad = wm * 2 + wn / (WNC / 2), piece0 = (wn % (WNC / 2)) * (FN16 / 2);
-      u16* tb = static_cast<u16*>(p.out) + (size_t)item * p.out_seq_stride +
-                ((size_t)tile_row * p.tiles_n + tile_n) * (BM * BN) + (size_t)quad * ((BM / 2) * (BN / 2));
+      // dW: sixteen lanes store (or add) sixteen consecutive floats of a row
+      const int col = lane & 15, rq = lane >> 4;
 #pragma unroll
       for (int i = 0; i < FM16; ++i)
 #pragma unroll
-        for (int jp = 0; jp < FN16 / 2; ++jp) {
-          u32x4 pk;
-          pk[0] = pack_bf16(rd16(acc[i][2 * jp][0]), rd16(acc[i][2 * jp][1]));
-          pk[1] = pack_bf16(rd16(acc[i][2 * jp][2]), rd16(acc[i][2 * jp][3]));
-          pk[2] = pack_bf16(rd16(acc[i][2 * jp + 1][0]), rd16(acc[i][2 * jp + 1][1]));
-          pk[3] = pack_bf16(rd16(acc[i][2 * jp + 1][2]), rd16(acc[i][2 * jp + 1][3]));
-          // written once and read after the launch: non-temporal, so the stash does not push the operand
-          // panels out of the L2
-          __builtin_nontemporal_store(pk, (u32x4*)(tb + (i * QP + piece0 + jp) * 512 + lane * 8));
-        }
-      if constexpr (PERSIST) continue; else break;
-    }
-    // ---- row-major stash: the 32x32x16 MFMA (every other mode has left the round above)
-    unsigned adA[FM], adB[FN];
-    {
-      const int l = lane & 15, g4 = lane >> 4;
-      const int kr = 8 * (g4 >> 1) + (l >> 2);
-      const int f = ((kr & 3) << 2) ^ (kr & 2);
+        for (int j = 0; j < FN16; ++j) {
+          const int n = n0 + wn * WN + j * 16 + col;
+          if (n >= p.d_in) continue;
 #pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        const int ca = wm * WM + i * 32 + 16 * (g4 & 1) + 4 * (l & 3);
-        adA[i] = (unsigned)kr * PA + (unsigned)(((ca >> 3) ^ f) << 4) + (unsigned)((ca & 7) * 2);
-      }
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        const int cb = wn * WN + j * 32 + 16 * (g4 & 1) + 4 * (l & 3);
-        adB[j] = A_BYTES + (unsigned)kr * PB + (unsigned)(((cb >> 3) ^ f) << 4) + (unsigned)((cb & 7) * 2);
-      }
-    }
-    auto frA = [&](unsigned a) {
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a + 4 * PA));
-      return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    };
-    auto frB = [&](unsigned a) {
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a + 4 * PB));
-      return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    };
-
-    f32x16 acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    bf16x8 fa0[FM], fb0[FN], fa1[FM], fb1[FN];
-    constexpr int LPT = LA + LB;   // loads per wave and tile
-    // Token blocks in flight ahead of the one being multiplied: one less than the ring holds (the stash
-    // stores compete with the operand fetches; a fourth block in flight made this mode slower).
-    constexpr int AHEAD = NSTAGE - 1;
-    constexpr int NMF = FM * FN;
-
-    // Per-sequence mode, 256x256 tile: the two waves of the lower tile half read their fragments behind
-    // MFMAs 8..15 of a half block instead of 0..7, in the order the next half block first uses them
-    // (B0, A0, B1, B2, B3, A1, A2, A3), so the LDS serves two waves' reads at a time, not four.
-    // frag_of: the fragment read behind MFMA idx (-1: none).
-    auto frag_of = [](int idx, bool late, bool& is_a) -> int {
-      const int k = idx - (late ? NMF - FM - FN : 0);
-      if (k < 0 || k >= FM + FN) return -1;
-      if (!late) { is_a = k < FM; return is_a ? k : k - FM; }
-      if (k == 0) { is_a = false; return 0; }
-      if (k == 1) { is_a = true; return 0; }
-      if (k <= FN) { is_a = false; return k - 1; }
-      is_a = true; return k - FN;
-    };
-    const bool late_wave = NMF >= 2 * (FM + FN) && (wave_s & 2);
-
-#pragma unroll
-    for (int s = 0; s < AHEAD; ++s) issue_loads(s);
-
-    if (n_tiles > 0) {
-      __builtin_amdgcn_s_waitcnt(0x0f70 | (((AHEAD - 1) * LPT) & 15) | ((((AHEAD - 1) * LPT) >> 4) << 14));
-      __builtin_amdgcn_s_barrier();
-#pragma unroll
-      for (int i = 0; i < FM; ++i) fa0[i] = frA(smem_base + adA[i]);
-#pragma unroll
-      for (int j = 0; j < FN; ++j) fb0[j] = frB(smem_base + adB[j]);
-      // one token block; LATE: this wave's fragment-read slots (compile-time, so that both bodies stay
-      // straight-line code)
-      auto token_block = [&](int it, auto late_c) {
-        constexpr bool LATE = decltype(late_c)::value;
-        const unsigned sb = smem_base + ((unsigned)it % NSTAGE) * STAGE;
-        {
-          // written out MFMA by MFMA: one fragment's reads behind each MFMA of this wave's read slots
-#pragma unroll
-          for (int i = 0; i < FM; ++i) {
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-              const int idx = i * FN + j;
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa0[i], fb0[j], acc[i][j], 0, 0, 0);
-              bool is_a = false;
-              const int f = frag_of(idx, LATE, is_a);
-              if (f >= 0) {
-                if (is_a) fa1[f] = frA(sb + adA[f] + 16 * PA);
-                else fb1[f] = frB(sb + adB[f] + 16 * PB);
-              }
-            }
+          for (int v = 0; v < 4; ++v) {
+            const int m = m0 + wm * WM + i * 16 + 4 * rq + v;
+            if (m >= p.row_end) continue;
+            float* o = static_cast<float*>(p.out) + (size_t)(m - p.out_row0) * p.d_in + n;
+            const float val = WTD ? last_c * rd16(acc[i][j][v]) : rd16(acc[i][j][v]);
+            if (split) atomicAdd(o, val);        // beta already applied by the pass before
+            else *o = (p.beta != 0.f ? p.beta * *o : 0.f) + val;
           }
         }
-        // block it+1 has landed (this wave's part; the barrier makes it everyone's) and this wave's fragment
-        // reads of block it are complete: its stage may be overwritten after the barrier
-        __builtin_amdgcn_s_waitcnt(0x0f70 | (((AHEAD - 2) * LPT) & 15) | ((((AHEAD - 2) * LPT) >> 4) << 14));
-        __builtin_amdgcn_s_barrier();
-        const unsigned sn = smem_base + ((unsigned)(it + 1) % NSTAGE) * STAGE;
-        // second half block: its 16 MFMAs carry the fragment reads of the next block's first half and the
-        // DMA instructions of the block AHEAD ahead
-        {
-          v4i ra, rb;
-          next_block(ld, ra, rb);
-          const unsigned stage = smem_base + ((unsigned)(it + AHEAD) % NSTAGE) * STAGE;
-#pragma unroll
-          for (int i = 0; i < FM; ++i) {
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-              const int idx = i * FN + j;
-              {
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa1[i], fb1[j], acc[i][j], 0, 0, 0);
-            }
-              bool is_a = false;
-              const int f = frag_of(idx, LATE, is_a);
-              if (f >= 0) {
-                if (is_a) fa0[f] = frA(sn + adA[f]);
-                else fb0[f] = frB(sn + adB[f]);
-              }
-              // the LPT DMA instructions spread evenly over the NMF MFMAs
-#pragma unroll
-              for (int q = idx * LPT / NMF; q < (idx + 1) * LPT / NMF; ++q) {
-                if (q < LA) load_lds16(ra, stage + (unsigned)(wave_s * LA + q) * 1024, offA[q]);
-                else load_lds16(rb, stage + A_BYTES + (unsigned)(wave_s * LB + (q - LA)) * 1024, offB[q - LA]);
-              }
-            }
-          }
-        }
-      };
-      if (late_wave) {
-        for (int it = 0; it < n_tiles; ++it) token_block(it, std::true_type{});
-      } else {
-        for (int it = 0; it < n_tiles; ++it) token_block(it, std::false_type{});
-      }
     }
-    __builtin_amdgcn_s_waitcnt(0x0f70);
-
-    // a 256-register tile lives in AGPRs (one wave per SIMD); smaller tiles stay in VGPRs
-    [[maybe_unused]] auto rd = [](float a) {
-      if constexpr (FM * FN * 16 > 128) return acc_read(a); else return a;
-    };
-    {
-      __builtin_amdgcn_s_barrier();
-      // the last MFMAs have retired before the accumulators are read by hand (acc_read is opaque to the
-      // compiler's hazard tracking)
-      asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-      constexpr unsigned PT = 80;
-      const unsigned W = smem_base + (unsigned)wave * 8192;
-      const int h = lane >> 5, nl = lane & 31;
-      const int l = lane & 15, gq = lane >> 4;
-      u16* outp = static_cast<u16*>(p.out) + (size_t)item * p.out_seq_stride;
-#pragma unroll
-      for (int i = 0; i < FM; ++i) {
-#pragma unroll
-        for (int jp = 0; jp < FN / 2; ++jp) {
-#pragma unroll
-          for (int jj = 0; jj < 2; ++jj) {
-            const int j = jp * 2 + jj;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              v2u pk;
-              pk.x = pack_bf16(rd(acc[i][j][4 * g]), rd(acc[i][j][4 * g + 1]));
-              pk.y = pack_bf16(rd(acc[i][j][4 * g + 2]), rd(acc[i][j][4 * g + 3]));
-              const unsigned a = W + (unsigned)(jj * 32 + nl) * PT + (unsigned)(8 * g + 4 * h) * 2;
-              *(v2u __attribute__((address_space(3)))*)(a) = pk;
-            }
-          }
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            const int rb = s >> 1, pc = (s & 1) * 4 + gq;
-            const unsigned a = W + (unsigned)(8 * pc + (l >> 2)) * PT + (unsigned)(16 * rb + 4 * (l & 3)) * 2;
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a));
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a + 4 * PT));
-            const int m = m0 + wm * WM + i * 32 + 16 * rb + l;
-            const int n = n0 + wn * WN + jp * 64 + 8 * pc;
-            if (m < p.row_end && n < p.d_in) {
-              // Half a line, of a row that starts anywhere in a line.  Left to the L2 the halves meet there; stored
-              // non-temporally each goes to memory by itself: 2216x632, 83 sequences of 41 tokens: 57 us against 158;
-              // 3256x2560, 28 of 346: 291 against 367; 568x1104, 79 of 213: 46 against 64.  Widths whose rows start at lines
-              // are level on average (256x1536, 85 of 750: 83 against 74; 512x3328, 40 of 24: 40 against 50).
-              *(s16x8*)(outp + (size_t)(m - p.out_row0) * p.d_in + n) =
-                  __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            }
-          }
-        }
-      }
-    }
-    if constexpr (!PERSIST) break;
   }
 }
 
-
-template <int BM, int BN, int NSTAGE, int OCC, bool PER_SEQ, bool PERSIST = false, bool TILED = false, bool WTD = false>
+template <int BT, int OCC, bool WTD>
 __global__ __launch_bounds__(256, OCC) void seq_grad_stream_kernel(StreamParams p) {
-  seq_grad_stream_body<BM, BN, NSTAGE, PER_SEQ, PERSIST, TILED, WTD, 4>(p);
+  seq_grad_stream_body<BT, WTD, 4>(p);
 }
 
-template <int BM, int BN, int NSTAGE, int OCC, bool PER_SEQ, bool PERSIST = false, bool TILED = false, bool WTD = false>
+template <int BT, int OCC, bool WTD>
 __global__ __launch_bounds__(512, OCC) void seq_grad_stream_waves8_kernel(StreamParams p) {
-  seq_grad_stream_body<BM, BN, NSTAGE, PER_SEQ, PERSIST, TILED, WTD, 8>(p);
+  seq_grad_stream_body<BT, WTD, 8>(p);
 }
 
 // o[i] = beta * o[i] (0 for beta = 0, whatever o held), ahead of the atomic accumulation.
@@ -811,10 +488,10 @@ __global__ __launch_bounds__(256) void apply_beta_kernel(float* __restrict__ o, 
 // tiles whose token chunks are accumulated with atomics while the tiles before them are stored whole.
 // One workgroup per 16 rows of a tile.
 __global__ __launch_bounds__(256) void apply_beta_tiles_kernel(float* __restrict__ out, int d_in, int row0, int row_end,
-                                                               int out_row0, int tiles_m, int tiles_n, int first_tile,
+                                                               int out_row0, TileGrid grid, int first_tile,
                                                                float beta) {
   int tile_m, tile_n;
-  strip_tile_coords(first_tile + (int)(blockIdx.x >> 4), tiles_m, tiles_n, tile_m, tile_n);
+  tile_coords(first_tile + (int)(blockIdx.x >> 4), grid, tile_m, tile_n);
   const int n = tile_n * 256 + (threadIdx.x & 63) * 4;
   if (n >= d_in) return;
 #pragma unroll
@@ -828,59 +505,43 @@ __global__ __launch_bounds__(256) void apply_beta_tiles_kernel(float* __restrict
   }
 }
 
-__global__ void queue_zero_kernel(unsigned* queue) {
-  if (threadIdx.x < 8) queue[threadIdx.x] = 0u;
-}
-
-// n_wg > 0 (per-sequence mode, 256x256 tile): persistent launch of n_wg workgroups, a multiple of eight,
-// pulling work from `queue` (eight device counters, zeroed here on the stream).
-template <int BM, int BN, int NSTAGE, int OCC, bool PER_SEQ, bool PERSIST = false, bool TILED = false, bool WTD = false, int NW = 4>
-hipError_t launch_stream(const SeqGradArgs& a, const ContractionPlan& pl, hipStream_t s, int n_wg = 0,
-                         unsigned* queue = nullptr) {
+template <int BT, int OCC, bool WTD, int NW>
+hipError_t launch_stream(const SeqGradArgs& a, const ContractionPlan& pl, hipStream_t s) {
   StreamParams p;
-  p.queue = queue;
   p.c = a.c;
   p.X = static_cast<const u16*>(a.X); p.Delta = static_cast<const u16*>(a.Delta); p.off = a.off; p.out = a.out;
   p.d_in = a.d_in; p.d_out = a.d_out; p.n_seq = a.n_seq; p.n_tokens = a.n_tokens;
   p.row0 = a.row0; p.row_end = a.row0 + a.rows; p.out_row0 = a.out_row0;
-  p.out_seq_stride = a.out_seq_stride; p.beta = a.beta;
-  p.tiles_m = pl.tiles_m;
-  p.tiles_n = pl.tiles_n;
+  p.beta = a.beta;
+  if (pl.blocks <= 0) return hipSuccess;
+  if (pl.blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  p.grid = tile_grid(pl.tiles_m, pl.tiles_n);
   p.n_chunks = pl.n_chunks;
   p.chunk_tokens = pl.chunk_tokens;
   p.whole_tiles = pl.whole_tiles;
   for (int x = 0; x <= 8; ++x) p.xcd_start[x] = pl.xcd_start[x];
-  if (pl.blocks <= 0) return hipSuccess;
-  if (pl.blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   p.n_blocks = (unsigned)pl.blocks;
-  constexpr size_t ring = (size_t)NSTAGE * BK * (BM + BN) * 2;
-  constexpr size_t smem = ring > 32768 ? ring : 32768;      // the stash epilogue stages 8 KiB per wave
-  static_assert(NW == 4 || NW == 8, "waves per workgroup");
+  constexpr size_t smem = (size_t)NSTAGE * BK * BT * 2 * 2;
   auto kern = [] {
-    if constexpr (NW == 8) return &seq_grad_stream_waves8_kernel<BM, BN, NSTAGE, OCC, PER_SEQ, PERSIST, TILED, WTD>;
-    else return &seq_grad_stream_kernel<BM, BN, NSTAGE, OCC, PER_SEQ, PERSIST, TILED, WTD>;
+    if constexpr (NW == 8) return &seq_grad_stream_waves8_kernel<BT, OCC, WTD>;
+    else return &seq_grad_stream_kernel<BT, OCC, WTD>;
   }();
   // once per process (static initialisation is thread-safe); a failure is returned by every call
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (attr != hipSuccess) return attr;
-  if (!PER_SEQ && p.whole_tiles > 0) {
-    const int rest = p.tiles_m * p.tiles_n - p.whole_tiles;
+  if (p.whole_tiles > 0) {
+    const int rest = p.grid.m * p.grid.n - p.whole_tiles;
     hipLaunchKernelGGL(apply_beta_tiles_kernel, dim3((unsigned)rest * 16), dim3(256), 0, s, static_cast<float*>(a.out),
-                       a.d_in, a.row0, a.row0 + a.rows, a.out_row0, p.tiles_m, p.tiles_n, p.whole_tiles, a.beta);
-  } else if (!PER_SEQ && p.n_chunks > 1) {
+                       a.d_in, a.row0, a.row0 + a.rows, a.out_row0, p.grid, p.whole_tiles, a.beta);
+  } else if (p.n_chunks > 1) {
     // the band of output rows this launch owns is contiguous in dW
     float* band = static_cast<float*>(a.out) + (size_t)(a.row0 - a.out_row0) * a.d_in;
     const long long n = (long long)a.rows * a.d_in;
     const hipError_t e = launch_apply_beta(band, n, a.beta, s);
     if (e != hipSuccess) return e;
   }
-  if constexpr (PERSIST) {
-    hipLaunchKernelGGL(queue_zero_kernel, dim3(1), dim3(64), 0, s, queue);
-    hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(64 * NW), smem, s, p);
-  } else {
-    hipLaunchKernelGGL(kern, dim3(p.n_blocks), dim3(64 * NW), smem, s, p);
-  }
+  hipLaunchKernelGGL(kern, dim3(p.n_blocks), dim3(64 * NW), smem, s, p);
   return hipGetLastError();
 }
 
@@ -891,28 +552,23 @@ hipError_t launch_apply_beta(float* o, long long n, float beta, hipStream_t s) {
   return hipGetLastError();
 }
 
+// A sum of more tiles than compute units whose tokens are not cut into chunks: a workgroup's tiles follow each other as one
+// stream of token blocks (seq_grad_walk.hip).  27648x5120, weighted: 1279 tokens of eight sequences 490 -> 405 us, 4096 1023 -> 967,
+// 8000 1855 -> 1810; plain 4096: 991 -> 918; 28672x4096, plain, 65536: 11.09 -> 10.98 ms.  Weighted sums of many tokens are at the
+// power limit, where the walk of a tile dwarfs what it costs besides and the segments' bookkeeping is paid in clock: 16384 2796 ->
+// 2776 us, 32768 5.53 -> 5.56 ms, 65536 11.05 -> 11.23.
+constexpr int kWalkTokens = 16384;
+
 // bf16: the per-sequence stash, the plain sum over all tokens, or (c != nullptr) the weighted sum.
 hipError_t launch_seq_grad_stream(const SeqGradArgs& a, hipStream_t s) {
   const ContractionPlan pl =
-      plan_contraction(a.rows, a.d_in, a.n_tokens, a.n_seq, a.off_host, a.per_sequence, a.c != nullptr, a.budget);
-  // a workgroup budget applies to the large tile's per-sequence launches that would not fit it anyway
-  if (a.per_sequence && a.tile_order) {
-    // the caller has checked stash_tile_order_ok; anything else would scatter the stores
-    if (a.rows % pl.tile || a.d_in % pl.tile || a.row0 % pl.tile || a.out_row0 % pl.tile) return hipErrorInvalidValue;
-    if (a.max_workgroups > 0 && a.queue && pl.tile == 256 && pl.blocks > a.max_workgroups)
-      return launch_stream<256, 256, 4, 1, true, true, true>(a, pl, s, a.max_workgroups / 8 * 8, a.queue);
-    return pl.tile == 256 ? launch_stream<256, 256, 4, 1, true, false, true>(a, pl, s)
-                          : launch_stream<128, 128, 4, 2, true, false, true>(a, pl, s);
-  }
-  if (a.per_sequence && a.max_workgroups > 0 && a.queue && pl.tile == 256 && pl.blocks > a.max_workgroups)
-    return launch_stream<256, 256, 4, 1, true, true>(a, pl, s, a.max_workgroups / 8 * 8, a.queue);
-  if (a.per_sequence)
-    return pl.tile == 256 ? launch_stream<256, 256, 4, 1, true>(a, pl, s) : launch_stream<128, 128, 4, 2, true>(a, pl, s);
+      plan_contraction(a.rows, a.d_in, a.n_tokens, a.n_seq, a.off_host, a.per_sequence, a.c != nullptr, a.max_workgroups > 0);
+  const bool big = pl.tile == 256;
+  const bool rounds = big && pl.n_chunks == 1 && (long long)pl.tiles_m * pl.tiles_n > 256;
+  if (a.per_sequence || (rounds && (a.c == nullptr || a.n_tokens <= kWalkTokens))) return launch_seq_grad_walk(a, pl, s);
   if (a.c != nullptr)       // the weighted sum: segments of one sequence each, accumulators rescaled in between
-    return pl.tile == 256 ? launch_stream<256, 256, 4, 1, false, false, false, true, 8>(a, pl, s)
-                          : launch_stream<128, 128, 4, 2, false, false, false, true>(a, pl, s);
-  return pl.tile == 256 ? launch_stream<256, 256, 4, 1, false, false, false, false, 8>(a, pl, s)
-                        : launch_stream<128, 128, 4, 2, false>(a, pl, s);
+    return big ? launch_stream<256, 1, true, 8>(a, pl, s) : launch_stream<128, 2, true, 4>(a, pl, s);
+  return big ? launch_stream<256, 1, false, 8>(a, pl, s) : launch_stream<128, 2, false, 4>(a, pl, s);
 }
 
 // Schedule probe: the plain sum over all tokens on the 256x256 tile with four or eight waves per workgroup.
@@ -920,8 +576,7 @@ hipError_t launch_seq_grad_stream_waves(const SeqGradArgs& a, int waves, hipStre
   if (a.per_sequence || a.c != nullptr || (waves != 4 && waves != 8)) return hipErrorInvalidValue;
   const ContractionPlan pl = plan_contraction(a.rows, a.d_in, a.n_tokens, a.n_seq, a.off_host, false);
   if (pl.tile != 256) return hipErrorInvalidValue;
-  return waves == 8 ? launch_stream<256, 256, 4, 1, false, false, false, false, 8>(a, pl, s)
-                    : launch_stream<256, 256, 4, 1, false>(a, pl, s);
+  return waves == 8 ? launch_stream<256, 1, false, 8>(a, pl, s) : launch_stream<256, 1, false, 4>(a, pl, s);
 }
 
 }  // namespace isopo

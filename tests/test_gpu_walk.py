@@ -1,0 +1,75 @@
+"""The bf16 contractions whose workgroups walk lists of (sequence, tile) pairs, against 64-bit sums where the lists and the walks
+over the tokens change: tile counts that are no multiple of eight, sequences that are empty or shorter than the loads run ahead,
+more of them than are sorted by length, sums of more tiles than compute units on either side of the first token block."""
+import pytest
+import torch
+
+from paper_2512_23353_amd import isopo
+from paper_2512_23353_amd import workloads as wl
+
+from helpers import bf16_plan, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(d_in, d_out, lens, device):
+    return to_device(wl.custom_layer(d_in, d_out, lens, dtype="bf16", seed=len(lens) + d_in, sigma_delta=1e-2, rho=0.3), device)[0]
+
+
+def _check_stash(layer, S, lens):
+    for i, n in enumerate(lens):
+        r = slice(int(layer.off_host[i]), int(layer.off_host[i + 1]))
+        X, D = layer.X[r].double(), layer.Delta[r].double()
+        G, M = D.T.contiguous() @ X, D.abs().T.contiguous() @ X.abs()
+        # exact products, at most one rounding of the running sum per token (2^-23 truncated), one rounding to bf16
+        assert ((S[i].double() - G).abs() <= 2.0 ** -8 * G.abs() + n * 2.0 ** -23 * 1.01 * M).all(), i
+
+
+@pytest.mark.parametrize("d_in,d_out,lens,tile", [
+    (264, 776, [0, 1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160] * 4, 128),  # every length of walk there is to get wrong
+    (264, 2056, [40, 0, 7, 300, 1, 97] * 7, 128),                            # 51 tiles, 42 sequences
+    (1000, 2728, [900, 33, 600] * 5, 256),                                   # 44 wide tiles
+    (4104, 4360, [800, 0, 33, 700], 256),                                    # 306, few sequences
+    (8, 136, [3, 0, 40] * 100, 128),                                         # more sequences than are sorted
+])
+def test_row_major_lists(gpu_device, d_in, d_out, lens, tile):
+    assert bf16_plan(d_in, d_out, lens, True).tile == tile
+    layer = _layer(d_in, d_out, lens, gpu_device)
+    S = torch.full((len(lens), d_out, d_in), float("nan"), dtype=torch.bfloat16, device=gpu_device)
+    _check_stash(layer, isopo.seq_grads(layer, S), lens)
+
+
+@pytest.mark.parametrize("d_in,d_out,lens", [
+    (256, 768, [0, 1, 31, 32, 33, 64, 65, 96, 97, 128, 129] * 9), (768, 2816, [40, 0, 200, 33, 1, 640, 97] * 2),
+    (256, 512, [3, 0, 40] * 100)])
+def test_tile_order_lists(gpu_device, d_in, d_out, lens):
+    """The same elements as in the row-major stash, bit for bit, so the two layouts' weighted sums are equal."""
+    layer = _layer(d_in, d_out, lens, gpu_device)
+    layout, tile = isopo.stash_layout(layer)
+    assert layout == isopo.STASH_TILE_ORDER
+    rows = isopo.seq_grads(layer)
+    _check_stash(layer, rows, lens)
+    tiled = isopo.seq_grads(layer, torch.full_like(rows, float("nan")), layout=layout)
+    c = torch.randn(len(lens), generator=torch.Generator().manual_seed(1)).to(gpu_device)
+    assert torch.equal(isopo.weighted_grad(layer, c, rows), isopo.weighted_grad(layer, c, tiled, layout=layout))
+
+
+@pytest.mark.parametrize("lens,beta", [([1], 0.0), ([32, 33], 0.5), ([0, 200, 64, 0, 1, 31], 0.0), ([97] * 5, -1.5), ([0, 40], 2.0)])
+@pytest.mark.parametrize("weighted", [True, False])
+def test_sums_of_many_tiles(gpu_device, lens, beta, weighted):
+    d_in, d_out = 4104, 4368                     # 17 x 18 wide tiles, ragged both ways
+    plan = bf16_plan(d_in, d_out, lens, False, weighted=weighted)
+    assert plan.tile == 256 and plan.n_chunks == 1 and plan.tiles_m * plan.tiles_n > 256
+    layer = _layer(d_in, d_out, lens, gpu_device)
+    gen = torch.Generator().manual_seed(len(lens))
+    c = torch.randn(len(lens), generator=gen)
+    if len(lens) != 2 or lens[0] == 0:           # [0, 40]: no sequence is left
+        c[1:2] = 0.0
+    start = torch.randn((d_out, d_in), generator=gen).to(gpu_device)
+    got = isopo.weighted_grad(layer, c.to(gpu_device) if weighted else None, beta=beta, dW=start.clone())
+    w = torch.repeat_interleave(c, torch.tensor(lens)).to(gpu_device).double()[:, None] if weighted else 1.0
+    X, D = layer.X.double(), layer.Delta.double() * w
+    G = beta * start.double() + D.T.contiguous() @ X
+    M = abs(beta) * start.double().abs() + D.abs().T.contiguous() @ X.abs()
+    # exact products; one rounding of the running sum per token, three per change of sequence, three of the result
+    assert ((got.double() - G).abs() <= (sum(lens) + 3 * len(lens) + 3) * 2.0 ** -23 * M).all()
