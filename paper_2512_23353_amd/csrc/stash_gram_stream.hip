@@ -53,9 +53,9 @@ struct Params {
 __device__ __forceinline__ void load_lds16(const void* gptr, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(gptr) : "memory");
 }
-// The same with the non-temporal cache policy, for the one-pass kernels (up to 256 sequences): every stash
-// byte is read once, and keeping it out of the caches' replacement order is worth 13 % of the pass for up
-// to 128 sequences (6.2 -> 7.05 TB/s on a 3.8 GB stash) and 3 % for 129..256 (72 GB stash).  The super-block
+// The same with the non-temporal cache policy, for the one-pass kernels (up to 256 sequences) on stashes that the last-level
+// cache does not hold: every byte is read once, and keeping it out of the caches' replacement order is worth 13 % of the pass
+// for up to 128 sequences (6.2 -> 7.05 TB/s on a 3.8 GB stash) and 3 % for 129..256 (72 GB stash).  The super-block
 // pair kernel reads a row once per pair and keeps the default policy.
 __device__ __forceinline__ void load_lds16_nt(const void* gptr, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(lds_addr), "v"(gptr) : "memory");
@@ -64,7 +64,8 @@ __device__ __forceinline__ void load_lds16_nt(const void* gptr, unsigned lds_add
 // MB   side of an MFMA block, 32 or 16 (fp32, and n_seq <= 16)
 // NB   MB-row blocks that carry sequences (pairs are formed among these)
 // NBL  row blocks of the LDS layout: 1, 2, 4 or 8 (NBL >= NB); stage = MB*NBL rows x KW elements
-template <bool BF16, int MB, int NB, int NBL>
+// ONCE load with the non-temporal policy
+template <bool BF16, int MB, int NB, int NBL, bool ONCE>
 __global__ __launch_bounds__(256, 1) void stash_gram_stream_kernel(Params p) {
   static_assert(BF16 || MB == 16, "fp32 products are formed in 16x16 blocks");
   constexpr int ES = BF16 ? 2 : 4, EPV = 16 / ES;   // bytes per element, elements per 16-byte vector
@@ -110,7 +111,8 @@ __global__ __launch_bounds__(256, 1) void stash_gram_stream_kernel(Params p) {
       const long long last = (n_elems - EPV) * ES;
       if (byte > last) byte = last;                               // tail: stays inside the row, zeroed at read time
       if (k >= my_count) byte = 0;                                // look-ahead past the end: harmless re-read
-      load_lds16_nt(src[q] + byte, stage + (unsigned)(wave_s * LPW + q) * 1024);
+      if constexpr (ONCE) load_lds16_nt(src[q] + byte, stage + (unsigned)(wave_s * LPW + q) * 1024);
+      else load_lds16(src[q] + byte, stage + (unsigned)(wave_s * LPW + q) * 1024);
     }
   };
 
@@ -202,11 +204,11 @@ __global__ __launch_bounds__(256, 1) void stash_gram_stream_kernel(Params p) {
   for (int e = threadIdx.x; e < tri(NB) * AV * 64; e += 256) out[e] = (p.first ? 0.f : out[e]) + red[e];
 }
 
-template <bool BF16, int MB, int NB, int NBL>
+template <bool BF16, int MB, int NB, int NBL, bool ONCE>
 hipError_t launch(const Params& p, int blocks, hipStream_t s) {
   constexpr size_t smem = (size_t)kStages * kStageBytes;
   static_assert((size_t)tri(NB) * MB * MB * 4 <= smem, "reduction scratch fits the ring");
-  auto kern = stash_gram_stream_kernel<BF16, MB, NB, NBL>;
+  auto kern = stash_gram_stream_kernel<BF16, MB, NB, NBL, ONCE>;
   // once per process (static initialisation is thread-safe); a failure is returned by every call
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -217,26 +219,28 @@ hipError_t launch(const Params& p, int blocks, hipStream_t s) {
 
 // fp32: 16x16 blocks throughout.  The fp32 MFMA's rate is the same for either shape, and of 32x32 blocks more lies below
 // the diagonal or past the last sequence (40 sequences: 6 of 16x16 against 3 of 32x32, half the MFMA cycles).
+template <bool ONCE>
 hipError_t launch_f32(const Params& p, int blocks, hipStream_t s) {
   switch ((p.n_seq + 15) / 16) {
-    case 1: return launch<false, 16, 1, 1>(p, blocks, s);
-    case 2: return launch<false, 16, 2, 2>(p, blocks, s);
-    case 3: return launch<false, 16, 3, 4>(p, blocks, s);
-    case 4: return launch<false, 16, 4, 4>(p, blocks, s);
-    case 5: return launch<false, 16, 5, 8>(p, blocks, s);
-    case 6: return launch<false, 16, 6, 8>(p, blocks, s);
-    case 7: return launch<false, 16, 7, 8>(p, blocks, s);
-    default: return launch<false, 16, 8, 8>(p, blocks, s);
+    case 1: return launch<false, 16, 1, 1, ONCE>(p, blocks, s);
+    case 2: return launch<false, 16, 2, 2, ONCE>(p, blocks, s);
+    case 3: return launch<false, 16, 3, 4, ONCE>(p, blocks, s);
+    case 4: return launch<false, 16, 4, 4, ONCE>(p, blocks, s);
+    case 5: return launch<false, 16, 5, 8, ONCE>(p, blocks, s);
+    case 6: return launch<false, 16, 6, 8, ONCE>(p, blocks, s);
+    case 7: return launch<false, 16, 7, 8, ONCE>(p, blocks, s);
+    default: return launch<false, 16, 8, 8, ONCE>(p, blocks, s);
   }
 }
 
+template <bool ONCE>
 hipError_t launch_bf16(const Params& p, int blocks, hipStream_t s) {
-  if (p.n_seq <= 16) return launch<true, 16, 1, 1>(p, blocks, s);
+  if (p.n_seq <= 16) return launch<true, 16, 1, 1, ONCE>(p, blocks, s);
   switch ((p.n_seq + 31) / 32) {
-    case 1: return launch<true, 32, 1, 1>(p, blocks, s);
-    case 2: return launch<true, 32, 2, 2>(p, blocks, s);
-    case 3: return launch<true, 32, 3, 4>(p, blocks, s);
-    default: return launch<true, 32, 4, 4>(p, blocks, s);
+    case 1: return launch<true, 32, 1, 1, ONCE>(p, blocks, s);
+    case 2: return launch<true, 32, 2, 2, ONCE>(p, blocks, s);
+    case 3: return launch<true, 32, 3, 4, ONCE>(p, blocks, s);
+    default: return launch<true, 32, 4, 4, ONCE>(p, blocks, s);
   }
 }
 
@@ -612,7 +616,12 @@ hipError_t launch_stash_gram_stream(const StashGramArgs& a, hipStream_t s) {
   p.stash = a.stash; p.seq_stride = a.seq_stride; p.p0 = a.p0; p.p1 = a.p1;
   p.n_seq = a.n_seq; p.first = a.first ? 1 : 0; p.partials = a.partials;
   p.slot_floats = (long long)stash_gram_slot_floats(a.n_seq, a.bf16);
-  return a.bf16 ? launch_bf16(p, a.slots, s) : launch_f32(p, a.slots, s);
+  // What the last-level cache holds (256 MiB) is left in it for the weighted sum that follows, and is there from the
+  // contraction before.  Whole calls, non-temporal / default: 1000x2728 bf16, 24 sequences (131 MB) 136.6 / 130.7 us, 40 (218 MB)
+  // 160.9 / 150.0, 80 (436 MB) 305.8 / 324.2; 4096x1024 bf16, 32 (268 MB) 181.0 / 179.4, 48 (403 MB) 271.4 / 275.4.
+  const bool once = (a.p1 - a.p0) * a.n_seq * (a.bf16 ? 2 : 4) > 256LL << 20;
+  if (a.bf16) return once ? launch_bf16<true>(p, a.slots, s) : launch_bf16<false>(p, a.slots, s);
+  return once ? launch_f32<true>(p, a.slots, s) : launch_f32<false>(p, a.slots, s);
 }
 
 }  // namespace isopo
