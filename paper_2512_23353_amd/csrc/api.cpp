@@ -69,6 +69,14 @@ isopo_status check_layer(const isopo_layer* l, bool need_dev) {
 constexpr double kRateContraction = 1.0e15;   // flop/s, per-sequence gradient kernel
 constexpr double kRateGhost = 7.0e14;         // token-pair-features/s, ghost kernel
 constexpr double kRateStash = 3.7e12;         // B/s, stash write / read
+// fp32: the contraction's fp32 products per second, its stash's passes, and the ghost kernel, which walks all features of a tile
+// pair in one workgroup.  2048x4096: ghost 205 .. 255 us up to 1200 tokens, 2.2 ms at 4800, materialised with 8 sequences 134 and
+// 509, with 32 440 and 777; priced with the bf16 rates the ghost path was taken for 16 sequences of 150 tokens of a 1024x1024
+// layer (243 us against 60) and for most fp32 layers of under 3000 tokens.
+constexpr double kRateContractionF32 = 1.7e14;
+constexpr double kRateStashF32 = 5.0e12;
+constexpr double kRateGhostF32 = 6.0e13;
+constexpr double kGhostWalkF32 = 4.0e-8;      // s per feature
 constexpr double kLaunch = 6.0e-6;            // s per kernel launch in the chain
 
 void cost_model(const isopo_layer* l, double* t_ghost, double* t_mat) {
@@ -79,9 +87,10 @@ void cost_model(const isopo_layer* l, double* t_ghost, double* t_mat) {
   // few tile pairs: the bf16 kernel cuts the features into ranges (a shorter walk) and a second kernel sums
   // the ranges' parts
   const long long tiles = (l->n_tokens + 127) / 128, tile_pairs = tiles * (tiles + 1) / 2;
-  const int split = l->dtype == ISOPO_BF16 ? ghost_feature_split((int)l->n_tokens, l->d_in, l->d_out) : 1;
-  const double walk = ghost_walk_time(tile_pairs, l->d_in, l->d_out, split);
-  const double pairs = nt * nt * (di + d_o) / kRateGhost;
+  const int split = ghost_feature_split((int)l->n_tokens, l->d_in, l->d_out);
+  const bool bf16 = l->dtype == ISOPO_BF16;
+  const double walk = bf16 ? ghost_walk_time(tile_pairs, l->d_in, l->d_out, split) : (di + d_o) * kGhostWalkF32;
+  const double pairs = nt * nt * (di + d_o) / (bf16 ? kRateGhost : kRateGhostF32);
   // five short launches back to back (fill, token map, products, parts, finish) cost about three isolated ones
   *t_ghost = (walk > pairs ? walk : pairs) + 3 * kLaunch;
   // materialised: every tile is padded to whole 32-token blocks per sequence
@@ -90,8 +99,8 @@ void cost_model(const isopo_layer* l, double* t_ghost, double* t_mat) {
     const int len = l->seq_offsets_host[i + 1] - l->seq_offsets_host[i];
     n_pad += (double)((len + 31) / 32) * 32.0;
   }
-  const double pass = b * D * (double)elem_size(l->dtype) / kRateStash;      // one pass over the stash
-  const double contract = 2.0 * n_pad * D / kRateContraction;
+  const double pass = b * D * (double)elem_size(l->dtype) / (bf16 ? kRateStash : kRateStashF32);      // one pass over the stash
+  const double contract = 2.0 * n_pad * D / (bf16 ? kRateContraction : kRateContractionF32);
   *t_mat = (contract > pass ? contract : pass) + pass + 3 * kLaunch;
 }
 
