@@ -124,7 +124,7 @@ isopo_status isopo_gram_cost_model(const isopo_layer* layer, double* t_ghost, do
  *                      the unsplit unweighted mode has one item
  *   workgroups         grid size of a launch with one workgroup per pair (some workgroups may find their XCD's
  *                      range exhausted and exit).  Both hold for a sum cut into chunks.  The per-sequence launches, and
- *                      uncut sums of more than 256 tiles, run at most 256 workgroups (512 with the 128 tile; or the
+ *                      uncut sums, run at most 256 workgroups (512 with the 128 tile; or the
  *                      budget of isopo_seq_grads_limited), each with a list of pairs of its own: every sequence's tiles
  *                      are dealt evenly to the XCDs, the longest sequences' first, and there the fields describe one
  *                      equal-work cut of the pairs that no launch follows.  isopo_seq_grads_limited also takes the 256

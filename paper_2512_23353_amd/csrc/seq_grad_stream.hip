@@ -1,7 +1,7 @@
 // Token-reduction contraction, bf16, streaming variant, a work item per workgroup: the sums over all tokens,
-// dW = Delta^T X and dW = Delta^T diag(c_tok) X.  (The per-sequence gradients, and the sums of layers with many tiles
-// for few tokens, are formed by the kernel of seq_grad_walk.hip, whose workgroups walk lists of items; launch_seq_grad_stream
-// routes to it.)
+// dW = Delta^T X and dW = Delta^T diag(c_tok) X, where their tokens are cut into chunks or (weighted) are many.  (The
+// per-sequence gradients and the other sums are formed by the kernel of seq_grad_walk.hip, whose workgroups walk lists of items;
+// launch_seq_grad_stream routes to it.)
 //
 // Design (gfx950):
 //  * Operand tiles go from HBM/L2 straight into LDS with buffer_load ... lds
@@ -552,11 +552,14 @@ hipError_t launch_apply_beta(float* o, long long n, float beta, hipStream_t s) {
   return hipGetLastError();
 }
 
-// A sum of more tiles than compute units whose tokens are not cut into chunks: a workgroup's tiles follow each other as one
-// stream of token blocks (seq_grad_walk.hip).  27648x5120, weighted: 1279 tokens of eight sequences 490 -> 405 us, 4096 1023 -> 967,
-// 8000 1855 -> 1810; plain 4096: 991 -> 918; 28672x4096, plain, 65536: 11.09 -> 10.98 ms.  Weighted sums of many tokens are at the
-// power limit, where the walk of a tile dwarfs what it costs besides and the segments' bookkeeping is paid in clock: 16384 2796 ->
-// 2776 us, 32768 5.53 -> 5.56 ms, 65536 11.05 -> 11.23.
+// A sum whose tokens are not cut into chunks walks its tiles (seq_grad_walk.hip).  Of more tiles than compute units, a workgroup's
+// tiles follow each other as one stream of token blocks: 27648x5120, weighted: 1279 tokens of eight sequences 490 -> 405 us, 4096
+// 1023 -> 967, 8000 1855 -> 1810; plain 4096: 991 -> 918; 28672x4096, plain, 65536: 11.09 -> 10.98 ms.  Of one round of tiles, what is
+// left of it is the shorter token block, segments that need no even number of blocks and stores of 16 bytes: 8192x2048, 2300 tokens
+// of eight sequences 79 -> 70 us; 4096x4096, 3200 of 16: 114 -> 106; 5000x3000, 5300 of 40: 181 -> 168; 8960x1536, 15000 of 256: 578 ->
+// 538, 10700 of 16: 248 -> 244; plain 4096x4096, 6000: 166 -> 158; 3584x4096, 84000: 1845 -> 1818.  Weighted sums of many tokens are at
+// the power limit, where the walk of a tile dwarfs what it costs besides and the segments' bookkeeping is paid in clock: 27648x5120,
+// 16384 tokens 2796 -> 2776 us, 32768 5.53 -> 5.56 ms, 65536 11.05 -> 11.23.
 constexpr int kWalkTokens = 16384;
 
 // bf16: the per-sequence stash, the plain sum over all tokens, or (c != nullptr) the weighted sum.
@@ -564,8 +567,8 @@ hipError_t launch_seq_grad_stream(const SeqGradArgs& a, hipStream_t s) {
   const ContractionPlan pl =
       plan_contraction(a.rows, a.d_in, a.n_tokens, a.n_seq, a.off_host, a.per_sequence, a.c != nullptr, a.max_workgroups > 0);
   const bool big = pl.tile == 256;
-  const bool rounds = big && pl.n_chunks == 1 && (long long)pl.tiles_m * pl.tiles_n > 256;
-  if (a.per_sequence || (rounds && (a.c == nullptr || a.n_tokens <= kWalkTokens))) return launch_seq_grad_walk(a, pl, s);
+  const bool uncut = big && pl.n_chunks == 1;
+  if (a.per_sequence || (uncut && (a.c == nullptr || a.n_tokens <= kWalkTokens))) return launch_seq_grad_walk(a, pl, s);
   if (a.c != nullptr)       // the weighted sum: segments of one sequence each, accumulators rescaled in between
     return big ? launch_stream<256, 1, true, 8>(a, pl, s) : launch_stream<128, 2, true, 4>(a, pl, s);
   return big ? launch_stream<256, 1, false, 8>(a, pl, s) : launch_stream<128, 2, false, 4>(a, pl, s);

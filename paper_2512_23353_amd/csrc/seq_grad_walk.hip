@@ -1,6 +1,6 @@
 // Streaming bf16 contraction, workgroups that walk a list of work: the per-sequence gradients G_i = Delta_i^T X_i
 // (`grad_out.T @ act_in` of both hook listings), row-major and in tile order, and the sums over all tokens (dW = Delta^T X,
-// dW = Delta^T diag(c_tok) X) of layers with more output tiles than compute units.
+// dW = Delta^T diag(c_tok) X) whose tokens are not cut into chunks.
 //
 // Tiles, LDS ring, swizzle and transposing fragment reads are those of seq_grad_stream.hip.  Two things bound a launch besides
 // the matrix cores and the board's power:

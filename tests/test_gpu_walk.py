@@ -73,3 +73,22 @@ def test_sums_of_many_tiles(gpu_device, lens, beta, weighted):
     M = abs(beta) * start.double().abs() + D.abs().T.contiguous() @ X.abs()
     # exact products; one rounding of the running sum per token, three per change of sequence, three of the result
     assert ((got.double() - G).abs() <= (sum(lens) + 3 * len(lens) + 3) * 2.0 ** -23 * M).all()
+
+
+@pytest.mark.parametrize("lens,beta", [([2048], 0.0), ([1000, 0, 33, 1100], 0.5), ([31] * 70, 0.0)])
+@pytest.mark.parametrize("weighted", [True, False])
+def test_uncut_sums_of_one_round(gpu_device, lens, beta, weighted):
+    d_in, d_out = 3000, 5000                     # 240 wide tiles, ragged both ways: one to a workgroup
+    plan = bf16_plan(d_in, d_out, lens, False, weighted=weighted)
+    assert plan.tile == 256 and plan.n_chunks == 1 and plan.tiles_m * plan.tiles_n <= 256
+    layer = _layer(d_in, d_out, lens, gpu_device)
+    gen = torch.Generator().manual_seed(len(lens))
+    c = torch.randn(len(lens), generator=gen)
+    start = torch.randn((d_out, d_in), generator=gen).to(gpu_device)
+    got = isopo.weighted_grad(layer, c.to(gpu_device) if weighted else None, beta=beta, dW=start.clone())
+    w = torch.repeat_interleave(c, torch.tensor(lens)).to(gpu_device).double()[:, None] if weighted else 1.0
+    X, D = layer.X.double(), layer.Delta.double() * w
+    G = beta * start.double() + D.T.contiguous() @ X
+    M = abs(beta) * start.double().abs() + D.abs().T.contiguous() @ X.abs()
+    # as above
+    assert ((got.double() - G).abs() <= (sum(lens) + 3 * len(lens) + 3) * 2.0 ** -23 * M).all()
