@@ -10,6 +10,8 @@
 #include "common.h"
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace isopo {
 namespace {
 
@@ -30,10 +32,10 @@ __device__ double block_sum(double x, double* red) {
 // U = H Q^T.
 // One workgroup per problem, fp64 throughout: bound by the latency of its dependent steps and, with sixteen waves on four
 // vector units, by what each of them issues, so that sums run over sixteen lanes where sixteen rows wait side by side.
-// 16 / 32 / 64 / 128 / 256 / 512 / 1024 sequences: 0.06 / 0.11 / 0.24 / 0.84 / 5.7 / 45 / 380 ms, where a Jacobi iteration (two
-// barriers per round of n/2 rotations, up to 94 sequences) and implicit QL (a sequential chain of about 25 dependent
-// operations per plane rotation) took 0.09 / 0.26 / 1.19 / 5.5 / 22 / 100 / 630; errors of D, U^T U and U D U^T 2e-16 .. 1e-14
-// of the largest eigenvalue, a fifth of the Jacobi iteration's.  At 64 sequences half of the time is the reduction.
+// 16 / 32 / 64 / 96 / 128 / 256 / 512 / 1024 sequences: 0.06 / 0.09 / 0.18 / 0.38 / 0.66 / 5.7 / 45 / 380 ms, where a Jacobi
+// iteration (two barriers per round of n/2 rotations, up to 94 sequences) and implicit QL (a sequential chain of about 25
+// dependent operations per plane rotation) took 0.09 / 0.26 / 1.19 ms at 16 / 32 / 64 and 5.5 / 22 / 100 / 630 from 128 on; errors
+// of D, U^T U and U D U^T 2e-16 .. 1e-14 of the largest eigenvalue, a fifth of the Jacobi iteration's.
 // K is scaled by a power of two so that its largest entry lies in [1, 2) (exact; D is scaled back at the end).
 //   A (n x n, kept bit-symmetric; LDS up to 128 sequences, else U's own memory): rows k+1.. of the trailing block are
 //     updated as A -= v w^T + w v^T; row k then holds v_k for the back-transformation
@@ -167,6 +169,149 @@ __host__ __device__ constexpr int eigh_pitch(int m) {
   return (m <= 64 || m * odd <= 128 * 128) ? odd : m;
 }
 
+// The reduction of up to 16 NE rows to tridiagonal form with the matrix in registers and one barrier per column.  Sixteen
+// lanes hold a row (lane `sub` its elements sub + 16 t) and a lane RN rows, so WV waves hold them all; zeros stand beyond n.
+// What a column costs is the chain of its dependent steps (row, norm, v, A v, barrier, w) and what the waves of a vector unit
+// issue.  So every sixteen lanes form the next column's reflector by themselves, from the row that its owner put into LDS
+// ahead of the update together with A v: no barrier stands between the update and the next product, and with four waves
+// (one per vector unit) saying it sixteen times over costs what saying it once does.  The waves past WV wait at the barriers.
+// Columns that are through are left out sixteen at a time.  Seven problems of 16 / 32 / 64 / 72 / 96 / 128 sequences, against
+// the matrix in LDS with two barriers per column: 65 / 118 / 248 / 365 / 525 / 856 us -> 57 / 93 / 177 / 300 / 380 / 656.
+//   pbuf, rbuf (two of 16 NE each, by the column's parity): tau A v, and row k + 1 as column k finds it
+//   A: row k receives v_k, which the updates read by row and the back-transformation later
+// Rounding: v_i w_j + w_i v_j is formed from two rounded products, so (i, j) and (j, i) stay the same bits, and so do the
+// copies of a row that different lanes form.
+template <int NE, int RN, int WV>
+__device__ __forceinline__ void tridiagonalise(double* A, int lda, int n, double* d, double* e, double* htau, double* pbuf,
+                                               double* rbuf) {
+  constexpr int M = 16 * NE, GR = 4 * WV;                    // rows in all; rows held side by side
+  static_assert(NE <= 8 && GR * RN == M, "the waves hold the matrix");
+  const int tid = threadIdx.x, sub = tid & 15, g = tid >> 4;
+  const bool worker = __builtin_amdgcn_readfirstlane(tid >> 6) < WV;
+  double x[RN][NE], v[NE];
+  double tk = 0.0, v0 = 0.0;
+  // v, tau and v's first element of column k, 16 T0 <= k < 16 T0 + 16, from row k
+  auto reflector = [&](auto t0_c, const double (&a)[NE], int k) __attribute__((always_inline)) {
+    constexpr int T0 = decltype(t0_c)::value;
+    double sig = 0.0;
+#pragma unroll
+    for (int t = T0; t < NE; ++t) sig += sub + 16 * t > k + 1 ? a[t] * a[t] : 0.0;
+    const double diag = lane_value(a[T0], k & 15);
+    double x0 = lane_value(a[T0], (k + 1) & 15);
+    if constexpr (T0 + 1 < NE) {
+      const double y = lane_value(a[T0 + 1], 0);             // not left to an index into the row's registers
+      x0 = (k & 15) == 15 ? y : x0;
+    }
+    sig = row_sum(sig);
+    const bool reduced = sig < kNoSquare;                    // column already reduced
+    const double nrm = quick_sqrt(x0 * x0 + sig);
+    const double alpha = x0 > 0.0 ? -nrm : nrm;
+    v0 = reduced ? 0.0 : x0 - alpha;
+    tk = reduced ? 0.0 : 2.0 * quick_rcp(v0 * v0 + sig);
+#pragma unroll
+    for (int t = T0; t < NE; ++t) {
+      const int j = sub + 16 * t;
+      v[t] = j < k + 1 || reduced ? 0.0 : (j == k + 1 ? v0 : a[t]);
+    }
+    if (g == 0) {
+      if (sub == 0) { d[k] = diag; e[k] = reduced ? x0 : alpha; htau[k] = tk; }
+#pragma unroll
+      for (int t = T0; t < NE; ++t)
+        if (sub + 16 * t < n) A[(size_t)k * lda + sub + 16 * t] = v[t];
+    }
+  };
+  if (worker) {
+#pragma unroll
+    for (int t = 0; t < NE; ++t) {
+      const int j = sub + 16 * t;
+      v[t] = j < n ? A[j] : 0.0;
+#pragma unroll
+      for (int r = 0; r < RN; ++r) x[r][t] = j < n && g + GR * r < n ? A[(size_t)(g + GR * r) * lda + j] : 0.0;
+    }
+  }
+  __syncthreads();
+  if (worker) {
+    double a[NE];
+#pragma unroll
+    for (int t = 0; t < NE; ++t) a[t] = v[t];
+    reflector(std::integral_constant<int, 0>{}, a, 0);
+  }
+  auto columns = [&](auto t0_c) __attribute__((always_inline)) {
+    constexpr int T0 = decltype(t0_c)::value, R0 = 16 * T0 / GR;
+    const int last = 16 * T0 + 14 < n - 3 ? 16 * T0 + 14 : n - 3;
+    for (int k = T0 > 0 ? 16 * T0 - 1 : 0; k <= last; ++k) {  // columns k + 1 and up are live, so elements 16 T0 and up
+      double* p = pbuf + (k & 1) * M;
+      double* row = rbuf + (k & 1) * M;
+      if (worker) {
+#pragma unroll
+        for (int r = R0; r < RN; ++r) {
+          const int i = g + GR * r;
+          double acc = 0.0;
+#pragma unroll
+          for (int t = T0; t < NE; ++t) acc += x[r][t] * v[t];
+          acc = row_sum(acc);
+          if (sub == 0) p[i] = i > k ? tk * acc : 0.0;        // rows that are through hold no more than numbers
+          if (i == k + 1) {
+#pragma unroll
+            for (int t = T0; t < NE; ++t) row[sub + 16 * t] = x[r][t];
+          }
+        }
+      }
+      __syncthreads();
+      if (worker) {
+        double wj[NE], a[NE], kk = 0.0;
+#pragma unroll
+        for (int t = T0; t < NE; ++t) { wj[t] = p[sub + 16 * t]; a[t] = row[sub + 16 * t]; }
+        double vi[RN], wi[RN];
+#pragma unroll
+        for (int r = R0; r < RN; ++r) {
+          const int i = g + GR * r;
+          wi[r] = p[i];
+          vi[r] = i > k && i < n ? A[(size_t)k * lda + i] : 0.0;      // rows beyond n stay zeros
+        }
+        double w1 = p[k + 1];
+        const double v1 = v0;
+#pragma unroll
+        for (int t = T0; t < NE; ++t) kk += wj[t] * v[t];
+        kk = 0.5 * tk * row_sum(kk);
+        w1 = __dsub_rn(w1, __dmul_rn(kk, v1));
+        double vj[NE];
+#pragma unroll
+        for (int t = T0; t < NE; ++t) {
+          vj[t] = v[t];
+          wj[t] = __dsub_rn(wj[t], __dmul_rn(kk, vj[t]));
+          a[t] = __dsub_rn(a[t], __dadd_rn(__dmul_rn(v1, wj[t]), __dmul_rn(w1, vj[t])));
+        }
+#pragma unroll
+        for (int r = R0; r < RN; ++r) {
+          const double w = __dsub_rn(wi[r], __dmul_rn(kk, vi[r]));
+#pragma unroll
+          for (int t = T0; t < NE; ++t)
+            x[r][t] = __dsub_rn(x[r][t], __dadd_rn(__dmul_rn(vi[r], wj[t]), __dmul_rn(w, vj[t])));
+        }
+        reflector(t0_c, a, k + 1);                            // of the last two rows: nothing to clear
+      }
+    }
+  };
+  columns(std::integral_constant<int, 0>{});
+  if constexpr (NE > 1) columns(std::integral_constant<int, 1>{});
+  if constexpr (NE > 2) columns(std::integral_constant<int, 2>{});
+  if constexpr (NE > 3) columns(std::integral_constant<int, 3>{});
+  if constexpr (NE > 4) columns(std::integral_constant<int, 4>{});
+  if constexpr (NE > 5) columns(std::integral_constant<int, 5>{});
+  if constexpr (NE > 6) columns(std::integral_constant<int, 6>{});
+  if constexpr (NE > 7) columns(std::integral_constant<int, 7>{});
+  // the last row's diagonal element
+  if (worker) {
+#pragma unroll
+    for (int r = 0; r < RN; ++r)
+#pragma unroll
+      for (int t = 0; t < NE; ++t)
+        if (g + GR * r == n - 1 && sub + 16 * t == n - 1) d[n - 1] = x[r][t];
+  }
+  __syncthreads();
+}
+
 template <int THREADS, int MAXN, bool LDS, bool QLDS>
 __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __restrict__ Kb, int m,
                                                               double* __restrict__ Db, double* __restrict__ Ub,
@@ -178,6 +323,7 @@ __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __res
   __shared__ short perm[MAXN], list[MAXN], org[MAXN], rot_a[MAXN], rot_b[MAXN];
   __shared__ short n_live[MAXN], n_rot[MAXN], scan[MAXN];       // per block, at its first index
   __shared__ double red[THREADS / 64];
+  __shared__ double tri_rows[LDS ? 2 * MAXN : 1];
   __shared__ int bad;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = tid & 15;
   constexpr int WAVES = THREADS / 64;
@@ -221,91 +367,99 @@ __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __res
     for (int j = lane; j < n; j += 64) A[(size_t)i * lda + j] *= down;      // the elements this thread wrote
   __syncthreads();
 
-  // ---- tridiagonalisation: two barriers per column, sixteen lanes per row ----
-  // The reflector of column k from row k of the (symmetric) matrix, by the sixteen lanes that hold the row (lane `sub` its
-  // elements k + sub + 16 t): sig the sum of squares behind element k + 1, x0 that element, diag element k.
-  auto reflector = [&](int k, double sig, double x0, double diag) {
-    double* vk = v + (k & 1) * MAXN;
-    if (sub == 0) d[k] = diag;
-    if (sig < kNoSquare) {                                    // column already reduced
-      if (sub == 0) { e[k] = x0; htau[k] = 0.0; }
-      return;
-    }
-    const double nrm = quick_sqrt(x0 * x0 + sig);
-    const double alpha = x0 > 0.0 ? -nrm : nrm;
-    const double v0 = x0 - alpha;
-    if (sub == 0) { e[k] = alpha; htau[k] = 2.0 * quick_rcp(v0 * v0 + sig); }
-    for (int j = k + sub; j < n; j += 16) {
-      if (j == k) continue;
-      double* a = A + (size_t)k * lda + j;                    // kept there for the back-transformation
-      const double vj = j == k + 1 ? v0 : *a;
-      vk[j] = vj;
-      *a = vj;
-    }
-  };
-  if (group == 0 && n > 2) {
-    double sig = 0.0, x0 = 0.0, diag = 0.0;
-    for (int j = sub; j < n; j += 16) {
-      const double x = A[j];
-      if (j == 0) diag = x;
-      else if (j == 1) x0 = x;
-      else sig += x * x;
-    }
-    reflector(0, row_sum(sig), __shfl(x0, 1, 16), diag);
-  }
-  __syncthreads();
-  for (int k = 0; k + 2 < n; ++k) {
-    const double tk = htau[k];
-    const double* vk = v + (k & 1) * MAXN;
-    if (tk != 0.0) {                                          // uniform
-      // p = tau A22 v
-      for (int i = k + 1 + group; i < n; i += GROUPS) {
-        const double* row = A + (size_t)i * lda;
-        double acc = 0.0;
-#pragma unroll 4
-        for (int j = k + 1 + sub; j < n; j += 16) acc += row[j] * vk[j];
-        acc = row_sum(acc);
-        if (sub == 0) w[i] = tk * acc;
+  if constexpr (LDS) {
+    // four waves, up to 96 sequences eight; past them a lane's registers hold eight elements of two rows, so sixteen
+    if constexpr (THREADS == 512) tridiagonalise<2, 2, 4>(A, lda, n, d, e, htau, v, tri_rows);        // up to 32 sequences
+    else if constexpr (MAXN == 64) tridiagonalise<4, 4, 4>(A, lda, n, d, e, htau, v, tri_rows);
+    else if (n <= 96) tridiagonalise<6, 3, 8>(A, lda, n, d, e, htau, v, tri_rows);
+    else tridiagonalise<8, 2, 16>(A, lda, n, d, e, htau, v, tri_rows);
+  } else {
+    // ---- tridiagonalisation: two barriers per column, sixteen lanes per row ----
+    // The reflector of column k from row k of the (symmetric) matrix, by the sixteen lanes that hold the row (lane `sub` its
+    // elements k + sub + 16 t): sig the sum of squares behind element k + 1, x0 that element, diag element k.
+    auto reflector = [&](int k, double sig, double x0, double diag) {
+      double* vk = v + (k & 1) * MAXN;
+      if (sub == 0) d[k] = diag;
+      if (sig < kNoSquare) {                                    // column already reduced
+        if (sub == 0) { e[k] = x0; htau[k] = 0.0; }
+        return;
       }
-    }
-    __syncthreads();
-    // every sixteen lanes form p.v by themselves (the same sum in the same order: the same bits), then
-    // A22 -= v w^T + w v^T with w = p - (tau/2)(p.v) v formed where it is used; the two products are added
-    // before they are subtracted, so (i, j) and (j, i) get the same bits
-    double kk = 0.0;
-    if (tk != 0.0) {
-#pragma unroll 4
-      for (int j = k + 1 + sub; j < n; j += 16) kk += w[j] * vk[j];
-      kk = 0.5 * tk * row_sum(kk);
-    }
-    for (int i = k + 1 + group; i < n; i += GROUPS) {
-      const bool next_row = i == k + 1;                       // whose lanes form the next reflector
-      if (tk == 0.0 && !next_row) continue;
-      const double vi = tk != 0.0 ? vk[i] : 0.0, wi = tk != 0.0 ? __dsub_rn(w[i], __dmul_rn(kk, vi)) : 0.0;
-      double* row = A + (size_t)i * lda;
+      const double nrm = quick_sqrt(x0 * x0 + sig);
+      const double alpha = x0 > 0.0 ? -nrm : nrm;
+      const double v0 = x0 - alpha;
+      if (sub == 0) { e[k] = alpha; htau[k] = 2.0 * quick_rcp(v0 * v0 + sig); }
+      for (int j = k + sub; j < n; j += 16) {
+        if (j == k) continue;
+        double* a = A + (size_t)k * lda + j;                    // kept there for the back-transformation
+        const double vj = j == k + 1 ? v0 : *a;
+        vk[j] = vj;
+        *a = vj;
+      }
+    };
+    if (group == 0 && n > 2) {
       double sig = 0.0, x0 = 0.0, diag = 0.0;
-#pragma unroll 4
-      for (int j = k + 1 + sub; j < n; j += 16) {
-        double x = row[j];
-        if (tk != 0.0) {
-          const double vj = vk[j], wj = __dsub_rn(w[j], __dmul_rn(kk, vj));
-          const double p1 = __dmul_rn(vi, wj), p2 = __dmul_rn(wi, vj);
-          x = __dsub_rn(x, __dadd_rn(p1, p2));
-          row[j] = x;
-        }
-        if (j == i) diag = x;
-        else if (j == i + 1) x0 = x;
-        else sig += x * x;                                    // of use in the next row only
+      for (int j = sub; j < n; j += 16) {
+        const double x = A[j];
+        if (j == 0) diag = x;
+        else if (j == 1) x0 = x;
+        else sig += x * x;
       }
-      if (next_row && k + 3 < n) reflector(k + 1, row_sum(sig), __shfl(x0, 1, 16), diag);
+      reflector(0, row_sum(sig), __shfl(x0, 1, 16), diag);
+    }
+    __syncthreads();
+    for (int k = 0; k + 2 < n; ++k) {
+      const double tk = htau[k];
+      const double* vk = v + (k & 1) * MAXN;
+      if (tk != 0.0) {                                          // uniform
+        // p = tau A22 v
+        for (int i = k + 1 + group; i < n; i += GROUPS) {
+          const double* row = A + (size_t)i * lda;
+          double acc = 0.0;
+  #pragma unroll 4
+          for (int j = k + 1 + sub; j < n; j += 16) acc += row[j] * vk[j];
+          acc = row_sum(acc);
+          if (sub == 0) w[i] = tk * acc;
+        }
+      }
+      __syncthreads();
+      // every sixteen lanes form p.v by themselves (the same sum in the same order: the same bits), then
+      // A22 -= v w^T + w v^T with w = p - (tau/2)(p.v) v formed where it is used; the two products are added
+      // before they are subtracted, so (i, j) and (j, i) get the same bits
+      double kk = 0.0;
+      if (tk != 0.0) {
+  #pragma unroll 4
+        for (int j = k + 1 + sub; j < n; j += 16) kk += w[j] * vk[j];
+        kk = 0.5 * tk * row_sum(kk);
+      }
+      for (int i = k + 1 + group; i < n; i += GROUPS) {
+        const bool next_row = i == k + 1;                       // whose lanes form the next reflector
+        if (tk == 0.0 && !next_row) continue;
+        const double vi = tk != 0.0 ? vk[i] : 0.0, wi = tk != 0.0 ? __dsub_rn(w[i], __dmul_rn(kk, vi)) : 0.0;
+        double* row = A + (size_t)i * lda;
+        double sig = 0.0, x0 = 0.0, diag = 0.0;
+  #pragma unroll 4
+        for (int j = k + 1 + sub; j < n; j += 16) {
+          double x = row[j];
+          if (tk != 0.0) {
+            const double vj = vk[j], wj = __dsub_rn(w[j], __dmul_rn(kk, vj));
+            const double p1 = __dmul_rn(vi, wj), p2 = __dmul_rn(wi, vj);
+            x = __dsub_rn(x, __dadd_rn(p1, p2));
+            row[j] = x;
+          }
+          if (j == i) diag = x;
+          else if (j == i + 1) x0 = x;
+          else sig += x * x;                                    // of use in the next row only
+        }
+        if (next_row && k + 3 < n) reflector(k + 1, row_sum(sig), __shfl(x0, 1, 16), diag);
+      }
+      __syncthreads();
+    }
+    if (tid == 0) {
+      if (n >= 2) { d[n - 2] = A[(size_t)(n - 2) * lda + n - 2]; e[n - 2] = A[(size_t)(n - 2) * lda + n - 1]; }
+      d[n - 1] = A[(size_t)(n - 1) * lda + n - 1];
     }
     __syncthreads();
   }
-  if (tid == 0) {
-    if (n >= 2) { d[n - 2] = A[(size_t)(n - 2) * lda + n - 2]; e[n - 2] = A[(size_t)(n - 2) * lda + n - 1]; }
-    d[n - 1] = A[(size_t)(n - 1) * lda + n - 1];
-  }
-  __syncthreads();
   double size = 0.0;                                          // of the tridiagonal matrix: largest sum of a row's magnitudes
 #pragma unroll 4
   for (int i = lane; i < n; i += 64) {
@@ -602,18 +756,20 @@ __global__ __launch_bounds__(kSolveThreads) void eigh_solve_kernel(EighSolveArgs
   __shared__ int bad;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = a.n_seq;
   const size_t prob = blockIdx.x;        // one problem per workgroup
-  a.D += prob * m; a.U += prob * m * m; a.A += prob * m; a.c += prob * a.n_lambda * m;
-  if (a.ema_state) a.ema_state += prob * 2;
-  if (a.info) a.info += prob;
+  const double* const D = a.D + prob * m;
+  const double* const U = a.U + prob * m * m;
+  const float* const A = a.A + prob * m;
+  float* const c = a.c + prob * a.n_lambda * m;
+  float* const ema_state = a.ema_state ? a.ema_state + prob * 2 : nullptr;
   double tr = 0.0;
-  for (int j = tid; j < m; j += kSolveThreads) tr += a.D[j];
+  for (int j = tid; j < m; j += kSolveThreads) tr += D[j];
   if (tid == 0) bad = 0;
   // y = U^T A: a wave takes every sixteenth row, lanes along the row
   for (int j0 = 0; j0 < m; j0 += 64) {
     const int j = j0 + lane < m ? j0 + lane : m - 1;
     double s = 0.0;
 #pragma unroll 4
-    for (int i = wave; i < m; i += WAVES) s += a.U[(size_t)i * m + j] * (double)a.A[i];
+    for (int i = wave; i < m; i += WAVES) s += U[(size_t)i * m + j] * (double)A[i];
     part[wave][lane] = s;
     __syncthreads();
     if (wave == 0 && j0 + lane < m) {
@@ -629,11 +785,11 @@ __global__ __launch_bounds__(kSolveThreads) void eigh_solve_kernel(EighSolveArgs
     double scale = 1.0;                                   // ABSOLUTE
     if (a.reg_mode == 1) scale = mean_d;                  // this batch's mean eigenvalue
     if (a.reg_mode == 2) {                                // trailing mean over minibatches, this one included
-      const double prev = (double)a.ema_state[0];
-      const bool first = a.ema_state[1] == 0.f;
+      const double prev = (double)ema_state[0];
+      const bool first = ema_state[1] == 0.f;
       scale = first ? mean_d : (double)a.ema_decay * prev + (1.0 - (double)a.ema_decay) * mean_d;
-      a.ema_state[0] = (float)scale;
-      a.ema_state[1] = a.ema_state[1] + 1.f;
+      ema_state[0] = (float)scale;
+      ema_state[1] = ema_state[1] + 1.f;
     }
     sh_scale = scale;
   }
@@ -642,7 +798,7 @@ __global__ __launch_bounds__(kSolveThreads) void eigh_solve_kernel(EighSolveArgs
   for (int l = 0; l < a.n_lambda; ++l) {
     const double reg = (double)a.lambdas[l] * scale;
     for (int j = tid; j < m; j += kSolveThreads) {
-      const double den = a.D[j] + reg;
+      const double den = D[j] + reg;
       f[j] = den > 0.0 ? y[j] / den : 0.0;
       if (!(den > 0.0)) atomicAdd(&bad, 1);
     }
@@ -653,17 +809,17 @@ __global__ __launch_bounds__(kSolveThreads) void eigh_solve_kernel(EighSolveArgs
       for (int j = lane; j < m; j += 64) {
         const double fj = f[j];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) s[q] += a.U[(size_t)(i0 + q < m ? i0 + q : m - 1) * m + j] * fj;
+        for (int q = 0; q < 4; ++q) s[q] += U[(size_t)(i0 + q < m ? i0 + q : m - 1) * m + j] * fj;
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const double t = wave_total(s[q]);
-        if (lane == 0 && i0 + q < m) a.c[(size_t)l * m + i0 + q] = (float)t;
+        if (lane == 0 && i0 + q < m) c[(size_t)l * m + i0 + q] = (float)t;
       }
     }
     __syncthreads();
   }
-  if (a.info && tid == 0) *a.info = bad;
+  if (a.info && tid == 0) a.info[prob] = bad;
 }
 
 }  // namespace
