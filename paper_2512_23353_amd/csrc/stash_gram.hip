@@ -49,63 +49,94 @@ __global__ __launch_bounds__(1024) void stash_gram_finish_kernel(const float* __
   }
 }
 
-template <bool BF16, bool OUTB>
-__global__ __launch_bounds__(256) void stash_weighted_sum_kernel(const void* __restrict__ stash, long long seq_stride,
-                                                                 long long n_vec, int n_seq,
-                                                                 const float* __restrict__ c, float beta,
-                                                                 void* __restrict__ dW_out) {
-  constexpr int kV = BF16 ? 8 : 4;
-  for (long long vi = (long long)blockIdx.x * blockDim.x + threadIdx.x; vi < n_vec;
-       vi += (long long)gridDim.x * blockDim.x) {
-    float s[kV];
+// The weighted sum: a thread takes VPT 16-byte vectors of every sequence, kSumThreads apart, so a workgroup reads VPT runs of 4 KiB
+// side by side and VPT * 8 loads of a thread are in flight.  Bound by HBM; which VPT where: launch_stash_weighted_sum's rule.
+constexpr int kSumThreads = 256;
+
+// Past the last-level cache many times over nothing of dW would stay there: non-temporal.
+template <int VPT, class V>
+__device__ __forceinline__ void store_result(V* o, V v) {
+  if constexpr (VPT == 4) __builtin_nontemporal_store(v, o); else *o = v;
+}
+
+// acc[q][e] += sum_i c_i * element e of vector q (at src + at[q] in sequence i)
+template <bool BF16, int VPT>
+__device__ __forceinline__ void sum_vectors(const char* __restrict__ src, size_t seq_bytes, const long long (&at)[VPT], int n_seq,
+                                            const float* __restrict__ c, float (&acc)[VPT][BF16 ? 8 : 4]) {
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int e = 0; e < kV; ++e) s[e] = 0.f;
-    const char* src = static_cast<const char*>(stash) + vi * 16;
+  for (int q = 0; q < VPT; ++q)
+#pragma unroll
+    for (int e = 0; e < (BF16 ? 8 : 4); ++e) acc[q][e] = 0.f;
 #pragma unroll 8
-    for (int i = 0; i < n_seq; ++i) {
-      const float ci = c[i];
-      typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-      const u32x4* vp = reinterpret_cast<const u32x4*>(src + (size_t)i * seq_stride * (BF16 ? 2 : 4));
-      const u32x4 vv = __builtin_nontemporal_load(vp);     // read once: 5.2 -> 5.8 TB/s with the full grid below
-      const uint4 v = make_uint4(vv[0], vv[1], vv[2], vv[3]);
-      if constexpr (BF16) {
-        const unsigned w[4] = {v.x, v.y, v.z, v.w};
+  for (int i = 0; i < n_seq; ++i) {
+    const float ci = c[i];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          s[2 * e] += ci * __builtin_bit_cast(float, w[e] << 16);
-          s[2 * e + 1] += ci * __builtin_bit_cast(float, w[e] & 0xffff0000u);
-        }
-      } else {
-        const float4 f = __builtin_bit_cast(float4, v);
-        s[0] += ci * f.x; s[1] += ci * f.y; s[2] += ci * f.z; s[3] += ci * f.w;
-      }
-    }
-    if constexpr (OUTB) {
-      // bf16 dW (bf16 stash only): the thread's eight values are one 16-byte vector
-      static_assert(!OUTB || BF16, "a bf16 dW is formed from a bf16 stash");
-      uint4* o = static_cast<uint4*>(dW_out) + vi;
-      unsigned w[4] = {0u, 0u, 0u, 0u};
-      if (beta != 0.f) {
-        const uint4 old = *o;
-        w[0] = old.x; w[1] = old.y; w[2] = old.z; w[3] = old.w;
-      }
+    for (int q = 0; q < VPT; ++q) {
+      // read once: non-temporal
+      const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (size_t)i * seq_bytes + at[q]));
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float lo = s[2 * e] + beta * __builtin_bit_cast(float, w[e] << 16);
-        const float hi = s[2 * e + 1] + beta * __builtin_bit_cast(float, w[e] & 0xffff0000u);
-        w[e] = (unsigned)f32_to_bf16_bits(lo) | ((unsigned)f32_to_bf16_bits(hi) << 16);
-      }
-      *o = make_uint4(w[0], w[1], w[2], w[3]);
-    } else {
-      float* o = static_cast<float*>(dW_out) + vi * kV;
-#pragma unroll
-      for (int e = 0; e < kV; e += 4) {
-        float4 r = make_float4(s[e], s[e + 1], s[e + 2], s[e + 3]);
-        if (beta != 0.f) {
-          const float4 old = *reinterpret_cast<const float4*>(o + e);
-          r.x += beta * old.x; r.y += beta * old.y; r.z += beta * old.z; r.w += beta * old.w;
+        if constexpr (BF16) {
+          acc[q][2 * e] += ci * __builtin_bit_cast(float, w[e] << 16);
+          acc[q][2 * e + 1] += ci * __builtin_bit_cast(float, w[e] & 0xffff0000u);
+        } else {
+          const unsigned bits = w[e];
+          acc[q][e] += ci * __builtin_bit_cast(float, bits);
         }
-        *reinterpret_cast<float4*>(o + e) = r;
+      }
+    }
+  }
+}
+
+template <bool BF16, bool OUTB, int VPT>
+__global__ __launch_bounds__(kSumThreads) void stash_weighted_sum_kernel(const void* __restrict__ stash, long long seq_stride,
+                                                                         long long n_vec, int n_seq,
+                                                                         const float* __restrict__ c, float beta,
+                                                                         void* __restrict__ dW_out) {
+  constexpr int kV = BF16 ? 8 : 4;
+  for (long long v0 = (long long)blockIdx.x * (kSumThreads * VPT) + threadIdx.x; v0 < n_vec;
+       v0 += (long long)gridDim.x * (kSumThreads * VPT)) {
+    float acc[VPT][kV];
+    long long at[VPT];
+#pragma unroll
+    for (int q = 0; q < VPT; ++q) {
+      const long long v = v0 + q * kSumThreads;
+      at[q] = (v < n_vec ? v : v0) * 16;
+    }
+    sum_vectors<BF16, VPT>(static_cast<const char*>(stash), (size_t)seq_stride * (BF16 ? 2 : 4), at, n_seq, c, acc);
+#pragma unroll
+    for (int q = 0; q < VPT; ++q) {
+      const long long vi = v0 + q * kSumThreads;
+      if (vi >= n_vec) break;
+      const float (&s)[kV] = acc[q];
+      if constexpr (OUTB) {
+        // bf16 dW (bf16 stash only): the thread's eight values are one 16-byte vector
+        static_assert(!OUTB || BF16, "a bf16 dW is formed from a bf16 stash");
+        uint4* o = static_cast<uint4*>(dW_out) + vi;
+        unsigned w[4] = {0u, 0u, 0u, 0u};
+        if (beta != 0.f) {
+          const uint4 old = *o;
+          w[0] = old.x; w[1] = old.y; w[2] = old.z; w[3] = old.w;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float lo = s[2 * e] + beta * __builtin_bit_cast(float, w[e] << 16);
+          const float hi = s[2 * e + 1] + beta * __builtin_bit_cast(float, w[e] & 0xffff0000u);
+          w[e] = (unsigned)f32_to_bf16_bits(lo) | ((unsigned)f32_to_bf16_bits(hi) << 16);
+        }
+        *o = make_uint4(w[0], w[1], w[2], w[3]);
+      } else {
+        float* o = static_cast<float*>(dW_out) + vi * kV;
+#pragma unroll
+        for (int e = 0; e < kV; e += 4) {
+          float4 r = make_float4(s[e], s[e + 1], s[e + 2], s[e + 3]);
+          if (beta != 0.f) {
+            const float4 old = *reinterpret_cast<const float4*>(o + e);
+            r.x += beta * old.x; r.y += beta * old.y; r.z += beta * old.z; r.w += beta * old.w;
+          }
+          store_result<VPT>(reinterpret_cast<f32x4*>(o + e), f32x4{r.x, r.y, r.z, r.w});
+        }
       }
     }
   }
@@ -114,61 +145,57 @@ __global__ __launch_bounds__(256) void stash_weighted_sum_kernel(const void* __r
 // The same from a stash in tile order (see stash_tile_order_ok): a thread's eight values are four rows of
 // two columns of dW, 16 apart; a wave stores, per value, four rows' runs of 16 consecutive floats, and the
 // values q and q + 4 complete each other's 128-byte lines.
-template <int T, bool OUTB>
-__global__ __launch_bounds__(256) void stash_weighted_sum_tiled_kernel(const void* __restrict__ stash, long long seq_stride,
+template <int T, bool OUTB, int VPT>
+__global__ __launch_bounds__(kSumThreads) void stash_weighted_sum_tiled_kernel(const void* __restrict__ stash, long long seq_stride,
                                                                        long long n_vec, int n_seq,
                                                                        const float* __restrict__ c, float beta,
                                                                        void* __restrict__ dW_out, int d_in, int tiles_n) {
   constexpr int NP = T / 64;                       // 16x32 pieces per 16-row strip of a quadrant
   constexpr int QV = (T / 2) * (T / 2) / 8;        // 16-byte vectors per quadrant
   constexpr int TV = T * T / 8;                    // ... per tile
-  for (long long vi = (long long)blockIdx.x * blockDim.x + threadIdx.x; vi < n_vec;
-       vi += (long long)gridDim.x * blockDim.x) {
-    float s[8];
+  static_assert(TV % (kSumThreads * VPT) == 0, "a workgroup's vectors are there");
+  for (long long v0 = (long long)blockIdx.x * (kSumThreads * VPT) + threadIdx.x; v0 < n_vec;
+       v0 += (long long)gridDim.x * (kSumThreads * VPT)) {
+    float acc[VPT][8];
+    long long at[VPT];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) s[e] = 0.f;
-    const char* src = static_cast<const char*>(stash) + vi * 16;
-#pragma unroll 8
-    for (int i = 0; i < n_seq; ++i) {
-      const float ci = c[i];
-      typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-      const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (size_t)i * seq_stride * 2));
+    for (int u = 0; u < VPT; ++u) at[u] = (v0 + u * kSumThreads) * 16;
+    sum_vectors<true, VPT>(static_cast<const char*>(stash), (size_t)seq_stride * 2, at, n_seq, c, acc);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        s[2 * e] += ci * __builtin_bit_cast(float, w[e] << 16);
-        s[2 * e + 1] += ci * __builtin_bit_cast(float, w[e] & 0xffff0000u);
-      }
-    }
-    const long long tile = vi / TV;
-    const int r = (int)(vi % TV), quad = r / QV, r2 = r % QV, piece = r2 / 64, lane = r2 % 64;
-    const int strip = piece / NP, jp = piece % NP;
-    const int tile_m = (int)(tile / tiles_n), tile_n = (int)(tile % tiles_n);
-    const int n0 = tile_n * T + (quad & 1) * (T / 2) + jp * 32 + (lane & 15);
-    const int m0 = tile_m * T + (quad >> 1) * (T / 2) + strip * 16 + 4 * (lane >> 4);
-    if constexpr (OUTB) {
-      // bf16 dW: neighbouring lanes hold neighbouring columns; the even lane takes its neighbour's values of
-      // the left 16 columns and stores pairs there, the odd lane does the same for the right 16 columns
-      // (n_vec is a multiple of 64 for a stash in tile order, so every lane of a wave is here)
-      __bf16* dW = static_cast<__bf16*>(dW_out);
-      const bool odd = lane & 1;
+    for (int u = 0; u < VPT; ++u) {
+      const long long vi = v0 + u * kSumThreads;
+      const float (&s)[8] = acc[u];
+      const long long tile = vi / TV;
+      const int r = (int)(vi % TV), quad = r / QV, r2 = r % QV, piece = r2 / 64, lane = r2 % 64;
+      const int strip = piece / NP, jp = piece % NP;
+      const int tile_m = (int)(tile / tiles_n), tile_n = (int)(tile % tiles_n);
+      const int n0 = tile_n * T + (quad & 1) * (T / 2) + jp * 32 + (lane & 15);
+      const int m0 = tile_m * T + (quad >> 1) * (T / 2) + strip * 16 + 4 * (lane >> 4);
+      if constexpr (OUTB) {
+        // bf16 dW: neighbouring lanes hold neighbouring columns; the even lane takes its neighbour's values of
+        // the left 16 columns and stores pairs there, the odd lane does the same for the right 16 columns
+        // (n_vec is a multiple of 64 for a stash in tile order, so every lane of a wave is here)
+        __bf16* dW = static_cast<__bf16*>(dW_out);
+        const bool odd = lane & 1;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float got = __shfl_xor(odd ? s[q] : s[q + 4], 1, kWave);
-        float lo = odd ? got : s[q], hi = odd ? s[q + 4] : got;
-        unsigned* o = reinterpret_cast<unsigned*>(dW + (size_t)(m0 + q) * d_in + (n0 & ~1) + (odd ? 16 : 0));
-        if (beta != 0.f) {
-          const unsigned old = *o;
-          lo += beta * __builtin_bit_cast(float, old << 16);
-          hi += beta * __builtin_bit_cast(float, old & 0xffff0000u);
+        for (int q = 0; q < 4; ++q) {
+          const float got = __shfl_xor(odd ? s[q] : s[q + 4], 1, kWave);
+          float lo = odd ? got : s[q], hi = odd ? s[q + 4] : got;
+          unsigned* o = reinterpret_cast<unsigned*>(dW + (size_t)(m0 + q) * d_in + (n0 & ~1) + (odd ? 16 : 0));
+          if (beta != 0.f) {
+            const unsigned old = *o;
+            lo += beta * __builtin_bit_cast(float, old << 16);
+            hi += beta * __builtin_bit_cast(float, old & 0xffff0000u);
+          }
+          *o = (unsigned)f32_to_bf16_bits(lo) | ((unsigned)f32_to_bf16_bits(hi) << 16);
         }
-        *o = (unsigned)f32_to_bf16_bits(lo) | ((unsigned)f32_to_bf16_bits(hi) << 16);
-      }
-    } else {
-      float* dW = static_cast<float*>(dW_out);
+      } else {
+        float* dW = static_cast<float*>(dW_out);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        float* o = dW + (size_t)(m0 + (q & 3)) * d_in + n0 + 16 * (q >> 2);
-        *o = (beta != 0.f ? beta * *o : 0.f) + s[q];
+        for (int q = 0; q < 8; ++q) {
+          float* o = dW + (size_t)(m0 + (q & 3)) * d_in + n0 + 16 * (q >> 2);
+          store_result<VPT>(o, (beta != 0.f ? beta * *o : 0.f) + s[q]);
+        }
       }
     }
   }
@@ -206,33 +233,54 @@ hipError_t launch_stash_gram_finish(const float* partials, bool bf16, int slots,
   return hipGetLastError();
 }
 
+// Vectors per thread.  Four (and non-temporal stores) over stashes of 2 GiB and up: 4096x14336, 32 sequences 751 -> 632 us (6.3
+// TB/s); 1536x8960, 256 1229 -> 1070; 5120x13824, 16 496 -> 455; below they lose (3584x5120, 48: 323 / 340; 2048x3072, 128: 296 / 345).
+// Two where the chip's compute units then get like numbers of workgroups, the fullest no more than an eighth above the mean:
+// 4096x1024, 32 sequences 54.5 -> 45.5 us; 1024x2048, 64 52.6 -> 45.2; 2048x4096, 16 55.1 -> 48.8; 3000x5000, 40 222 -> 207; fp32
+// 2048x4096, 8 50.6 -> 46.3; where they do not, half as many workgroups are worse (768x3072, 100: 84 / 92; 1000x2728, 24: 23.6 / 24.8;
+// 2984x560, 101: 63 / 114).
+static int sum_vectors_per_thread(long long n_vec, int n_seq) {
+  if (n_vec * n_seq >= (2LL << 30) / 16 && n_vec >= 3 << 19) return 4;
+  const long long blocks = (n_vec + 2 * kSumThreads - 1) / (2 * kSumThreads), fullest = (blocks + 255) / 256;
+  return blocks >= 512 && fullest * 256 * 8 <= blocks * 9 ? 2 : 1;
+}
+
+static unsigned sum_blocks(long long n_vec, int vpt) {
+  // (the kernels' loops stride over the rest of a stash beyond 2^39 elements)
+  const long long blocks = (n_vec + kSumThreads * vpt - 1) / (kSumThreads * vpt);
+  return (unsigned)(blocks > 0x7fffffffLL ? 0x7fffffffLL : blocks);
+}
+
+template <bool BF16, bool OUTB>
+static hipError_t launch_rows_t(const void* stash, long long seq_stride, long long n_vec, int n_seq, const float* c, float beta,
+                                void* dW, hipStream_t s) {
+  const int vpt = sum_vectors_per_thread(n_vec, n_seq);
+  auto kern = vpt == 4   ? stash_weighted_sum_kernel<BF16, OUTB, 4>
+              : vpt == 2 ? stash_weighted_sum_kernel<BF16, OUTB, 2>
+                         : stash_weighted_sum_kernel<BF16, OUTB, 1>;
+  hipLaunchKernelGGL(kern, dim3(sum_blocks(n_vec, vpt)), dim3(kSumThreads), 0, s, stash, seq_stride, n_vec, n_seq, c, beta, dW);
+  return hipGetLastError();
+}
+
 hipError_t launch_stash_weighted_sum(const void* stash, bool bf16, long long seq_stride, long long n_elem, int n_seq,
                                      const float* c, float beta, void* dW, bool dw_bf16, hipStream_t s) {
   const long long n_vec = n_elem / (bf16 ? 8 : 4);
   if (n_vec <= 0) return hipSuccess;
   if (dw_bf16 && !bf16) return hipErrorInvalidValue;
-  // one 16-byte vector per thread (the kernel's loop strides over the rest of a stash beyond 2^39 elements)
-  long long blocks = (n_vec + 255) / 256;
-  if (blocks > 0x7fffffffLL) blocks = 0x7fffffffLL;
-  if (bf16 && dw_bf16)
-    hipLaunchKernelGGL((stash_weighted_sum_kernel<true, true>), dim3((unsigned)blocks), dim3(256), 0, s, stash, seq_stride,
-                       n_vec, n_seq, c, beta, dW);
-  else if (bf16)
-    hipLaunchKernelGGL((stash_weighted_sum_kernel<true, false>), dim3((unsigned)blocks), dim3(256), 0, s, stash, seq_stride,
-                       n_vec, n_seq, c, beta, dW);
-  else
-    hipLaunchKernelGGL((stash_weighted_sum_kernel<false, false>), dim3((unsigned)blocks), dim3(256), 0, s, stash, seq_stride,
-                       n_vec, n_seq, c, beta, dW);
-  return hipGetLastError();
+  if (!bf16) return launch_rows_t<false, false>(stash, seq_stride, n_vec, n_seq, c, beta, dW, s);
+  return dw_bf16 ? launch_rows_t<true, true>(stash, seq_stride, n_vec, n_seq, c, beta, dW, s)
+                 : launch_rows_t<true, false>(stash, seq_stride, n_vec, n_seq, c, beta, dW, s);
 }
 
 template <int T, bool OUTB>
 static hipError_t launch_tiled_t(const void* stash, long long D, long long n_vec, int n_seq, const float* c, float beta,
                                  void* dW, int d_in, hipStream_t s) {
-  long long blocks = (n_vec + 255) / 256;
-  if (blocks > 0x7fffffffLL) blocks = 0x7fffffffLL;
-  hipLaunchKernelGGL((stash_weighted_sum_tiled_kernel<T, OUTB>), dim3((unsigned)blocks), dim3(256), 0, s, stash, D, n_vec,
-                     n_seq, c, beta, dW, d_in, d_in / T);
+  const int vpt = sum_vectors_per_thread(n_vec, n_seq);
+  auto kern = vpt == 4   ? stash_weighted_sum_tiled_kernel<T, OUTB, 4>
+              : vpt == 2 ? stash_weighted_sum_tiled_kernel<T, OUTB, 2>
+                         : stash_weighted_sum_tiled_kernel<T, OUTB, 1>;
+  hipLaunchKernelGGL(kern, dim3(sum_blocks(n_vec, vpt)), dim3(kSumThreads), 0, s, stash, D, n_vec, n_seq, c, beta, dW, d_in,
+                     d_in / T);
   return hipGetLastError();
 }
 
