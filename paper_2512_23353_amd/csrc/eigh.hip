@@ -32,7 +32,7 @@ __device__ double block_sum(double x, double* red) {
 // U = H Q^T.
 // One workgroup per problem, fp64 throughout: bound by the latency of its dependent steps and, with sixteen waves on four
 // vector units, by what each of them issues, so that sums run over sixteen lanes where sixteen rows wait side by side.
-// 16 / 32 / 64 / 96 / 128 / 256 / 512 / 1024 sequences: 0.06 / 0.09 / 0.18 / 0.38 / 0.66 / 5.7 / 45 / 380 ms, where a Jacobi
+// 16 / 32 / 64 / 96 / 128 / 256 / 512 / 1024 sequences: 0.04 / 0.07 / 0.14 / 0.32 / 0.55 / 5.5 / 45 / 380 ms, where a Jacobi
 // iteration (two barriers per round of n/2 rotations, up to 94 sequences) and implicit QL (a sequential chain of about 25
 // dependent operations per plane rotation) took 0.09 / 0.26 / 1.19 ms at 16 / 32 / 64 and 5.5 / 22 / 100 / 630 from 128 on; errors
 // of D, U^T U and U D U^T 2e-16 .. 1e-14 of the largest eigenvalue, a fifth of the Jacobi iteration's.
@@ -75,16 +75,21 @@ __device__ __forceinline__ double row_sum(double x) {
   return dpp_add<0x140, 0xf>(x);                     // mirrored within sixteen
 }
 __device__ __forceinline__ double quad_sum(double x) { return dpp_add<0x4E, 0xf>(dpp_add<0xB1, 0xf>(x)); }
+__device__ __forceinline__ double oct_sum(double x) { return dpp_add<0x141, 0xf>(quad_sum(x)); }
 __device__ __forceinline__ int row_count(int x) {    // the same for counts
   x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false);
   x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, false);
   x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);
   return x + __builtin_amdgcn_update_dpp(0, x, 0x140, 0xf, 0xf, false);
 }
+template <int CTRL>
+__device__ __forceinline__ double dpp_mul(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
+  return x * __hiloint2double(hi, lo);
+}
 __device__ __forceinline__ double row_product(double x) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) x *= __shfl_xor(x, o, 64);
-  return x;
+  return dpp_mul<0x140>(dpp_mul<0x141>(dpp_mul<0x4E>(dpp_mul<0xB1>(x))));
 }
 __device__ __forceinline__ double lane_value(double x, int src) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(x), src);
@@ -107,13 +112,14 @@ __device__ __forceinline__ double quick_rcp(double x) {
 }
 __device__ __forceinline__ double quick_sqrt(double x) { return x > 0.0 ? x * rsqrt(x) : 0.0; }
 
-// Root j of 1 + rho sum_i z_i^2 / (d_i - x) over the k poles d (ascending, distinct), as d[org] + tau; LPR lanes (4 or 16,
-// lane `sub` of them): the interpolation is repeated in every one of them, so few lanes where there are few poles.  False
-// where `limit` steps did not get there.
-template <int LPR>
+// Root j of 1 + rho sum_i z_i^2 / (d_i - x) over the k poles d (ascending, distinct), as d[org] + tau; LPR lanes (4, 8 or 16,
+// lane `sub` of them): the interpolation is repeated in every one of them, so few lanes where there are few poles.  Up to
+// PER poles a lane are held in registers, a step's terms are then independent of each other and of the LDS; PER = 0: any
+// number, read at every step.  False where `limit` steps did not get there.
+template <int LPR, int PER>
 __device__ __forceinline__ bool secular_root(const double* d, const double* z, int k, double rho, int j, int sub, int limit,
                                              int& org, double& tau) {
-  auto lanes_sum = [](double x) { return LPR == 4 ? quad_sum(x) : row_sum(x); };
+  auto lanes_sum = [](double x) { return LPR == 4 ? quad_sum(x) : (LPR == 8 ? oct_sum(x) : row_sum(x)); };
   const bool last = j == k - 1;
   double zz = 0.0;
   if (last) {
@@ -123,6 +129,7 @@ __device__ __forceinline__ bool secular_root(const double* d, const double* z, i
   const double gap = last ? rho * zz : d[j + 1] - d[j];
   // which half of the interval
   double mid = 0.0;
+#pragma unroll 4
   for (int i = sub; i < k; i += LPR) mid += z[i] * z[i] * quick_rcp((d[i] - d[j]) - 0.5 * gap);
   mid = 1.0 + rho * lanes_sum(mid);
   double lo, hi;
@@ -133,12 +140,31 @@ __device__ __forceinline__ bool secular_root(const double* d, const double* z, i
   tau = 0.5 * (lo + hi);
   const double near = 4.0 * kUlp * quick_sqrt((double)k);
   const double dorg = d[org], dj = d[j] - dorg, dj1 = last ? 0.0 : d[j + 1] - dorg;
+  [[maybe_unused]] double pole[PER > 0 ? PER : 1], before[PER > 0 ? PER : 1], behind[PER > 0 ? PER : 1];
+#pragma unroll
+  for (int t = 0; t < PER; ++t) {
+    const int i = sub + LPR * t;
+    pole[t] = i < k ? d[i] - dorg : 1e300;                       // none there: nothing of the sums
+    const double rzz = i < k ? rho * z[i] * z[i] : 0.0;
+    before[t] = i <= j ? rzz : 0.0;
+    behind[t] = i <= j ? 0.0 : rzz;
+  }
   for (int it = 0; it < limit; ++it) {
     double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;         // poles up to j, and after it
-    for (int i = sub; i < k; i += LPR) {
-      const double inv = quick_rcp((d[i] - dorg) - tau), r = rho * z[i] * z[i] * inv, dr = r * inv;
-      if (i <= j) { psi += r; dpsi += dr; }
-      else { phi += r; dphi += dr; }
+    auto term = [&](double from_org, double before, double behind) __attribute__((always_inline)) {
+      const double inv = quick_rcp(from_org - tau), inv2 = inv * inv;
+      psi = fma(before, inv, psi); dpsi = fma(before, inv2, dpsi);
+      phi = fma(behind, inv, phi); dphi = fma(behind, inv2, dphi);
+    };
+    if constexpr (PER > 0) {
+#pragma unroll
+      for (int t = 0; t < PER; ++t) term(pole[t], before[t], behind[t]);
+    } else {
+#pragma unroll 2
+      for (int i = sub; i < k; i += LPR) {
+        const double rzz = rho * z[i] * z[i];
+        term(d[i] - dorg, i <= j ? rzz : 0.0, i <= j ? 0.0 : rzz);
+      }
     }
     psi = lanes_sum(psi); dpsi = lanes_sum(dpsi); phi = lanes_sum(phi); dphi = lanes_sum(dphi);
     const double w = 1.0 + psi + phi;
@@ -176,7 +202,8 @@ __host__ __device__ constexpr int eigh_pitch(int m) {
 // ahead of the update together with A v: no barrier stands between the update and the next product, and with four waves
 // (one per vector unit) saying it sixteen times over costs what saying it once does.  The waves past WV wait at the barriers.
 // Columns that are through are left out sixteen at a time.  Seven problems of 16 / 32 / 64 / 72 / 96 / 128 sequences, against
-// the matrix in LDS with two barriers per column: 65 / 118 / 248 / 365 / 525 / 856 us -> 57 / 93 / 177 / 300 / 380 / 656.
+// the matrix in LDS with two barriers per column: 65 / 118 / 248 / 365 / 525 / 856 us -> 57 / 93 / 177 / 300 / 380 / 656,
+// with the merges as they were then.
 //   pbuf, rbuf (two of 16 NE each, by the column's parity): tau A v, and row k + 1 as column k finds it
 //   A: row k receives v_k, which the updates read by row and the back-transformation later
 // Rounding: v_i w_j + w_i v_j is formed from two rounded products, so (i, j) and (j, i) stay the same bits, and so do the
@@ -508,16 +535,19 @@ __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __res
   }
   double* const rot_c = v;                                    // the reflectors' vectors are done with
   double* const rot_s = w;
+  const float inv_n = 1.0f / (float)n;
   __syncthreads();
   for (int lev = 1; lev < levels; ++lev) {
-    const int nb = 1 << (levels - lev);                       // blocks before the merges of this level
+    // Blocks before the merges of this level.  Their bounds are asked for in every step: by shifts, where 64-bit divisions were
+    // a third of a merge.
+    const int sh = levels - lev, nb = 1 << sh;
     auto block_of = [&](int i, int& b0, int& b1, int& b2) {
-      int s = (int)((long long)i * (nb >> 1) / n);
-      while ((int)((long long)(2 * s + 2) * n / nb) <= i) ++s;
-      while ((int)((long long)(2 * s) * n / nb) > i) --s;
-      b0 = (int)((long long)(2 * s) * n / nb);
-      b1 = (int)((long long)(2 * s + 1) * n / nb);
-      b2 = (int)((long long)(2 * s + 2) * n / nb);
+      int s = (int)((float)(i * (nb >> 1)) * inv_n);          // or next to it
+      while (((2 * s + 2) * n >> sh) <= i) ++s;
+      while ((2 * s * n >> sh) > i) --s;
+      b0 = 2 * s * n >> sh;
+      b1 = (2 * s + 1) * n >> sh;
+      b2 = (2 * s + 2) * n >> sh;
     };
     // z, into sorted order; no scan asked for yet
     for (int i = group; i < n; i += GROUPS) {
@@ -606,20 +636,33 @@ __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __res
       }
       dk[i] = ds[list[i]];                                    // deflated ones too, behind the others
       zk[i] = zs[list[i]];
+      list[i] = perm[list[i]];                                // from here on: the old vector at sorted position i
     }
     __syncthreads();
-    constexpr int LPR = MAXN <= 128 ? 4 : 16;
-    for (int i = tid / LPR; i < n; i += THREADS / LPR) {
-      int b0, b1, b2;
-      block_of(i, b0, b1, b2);
-      const int k = n_live[b0], j = i - b0;
-      if (j < k) {
-        int o;
-        double t;
-        if (!secular_root<LPR>(dk + b0, zk + b0, k, 2.0 * fabs(e[b1 - 1]), j, tid % LPR, root_steps, o, t)) bad = 1;
-        if (tid % LPR == 0) { org[i] = (short)o; rtau[i] = t; }
+    auto roots = [&](auto lanes_c, auto per_c) __attribute__((always_inline)) {
+      constexpr int LPR = decltype(lanes_c)::value, PER = decltype(per_c)::value;
+      for (int i = tid / LPR; i < n; i += THREADS / LPR) {
+        int b0, b1, b2;
+        block_of(i, b0, b1, b2);
+        const int k = n_live[b0], j = i - b0;
+        if (j < k) {
+          int o;
+          double t;
+          if (!secular_root<LPR, PER>(dk + b0, zk + b0, k, 2.0 * fabs(e[b1 - 1]), j, tid % LPR, root_steps, o, t)) bad = 1;
+          if (tid % LPR == 0) { org[i] = (short)o; rtau[i] = t; }
+        }
       }
-    }
+    };
+    // A merged block holds at most 2 << lev indices.  Few lanes a root, so that every vector unit has one wave or two: what all
+    // lanes of a root repeat is issued least often.  64 sequences with this, the bounds by shifts, vectors fetched a step early and
+    // U written by way of the LDS: 177 -> 141 us for seven problems, 128: 656 -> 547, 16: 57 -> 43.
+    constexpr std::integral_constant<int, 4> c4{};
+    constexpr std::integral_constant<int, 8> c8{};
+    if constexpr (MAXN > 128) roots(std::integral_constant<int, 16>{}, std::integral_constant<int, 0>{});
+    else if (2 << lev <= 16) roots(c4, c4);
+    else if (2 << lev <= 32) roots(c4, c8);
+    else if (MAXN == 64 || 2 << lev <= 64) roots(c8, c8);
+    else roots(c4, std::integral_constant<int, 0>{});
     __syncthreads();
     for (int i = group; i < n; i += GROUPS) {
       int b0, b1, b2;
@@ -657,16 +700,26 @@ __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __res
         const double dorg = live ? dk[b0 + org[j]] : 0.0, t = live ? rtau[j] : 0.0;
         f64x4 acc = {0.0, 0.0, 0.0, 0.0};
         double s = 0.0;
+        // what a step reads is fetched one step early
+        double x_next, dk_next, zh_next;
+        auto fetch = [&](int i) {
+          const int ic = i < n ? i : n - 1;
+          x_next = Qt[(size_t)list[ic] * ldq + r];
+          dk_next = dk[ic];
+          zh_next = zh[ic];
+        };
+        fetch(lo + l4);
         for (int i0 = lo; i0 < hi; i0 += 4) {
-          const int i = i0 + l4, ic = i < n ? i : n - 1;
+          const int i = i0 + l4;
+          const double x = x_next, dki = dk_next, zhi = zh_next;
+          fetch(i + 4);
           double u = 0.0;
           if (live) {
-            if (i >= b0 && i < b0 + k) u = zh[ic] * quick_rcp((dk[ic] - dorg) - t);
+            if (i >= b0 && i < b0 + k) u = zhi * quick_rcp((dki - dorg) - t);
           } else {
             u = i == j ? 1.0 : 0.0;
           }
           s += u * u;
-          const double x = Qt[(size_t)perm[list[ic]] * ldq + r];
           acc = __builtin_amdgcn_mfma_f64_16x16x4f64(u, x, acc, 0, 0, 0);
         }
         s += __shfl_xor(s, 16, 64);
@@ -689,13 +742,33 @@ __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __res
     double* const swap = Qt; Qt = Qnext; Qnext = swap;
   }
 
-  // ---- U = H_0 ... H_{n-3} Q^T: sixteen lanes (a wave, past 256 elements) per vector, its elements in registers ----
-  constexpr int VL = MAXN <= 256 ? 16 : 64, NE = MAXN / VL;
+  // ascending order by rank (ties broken by index)
+  for (int i = group; i < n; i += GROUPS) {
+    const double di = d[i];
+    int rank = 0;
+    for (int j = sub; j < n; j += 16) {
+      const double dj = d[j];
+      rank += (dj < di || (dj == di && j < i)) ? 1 : 0;
+    }
+    rank = row_count(rank);
+    if (sub == 0) {
+      D[rank] = di * up;
+      perm[rank] = (short)i;
+      list[i] = (short)rank;
+    }
+  }
+
+  // ---- U = H_0 ... H_{n-3} Q^T: sixteen lanes (a wave, past 256 elements) per vector, its elements in registers; past 64
+  // sequences two vectors at a time, which share the reflectors' reads (128: with the output below 618 us against 664 for seven problems) ----
+  constexpr int VL = MAXN <= 256 ? 16 : 64, NE = MAXN / VL, NV = MAXN == 128 ? 2 : 1, VS = THREADS / VL;
   const int vl = tid % VL;
-  for (int i = tid / VL; i < n; i += THREADS / VL) {
-    double x[NE], ahead[NE];                                  // ahead: the next reflector's vector, fetched one step early
+  for (int i = tid / VL; i < n; i += VS * NV) {
+    double x[NV][NE], ahead[NE];                              // ahead: the next reflector's vector, fetched one step early
 #pragma unroll
-    for (int t = 0; t < NE; ++t) x[t] = t * VL + vl < n ? Qt[(size_t)i * ldq + t * VL + vl] : 0.0;
+    for (int u = 0; u < NV; ++u)
+#pragma unroll
+      for (int t = 0; t < NE; ++t)
+        x[u][t] = t * VL + vl < n && i + VS * u < n ? Qt[(size_t)(i + VS * u) * ldq + t * VL + vl] : 0.0;
     auto fetch = [&](int k) {
 #pragma unroll
       for (int t = 0; t < NE; ++t) {
@@ -706,38 +779,47 @@ __global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __res
     fetch(n - 3);
     for (int k = n - 3; k >= 0; --k) {
       const double tk = htau[k];
-      double vk[NE], dot = 0.0;
+      double vk[NE];
 #pragma unroll
       for (int t = 0; t < NE; ++t) vk[t] = ahead[t];
       fetch(k - 1);
       if (tk == 0.0) continue;                                // uniform
 #pragma unroll
-      for (int t = 0; t < NE; ++t) dot += vk[t] * x[t];
-      dot = tk * (VL == 16 ? row_sum(dot) : wave_total(dot));
+      for (int u = 0; u < NV; ++u) {
+        double dot = 0.0;
 #pragma unroll
-      for (int t = 0; t < NE; ++t) x[t] -= dot * vk[t];
+        for (int t = 0; t < NE; ++t) dot += vk[t] * x[u][t];
+        dot = tk * (VL == 16 ? row_sum(dot) : wave_total(dot));
+#pragma unroll
+        for (int t = 0; t < NE; ++t) x[u][t] -= dot * vk[t];
+      }
     }
 #pragma unroll
-    for (int t = 0; t < NE; ++t)
-      if (t * VL + vl < n) Qt[(size_t)i * ldq + t * VL + vl] = x[t];
-  }
-  // ascending order by rank (ties broken by index), eigenvectors as columns of U
-  for (int i = tid; i < n; i += THREADS) {
-    const double di = d[i];
-    int rank = 0;
-#pragma unroll 8
-    for (int j = 0; j < n; ++j) {
-      const double dj = d[j];
-      rank += (dj < di || (dj == di && j < i)) ? 1 : 0;
-    }
-    D[rank] = di * up;
-    perm[rank] = (short)i;
+    for (int u = 0; u < NV; ++u)
+#pragma unroll
+      for (int t = 0; t < NE; ++t)
+        if (t * VL + vl < n && i + VS * u < n) Qt[(size_t)(i + VS * u) * ldq + t * VL + vl] = x[u][t];
   }
   __syncthreads();
-  for (int c = lane; c < n; c += 64) {
-    const double* q = Qt + (size_t)perm[c] * ldq;
+  // eigenvectors as columns of U, by rank
+  if constexpr (LDS) {
+    // by way of A's memory, whose reflectors are done with: vectors are read and U is written along rows.  Rows lie n apart,
+    // turned by their index where n is even, so that a column's elements lie in different banks.
+    auto at = [&](int r, int c) { const int x = c + r; return (size_t)r * n + (n & 1 ? c : (x < n ? x : x - n)); };
+    for (int i = wave; i < n; i += WAVES) {
+      const int c = list[i];
+      for (int r = lane; r < n; r += 64) A[at(r, c)] = Qt[(size_t)i * ldq + r];
+    }
+    __syncthreads();
 #pragma unroll 4
-    for (int r = wave; r < n; r += WAVES) U[(size_t)r * n + c] = q[r];
+    for (int r = wave; r < n; r += WAVES)
+      for (int c = lane; c < n; c += 64) U[(size_t)r * n + c] = A[at(r, c)];
+  } else {
+    for (int c = lane; c < n; c += 64) {
+      const double* q = Qt + (size_t)perm[c] * ldq;
+#pragma unroll 4
+      for (int r = wave; r < n; r += WAVES) U[(size_t)r * n + c] = q[r];
+    }
   }
   if (info && tid == 0) *info = bad;
 }
