@@ -49,6 +49,14 @@ __device__ __forceinline__ double lane_value(double x, int src) {
   return __hiloint2double(hi, lo);
 }
 
+// x, as a value that the compiler knows nothing about: comparisons with it are made where they stand.  (Hoisted out of the
+// panels' loop, a mask for each of 32 columns fills the scalar registers several times over.)
+template <class T>
+__device__ __forceinline__ T fresh(T x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // Panel rows in LDS: one padding element after every 32 rows of a column, so that the trailing update's
 // lanes, which read groups of four consecutive rows 32 bytes apart, spread over all banks.
 __device__ __forceinline__ int panel_pos(int lr) { return lr + (lr >> 5); }
@@ -66,12 +74,13 @@ __host__ __device__ constexpr int transform_front(int m) { return m + transform_
 // of the diagonal block's rows come from their lanes (v_readlane), so that a column is one reciprocal square root and a
 // chain of multiply-adds, without an LDS round trip or a barrier (one of each per column, and a 64-bit division and
 // square root in every thread, made a column 0.8 us).  Sequences,
-// us before and now: 16, 11.4 and 8.3; 32, 23 and 14; 64, 49 and 26; 128, 112 and 60; 256, 328 and 226; 1024, 8980 and
-// 6270 (of which launch and regulariser 6).  The upper triangle of the diagonal block is carried
-// along and never read.  The trailing matrix (rows up to and including the row of A) then takes the rank-NB update in TB x TB
-// register blocks whose factors come from the panel in LDS: 4 x 4 where the matrix is in global memory, 2 x 2 where it
-// is in LDS and 4 x 4 blocks would leave most threads without one.
-template <int kThreads, int NB, int TB>
+// us before and now: 16, 11.4 and 7.8; 32, 23 and 13; 64, 49 and 25; 128, 112 and 57; 256, 328 and 186; 1024, 8980 and
+// 5080 (of which launch and regulariser 6).  The upper triangle of the diagonal block is carried
+// along and never read.  The trailing matrix (rows up to and including the row of A) then takes the rank-NB update in
+// 16 x 16 blocks, a wave each, on the matrix cores, whose factors come from the panel in LDS: a lane reads two values for
+// sixteen multiply-adds of its own (register blocks of 4 x 4, a lane each, read eight and were bound by the LDS: 256 sequences
+// 225 us, 130 98 against 73).
+template <int kThreads, int NB>
 __device__ bool cholesky_solve(const float* __restrict__ K, const float* __restrict__ A, int m, double reg,
                                double* __restrict__ M, double* cs /* LDS [m] */, double* inv_diag /* LDS [m] */,
                                double* PT /* LDS */, int* fail /* LDS */, int* fail_col) {
@@ -111,23 +120,30 @@ __device__ bool cholesky_solve(const float* __restrict__ K, const float* __restr
       const int lr = lane < NB ? lane : base + lane;
       const bool has = lr < nrows;
       double row[NB], pivot = 1.0, inv = 0.0;
+      // (read whether wanted or not: a branch per entry costs more, and what its masks take of the scalar registers)
+      const double* const from = lane < NB ? diag + lane : PT + panel_pos(has ? lr : 0);
+      const int pitch = lane < NB ? NB + 1 : RS, wanted = has ? nbk : 0;
 #pragma unroll
       for (int q = 0; q < NB; ++q) {
-        row[q] = lane == q ? 1.0 : 0.0;
-        if (has && q < nbk) row[q] = lane < NB ? diag[q * (NB + 1) + lane] : PT[q * RS + panel_pos(lr)];
+        const double x = from[q * pitch];
+        row[q] = q < fresh(wanted) ? x : (fresh(lane) == q ? 1.0 : 0.0);
       }
 #pragma unroll
       for (int kk = 0; kk < NB; ++kk) {
-        if (lane == kk) { pivot = row[kk]; inv = rsqrt(row[kk]); }
+        if (fresh(lane) == kk) { pivot = row[kk]; inv = rsqrt(row[kk]); }
         row[kk] *= lane_value(inv, kk);                  // the entry of L; the pivot's own lane: d / sqrt(d)
 #pragma unroll
-        for (int q = kk + 1; q < NB; ++q) row[q] -= row[kk] * lane_value(row[kk], q);
-        __builtin_amdgcn_sched_barrier(0);               // entries of later columns fetched ahead would not fit the registers
+        for (int q0 = kk + 1; q0 < NB; q0 += 8) {
+          // eight entries at a time: more, fetched ahead, would not fit the scalar registers
+          const double x = fresh(row[kk]);
+#pragma unroll
+          for (int q = q0; q < q0 + 8 && q < NB; ++q) row[q] = fresh(row[q] - row[kk] * lane_value(x, q));
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
       if (has && (lane >= NB || base == 0)) {
 #pragma unroll
-        for (int q = 0; q < NB; ++q)
-          if (q < nbk) PT[q * RS + panel_pos(lr)] = row[q];
+        for (int q = 0; q < NB; ++q) PT[q * RS + panel_pos(lr)] = row[q];      // columns from nbk on: read by nobody
       }
       if (base == 0) {
         if (lane < nbk) inv_diag[k0 + lane] = inv;
@@ -141,12 +157,20 @@ __device__ bool cholesky_solve(const float* __restrict__ K, const float* __restr
       const int lr = e / NB, kk = e % NB;
       if (kk < nbk) M[(size_t)(k0 + lr) * m + k0 + kk] = PT[kk * RS + panel_pos(lr)];
     }
-    // trailing update: rows t0 .. m (the row of A included), columns t0 .. min(row, m - 1)
+    // trailing update: rows t0 .. m (the row of A included), columns t0 .. min(row, m - 1), in 16x16 blocks on and below the
+    // diagonal, row by row (nbr is nbq, or nbq + 1 where the row of A opens a block row).  Lane l supplies row l % 16, column
+    // l / 16 of a step of the left factor and the same of the right one, and holds rows 4 q + l / 16 of column l % 16.
     const int t0 = k0 + nbk;
-    const int nbr = (m + 1 - t0 + TB - 1) / TB, nbq = (m - t0 + TB - 1) / TB;
-    // the blocks on and below the diagonal, row by row (nbr is nbq, or nbq + 1 where the row of A opens a block row)
+    const int nbr = (m + 1 - t0 + 15) / 16, nbq = (m - t0 + 15) / 16;
     const int below = nbq * (nbq + 1) / 2, blocks = below + (nbr - nbq) * nbq;
-    for (int e = tid; e < blocks; e += kThreads) {
+    const int l16 = lane & 15, l4 = lane >> 4;
+    constexpr int kWaves = kThreads / kWave;
+    typedef double f64x4 __attribute__((ext_vector_type(4)));
+    f64x4 next = {0.0, 0.0, 0.0, 0.0};
+    int next_r0 = t0, next_q0 = t0;
+    // a block's entries, fetched while the one before is multiplied
+    auto fetch = [&](int e) {
+      if (e >= blocks) return;
       int br, bq;
       if (e < below) {
         br = (int)((sqrtf(8.f * (float)e + 1.f) - 1.f) * 0.5f);
@@ -157,41 +181,38 @@ __device__ bool cholesky_solve(const float* __restrict__ K, const float* __restr
         br = nbq;
         bq = e - below;
       }
-      const int r0 = t0 + TB * br, q0 = t0 + TB * bq;
-      // the block's entries are fetched together, ahead of the products (one after the other, a fetch and a store each,
-      // was most of a panel's time where the matrix is in global memory)
-      int lr[TB], lq[TB];
-      double cur[TB][TB];
+      next_r0 = t0 + 16 * br;
+      next_q0 = t0 + 16 * bq;
+      const int q = next_q0 + l16 < m ? next_q0 + l16 : m - 1;
 #pragma unroll
-      for (int i = 0; i < TB; ++i) {
-        const int r = r0 + i <= m ? r0 + i : m, q = q0 + i < m ? q0 + i : m - 1;
-        lr[i] = panel_pos(r - k0);
-        lq[i] = panel_pos(q - k0);
-#pragma unroll
-        for (int j = 0; j < TB; ++j) cur[i][j] = M[(size_t)r * m + (q0 + j < m ? q0 + j : m - 1)];
+      for (int v = 0; v < 4; ++v) {
+        const int r = next_r0 + 4 * v + l4;
+        next[v] = M[(size_t)(r <= m ? r : m) * m + q];
       }
-      auto products = [&](int kk) {
-        double a[TB], b[TB];
+    };
+    const int first_block = __builtin_amdgcn_readfirstlane(tid / kWave);
+    fetch(first_block);
+    for (int e = first_block; e < blocks; e += kWaves) {
+      f64x4 cur = next;
+      const int r0 = next_r0, q0 = next_q0;
+      fetch(e + kWaves);
+      const int lr = panel_pos((r0 + l16 <= m ? r0 + l16 : m) - k0), lq = panel_pos((q0 + l16 < m ? q0 + l16 : m - 1) - k0);
+      double a[NB / 4], b[NB / 4];
 #pragma unroll
-        for (int i = 0; i < TB; ++i) { a[i] = PT[kk * RS + lr[i]]; b[i] = PT[kk * RS + lq[i]]; }
-#pragma unroll
-        for (int i = 0; i < TB; ++i)
-#pragma unroll
-          for (int j = 0; j < TB; ++j) cur[i][j] -= a[i] * b[j];
-      };
-      if (nbk == NB) {                                   // always, but for a last panel, which has only the row of A below it
-#pragma unroll TB == 2 ? 16 : 4
-        for (int kk = 0; kk < NB; ++kk) products(kk);
-      } else {
-        for (int kk = 0; kk < nbk; ++kk) products(kk);
+      for (int step = 0; step < NB / 4; ++step) {
+        const int kk = 4 * step + l4;
+        const bool live = kk < nbk;                       // of a last panel, which has only the row of A below it
+        a[step] = live ? -PT[(live ? kk : 0) * RS + lr] : 0.0;
+        b[step] = live ? PT[(live ? kk : 0) * RS + lq] : 0.0;
       }
 #pragma unroll
-      for (int i = 0; i < TB; ++i)
+      for (int step = 0; step < NB / 4; ++step) cur = __builtin_amdgcn_mfma_f64_16x16x4f64(a[step], b[step], cur, 0, 0, 0);
+      const int q = q0 + l16;
 #pragma unroll
-        for (int j = 0; j < TB; ++j) {
-          const int r = r0 + i, q = q0 + j;
-          if (r <= m && q < m && q <= r) M[(size_t)r * m + q] = cur[i][j];
-        }
+      for (int v = 0; v < 4; ++v) {
+        const int r = r0 + 4 * v + l4;
+        if (r <= m && q < m && q <= r) M[(size_t)r * m + q] = cur[v];
+      }
     }
     __syncthreads();
   }
@@ -301,8 +322,8 @@ __global__ __launch_bounds__(kThreads) void transform_kernel(const float* __rest
       double* inv_diag = reinterpret_cast<double*>(smem);
       double* PT = inv_diag + transform_front(m);
       int fail_col = 0;
-      const bool ok = m <= kTransformWidePanelMax ? cholesky_solve<kThreads, 32, 4>(K, A, m, reg, Mg, f2s, inv_diag, PT, &fail, &fail_col)
-                                                  : cholesky_solve<kThreads, 16, 4>(K, A, m, reg, Mg, f2s, inv_diag, PT, &fail, &fail_col);
+      const bool ok = m <= kTransformWidePanelMax ? cholesky_solve<kThreads, 32>(K, A, m, reg, Mg, f2s, inv_diag, PT, &fail, &fail_col)
+                                                  : cholesky_solve<kThreads, 16>(K, A, m, reg, Mg, f2s, inv_diag, PT, &fail, &fail_col);
       for (int i = tid; i < m; i += kThreads) c[i] = ok ? (float)f2s[i] : __builtin_nanf("");
       if (info && tid == 0) info[prob] = ok ? 0 : fail_col + 1;
     } else {
@@ -310,7 +331,7 @@ __global__ __launch_bounds__(kThreads) void transform_kernel(const float* __rest
       double* inv_diag = reinterpret_cast<double*>(smem);
       double* Ml = inv_diag + transform_front(m);
       int fail_col = 0;
-      const bool ok = cholesky_solve<kThreads, 16, 2>(K, A, m, reg, Ml, f2s, inv_diag, Ml + (size_t)(m + 1) * m, &fail, &fail_col);
+      const bool ok = cholesky_solve<kThreads, 16>(K, A, m, reg, Ml, f2s, inv_diag, Ml + (size_t)(m + 1) * m, &fail, &fail_col);
       for (int i = tid; i < m; i += kThreads) c[i] = ok ? (float)f2s[i] : __builtin_nanf("");
       if (info && tid == 0) info[prob] = ok ? 0 : fail_col + 1;
     }
@@ -350,7 +371,8 @@ hipError_t launch_transform(const TransformArgs& a, hipStream_t s) {
   const bool lds = a.n_seq <= kTransformLdsMax;
   const size_t smem = a.variant == 1 ? transform_lds_bytes(a.n_seq) : 0;
   double* gws = (a.variant == 1 && !lds) ? a.workspace : nullptr;
-  // the matrix in global memory: 512 threads have the registers for panels of 32 columns (256 sequences: 229 us against 309
+  // the matrix in global memory: 512 threads have the registers for panels of 32 columns (256 sequences, with register blocks for the
+  // trailing update: 229 us against 309
   // with 1024, 328 before), 1024 the loads in flight for the larger ones (1024 sequences: 6.0 ms against 6.8 and 9.0)
   if (!lds) return a.variant == 1 && a.n_seq <= kTransformWidePanelMax ? launch_transform_t<512, true>(a, smem, gws, s)
                                                                        : launch_transform_t<1024, true>(a, smem, gws, s);
