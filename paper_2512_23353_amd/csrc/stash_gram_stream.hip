@@ -361,20 +361,54 @@ __global__ __launch_bounds__(256) void stash_gram_pair_kernel(LargeParams p) {
 // ---- 129..256 sequences in one pass ---------------------------------------------------------------
 // A 128-element slice of all 256 rows is two 32 KiB half-stages (rows 0..127 and 128..255, 256 bytes
 // per row: shorter runs per row stream noticeably slower from HBM).  LDS holds a ring of five
-// half-stages: two are multiplied while three are in flight.  The 36 upper-triangle 32x32 blocks of the
-// 8x8 block grid are dealt to the four waves by block row: wave w takes rows w and 7-w, nine blocks
-// each, and reads the row-block fragments it needs per 16-element step.  Every wave walks every step.
+// half-stages: two are multiplied while three are in flight.  Eight waves share the loads and
+// the products (four, nine products each: 1536x8960, 256 sequences 1250 us against 1225; 1000x2728, 255 258 / 244;
+// 4096x1024, 160 330 / 314).  The 36 upper-triangle 32x32 blocks of the 8x8 block grid are dealt to them four or five each
+// so that no wave needs more row blocks than it has products: it reads their fragments per 16-element step.
+// Every wave walks every step.
 // The fragments of step s + 1 are read between the MFMAs of step s (two register sets), so no MFMA
 // waits for the LDS.  A slice that is not whole (only the last one of [p0, p1) can be) takes a plain
 // masking loop after the main one.  The stash is read exactly once; partials have the large path's layout.
 constexpr int kWideHalves = 5;
+constexpr int kWideWaves = 8;
+struct WideBlocks {
+  int n, bi[5], bj[5];                               // a wave's blocks
+  constexpr bool reads(int b) const {
+    for (int q = 0; q < n; ++q)
+      if (bi[q] == b || bj[q] == b) return true;
+    return false;
+  }
+  constexpr int rows() const {
+    int r = 0;
+    for (int b = 0; b < 8; ++b) r += reads(b) ? 1 : 0;
+    return r;
+  }
+};
+constexpr WideBlocks kWide[kWideWaves] = {
+    {4, {0, 0, 0, 0, 0}, {0, 1, 2, 3, 0}}, {5, {0, 0, 0, 0, 7}, {4, 5, 6, 7, 7}},
+    {4, {1, 1, 1, 1, 0}, {1, 2, 3, 4, 0}}, {5, {1, 1, 1, 6, 6}, {5, 6, 7, 6, 7}},
+    {4, {2, 2, 2, 2, 0}, {2, 3, 4, 5, 0}}, {5, {2, 2, 5, 5, 5}, {6, 7, 5, 6, 7}},
+    {5, {3, 3, 3, 3, 3}, {3, 4, 5, 6, 7}}, {4, {4, 4, 4, 4, 0}, {4, 5, 6, 7, 0}}};
+constexpr bool wide_blocks_once() {
+  for (int i = 0; i < 8; ++i)
+    for (int j = i; j < 8; ++j) {
+      int seen = 0;
+      for (const WideBlocks& w : kWide)
+        for (int q = 0; q < w.n; ++q) seen += w.bi[q] == i && w.bj[q] == j ? 1 : 0;
+      if (seen != 1) return false;
+    }
+  return true;
+}
+static_assert(wide_blocks_once(), "every block on or above the diagonal has one wave");
 
 template <int W>
 __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_base, int lane, int wave_s,
-                                          const char* const (&src)[2][8], const int (&vec_off)[8],
+                                          const char* const (&src)[2][4], const int (&vec_off)[4],
                                           long long n_elems, long long my_first, long long my_count) {
-  constexpr int RB = 256, KW = 128, VPR = 16, LPW = 8, STEPS = 8;
-  constexpr int R0 = W, R1 = 7 - W;                  // this wave's two block rows
+  constexpr int RB = 256, KW = 128, VPR = 16, LPW = 32 / kWideWaves, STEPS = 8;
+  constexpr WideBlocks mine = kWide[W];
+  constexpr int NB = mine.n, ROWS = mine.rows();
+  static_assert(ROWS <= NB, "a read behind each of the first MFMAs");
   auto issue = [&](long long j) {                    // half-stage j = 2 * slice + half
     const long long e0 = (my_first + (j >> 1)) * KW;
     const unsigned stage = smem_base + (unsigned)(j % kWideHalves) * kStageBytes;
@@ -388,28 +422,24 @@ __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_ba
       load_lds16_nt((h ? src[1][q] : src[0][q]) + byte, stage + (unsigned)(wave_s * LPW + q) * 1024);
     }
   };
-  f32x16 acc[9];
+  f32x16 acc[NB];
 #pragma unroll
-  for (int b = 0; b < 9; ++b)
+  for (int b = 0; b < NB; ++b)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
   const int frow = lane & 31, half = lane >> 5;
-  // the nine products of one 16-element step from this wave's fragments of row blocks R0..7
+  // the products of one 16-element step
   auto multiply = [&](const v4u (&frag)[8]) {
-    int q = 0;
 #pragma unroll
-    for (int bj = R0; bj < 8; ++bj, ++q)
-      acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, frag[R0]),
-                                                       __builtin_bit_cast(bf16x8, frag[bj]), acc[q], 0, 0, 0);
-#pragma unroll
-    for (int bj = R1; bj < 8; ++bj, ++q)
-      acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, frag[R1]),
-                                                       __builtin_bit_cast(bf16x8, frag[bj]), acc[q], 0, 0, 0);
+    for (int q = 0; q < NB; ++q)
+      acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, frag[mine.bi[q]]),
+                                                       __builtin_bit_cast(bf16x8, frag[mine.bj[q]]), acc[q], 0, 0, 0);
   };
   auto read_step = [&](v4u (&frag)[8], unsigned sb0, unsigned sb1, int st) {
     const int vec = st * 2 + half;
 #pragma unroll
-    for (int b = R0; b < 8; ++b) {                   // row blocks below R0 pair with no block of this wave
+    for (int b = 0; b < 8; ++b) {
+      if (!mine.reads(b)) continue;
       const int row = (b & 3) * 32 + frow;
       frag[b] = *(lds_v4u_ptr)((b < 4 ? sb0 : sb1) + (unsigned)row * RB + (unsigned)((vec ^ (row & (VPR - 1))) * 16));
     }
@@ -437,16 +467,16 @@ __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_ba
     for (int st = 0; st < STEPS; ++st) {
       if (st + 1 < STEPS) read_step(frag[(st + 1) & 1], sb0, sb1, st + 1);
       multiply(frag[st & 1]);
-      if (st == 0) __builtin_amdgcn_sched_group_barrier(0x100, 8 - R0, 0);      // step 0's own reads first
+      if (st == 0) __builtin_amdgcn_sched_group_barrier(0x100, ROWS, 0);        // step 0's own reads first
       if (st + 1 < STEPS) {
 #pragma unroll
-        for (int r = 0; r < 8 - R0; ++r) {
+        for (int r = 0; r < ROWS; ++r) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, 9 - (8 - R0), 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, NB - ROWS, 0);
       } else {
-        __builtin_amdgcn_sched_group_barrier(0x008, 9, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
       }
     }
   }
@@ -466,29 +496,24 @@ __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_ba
       v4u frag[8];
       read_step(frag, sb0, sb1, st);
 #pragma unroll
-      for (int b = R0; b < 8; ++b)
-        if (dead) frag[b] = v4u{0u, 0u, 0u, 0u};
+      for (int b = 0; b < 8; ++b)
+        if (mine.reads(b) && dead) frag[b] = v4u{0u, 0u, 0u, 0u};
       multiply(frag);
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);
 
   float* out = p.partials + (long long)blockIdx.x * p.slot_floats;
-  int q = 0;
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int bi = pass == 0 ? R0 : R1;
+  for (int q = 0; q < NB; ++q) {
+    float* o = out + ((long long)(mine.bi[q] * 8 + mine.bj[q]) * 16) * 64 + lane;
 #pragma unroll
-    for (int bj = bi; bj < 8; ++bj, ++q) {
-      float* o = out + ((long long)(bi * 8 + bj) * 16) * 64 + lane;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) o[v * 64] = (p.first ? 0.f : o[v * 64]) + acc[q][v];
-    }
+    for (int v = 0; v < 16; ++v) o[v * 64] = (p.first ? 0.f : o[v * 64]) + acc[q][v];
   }
 }
 
-__global__ __launch_bounds__(256) void stash_gram_wide_kernel(LargeParams p) {
-  constexpr int KW = 128, VPR = 16, RPL = 4, LPW = 8;
+__global__ __launch_bounds__(64 * kWideWaves) void stash_gram_wide_kernel(LargeParams p) {
+  constexpr int KW = 128, VPR = 16, RPL = 4, LPW = 32 / kWideWaves;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const unsigned smem_base = (unsigned)(size_t)(lds_void_ptr)smem;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -517,7 +542,11 @@ __global__ __launch_bounds__(256) void stash_gram_wide_kernel(LargeParams p) {
     case 0: wide_body<0>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
     case 1: wide_body<1>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
     case 2: wide_body<2>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    default: wide_body<3>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 3: wide_body<3>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 4: wide_body<4>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 5: wide_body<5>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 6: wide_body<6>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    default: wide_body<7>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
   }
 }
 
@@ -596,7 +625,7 @@ hipError_t launch_stash_gram_large(const StashGramArgs& a, hipStream_t s) {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(stash_gram_wide_kernel),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(stash_gram_wide_kernel, dim3(gx), dim3(256), smem, s, p);
+    hipLaunchKernelGGL(stash_gram_wide_kernel, dim3(gx), dim3(64 * kWideWaves), smem, s, p);
     return hipGetLastError();
   }
   hipError_t e = launch_pair<true>(p, gx, p.nsb, s);
