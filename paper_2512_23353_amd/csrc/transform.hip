@@ -371,9 +371,8 @@ hipError_t launch_transform(const TransformArgs& a, hipStream_t s) {
   const bool lds = a.n_seq <= kTransformLdsMax;
   const size_t smem = a.variant == 1 ? transform_lds_bytes(a.n_seq) : 0;
   double* gws = (a.variant == 1 && !lds) ? a.workspace : nullptr;
-  // the matrix in global memory: 512 threads have the registers for panels of 32 columns (256 sequences, with register blocks for the
-  // trailing update: 229 us against 309
-  // with 1024, 328 before), 1024 the loads in flight for the larger ones (1024 sequences: 6.0 ms against 6.8 and 9.0)
+  // the matrix in global memory: 512 threads have the registers for panels of 32 columns (256 sequences, with register blocks
+  // for the trailing update: 229 us against 309 with 1024, 328 before), 1024 the loads in flight for the larger ones (1024 sequences: 6.0 ms against 6.8 and 9.0)
   if (!lds) return a.variant == 1 && a.n_seq <= kTransformWidePanelMax ? launch_transform_t<512, true>(a, smem, gws, s)
                                                                        : launch_transform_t<1024, true>(a, smem, gws, s);
   // more threads for the larger problems' trailing updates
