@@ -400,19 +400,33 @@ constexpr bool wide_blocks_once() {
   return true;
 }
 static_assert(wide_blocks_once(), "every block on or above the diagonal has one wave");
+// Row blocks that hold no sequence are neither loaded nor multiplied: a slice of 256 rows takes as long whether they are read
+// from memory or are all the last one again.  4096x1024, 160 sequences 314 -> 243 us; 512x3072, 130 127 -> 104; 2048x4096, 192
+// 726 -> 593 (with four waves before); 2048x3072, 224 582 -> 511.
+constexpr WideBlocks wide_blocks(int wave, int row_blocks) {
+  WideBlocks w{0, {0, 0, 0, 0, 0}, {0, 0, 0, 0, 0}};
+  for (int q = 0; q < kWide[wave].n; ++q)
+    if (kWide[wave].bj[q] < row_blocks) {
+      w.bi[w.n] = kWide[wave].bi[q];
+      w.bj[w.n] = kWide[wave].bj[q];
+      ++w.n;
+    }
+  return w;
+}
 
-template <int W>
+template <int W, int RBLOCKS>
 __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_base, int lane, int wave_s,
                                           const char* const (&src)[2][4], const int (&vec_off)[4],
                                           long long n_elems, long long my_first, long long my_count) {
   constexpr int RB = 256, KW = 128, VPR = 16, LPW = 32 / kWideWaves, STEPS = 8;
-  constexpr WideBlocks mine = kWide[W];
+  constexpr WideBlocks mine = wide_blocks(W, RBLOCKS);
   constexpr int NB = mine.n, ROWS = mine.rows();
-  static_assert(ROWS <= NB, "a read behind each of the first MFMAs");
+  constexpr bool LOADS1 = 4 + W / 2 < RBLOCKS;       // a wave's loads of the second half are of half a row block
   auto issue = [&](long long j) {                    // half-stage j = 2 * slice + half
     const long long e0 = (my_first + (j >> 1)) * KW;
     const unsigned stage = smem_base + (unsigned)(j % kWideHalves) * kStageBytes;
     const int h = (int)(j & 1);
+    if (h && !LOADS1) return;                        // the waits below count the first half's loads only
 #pragma unroll
     for (int q = 0; q < LPW; ++q) {
       long long byte = e0 * 2 + vec_off[q];
@@ -422,7 +436,7 @@ __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_ba
       load_lds16_nt((h ? src[1][q] : src[0][q]) + byte, stage + (unsigned)(wave_s * LPW + q) * 1024);
     }
   };
-  f32x16 acc[NB];
+  f32x16 acc[NB > 0 ? NB : 1];
 #pragma unroll
   for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -471,10 +485,10 @@ __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_ba
       if (st + 1 < STEPS) {
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          if (r < NB) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, NB - ROWS, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, NB > ROWS ? NB - ROWS : 0, 0);
       } else {
         __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
       }
@@ -512,6 +526,7 @@ __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_ba
   }
 }
 
+template <int RBLOCKS>
 __global__ __launch_bounds__(64 * kWideWaves) void stash_gram_wide_kernel(LargeParams p) {
   constexpr int KW = 128, VPR = 16, RPL = 4, LPW = 32 / kWideWaves;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -539,14 +554,14 @@ __global__ __launch_bounds__(64 * kWideWaves) void stash_gram_wide_kernel(LargeP
   }
   // every wave runs the same loop (same barriers), specialised on its block rows
   switch (wave_s) {
-    case 0: wide_body<0>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 1: wide_body<1>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 2: wide_body<2>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 3: wide_body<3>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 4: wide_body<4>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 5: wide_body<5>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 6: wide_body<6>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    default: wide_body<7>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 0: wide_body<0, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 1: wide_body<1, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 2: wide_body<2, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 3: wide_body<3, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 4: wide_body<4, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 5: wide_body<5, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 6: wide_body<6, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    default: wide_body<7, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
   }
 }
 
@@ -574,6 +589,17 @@ __global__ __launch_bounds__(1024) void stash_gram_large_finish_kernel(const flo
     K[(size_t)i * n_seq + j] = s;
     K[(size_t)j * n_seq + i] = s;
   }
+}
+
+template <int RBLOCKS>
+hipError_t launch_wide(const LargeParams& p, int gx, hipStream_t s) {
+  constexpr size_t smem = (size_t)kWideHalves * kStageBytes;          // 160 KiB: the whole LDS of a CU
+  // once per process (static initialisation is thread-safe); a failure is returned by every call
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(stash_gram_wide_kernel<RBLOCKS>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(stash_gram_wide_kernel<RBLOCKS>, dim3(gx), dim3(64 * kWideWaves), smem, s, p);
+  return hipGetLastError();
 }
 
 template <bool DIAG>
@@ -619,15 +645,10 @@ hipError_t launch_stash_gram_large(const StashGramArgs& a, hipStream_t s) {
   p.nsb = (a.n_seq + 127) / 128; p.nbp = 4 * p.nsb;
   p.slot_floats = (long long)stash_gram_large_slot_floats(a.n_seq);
   const int gx = stash_gram_large_slots(a.n_seq);
-  if (a.n_seq <= 256) {
-    constexpr size_t smem = (size_t)kWideHalves * kStageBytes;          // 160 KiB: the whole LDS of a CU
-    // once per process (static initialisation is thread-safe); a failure is returned by every call
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(stash_gram_wide_kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(stash_gram_wide_kernel, dim3(gx), dim3(64 * kWideWaves), smem, s, p);
-    return hipGetLastError();
-  }
+  if (a.n_seq <= 160) return launch_wide<5>(p, gx, s);
+  if (a.n_seq <= 192) return launch_wide<6>(p, gx, s);
+  if (a.n_seq <= 224) return launch_wide<7>(p, gx, s);
+  if (a.n_seq <= 256) return launch_wide<8>(p, gx, s);
   hipError_t e = launch_pair<true>(p, gx, p.nsb, s);
   if (e != hipSuccess) return e;
   return launch_pair<false>(p, gx, p.nsb * (p.nsb - 1) / 2, s);
