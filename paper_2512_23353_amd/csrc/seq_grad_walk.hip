@@ -268,7 +268,9 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p) {
   {
     // lane (l, g4): token rows 8 g4 + l / 4 (+ 4 for the second read), features 4 (l % 4) ..+3 of the
     // fragment's 16; the transposing read leaves lane l with tokens 8 g4 ..+7 of feature l.  PAIRED: fragments 2q and 2q + 1
-    // take features 8 (l % 4) ..+3 and +4 ..+7 of their 32.
+    // take features 8 (l % 4) ..+3 and +4 ..+7 of their 32, for l % 4 = 2 and 3 the other way round: the swizzle puts rows 8 apart
+    // into the same four 16-byte columns, two apart, so that they meet in opposite halves.  (In the same halves every read
+    // took three cycles of the LDS where it takes two.)
     const int l = lane & 15, g4 = lane >> 4;
     const int kr = 8 * g4 + (l >> 2);
     const int f = swz(kr);
@@ -279,7 +281,7 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p) {
     }
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
-      const int cb = wn * WN + (PAIRED ? (j >> 1) * 32 + 8 * (l & 3) + 4 * (j & 1) : j * 16 + 4 * (l & 3));
+      const int cb = wn * WN + (PAIRED ? (j >> 1) * 32 + 8 * (l & 3) + 4 * ((j ^ (l >> 1)) & 1) : j * 16 + 4 * (l & 3));
       adB[j] = smem_base + HALF + (unsigned)kr * P + (unsigned)(((cb >> 3) ^ f) << 4) + (unsigned)((cb & 7) * 2);
     }
   }
@@ -494,11 +496,11 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p) {
         if constexpr (SEQ) {
 #pragma unroll
           for (int j = 0; j < FN / 2; ++j) {
-            u32x4 pk;
-            pk[0] = pack_bf16(rd(acc[i][2 * j][0]), rd(acc[i][2 * j][1]));
-            pk[1] = pack_bf16(rd(acc[i][2 * j][2]), rd(acc[i][2 * j][3]));
-            pk[2] = pack_bf16(rd(acc[i][2 * j + 1][0]), rd(acc[i][2 * j + 1][1]));
-            pk[3] = pack_bf16(rd(acc[i][2 * j + 1][2]), rd(acc[i][2 * j + 1][3]));
+            const unsigned p0 = pack_bf16(rd(acc[i][2 * j][0]), rd(acc[i][2 * j][1]));
+            const unsigned p1 = pack_bf16(rd(acc[i][2 * j][2]), rd(acc[i][2 * j][3]));
+            const unsigned p2 = pack_bf16(rd(acc[i][2 * j + 1][0]), rd(acc[i][2 * j + 1][1]));
+            const unsigned p3 = pack_bf16(rd(acc[i][2 * j + 1][2]), rd(acc[i][2 * j + 1][3]));
+            const u32x4 pk = lane < 32 ? u32x4{p0, p1, p2, p3} : u32x4{p2, p3, p0, p1};
             // Half a line, of a row that starts anywhere in a line.  Left to the L2 the halves meet there; stored
             // non-temporally each goes to memory by itself: 2216x632, 83 sequences of 41 tokens: 57 us against 158;
             // 3256x2560, 28 of 346: 291 against 367; 568x1104, 79 of 213: 46 against 64.  Widths whose rows start at lines
