@@ -4,6 +4,9 @@
 // tested without a GPU.
 #include "kernels.h"
 
+#include <algorithm>
+#include <functional>
+
 namespace isopo {
 
 // Row-major per-sequence launches whose widths are no multiples of 256 (others may keep the stash in tile order, whose
@@ -28,6 +31,25 @@ static bool small_tiles_win(int rows, int d_in, int n_tokens, int n_seq) {
 
 static ContractionPlan plan_with_tile(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host, bool per_sequence,
                                       bool big);
+
+// What a (sequence, tile) pair costs besides its tokens, in tokens, where the list is cut into ranges of equal work.
+constexpr int kPairTokens = 192;
+
+// The item-major list of (item, tile) pairs cut into eight contiguous ranges of equal work, weight(i) per pair of item i: range x
+// opens at the first pair that starts at or beyond x eighths of the total.
+template <class Weight>
+static void cut_pairs(long long tiles, int n_items, Weight&& weight, int* first) {
+  long long total = 0, cum = 0;
+  for (int i = 0; i < n_items; ++i) total += weight(i) * tiles;
+  int i = 0;
+  first[0] = 0;
+  for (int x = 1; x < 8; ++x) {
+    const long long target = (x * total + 7) / 8;
+    while (i < n_items && cum + tiles * weight(i) <= target) cum += tiles * weight(i++);
+    first[x] = (int)(i == n_items ? tiles * n_items : i * tiles + (target - cum + weight(i) - 1) / weight(i));
+  }
+  first[8] = (int)(tiles * n_items);
+}
 
 ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
                                  bool per_sequence, bool weighted, bool budget) {
@@ -122,31 +144,142 @@ static ContractionPlan plan_with_tile(int rows, int d_in, int n_tokens, int n_se
   // cut into eight contiguous ranges of equal work.
   if (mapped && (!per_sequence || tiles % 8 != 0) && tiles * n_items <= 0x7fffffffLL) {
     // Work of item i: its tokens plus a fixed charge for the workgroup's prologue and epilogue.
-    const long long fixed = per_sequence ? 192 : 64;
     auto weight = [&](int i) -> long long {
-      if (per_sequence) return (off_host ? (long long)(off_host[i + 1] - off_host[i]) : 1024) + fixed;
+      if (per_sequence) return (off_host ? off_host[i + 1] - off_host[i] : 1024) + kPairTokens;
       const long long t0 = (long long)i * pl.chunk_tokens;
       const long long t1 = t0 + pl.chunk_tokens < n_tokens ? t0 + pl.chunk_tokens : n_tokens;
-      return (t1 - t0) + fixed;
+      return (t1 - t0) + 64;
     };
-    long long total = 0;
-    for (int i = 0; i < n_items; ++i) total += weight(i) * tiles;
-    // pair (i, t) starts at work cum_i + t*w_i; XCD x's range opens at the first pair starting at or
-    // beyond x/8 of the total
-    long long cum = 0;
-    int i = 0, most = 0;
-    for (int x = 1; x < 8; ++x) {
-      const long long target = (x * total + 7) / 8;
-      while (i < n_items && cum + tiles * weight(i) <= target) cum += tiles * weight(i++);
-      if (i == n_items) { pl.xcd_start[x] = (int)(tiles * n_items); continue; }
-      const long long w = weight(i);
-      pl.xcd_start[x] = (int)(i * tiles + (target - cum + w - 1) / w);
-    }
-    pl.xcd_start[8] = (int)(tiles * n_items);
+    cut_pairs(tiles, n_items, weight, pl.xcd_start);
+    int most = 0;
     for (int k = 0; k < 8; ++k) most = pl.xcd_start[k + 1] - pl.xcd_start[k] > most ? pl.xcd_start[k + 1] - pl.xcd_start[k] : most;
     pl.blocks = 8LL * most;
   }
   return pl;
+}
+
+// The per-sequence launch's walk.  Where every pair of 128x128 tiles has a workgroup at once, a workgroup takes one pair of the list
+// as it comes, cut into an equal-work range per XCD.  Else as many workgroups as are resident share the list, longest sequences
+// first, in the one of two arrangements with the smaller modelled time:
+//   dealt   every sequence's tiles over all XCDs: the more even one, and every XCD reads every sequence
+//   ranges  an equal-work range of the list per XCD: few XCDs read a sequence, and those with the long ones may have an uneven
+//           number of pairs per workgroup
+// t, the longest walk, and u, the bytes, overlap for the most part: max(t, u) + 0.6 min(t, u).  A walk is `block` per 32 tokens and,
+// for what is not hidden of a pair's first operands and of its stores, `around` blocks per pair; operands arrive at 8 TB/s, the
+// stash leaves at 4.5.  The operands are counted up to 24 tiles of 256x256, 40 of 128x128 (of more, neighbouring tiles on an XCD
+// share what it reads); another arrangement than dealt (than ranges, of up to 40 128x128 tiles) has to win by a margin.
+// Of 400 random layers, 1 to 512 sequences of 0 to 16384 tokens, against always dealt: 256x256 tiles 0.96x on average (1 slower by
+// more than 5 %), 128x128 tiles 0.91x (5).  768x384, 28 sequences of 0 to 4460 tokens: 59.7 -> 47.9 us; 288x216, 267 of 1470: 225 ->
+// 132; 768x1024, 400 of 4 to 8192: 521 -> 323; 1536x1536, one of 8000 and 31 of 100: 169 -> 154; 2048x2048, the same on a budget of 128
+// workgroups: 209 -> 146.
+WalkPlan plan_walk(int tile, int rows, int d_in, int n_seq, const int32_t* off_host, int max_workgroups, unsigned short* order) {
+  constexpr int kXcds = 8;
+  constexpr double kMargin = 1.05;
+  WalkPlan plan{};
+  const bool big = tile == 256;
+  const int tiles_m = (rows + tile - 1) / tile, tiles_n = (d_in + tile - 1) / tile, tiles = tiles_m * tiles_n, rest = tiles % kXcds;
+  const long long pairs = (long long)tiles * n_seq;
+  const int resident = max_workgroups > 0 ? max_workgroups / kXcds : (big ? 32 : 64);
+  auto length = [&](int i) { return off_host ? off_host[i + 1] - off_host[i] : 1024; };
+  auto most_of = [&](const int* first) {
+    int most = 0;
+    for (int x = 0; x < kXcds; ++x) most = std::max(most, first[x + 1] - first[x]);
+    return most;
+  };
+  if (!big && pairs <= kXcds * resident) {
+    plan.one_each = plan.ranges = 1;
+    cut_pairs(tiles, n_seq, [&](int i) { return length(i) + kPairTokens; }, plan.first);
+    plan.per_xcd = most_of(plan.first);
+    return plan;
+  }
+
+  unsigned long long keys[1024];                                    // longest first, then as they come
+  for (int i = 0; i < n_seq; ++i) keys[i] = (unsigned long long)length(i) << 10 | (unsigned)(1023 - i);
+  std::sort(keys, keys + n_seq, std::greater<unsigned long long>());
+  for (int k = 0; k < n_seq; ++k) order[k] = (unsigned short)(1023 - (int)(keys[k] & 1023));
+  plan.sorted = 1;
+  const double around = big ? 4.0 : 3.0, block = big ? 0.6e-6 : 0.35e-6;
+  double weight[1024], total = 0.0;
+  long long tokens = 0;
+  for (int k = 0; k < n_seq; ++k) {
+    const int len = length(order[k]);
+    tokens += len;
+    weight[k] = (len > 32 ? (len + 31) / 32 : 1) + around;
+    total += tiles * weight[k];
+  }
+  int first[kXcds + 1], alone[2][kXcds] = {};
+  cut_pairs(tiles, n_seq, [&](int k) { return length(order[k]) + kPairTokens; }, first);
+  const int of_dealt = (int)std::min<long long>((pairs + kXcds - 1) / kXcds, resident), of_ranges = std::min(most_of(first), resident);
+  const double even = total / (kXcds * resident);
+  double t_dealt = even, t_ranges = even;
+  // The longest walk over W workgroups of the pairs that run(k, count) is called for, `count` of sequence k.  Those of the first
+  // sequences that outlast the rest's even share stay alone.
+  auto share_out = [&](auto&& runs, int W, int& ones) {
+    double left = 0.0, longest = 0.0, load[64] = {};
+    runs([&](int k, int count) { left += weight[k] * count; return true; });
+    ones = 0;
+    runs([&](int k, int count) {
+      if (ones + count >= W || weight[k] * (W - ones) < left) return false;
+      ones += count;
+      left -= weight[k] * count;
+      return true;
+    });
+    const int n = W - ones;
+    int skip = ones, at = 0, step = 1;
+    runs([&](int k, int count) {
+      if (skip > 0) {
+        longest = std::max(longest, weight[k]);
+        skip -= count;
+        return true;
+      }
+      for (int c = 0; c < count; ++c) {                             // to and fro, as PairWalk goes
+        load[at] += weight[k];
+        if (at + step < 0 || at + step == n) step = -step; else at += step;
+      }
+      return true;
+    });
+    return std::max(longest, *std::max_element(load, load + n));
+  };
+  if (weight[0] > even / 16.0) {                                    // else shares are even in either arrangement
+    for (int x = 0; x < kXcds; ++x) {
+      const double walk = share_out([&](auto&& run) {
+        for (int id = first[x]; id < first[x + 1];) {
+          const int k = id / tiles, upto = std::min((k + 1) * tiles, first[x + 1]);
+          if (!run(k, upto - id)) break;
+          id = upto;
+        }
+      }, of_ranges, alone[1][x]);
+      t_ranges = std::max(t_ranges, walk);
+    }
+    auto share = [&](int x, int k) { return tiles / kXcds + (((x - k * rest) & 7) < rest ? 1 : 0); };
+    int ones = 0;
+    t_dealt = share_out([&](auto&& run) {                           // XCD 0; the others have the same but for odd tiles
+      for (int k = 0; k < n_seq; ++k)
+        if (!run(k, share(0, k))) break;
+    }, of_dealt, ones);
+    for (int x = 0; x < kXcds; ++x)
+      for (int k = 0, at = 0; at < ones && k < n_seq; at += share(0, k), ++k)
+        if (alone[0][x] + share(x, k) < of_dealt) alone[0][x] += share(x, k);
+  }
+  // operands: panels of a tile's width, a sequence's whole on one XCD, or on every XCD those of its eighth of the tiles
+  const int whole = tiles_m + tiles_n, strip = tiles_n < 8 ? tiles_n : 8, eighth = (tiles + 7) / 8;
+  int dealt = 2 * tiles;
+  if (tiles > kXcds) dealt = kXcds * (std::min(eighth, strip) + (eighth + strip - 1) / strip);
+  dealt = std::min(std::max(dealt, whole), kXcds * whole);
+  const bool counted = tiles <= (big ? 24 : 40);
+  const double panel = counted ? (double)tokens * tile * 2.0 / 8.0e12 : 0.0;
+  auto time = [&](double walk, int panels) {
+    const double t = walk * block, u = panels * panel + (double)n_seq * rows * d_in * 2.0 / 4.5e12;
+    return std::max(t, u) + 0.6 * std::min(t, u);
+  };
+  t_dealt = time(t_dealt, dealt);
+  t_ranges = time(t_ranges, whole);
+  (counted && !big ? t_ranges : t_dealt) /= kMargin;
+  plan.ranges = t_ranges < t_dealt;
+  plan.per_xcd = plan.ranges ? of_ranges : of_dealt;
+  std::copy(alone[plan.ranges], alone[plan.ranges] + kXcds, plan.alone);
+  if (plan.ranges) std::copy(first, first + kXcds + 1, plan.first);
+  return plan;
 }
 
 // The fp32 contraction's launch: tile side, groups of four waves per tile, and for the sum over all tokens the number of

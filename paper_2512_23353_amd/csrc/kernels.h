@@ -51,11 +51,22 @@ struct ContractionPlan {
                                // (one workgroup each, all tokens); the chunks apply to the tiles after them
   int xcd_start[9];            // a split sum's XCD x walks (chunk, tile) pairs [xcd_start[x], xcd_start[x+1]) of the
                                // chunk-major list.  Per-sequence mode: such a cut of the (sequence, tile) list, or all
-                               // zero; the launch has its own lists (seq_grad_walk.hip)
+                               // zero; the launch has a plan of its own (WalkPlan)
   long long blocks;            // workgroups of a launch with one per pair
 };
 ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,
                                  bool per_sequence, bool weighted = false, bool budget = false);
+// How a per-sequence launch's workgroups walk the list of (sequence, tile) pairs (host arithmetic only; the walk itself:
+// PairWalk in seq_grad_walk.hip).
+struct WalkPlan {
+  int per_xcd;                 // workgroups of an XCD
+  int one_each;                // as many workgroups as pairs; else as many as are resident at a time (or the caller's budget)
+  int ranges, first[9];        // XCD x takes pairs [first[x], first[x + 1]) of the list; else every sequence's tiles are dealt
+  int alone[8];                // the first pairs of XCD x's list whose workgroups take no other
+  int sorted;                  // the list is in the plan's order of sequences, longest first; else in theirs
+};
+// max_workgroups: the caller's budget, 8 or more (256x256 tiles only); 0: none.  order: of n_seq sequences, where `sorted`
+WalkPlan plan_walk(int tile, int rows, int d_in, int n_seq, const int32_t* off_host, int max_workgroups, unsigned short* order);
 hipError_t launch_seq_grad(const SeqGradArgs& a, hipStream_t s);
 // Launch plan of the fp32 contraction (host arithmetic only).
 struct SplitContractionPlan {

@@ -4,6 +4,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "pair_walk.h"
 
 namespace isopo {
 
@@ -39,17 +40,6 @@ __device__ __forceinline__ float acc_read(float a) {
   float v;
   asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
   return v;
-}
-
-// Division of a tile index by a number the host knows: floor(n / d) is floor(n * mul / 2^32) or one more, mul = floor(2^32 / d).
-struct TileDiv {
-  unsigned d, mul;
-};
-inline TileDiv tile_div_by(unsigned d) { return {d, d > 1 ? (unsigned)((1ull << 32) / d) : 0xffffffffu}; }
-__device__ __forceinline__ int tile_div(int n, TileDiv v) {
-  unsigned q = __umulhi((unsigned)n, v.mul);
-  if ((unsigned)n - q * v.d >= v.d) ++q;
-  return (int)q;
 }
 
 // Column-blocked tile order: ids run down 8-column strips of the tile grid, so the 32 workgroups an

@@ -92,3 +92,22 @@ def bf16_plan(d_in, d_out, lengths, per_sequence, weighted=False, budget=False):
     return fn(ctypes.c_int(d_out), ctypes.c_int(d_in), ctypes.c_int(int(off[-1])), ctypes.c_int(len(lengths)),
               off.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), ctypes.c_bool(per_sequence), ctypes.c_bool(weighted),
               ctypes.c_bool(budget))
+
+
+class WalkPlan(ctypes.Structure):
+    _fields_ = [("per_xcd", ctypes.c_int), ("one_each", ctypes.c_int), ("ranges", ctypes.c_int), ("first", ctypes.c_int * 9),
+                ("alone", ctypes.c_int * 8), ("sorted", ctypes.c_int)]
+
+
+def walk_plan(d_in, d_out, lengths, budget=0):
+    """How the workgroups of a per-sequence bf16 launch share its (sequence, tile) pairs, and the order of the sequences."""
+    from paper_2512_23353_amd import isopo
+    fn = isopo.load()._ZN5isopo9plan_walkEiiiiPKiiPt
+    fn.restype = WalkPlan
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    order = np.zeros(len(lengths), dtype=np.uint16)
+    tile = bf16_plan(d_in, d_out, lengths, True, budget=budget > 0).tile
+    plan = fn(ctypes.c_int(tile), ctypes.c_int(d_out), ctypes.c_int(d_in), ctypes.c_int(len(lengths)),
+              off.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), ctypes.c_int(budget if tile == 256 else 0),
+              order.ctypes.data_as(ctypes.POINTER(ctypes.c_uint16)))
+    return plan, order

@@ -7,7 +7,7 @@ import torch
 from paper_2512_23353_amd import isopo
 from paper_2512_23353_amd import workloads as wl
 
-from helpers import bf16_plan, to_device
+from helpers import bf16_plan, to_device, walk_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -92,3 +92,28 @@ def test_uncut_sums_of_one_round(gpu_device, lens, beta, weighted):
     M = abs(beta) * start.double().abs() + D.abs().T.contiguous() @ X.abs()
     # as above
     assert ((got.double() - G).abs() <= (sum(lens) + 3 * len(lens) + 3) * 2.0 ** -23 * M).all()
+
+
+@pytest.mark.parametrize("d_in,d_out,lens,budget,kind", [
+    (1000, 2728, [8000] + [100] * 31, 0, "alone"), (1000, 2728, [100] * 20 + [8000] + [31] * 11, 128, "alone"),
+    (520, 1288, [20] * 399 + [9000], 0, "alone"),                    # more sequences than a byte counts
+    (768, 264, [2230, 0, 4000, 33] * 7, 0, "single"), (264, 264, [1, 0, 40], 0, "single"),
+    (768, 1024, [900] + [300, 0, 1, 33] * 99, 0, "ranges"), (768, 392, [2230, 0, 4000, 33] * 7, 0, "alone"),
+    (512, 512, [3000] + [60, 0] * 60, 0, "alone"),
+])
+def test_arrangements(gpu_device, d_in, d_out, lens, budget, kind):
+    """Launches whose pairs are dealt out in other ways: long pairs whose workgroups take no other, a workgroup per pair, ranges of
+    the list; in either layout, and twice in a row into the same stash."""
+    plan, _ = walk_plan(d_in, d_out, lens, budget)
+    assert kind == ("single" if plan.one_each else "alone" if any(plan.alone) else "ranges" if plan.ranges else "dealt")
+    layer = _layer(d_in, d_out, lens, gpu_device)
+    layout = isopo.stash_layout(layer)[0]
+    queue = torch.zeros(8, dtype=torch.int32, device=gpu_device)
+    S = torch.full((len(lens), d_out, d_in), float("nan"), dtype=torch.bfloat16, device=gpu_device)
+    for _ in range(2):
+        S.fill_(float("nan"))
+        _check_stash(layer, isopo.seq_grads(layer, S, max_workgroups=budget, queue=queue if budget else None), lens)
+    if layout == isopo.STASH_TILE_ORDER:
+        tiled = isopo.seq_grads(layer, torch.full_like(S, float("nan")), layout=layout)
+        c = torch.randn(len(lens), generator=torch.Generator().manual_seed(1)).to(gpu_device)
+        assert torch.equal(isopo.weighted_grad(layer, c, S), isopo.weighted_grad(layer, c, tiled, layout=layout))
