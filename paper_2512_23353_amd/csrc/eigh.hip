@@ -339,8 +339,11 @@ __device__ __forceinline__ void tridiagonalise(double* A, int lda, int n, double
   __syncthreads();
 }
 
+// Four waves per vector unit: with the 144 registers that 512 threads would be given a compute unit holds one workgroup, and a batch of
+// more problems than units takes two rounds (300 of 16 / 32 sequences 82 / 134 us against 51 / 87).  1024 threads have 128 either way,
+// of which 16 .. 28 bytes a lane go to scratch.
 template <int THREADS, int MAXN, bool LDS, bool QLDS>
-__global__ __launch_bounds__(THREADS) void divide_eigh_kernel(const float* __restrict__ Kb, int m,
+__global__ __launch_bounds__(THREADS, 4) void divide_eigh_kernel(const float* __restrict__ Kb, int m,
                                                               double* __restrict__ Db, double* __restrict__ Ub,
                                                               int32_t* __restrict__ infob, double* __restrict__ wsb,
                                                               size_t ws_stride, int root_steps) {
