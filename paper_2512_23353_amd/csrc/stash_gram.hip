@@ -233,16 +233,18 @@ hipError_t launch_stash_gram_finish(const float* partials, bool bf16, int slots,
   return hipGetLastError();
 }
 
-// Vectors per thread.  Four (and non-temporal stores) over stashes of 2 GiB and up: 4096x14336, 32 sequences 751 -> 632 us (6.3
-// TB/s); 1536x8960, 256 1229 -> 1070; 5120x13824, 16 496 -> 455; below they lose (3584x5120, 48: 323 / 340; 2048x3072, 128: 296 / 345).
-// Two where the chip's compute units then get like numbers of workgroups, the fullest no more than an eighth above the mean:
-// 4096x1024, 32 sequences 54.5 -> 45.5 us; 1024x2048, 64 52.6 -> 45.2; 2048x4096, 16 55.1 -> 48.8; 3000x5000, 40 222 -> 207; fp32
-// 2048x4096, 8 50.6 -> 46.3; where they do not, half as many workgroups are worse (768x3072, 100: 84 / 92; 1000x2728, 24: 23.6 / 24.8;
-// 2984x560, 101: 63 / 114).
-static int sum_vectors_per_thread(long long n_vec, int n_seq) {
-  if (n_vec * n_seq >= (2LL << 30) / 16 && n_vec >= 3 << 19) return 4;
+// Vectors per thread.  Four (and non-temporal stores) over stashes of 2 GiB and up of wide sequences: in tile order 4096x14336, 32
+// sequences 751 -> 632 us (6.3 TB/s), 1536x8960, 256 1229 -> 1070, 5120x13824, 16 496 -> 455; of 13 random ones of n_vec from 1.5 M on
+// 12 were level or gained (0.86 .. 1.02 of one vector; 2.1 M, 65 sequences 1.05), narrower ones lose to two.  Row by row only fp32
+// from 3 M (4.2 M, 90 sequences 1039 -> 893): eleven below and in bf16 took 0.99 .. 1.21 of one vector's time where two take 0.90 .. 0.98.
+// Two from four workgroups per compute unit on: 4096x1024, 32 sequences 54.5 -> 45.5 us; 2048x4096, 16 55.1 -> 48.8; of 90 random ones
+// 0.79 .. 1.06 of one vector's time.  Below that row by row they lose, whatever the remainder (2.7 .. 3.6 per unit 1.03 .. 1.38, fewer up
+// to four times the time: 2816x1024, 32 31 / 42 us; 460x3328 fp32, 53 50 / 61); in tile order they gain (0.87 .. 0.95, 1024x2048, 64
+// 52.6 -> 45.2) where the units get like numbers of workgroups, the fullest no more than an eighth above the mean, else not (0.99 .. 1.11).
+static int sum_vectors_per_thread(long long n_vec, int n_seq, bool bf16, bool tiled) {
+  if (n_vec * n_seq >= (2LL << 30) / 16 && (tiled ? n_vec >= 3 << 19 : !bf16 && n_vec >= 3 << 20)) return 4;
   const long long blocks = (n_vec + 2 * kSumThreads - 1) / (2 * kSumThreads), fullest = (blocks + 255) / 256;
-  return blocks >= 512 && fullest * 256 * 8 <= blocks * 9 ? 2 : 1;
+  return blocks >= 1024 || (tiled && blocks >= 512 && fullest * 256 * 8 <= blocks * 9) ? 2 : 1;
 }
 
 static unsigned sum_blocks(long long n_vec, int vpt) {
@@ -254,7 +256,7 @@ static unsigned sum_blocks(long long n_vec, int vpt) {
 template <bool BF16, bool OUTB>
 static hipError_t launch_rows_t(const void* stash, long long seq_stride, long long n_vec, int n_seq, const float* c, float beta,
                                 void* dW, hipStream_t s) {
-  const int vpt = sum_vectors_per_thread(n_vec, n_seq);
+  const int vpt = sum_vectors_per_thread(n_vec, n_seq, BF16, false);
   auto kern = vpt == 4   ? stash_weighted_sum_kernel<BF16, OUTB, 4>
               : vpt == 2 ? stash_weighted_sum_kernel<BF16, OUTB, 2>
                          : stash_weighted_sum_kernel<BF16, OUTB, 1>;
@@ -275,7 +277,7 @@ hipError_t launch_stash_weighted_sum(const void* stash, bool bf16, long long seq
 template <int T, bool OUTB>
 static hipError_t launch_tiled_t(const void* stash, long long D, long long n_vec, int n_seq, const float* c, float beta,
                                  void* dW, int d_in, hipStream_t s) {
-  const int vpt = sum_vectors_per_thread(n_vec, n_seq);
+  const int vpt = sum_vectors_per_thread(n_vec, n_seq, true, true);
   auto kern = vpt == 4   ? stash_weighted_sum_tiled_kernel<T, OUTB, 4>
               : vpt == 2 ? stash_weighted_sum_tiled_kernel<T, OUTB, 2>
                          : stash_weighted_sum_tiled_kernel<T, OUTB, 1>;

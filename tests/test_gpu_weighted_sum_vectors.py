@@ -22,6 +22,10 @@ pytestmark = pytest.mark.gpu
     ("bf16", 4096, 4096, 64),       # 2 GiB: four vectors
     ("bf16", 4096, 4096, 63),
     ("bf16", 3000, 5000, 73),       # row-major past 2 GiB, a ragged end
+    ("bf16", 1000, 4192, 6),        # row-major, 1024 workgroups of two vectors
+    ("bf16", 1000, 4184, 6),        # 1022: too few
+    ("f32", 4096, 3076, 43),        # 2 GiB of wide fp32 sequences: four, a ragged end
+    ("f32", 4096, 3068, 43),        # narrower: two
 ])
 @pytest.mark.parametrize("beta", [0.0, -0.5])
 def test_weighted_sum_of_stash(gpu_device, dtype, d_in, d_out, m, beta):
