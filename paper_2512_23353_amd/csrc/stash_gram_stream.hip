@@ -414,7 +414,7 @@ constexpr WideBlocks wide_blocks(int wave, int row_blocks) {
   return w;
 }
 
-template <int W, int RBLOCKS>
+template <int W, int RBLOCKS, bool ONCE>
 __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_base, int lane, int wave_s,
                                           const char* const (&src)[2][4], const int (&vec_off)[4],
                                           long long n_elems, long long my_first, long long my_count) {
@@ -433,7 +433,9 @@ __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_ba
       const long long last = (n_elems - 8) * 2;
       if (byte > last) byte = last;
       if ((j >> 1) >= my_count) byte = 0;
-      load_lds16_nt((h ? src[1][q] : src[0][q]) + byte, stage + (unsigned)(wave_s * LPW + q) * 1024);
+      const char* const from = (h ? src[1][q] : src[0][q]) + byte;
+      if constexpr (ONCE) load_lds16_nt(from, stage + (unsigned)(wave_s * LPW + q) * 1024);
+      else load_lds16(from, stage + (unsigned)(wave_s * LPW + q) * 1024);
     }
   };
   f32x16 acc[NB > 0 ? NB : 1];
@@ -526,7 +528,7 @@ __device__ __forceinline__ void wide_body(const LargeParams& p, unsigned smem_ba
   }
 }
 
-template <int RBLOCKS>
+template <int RBLOCKS, bool ONCE>
 __global__ __launch_bounds__(64 * kWideWaves) void stash_gram_wide_kernel(LargeParams p) {
   constexpr int KW = 128, VPR = 16, RPL = 4, LPW = 32 / kWideWaves;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -554,14 +556,14 @@ __global__ __launch_bounds__(64 * kWideWaves) void stash_gram_wide_kernel(LargeP
   }
   // every wave runs the same loop (same barriers), specialised on its block rows
   switch (wave_s) {
-    case 0: wide_body<0, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 1: wide_body<1, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 2: wide_body<2, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 3: wide_body<3, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 4: wide_body<4, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 5: wide_body<5, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    case 6: wide_body<6, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
-    default: wide_body<7, RBLOCKS>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 0: wide_body<0, RBLOCKS, ONCE>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 1: wide_body<1, RBLOCKS, ONCE>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 2: wide_body<2, RBLOCKS, ONCE>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 3: wide_body<3, RBLOCKS, ONCE>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 4: wide_body<4, RBLOCKS, ONCE>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 5: wide_body<5, RBLOCKS, ONCE>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    case 6: wide_body<6, RBLOCKS, ONCE>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
+    default: wide_body<7, RBLOCKS, ONCE>(p, smem_base, lane, wave_s, src, vec_off, n_elems, my_first, my_count); break;
   }
 }
 
@@ -591,16 +593,28 @@ __global__ __launch_bounds__(1024) void stash_gram_large_finish_kernel(const flo
   }
 }
 
-template <int RBLOCKS>
-hipError_t launch_wide(const LargeParams& p, int gx, hipStream_t s) {
+template <int RBLOCKS, bool ONCE>
+hipError_t launch_wide_t(const LargeParams& p, int gx, hipStream_t s) {
   constexpr size_t smem = (size_t)kWideHalves * kStageBytes;          // 160 KiB: the whole LDS of a CU
   // once per process (static initialisation is thread-safe); a failure is returned by every call
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(stash_gram_wide_kernel<RBLOCKS>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(stash_gram_wide_kernel<RBLOCKS, ONCE>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(stash_gram_wide_kernel<RBLOCKS>, dim3(gx), dim3(64 * kWideWaves), smem, s, p);
+  hipLaunchKernelGGL((stash_gram_wide_kernel<RBLOCKS, ONCE>), dim3(gx), dim3(64 * kWideWaves), smem, s, p);
   return hipGetLastError();
 }
+template <int RBLOCKS>
+hipError_t launch_wide(const LargeParams& p, int gx, bool once, hipStream_t s) {
+  return once ? launch_wide_t<RBLOCKS, true>(p, gx, s) : launch_wide_t<RBLOCKS, false>(p, gx, s);
+}
+
+// What the last-level cache holds (256 MiB) is left in it for the weighted sum that follows, and is there from the contraction
+// before; larger stashes are read non-temporally.  Whole calls, non-temporal / default: 1000x2728 bf16, 24 sequences (131 MB) 136.6
+// / 130.7 us, 40 (218 MB) 160.9 / 150.0, 80 (436 MB) 305.8 / 324.2; 4096x1024 bf16, 32 (268 MB) 181.0 / 179.4, 48 (403 MB) 271.4 /
+// 275.4; of 39 random stashes of 16 to 250 MB 0.86 .. 1.00 with the default.  129 to 256 sequences: 824x72, 199 (24 MB) 58.9 / 52.4;
+// 640x1208, 135 (209 MB) 130.9 / 122.9; 1600x408, 204 (266 MB) 262.8 / 263.1; 416x2152, 219 (392 MB) 232.1 / 247.6; 368x5200, 132
+// (505 MB) 288 / 322.
+bool read_once(long long elems, int n_seq, bool bf16) { return elems * n_seq * (bf16 ? 2 : 4) > 256LL << 20; }
 
 template <bool DIAG>
 hipError_t launch_pair(const LargeParams& p, int gx, int n_pairs, hipStream_t s) {
@@ -645,10 +659,11 @@ hipError_t launch_stash_gram_large(const StashGramArgs& a, hipStream_t s) {
   p.nsb = (a.n_seq + 127) / 128; p.nbp = 4 * p.nsb;
   p.slot_floats = (long long)stash_gram_large_slot_floats(a.n_seq);
   const int gx = stash_gram_large_slots(a.n_seq);
-  if (a.n_seq <= 160) return launch_wide<5>(p, gx, s);
-  if (a.n_seq <= 192) return launch_wide<6>(p, gx, s);
-  if (a.n_seq <= 224) return launch_wide<7>(p, gx, s);
-  if (a.n_seq <= 256) return launch_wide<8>(p, gx, s);
+  const bool once = read_once(a.p1 - a.p0, a.n_seq, true);
+  if (a.n_seq <= 160) return launch_wide<5>(p, gx, once, s);
+  if (a.n_seq <= 192) return launch_wide<6>(p, gx, once, s);
+  if (a.n_seq <= 224) return launch_wide<7>(p, gx, once, s);
+  if (a.n_seq <= 256) return launch_wide<8>(p, gx, once, s);
   hipError_t e = launch_pair<true>(p, gx, p.nsb, s);
   if (e != hipSuccess) return e;
   return launch_pair<false>(p, gx, p.nsb * (p.nsb - 1) / 2, s);
@@ -666,10 +681,7 @@ hipError_t launch_stash_gram_stream(const StashGramArgs& a, hipStream_t s) {
   p.stash = a.stash; p.seq_stride = a.seq_stride; p.p0 = a.p0; p.p1 = a.p1;
   p.n_seq = a.n_seq; p.first = a.first ? 1 : 0; p.partials = a.partials;
   p.slot_floats = (long long)stash_gram_slot_floats(a.n_seq, a.bf16);
-  // What the last-level cache holds (256 MiB) is left in it for the weighted sum that follows, and is there from the
-  // contraction before.  Whole calls, non-temporal / default: 1000x2728 bf16, 24 sequences (131 MB) 136.6 / 130.7 us, 40 (218 MB)
-  // 160.9 / 150.0, 80 (436 MB) 305.8 / 324.2; 4096x1024 bf16, 32 (268 MB) 181.0 / 179.4, 48 (403 MB) 271.4 / 275.4.
-  const bool once = (a.p1 - a.p0) * a.n_seq * (a.bf16 ? 2 : 4) > 256LL << 20;
+  const bool once = read_once(a.p1 - a.p0, a.n_seq, a.bf16);
   if (a.bf16) return once ? launch_bf16<true>(p, a.slots, s) : launch_bf16<false>(p, a.slots, s);
   return once ? launch_f32<true>(p, a.slots, s) : launch_f32<false>(p, a.slots, s);
 }
