@@ -96,8 +96,9 @@ typedef struct {
  * wants.  Pure host function.
  *   *chosen       the path taken (never AUTO)
  *   *ws_full      bytes that hold the whole stash [n_seq, d_out, d_in] (needed for keep_stash)
- *   *ws_min       the smallest workspace the call accepts (the stash is then
- *                 formed and consumed in chunks of output rows)
+ *   *ws_min       the smallest workspace the chosen path accepts (the stash is then
+ *                 formed and consumed in chunks of output rows).  With AUTO, an fp32 layer and no stash to keep, a
+ *                 smaller workspace that holds GHOST's is accepted too: that path is then taken
  * Any out pointer may be NULL. */
 isopo_status isopo_layer_gram_plan(const isopo_layer* layer, isopo_gram_path requested,
                                    isopo_gram_path* chosen, size_t* ws_full, size_t* ws_min);

@@ -619,9 +619,11 @@ def layer_step(layer: Layer, A: torch.Tensor, variant="interacting", lam: float 
                workspace: Optional[torch.Tensor] = None, stream=None) -> dict:
     """The three calls chained on one stream with no host synchronisation.  The returned workspace holds
     the stash in layout `stash_layout` (None: no stash was kept)."""
-    chosen, full, _ = gram_plan(layer, path)
+    chosen, full, least = gram_plan(layer, path)
     if workspace is None:
         workspace = alloc_workspace(full, layer.device)
+    if path == "auto" and workspace.numel() < least:
+        chosen = "ghost"                # what isopo_layer_gram then takes, or it raises
     stream = _stream(stream)
     keep = chosen == "materialised" and workspace.numel() >= full
     K, workspace = layer_gram(layer, path, workspace=workspace, keep_stash=KEEP_FAST if keep else 0, stream=stream)
