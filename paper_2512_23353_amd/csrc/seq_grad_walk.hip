@@ -445,6 +445,14 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p_) {
       for (; b < blocks; ++b) token_block(c0, c0, 0.f);
     }
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");         // the last MFMAs have retired
+    // The compiler sees no MFMA in asm, and the wait above does not hold back instructions on registers alone: where ordinary ones
+    // read the accumulators they get them from here.  (AGPRs are read by volatile asm; the builtin's results it waits for itself.)
+    if constexpr (!AGPR && !WTD) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) asm volatile("" : "+v"(acc[i][j]));
+    }
 
     // ---- epilogue: lane l holds, of block (i, j), rows 4 (l / 16) ..+3 of column l % 16 (SWAP: the transpose).  Nothing is
     // waited for: the next pair's operands are on their way, and as many stores go out on every way through here.
