@@ -3,6 +3,7 @@
 // (item, tile) pairs each of the eight XCDs walks.  Pure host arithmetic, no HIP calls, so that it can be
 // tested without a GPU.
 #include "kernels.h"
+#include "pair_walk.h"
 
 #include <algorithm>
 #include <functional>
@@ -187,7 +188,7 @@ WalkPlan plan_walk(int tile, int rows, int d_in, int n_seq, const int32_t* off_h
     return most;
   };
   if (!big && pairs <= kXcds * resident) {
-    plan.one_each = plan.ranges = 1;
+    plan.kind = kSingle;
     cut_pairs(tiles, n_seq, [&](int i) { return length(i) + kPairTokens; }, plan.first);
     plan.per_xcd = most_of(plan.first);
     return plan;
@@ -197,7 +198,6 @@ WalkPlan plan_walk(int tile, int rows, int d_in, int n_seq, const int32_t* off_h
   for (int i = 0; i < n_seq; ++i) keys[i] = (unsigned long long)length(i) << 10 | (unsigned)(1023 - i);
   std::sort(keys, keys + n_seq, std::greater<unsigned long long>());
   for (int k = 0; k < n_seq; ++k) order[k] = (unsigned short)(1023 - (int)(keys[k] & 1023));
-  plan.sorted = 1;
   const double around = big ? 4.0 : 3.0, block = big ? 0.6e-6 : 0.35e-6;
   double weight[1024], total = 0.0;
   long long tokens = 0;
@@ -275,10 +275,11 @@ WalkPlan plan_walk(int tile, int rows, int d_in, int n_seq, const int32_t* off_h
   t_dealt = time(t_dealt, dealt);
   t_ranges = time(t_ranges, whole);
   (counted && !big ? t_ranges : t_dealt) /= kMargin;
-  plan.ranges = t_ranges < t_dealt;
-  plan.per_xcd = plan.ranges ? of_ranges : of_dealt;
-  std::copy(alone[plan.ranges], alone[plan.ranges] + kXcds, plan.alone);
-  if (plan.ranges) std::copy(first, first + kXcds + 1, plan.first);
+  const bool ranges = t_ranges < t_dealt;
+  plan.kind = ranges ? kRanges : kDealt;
+  plan.per_xcd = ranges ? of_ranges : of_dealt;
+  std::copy(alone[ranges], alone[ranges] + kXcds, plan.alone);
+  if (ranges) std::copy(first, first + kXcds + 1, plan.first);
   return plan;
 }
 

@@ -60,12 +60,12 @@ ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, co
 // PairWalk in seq_grad_walk.hip).
 struct WalkPlan {
   int per_xcd;                 // workgroups of an XCD
-  int one_each;                // as many workgroups as pairs; else as many as are resident at a time (or the caller's budget)
-  int ranges, first[9];        // XCD x takes pairs [first[x], first[x + 1]) of the list; else every sequence's tiles are dealt
+  int kind;                    // WalkKind; but for `single` as many workgroups as are resident at a time (or the caller's budget)
+  int first[9];                // ranges and single: XCD x takes pairs [first[x], first[x + 1]) of the list
   int alone[8];                // the first pairs of XCD x's list whose workgroups take no other
-  int sorted;                  // the list is in the plan's order of sequences, longest first; else in theirs
 };
-// max_workgroups: the caller's budget, 8 or more (256x256 tiles only); 0: none.  order: of n_seq sequences, where `sorted`
+// max_workgroups: the caller's budget, 8 or more (256x256 tiles only); 0: none.  order: of the n_seq sequences in the list, longest
+// first (single: untouched, they come in their own)
 WalkPlan plan_walk(int tile, int rows, int d_in, int n_seq, const int32_t* off_host, int max_workgroups, unsigned short* order);
 hipError_t launch_seq_grad(const SeqGradArgs& a, hipStream_t s);
 // Launch plan of the fp32 contraction (host arithmetic only).

@@ -48,22 +48,22 @@ struct WalkParams {
   TileGrid grid;
   TileDiv by_tiles;                      // of the grid
   int per_xcd;                           // workgroups
-  int ranges;                            // per-sequence launch: see PairWalk
-  struct { int first, end, alone, unused; } xcd[8];
-  int sorted;                            // ... sequences in the order below, else as they come
-  int one_each;                          // ... as many workgroups as pairs
+  struct { int first, end, alone, unused; } xcd[8];                   // per-sequence launch: see PairWalk
   unsigned* queue;                       // a caller's scratch, cleared
-  unsigned short order[1024];            // longest first
+};
+struct OrderedWalkParams : WalkParams {
+  unsigned short order[1024];            // of the sequences in the list, longest first
 };
 
 // T: side of the output tile.  NW: waves per workgroup, a 2 x NW/2 arrangement of wave tiles; four on the per-sequence launch
 // (on the 256x256 tile one wave per SIMD with its 256 accumulators per lane pinned to the AGPRs), eight on the sums (two waves
 // per SIMD, 128 accumulators per lane in VGPRs), as in seq_grad_stream.hip.
-template <int T, int KIND, bool TILED, int NW>
-__device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p_) {
+template <int T, int KIND, int WALK, bool TILED, int NW, class Params>
+__device__ __forceinline__ void seq_grad_walk_body(const Params& p_) {
   static_assert(KIND == kSeq || !TILED, "tile order is a layout of the per-sequence stash");
   static_assert(NW == 4 || NW == 8, "waves per workgroup");
   constexpr bool SEQ = KIND == kSeq, WTD = KIND == kWeighted;
+  constexpr bool TABLE = SEQ && WALK != kSingle;               // a workgroup of one pair reads its sequence's offsets itself
   // The transposed products (rows of X's features, columns of Delta's): a lane then holds runs of a row of the result and
   // stores 16 bytes at a time, a row-major bf16 tile without a trip through LDS, an fp32 tile in a quarter of the stores.  Tile
   // order is defined by the plain ones.
@@ -99,8 +99,7 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p_) {
     asm volatile("" : "+s"(p.grid.m), "+s"(p.grid.n), "+s"(p.grid.strip.d), "+s"(p.grid.strip.mul), "+s"(p.grid.last.d),
                       "+s"(p.grid.last.mul));
   if constexpr (SEQ)
-    asm volatile("" : "+s"(p.by_tiles.d), "+s"(p.by_tiles.mul), "+s"(p.ranges), "+s"(first), "+s"(end), "+s"(alone),
-                      "+s"(p.sorted), "+s"(p.one_each));
+    asm volatile("" : "+s"(p.by_tiles.d), "+s"(p.by_tiles.mul), "+s"(first), "+s"(end), "+s"(alone));
 
   // ---- the ranges of tokens: the sequences in the order they are walked in, or the segments of the weighted sum ----
   // Weighted sum: the tokens are walked segment by segment (a segment: a sequence that has tokens and a non-zero
@@ -109,20 +108,19 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p_) {
   // where a new segment opens the accumulators are multiplied once by c_previous / c_new.  The epilogue multiplies by the last
   // segment's coefficient.  No operand is scaled or rounded.
   constexpr int kMaxSeq = 1024;            // the library's limit on sequences per layer
-  __shared__ int sh_tok[KIND == kSum ? 1 : kMaxSeq], sh_len[KIND == kSum ? 1 : kMaxSeq];
+  __shared__ int sh_tok[TABLE || WTD ? kMaxSeq : 1], sh_len[TABLE || WTD ? kMaxSeq : 1];
   __shared__ float sh_ratio[WTD ? kMaxSeq : 1];
-  __shared__ short sh_seq[SEQ ? kMaxSeq : 1];
+  __shared__ short sh_seq[TABLE ? kMaxSeq : 1];
   __shared__ int sh_count;
   __shared__ float sh_last_c;
   [[maybe_unused]] int n_seg = 0;
   [[maybe_unused]] float last_c = 0.f;
-  const bool table = SEQ && !p.one_each;                       // a workgroup of one pair reads its sequence's offsets itself
   [[maybe_unused]] auto offset = [&](int k) {
     return ((const __attribute__((address_space(4))) int32_t*)p.off)[uniform(k)];
   };
-  if (SEQ && table) {
+  if constexpr (TABLE) {
     for (int k = tid; k < p.n_seq; k += NT) {
-      const int s = p.sorted ? p_.order[k] : k, o = p.off[s];
+      const int s = p_.order[k], o = p.off[s];
       sh_tok[k] = o;
       sh_len[k] = p.off[s + 1] - o;
       sh_seq[k] = (short)s;
@@ -175,8 +173,8 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p_) {
   // two 64-bit additions; all else is behind one branch, taken where a block is the last of its range or the range is through.
   const unsigned rbA = (unsigned)p.d_out * 2u, rbB = (unsigned)p.d_in * 2u;
   const int tiles = p.grid.m * p.grid.n;
-  PairWalk<SEQ> ahead((int)blockIdx.x, p.per_xcd, tiles, SEQ ? p.n_seq : 1, p.by_tiles, SEQ ? p.ranges : 0, first, end, alone);    // of the loads
-  PairWalk<SEQ> walk = ahead;                                                                         // of the products
+  PairWalk<WALK> ahead((int)blockIdx.x, p.per_xcd, tiles, SEQ ? p.n_seq : 1, p.by_tiles, first, end, alone);   // of the loads
+  PairWalk<WALK> walk = ahead;                                 // of the products
   v4i da, db;
   int cut_a = 0, cut_b = 0;                                    // bytes of a row ahead of the panels
   int rem = 0;                                                 // rows left of the range at the cursor
@@ -215,7 +213,7 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p_) {
       const int k = SEQ ? ahead.i : 0;
       if constexpr (KIND == kSum) {
         range_open(0, p.n_tokens);
-      } else if (SEQ && !table) {
+      } else if constexpr (SEQ && !TABLE) {
         const int o = offset(k);
         range_open(o, offset(k + 1) - o);
       } else {
@@ -435,7 +433,10 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p_) {
         r_in = r_out;
       }
     } else {
-      const int blocks = blocks_of(!SEQ ? p.n_tokens : (table ? uniform(sh_len[walk.i]) : offset(walk.i + 1) - offset(walk.i)));
+      int tokens = p.n_tokens;
+      if constexpr (TABLE) tokens = uniform(sh_len[walk.i]);
+      else if constexpr (SEQ) tokens = offset(walk.i + 1) - offset(walk.i);
+      const int blocks = blocks_of(tokens);
       token_block(c1, c0, 0.f);
       int b = 1;
       for (; b + 1 < blocks; b += 2) {
@@ -456,7 +457,8 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p_) {
 
     // ---- epilogue: lane l holds, of block (i, j), rows 4 (l / 16) ..+3 of column l % 16 (SWAP: the transpose).  Nothing is
     // waited for: the next pair's operands are on their way, and as many stores go out on every way through here.
-    if constexpr (SEQ) seq = table ? uniform(sh_seq[walk.i]) : walk.i;
+    if constexpr (TABLE) seq = uniform(sh_seq[walk.i]);
+    else if constexpr (SEQ) seq = walk.i;
     int tile_m, tile_n;
     tile_coords(walk.tile(), p.grid, tile_m, tile_n);
     tile_m = uniform(tile_m);
@@ -543,44 +545,22 @@ __device__ __forceinline__ void seq_grad_walk_body(const WalkParams& p_) {
   __builtin_amdgcn_s_waitcnt(0x0f70);                          // loads into the LDS of a workgroup that is gone
 }
 
-template <int T, int OCC, int KIND, bool TILED>
-__global__ __launch_bounds__(256, OCC) void seq_grad_walk_kernel(WalkParams p) {
-  seq_grad_walk_body<T, KIND, TILED, 4>(p);
+template <int T, int OCC, int WALK, bool TILED, class Params>
+__global__ __launch_bounds__(256, OCC) void seq_grad_walk_kernel(Params p) {
+  seq_grad_walk_body<T, kSeq, WALK, TILED, 4>(p);
 }
 
 template <int T, int OCC, int KIND>
 __global__ __launch_bounds__(512, OCC) void seq_grad_walk_waves8_kernel(WalkParams p) {
-  seq_grad_walk_body<T, KIND, false, 8>(p);
+  seq_grad_walk_body<T, KIND, kDealt, false, 8>(p);
 }
 
-template <int T, int OCC, int KIND, bool TILED, int NW>
-hipError_t launch_walk(const SeqGradArgs& a, const ContractionPlan& pl, hipStream_t s) {
-  constexpr bool SEQ = KIND == kSeq;
-  const long long tiles = (long long)pl.tiles_m * pl.tiles_n, pairs = SEQ ? tiles * a.n_seq : tiles;
-  if (pairs <= 0) return hipSuccess;
-  if (pairs > 0x3fffffffLL) return hipErrorInvalidValue;
-  WalkParams p;
-  p.X = static_cast<const u16*>(a.X); p.Delta = static_cast<const u16*>(a.Delta); p.off = a.off; p.c = a.c; p.out = a.out;
-  p.d_in = a.d_in; p.d_out = a.d_out; p.n_seq = a.n_seq; p.n_tokens = a.n_tokens;
-  p.row0 = a.row0; p.row_end = a.row0 + a.rows; p.out_row0 = a.out_row0;
-  p.out_seq_stride = a.out_seq_stride; p.beta = a.beta;
-  p.grid = tile_grid(pl.tiles_m, pl.tiles_n);
-  p.by_tiles = tile_div_by((unsigned)tiles);
-  p.queue = SEQ && T == 256 && a.max_workgroups > 0 ? a.queue : nullptr;
-  p.ranges = p.sorted = p.one_each = 0;
-  p.per_xcd = (int)std::min<long long>((pairs + 7) / 8, 32 * OCC);
-  if constexpr (SEQ) {
-    const WalkPlan w = plan_walk(T, a.rows, a.d_in, a.n_seq, a.off_host, T == 256 ? a.max_workgroups : 0, p.order);
-    p.per_xcd = w.per_xcd;
-    p.ranges = w.ranges;
-    p.sorted = w.sorted;
-    p.one_each = w.one_each;
-    for (int x = 0; x < 8; ++x) p.xcd[x] = {w.first[x], w.first[x + 1], w.alone[x], 0};
-  }
+template <int T, int OCC, int KIND, int WALK, bool TILED, int NW, class Params>
+hipError_t launch_walk(const Params& p, hipStream_t s) {
   constexpr size_t smem = (size_t)NSTAGE * BK * T * 2 * 2;
   auto kern = [] {
     if constexpr (NW == 8) return &seq_grad_walk_waves8_kernel<T, OCC, KIND>;
-    else return &seq_grad_walk_kernel<T, OCC, KIND, TILED>;
+    else return &seq_grad_walk_kernel<T, OCC, WALK, TILED, Params>;
   }();
   // once per process (static initialisation is thread-safe); a failure is returned by every call
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -588,6 +568,45 @@ hipError_t launch_walk(const SeqGradArgs& a, const ContractionPlan& pl, hipStrea
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL(kern, dim3(8u * (unsigned)p.per_xcd), dim3(64 * NW), smem, s, p);
   return hipGetLastError();
+}
+
+// False: nothing to do, or (status) too much of it.
+bool fill_params(const SeqGradArgs& a, const ContractionPlan& pl, WalkParams& p, hipError_t& status) {
+  const long long tiles = (long long)pl.tiles_m * pl.tiles_n, pairs = tiles * (a.per_sequence ? a.n_seq : 1);
+  status = pairs > 0x3fffffffLL ? hipErrorInvalidValue : hipSuccess;
+  if (pairs <= 0 || status != hipSuccess) return false;
+  p.X = static_cast<const u16*>(a.X); p.Delta = static_cast<const u16*>(a.Delta); p.off = a.off; p.c = a.c; p.out = a.out;
+  p.d_in = a.d_in; p.d_out = a.d_out; p.n_seq = a.n_seq; p.n_tokens = a.n_tokens;
+  p.row0 = a.row0; p.row_end = a.row0 + a.rows; p.out_row0 = a.out_row0;
+  p.out_seq_stride = a.out_seq_stride; p.beta = a.beta;
+  p.grid = tile_grid(pl.tiles_m, pl.tiles_n);
+  p.by_tiles = tile_div_by((unsigned)tiles);
+  p.queue = nullptr;
+  return true;
+}
+
+template <int KIND>
+hipError_t launch_sum(const SeqGradArgs& a, const ContractionPlan& pl, hipStream_t s) {
+  WalkParams p;
+  hipError_t status;
+  if (!fill_params(a, pl, p, status)) return status;
+  p.per_xcd = std::min((pl.tiles_m * pl.tiles_n + 7) / 8, 32);
+  return launch_walk<256, 1, KIND, kDealt, false, 8>(p, s);
+}
+
+template <int T, int OCC, bool TILED>
+hipError_t launch_sequences(const SeqGradArgs& a, const ContractionPlan& pl, hipStream_t s) {
+  OrderedWalkParams p;
+  hipError_t status;
+  if (!fill_params(a, pl, p, status)) return status;
+  const int budget = T == 256 ? a.max_workgroups : 0;
+  const WalkPlan w = plan_walk(T, a.rows, a.d_in, a.n_seq, a.off_host, budget, p.order);
+  p.per_xcd = w.per_xcd;
+  if (budget > 0) p.queue = a.queue;
+  for (int x = 0; x < 8; ++x) p.xcd[x] = {w.first[x], w.first[x + 1], w.alone[x], 0};
+  if constexpr (T == 128)
+    if (w.kind == kSingle) return launch_walk<T, OCC, kSeq, kSingle, TILED, 4>(static_cast<const WalkParams&>(p), s);
+  return w.kind == kRanges ? launch_walk<T, OCC, kSeq, kRanges, TILED, 4>(p, s) : launch_walk<T, OCC, kSeq, kDealt, TILED, 4>(p, s);
 }
 
 }  // namespace
@@ -598,12 +617,12 @@ hipError_t launch_seq_grad_walk(const SeqGradArgs& a, const ContractionPlan& pl,
     if (a.tile_order) {
       // the caller has checked stash_tile_order_ok; anything else would scatter the stores
       if (a.rows % pl.tile || a.d_in % pl.tile || a.row0 % pl.tile || a.out_row0 % pl.tile) return hipErrorInvalidValue;
-      return big ? launch_walk<256, 1, kSeq, true, 4>(a, pl, s) : launch_walk<128, 2, kSeq, true, 4>(a, pl, s);
+      return big ? launch_sequences<256, 1, true>(a, pl, s) : launch_sequences<128, 2, true>(a, pl, s);
     }
-    return big ? launch_walk<256, 1, kSeq, false, 4>(a, pl, s) : launch_walk<128, 2, kSeq, false, 4>(a, pl, s);
+    return big ? launch_sequences<256, 1, false>(a, pl, s) : launch_sequences<128, 2, false>(a, pl, s);
   }
   if (!big || pl.n_chunks > 1) return hipErrorInvalidValue;
-  return a.c != nullptr ? launch_walk<256, 1, kWeighted, false, 8>(a, pl, s) : launch_walk<256, 1, kSum, false, 8>(a, pl, s);
+  return a.c != nullptr ? launch_sum<kWeighted>(a, pl, s) : launch_sum<kSum>(a, pl, s);
 }
 
 }  // namespace isopo

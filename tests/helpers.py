@@ -95,8 +95,7 @@ def bf16_plan(d_in, d_out, lengths, per_sequence, weighted=False, budget=False):
 
 
 class WalkPlan(ctypes.Structure):
-    _fields_ = [("per_xcd", ctypes.c_int), ("one_each", ctypes.c_int), ("ranges", ctypes.c_int), ("first", ctypes.c_int * 9),
-                ("alone", ctypes.c_int * 8), ("sorted", ctypes.c_int)]
+    _fields_ = [("per_xcd", ctypes.c_int), ("kind", ctypes.c_int), ("first", ctypes.c_int * 9), ("alone", ctypes.c_int * 8)]
 
 
 def walk_plan(d_in, d_out, lengths, budget=0):

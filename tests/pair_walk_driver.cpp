@@ -28,31 +28,37 @@ static void walk(int tile, int rows, int d_in, const std::vector<int>& len, int 
   const int n = (int)len.size(), tiles = ((rows + tile - 1) / tile) * ((d_in + tile - 1) / tile);
   std::vector<unsigned short> order((size_t)n);
   const WalkPlan p = plan_walk(tile, rows, d_in, n, off.data(), budget, order.data());
-  ++seen_plans[p.one_each ? 2 : (p.ranges ? 1 : 0)];
+  ++seen_plans[p.kind];
   const long long pairs = (long long)tiles * n;
   EXPECT(p.per_xcd >= 1 && p.per_xcd <= pairs);
   const int resident = budget ? budget / 8 : (tile == 256 ? 32 : 64);
-  EXPECT(p.one_each ? budget == 0 : p.per_xcd <= resident);
-  std::vector<char> seen(p.sorted ? n : 0, 0), met((size_t)pairs, 0);
-  for (int k = 0; p.sorted && k < n; ++k) {
+  EXPECT(p.kind == kSingle ? tile == 128 && pairs <= 512 : p.per_xcd <= resident);
+  std::vector<char> seen((size_t)n, 0), met((size_t)pairs, 0);
+  for (int k = 0; p.kind != kSingle && k < n; ++k) {
     EXPECT(order[k] < n && !seen[order[k]]);
     seen[order[k]] = 1;
     EXPECT(k == 0 || len[order[k - 1]] >= len[order[k]]);
   }
-  for (int b = 0; b < 8 * p.per_xcd; ++b) {
+  // one workgroup's list: how long it is, -1 where it meets a pair that is none or that was met
+  auto list = [&](auto w) {
     int count = 0;
-    const int first = p.ranges ? p.first[b & 7] : 0;
-    for (PairWalk<true> w(b, p.per_xcd, tiles, n, tile_div_by((unsigned)tiles), p.ranges, first, p.first[(b & 7) + 1],
-                          p.alone[b & 7]); w.more(); w.next()) {
-      EXPECT(w.i >= 0 && w.tile() >= 0 && w.tile() < tiles);
-      const size_t id = (size_t)w.i * tiles + w.tile();
-      EXPECT(!met[id]);
-      met[id] = 1;
-      ++count;
+    for (; w.more(); w.next(), ++count) {
+      if (w.i < 0 || w.tile() < 0 || w.tile() >= tiles) return -1;
+      char& m = met[(size_t)w.i * tiles + w.tile()];
+      if (m) return -1;
+      m = 1;
     }
-    EXPECT(p.alone[b & 7] >= 0 && p.alone[b & 7] < (p.one_each ? 1 : p.per_xcd));
-    EXPECT((!p.one_each && b >> 3 >= p.alone[b & 7]) || count <= 1);
-    seen_alone += !p.one_each && b >> 3 < p.alone[b & 7];
+    return count;
+  };
+  for (int b = 0; b < 8 * p.per_xcd; ++b) {
+    const int x = b & 7, first = p.first[x], end = p.first[x + 1], alone = p.alone[x];
+    const TileDiv by = tile_div_by((unsigned)tiles);
+    const int count = p.kind == kDealt    ? list(PairWalk<kDealt>(b, p.per_xcd, tiles, n, by, first, end, alone))
+                      : p.kind == kRanges ? list(PairWalk<kRanges>(b, p.per_xcd, tiles, n, by, first, end, alone))
+                                          : list(PairWalk<kSingle>(b, p.per_xcd, tiles, n, by, first, end, alone));
+    EXPECT(count >= 0 && alone >= 0 && alone < (p.kind == kSingle ? 1 : p.per_xcd));
+    EXPECT((p.kind != kSingle && b >> 3 >= alone) || count <= 1);
+    seen_alone += b >> 3 < alone;
   }
   for (char m : met) EXPECT(m);
 }

@@ -105,7 +105,7 @@ def test_arrangements(gpu_device, d_in, d_out, lens, budget, kind):
     """Launches whose pairs are dealt out in other ways: long pairs whose workgroups take no other, a workgroup per pair, ranges of
     the list; in either layout, and twice in a row into the same stash."""
     plan, _ = walk_plan(d_in, d_out, lens, budget)
-    assert kind == ("single" if plan.one_each else "alone" if any(plan.alone) else "ranges" if plan.ranges else "dealt")
+    assert kind == ("alone" if any(plan.alone) else ("dealt", "ranges", "single")[plan.kind])
     layer = _layer(d_in, d_out, lens, gpu_device)
     layout = isopo.stash_layout(layer)[0]
     queue = torch.zeros(8, dtype=torch.int32, device=gpu_device)
