@@ -686,7 +686,7 @@ def main() -> int:
                                              "projection at the 8 TB/s HBM peak, over this run's REINFORCE time; the write "
                                              "(issued under the MFMA-bound contraction) and everything else counted as free",
                       "what": "this library's own unweighted dW = Delta^T X over the same projections (advantages folded into Delta, as plain REINFORCE backprop does)", **context},
-        "roofline": {"bound": "mfma", "kernel": "seq_grad_stream_kernel<256,256,4,1,true,true,true,false> (per-sequence gradients -> stash in tile order, persistent launch)",
+        "roofline": {"bound": "mfma", "kernel": "seq_grad_walk_kernel (per-sequence gradients -> stash in tile order, 256x256 tiles, a list of pairs per workgroup)",
                      "achieved": achieved / 1e12, "peak": PEAK_BF16_MFMA / 1e12, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_BF16_MFMA, "avg_launch_ms": avg_launch_s * 1e3,
                      "whole_step_frac": total_flops / t_step / PEAK_BF16_MFMA,

@@ -119,18 +119,17 @@ isopo_status isopo_gram_cost_model(const isopo_layer* layer, double* t_ghost, do
  *                      tiles (a multiple of 256, the full rounds of one tile per compute unit) are not
  *                      split; the chunks apply to the tiles of the last, partial round only.  0: the
  *                      split, if any, applies to every tile
- *   xcd_start[9]       the item-major list of (item, tile) pairs is cut into 8 contiguous ranges of equal
- *                      work, XCD x walks [xcd_start[x], xcd_start[x+1]).  All zero: no list - per-sequence
- *                      mode with tiles % 8 == 0 gives XCD x the x-th eighth of every sequence's tiles,
- *                      the unsplit unweighted mode has one item
+ *   xcd_start[9]       the item-major list of (item, tile) pairs cut into 8 contiguous ranges of equal
+ *                      work, XCD x's [xcd_start[x], xcd_start[x+1]).  All zero: no list - per-sequence
+ *                      mode with tiles % 8 == 0, where the x-th eighth of every sequence's tiles is as even,
+ *                      and the unsplit unweighted mode, which has one item
  *   workgroups         grid size of a launch with one workgroup per pair (some workgroups may find their XCD's
- *                      range exhausted and exit).  Both hold for a sum cut into chunks.  The per-sequence launches, and
- *                      uncut sums, run at most 256 workgroups (512 with the 128 tile; or the
- *                      budget of isopo_seq_grads_limited), each with a list of pairs of its own: every sequence's tiles
- *                      are dealt evenly to the XCDs, the longest sequences' first, and there the fields describe one
- *                      equal-work cut of the pairs that no launch follows.  isopo_seq_grads_limited also takes the 256
- *                      tile on layers large enough for it whose widths are no multiples of 256 and for which 128 is
- *                      reported here */
+ *                      range exhausted and exit)
+ * Both are what a sum cut into chunks is launched with.  An uncut sum, and per-sequence gradients but for the smallest
+ * launches on the 128 tile, run at most 256 workgroups (512 with the 128 tile; or the budget of
+ * isopo_seq_grads_limited), each with a list of pairs of its own by the sequences' lengths, and the fields are a
+ * measure of the work.  isopo_seq_grads_limited also takes the 256 tile on layers large enough for it whose widths are
+ * no multiples of 256 and for which 128 is reported here */
 typedef struct {
   int32_t tile, workgroups_per_cu, tiles, n_chunks, chunk_tokens;
   int32_t xcd_start[9];
@@ -181,8 +180,8 @@ isopo_status isopo_seq_grads(const isopo_layer* layer, void* stash, void* stream
 
 /* isopo_seq_grads on a budget of compute units, for callers that overlap this layer's contraction with
  * bandwidth-bound work queued on another stream (the Gram pass and the stash-weighted sum of the layer
- * before): at most max_workgroups workgroups are resident at a time, each on a compute unit of its own,
- * and the other units stay free.  The result is the same stash, bit for bit.
+ * before): the launch has at most max_workgroups workgroups, each on a compute unit of its own, and the
+ * other units stay free.  The result is the same stash, bit for bit.
  *   max_workgroups  0: no limit (isopo_seq_grads).  Otherwise 8..256, rounded down to a multiple of 8
  *                   (the workgroups are dealt evenly to the 8 accelerator dies).  Honoured for bf16
  *                   layers large enough for the 256x256 tile (d_in and d_out of 256 at least and, over

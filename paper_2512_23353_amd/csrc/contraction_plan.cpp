@@ -1,6 +1,6 @@
 // Host-side launch plan of the streaming bf16 contraction (per-sequence gradients G_i = Delta_i^T X_i of
-// both hook listings, and the unweighted dW = Delta^T X): tile size, token split, and the ranges of
-// (item, tile) pairs each of the eight XCDs walks.  Pure host arithmetic, no HIP calls, so that it can be
+// both hook listings, and the sums over all tokens): tile size, token split, and which (item, tile) pairs
+// each of the eight XCDs and its workgroups take.  Pure host arithmetic, no HIP calls, so that it can be
 // tested without a GPU.
 #include "kernels.h"
 #include "pair_walk.h"

@@ -51,7 +51,7 @@ struct ContractionPlan {
                                // (one workgroup each, all tokens); the chunks apply to the tiles after them
   int xcd_start[9];            // a split sum's XCD x walks (chunk, tile) pairs [xcd_start[x], xcd_start[x+1]) of the
                                // chunk-major list.  Per-sequence mode: such a cut of the (sequence, tile) list, or all
-                               // zero; the launch has a plan of its own (WalkPlan)
+                               // zero, for the public query; the launch has a plan of its own (WalkPlan)
   long long blocks;            // workgroups of a launch with one per pair
 };
 ContractionPlan plan_contraction(int rows, int d_in, int n_tokens, int n_seq, const int32_t* off_host,

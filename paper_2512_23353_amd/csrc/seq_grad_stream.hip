@@ -559,7 +559,8 @@ hipError_t launch_apply_beta(float* o, long long n, float beta, hipStream_t s) {
 // of eight sequences 79 -> 70 us; 4096x4096, 3200 of 16: 114 -> 106; 5000x3000, 5300 of 40: 181 -> 168; 8960x1536, 15000 of 256: 578 ->
 // 538, 10700 of 16: 248 -> 244; plain 4096x4096, 6000: 166 -> 158; 3584x4096, 84000: 1845 -> 1818.  Weighted sums of many tokens are at
 // the power limit, where the walk of a tile dwarfs what it costs besides and the segments' bookkeeping is paid in clock: 27648x5120,
-// 16384 tokens 2796 -> 2776 us, 32768 5.53 -> 5.56 ms, 65536 11.05 -> 11.23.
+// 16384 tokens 2796 -> 2776 us, 32768 5.53 -> 5.56 ms, 65536 11.05 -> 11.23.  The line is not a sharp one: on twelve weighted layers
+// either side of it the two are within 0.97 .. 1.01 of each other.
 constexpr int kWalkTokens = 16384;
 
 // bf16: the per-sequence stash, the plain sum over all tokens, or (c != nullptr) the weighted sum.

@@ -8,15 +8,16 @@
 //    again for the stores of its tile (5 us per 256x256 tile, 18 us for the fp32 tile of a sum, against 0.55 us per block of 32
 //    tokens).  Here a workgroup's items are one stream of token blocks: the loads run on into the next item while the last
 //    blocks of this one are multiplied and its tile is stored, no barrier or wait stands between two items, and the only
-//    pipeline to fill is the first.  Which items those are is fixed at launch (PairWalk): no counters to clear and to wait for.
+//    pipeline to fill is the first.  Which items those are is fixed at launch (plan_walk, PairWalk in pair_walk.h): no counters
+//    to clear and to wait for.
 //  * what a wave issues.  One wave per SIMD has time for about three instructions beside each MFMA.  A token block of 64 MFMAs
-//    is 160 instructions (about 190 with a load's address formed by itself and the buffer descriptors copied and clamped per
-//    block), which shows in the launch's time also at the power limit.
+//    is 160 instructions, about 30 fewer than with a load's address formed by itself and the buffer descriptors copied and
+//    clamped per block.
 // 14336x4096, 32 sequences, 70429 tokens: 6.43 -> 6.19 ms (1.34 PFLOP/s); 1024x4096, the same tokens: 520 -> 485 us; 8960x1536,
 // 256 sequences, 85229: 2.88 -> 2.56 ms (HBM: 7 GB of stash); 1536x1536, 16 sequences, 10685: 60.5 -> 56 us; the weighted sum
 // 27648x5120 over 1279 tokens of 8 sequences: 490 -> 405 us.  Tried and level: loads issued half a block earlier (the ring has
 // room for it, since a block's stage is free at its barrier), the XCDs set off against each other in time so that their
-// stores do not meet, whole sequences per XCD.
+// stores do not meet.
 #include "pair_walk.h"
 #include "seq_grad_stream.h"
 

@@ -7,7 +7,7 @@ import torch
 from paper_2512_23353_amd import isopo
 from paper_2512_23353_amd import workloads as wl
 
-from helpers import bf16_plan, to_device
+from helpers import bf16_plan, to_device, walk_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -78,12 +78,14 @@ def test_weighted_sum_in_chunks(gpu_device, d_in, d_out, lens, tile):
 @pytest.mark.parametrize("d_in,d_out,lens,budget", [
     (264, 1280, [260] * 100, 64), (520, 1288, [300] * 60, 8), (1032, 2048, [780, 0, 801, 333] * 2, 224), (1032, 2048, [780] * 8, 256)])
 def test_budget_on_ragged_widths(gpu_device, d_in, d_out, lens, budget):
-    """Row-major layers that take 128-wide tiles without a budget: the budget is honoured all the same (the work counters
-    are used, which only the persistent launch does), and the stash is the unlimited call's bit for bit."""
+    """Row-major layers that take 128-wide tiles without a budget: the launch's plan keeps the budget all the same, and the
+    stash is the unlimited call's bit for bit.  (The scratch words are cleared by a launch on a budget and by no other: that
+    shows that a budget reached the kernel, not its size, which is the plan's.)"""
     prob = wl.custom_layer(d_in, d_out, lens, dtype="bf16", seed=d_in, sigma_delta=1e-2, rho=0.3)
     layer, _ = to_device(prob, gpu_device)
     assert isopo.contraction_plan(layer.ref(), True)["tile"] == 128
     assert bf16_plan(d_in, d_out, lens, True, budget=True).tile == 256
+    assert 8 * walk_plan(d_in, d_out, lens, budget)[0].per_xcd <= budget
     want = isopo.seq_grads(layer)
     for kw in ({}, {"layout": isopo.STASH_ROW_MAJOR}):
         queue = torch.full((8,), 12345, dtype=torch.int32, device=gpu_device)

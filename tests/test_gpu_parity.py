@@ -13,7 +13,7 @@ from oracle import isopo_oracle as orc
 from paper_2512_23353_amd import isopo
 from paper_2512_23353_amd import workloads as wl
 
-from helpers import TOL, assert_K_close, assert_c_close, assert_dW_close, oracle_step, rel_err, to_device
+from helpers import TOL, assert_K_close, assert_c_close, assert_dW_close, oracle_step, rel_err, to_device, walk_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -349,10 +349,10 @@ def test_stash_holds_per_sequence_gradients(gpu_device):
 @pytest.mark.parametrize("dims,n_seq", [((768, 512), 48), ((1536, 256), 44), ((768, 512), 3)])
 def test_per_sequence_gradients_with_xcd_work_ranges(gpu_device, dims, n_seq):
     """Tile counts that are no multiple of eight (6 tiles of 256x256, or 24/12 of
-    128x128 with few sequences): the launcher hands each XCD a contiguous range
-    of (sequence, tile) pairs balanced by tokens.  Ragged lengths with empty
-    sequences; every per-sequence gradient in the stash and K are checked, so a
-    pair that no XCD took, or two took, cannot pass."""
+    128x128 with few sequences): the XCDs have uneven numbers of (sequence, tile)
+    pairs, dealt out or in ranges as the launch's plan says.  Ragged lengths with
+    empty sequences; every per-sequence gradient in the stash and K are checked, so
+    a pair that no workgroup took cannot pass."""
     d_in, d_out = dims
     rng = np.random.default_rng(77)
     lengths = [int(x) for x in rng.integers(0, 160, n_seq)]
@@ -763,11 +763,11 @@ def test_hip_graph_replays_match_eager(gpu_device):
 
 @pytest.mark.parametrize("dims,budget", [((512, 768), 8), ((512, 768), 64), ((1024, 512), 224), ((768, 512), 16)])
 def test_per_sequence_gradients_on_a_compute_unit_budget(gpu_device, dims, budget):
-    """isopo_seq_grads_limited: a persistent launch of `budget` workgroups pulls
-    the (sequence, tile) items from per-XCD counters.  Same arithmetic per item,
-    so the stash must equal the unlimited launch bit for bit - with tile counts
-    that are and are not a multiple of eight, ragged and empty sequences, and
-    twice in a row on the same counters."""
+    """isopo_seq_grads_limited: a launch of `budget` workgroups at most, each of
+    which walks a list of (sequence, tile) pairs that the host's plan fixes.  Same
+    arithmetic per pair, so the stash must equal the unlimited launch bit for bit -
+    with tile counts that are and are not a multiple of eight, ragged and empty
+    sequences, and twice in a row on the same scratch words."""
     d_in, d_out = dims
     rng = np.random.default_rng(91)
     n_seq = 80
@@ -777,6 +777,7 @@ def test_per_sequence_gradients_on_a_compute_unit_budget(gpu_device, dims, budge
     layer, _ = to_device(prob, gpu_device)
     plan = isopo.contraction_plan(layer.ref(), True)
     assert plan["tile"] == 256 and plan["workgroups"] > budget
+    assert 8 * walk_plan(d_in, d_out, lengths, budget)[0].per_xcd == budget
     ref = isopo.seq_grads(layer)
     queue = torch.full((8,), 12345, dtype=torch.int32, device=gpu_device)       # the call zeroes it
     got = torch.full_like(ref, float("nan"))
@@ -796,11 +797,11 @@ def test_per_sequence_gradients_on_a_compute_unit_budget(gpu_device, dims, budge
 
 
 def test_hip_graph_replays_of_the_persistent_launch(gpu_device):
-    """isopo_layer_gram on a layer large enough for the persistent launch (one
-    workgroup per compute unit, work counters in the workspace zeroed by a
-    kernel, not a memset), captured in a HIP graph: every replay, with eager
-    work of the same kind between replays, must reproduce K and the stash bit
-    for bit for the buffers' current contents."""
+    """isopo_layer_gram on a layer with more (sequence, tile) pairs than compute
+    units, so that a workgroup walks several, captured in a HIP graph: every
+    replay, with eager work of the same kind between replays, must reproduce K
+    and the stash bit for bit for the buffers' current contents, whatever the
+    workspace held before."""
     rng = np.random.default_rng(23)
     lengths = [int(x) for x in rng.integers(1, 90, 96)]
     prob = wl.custom_layer(512, 768, lengths, dtype="bf16", seed=15, sigma_delta=1e-2)
@@ -825,7 +826,7 @@ def test_hip_graph_replays_of_the_persistent_launch(gpu_device):
     for rep in range(3):
         layer.X.copy_(X0 * (1.0 + rep))     # the graph reads the buffers' current contents
         K.fill_(float("nan"))
-        ws.fill_(0xFF)                      # counters included: the launch zeroes them itself
+        ws.fill_(0xFF)                      # whatever the workspace held
         graph.replay()
         torch.cuda.synchronize()
         run(K_eager, ws_eager)
