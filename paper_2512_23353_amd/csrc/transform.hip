@@ -74,7 +74,7 @@ __host__ __device__ constexpr int transform_front(int m) { return m + transform_
 // of the diagonal block's rows come from their lanes (v_readlane), so that a column is one reciprocal square root and a
 // chain of multiply-adds, without an LDS round trip or a barrier (one of each per column, and a 64-bit division and
 // square root in every thread, made a column 0.8 us).  Sequences, us before and now: 16, 11.4 and 7.8; 32, 23 and 13; 64, 49 and
-// 25; 128, 112 and 57; 256, 328 and 186 (231 where the Gram pass of a 7 GB stash ran just before); 1024, 8980 and 5080 (of which
+// 25; 128, 112 and 57; 256, 328 and 186 (230 to 270 right after the Gram pass of a stash of many GB); 1024, 8980 and 5080 (of which
 // launch and regulariser 6).  With the matrix in global memory the kernel spills 10 scalar registers, and at 1024 threads, whose
 // cap is 128 vector registers, 8 and 16 vector ones.  The upper triangle of the diagonal block is carried along and never read.
 // The trailing matrix (rows up to and including the row of A) then takes the rank-NB update in
