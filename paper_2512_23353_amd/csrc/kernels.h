@@ -222,7 +222,8 @@ struct TransformArgs {
   float* ema_state = nullptr;  // reg_mode 2: [batch][2] trailing mean of tr(K)/m, number of minibatches seen
   float ema_decay = 0.f;
 };
-constexpr int kTransformLdsMax = 128;
+constexpr int kTransformLdsMax = 128;         // more sequences: the interacting transform asks for a workspace
+constexpr int kTransformRegsMax = 256;        // ... and from here on uses it; up to here the matrix is in registers
 constexpr int kTransformWidePanelMax = 512;   // larger problems factor panels of 16 columns instead of 32 (the panel has to fit in LDS)
 hipError_t launch_transform(const TransformArgs& a, hipStream_t s);
 
