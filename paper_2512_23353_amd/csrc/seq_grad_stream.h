@@ -42,25 +42,28 @@ __device__ __forceinline__ float acc_read(float a) {
   return v;
 }
 
-// Column-blocked tile order: ids run down 8-column strips of the tile grid, so the 32 workgroups an
-// XCD runs at a time cover about 4 tile rows x 8 tile columns (12 operand panels) rather than
-// 2 x 16 (18 panels): fewer L2 misses per flop.
+// Column-blocked tile order: ids run down strips of `width` tile columns, so that the workgroups an XCD runs at a time cover a
+// compact block of tiles and few operand panels (strip_width in seq_grad_walk.hip says how wide).
+constexpr int kStrip = 8;                // ... where nothing else is said
 struct TileGrid {
-  int m, n;                              // tile rows and columns
-  TileDiv strip, last;                   // tiles of a full strip; columns of the last strip, where it is narrower
+  int m, n, width;                       // tile rows and columns; columns of a strip
+  TileDiv strip, across, last;           // tiles of a full strip; its width; columns of the last strip, where it is narrower
 };
-constexpr int kStrip = 8;
-inline TileGrid tile_grid(int m, int n) {
-  return {m, n, tile_div_by((unsigned)(m * kStrip)), tile_div_by((unsigned)(n % kStrip ? n % kStrip : kStrip))};
+inline TileGrid tile_grid(int m, int n, int width = kStrip) {
+  return {m, n, width, tile_div_by((unsigned)(m * width)), tile_div_by((unsigned)width),
+          tile_div_by((unsigned)(n % width ? n % width : width))};
 }
+// WIDTH: of a strip, where it is known (0: what the grid says)
+template <int WIDTH>
 __device__ __forceinline__ void tile_coords(int tile, const TileGrid& g, int& tile_m, int& tile_n) {
-  const int s = tile_div(tile, g.strip), c0 = s * kStrip, in_strip = tile - s * (int)g.strip.d;
-  if (c0 + kStrip <= g.n) {
-    tile_m = in_strip / kStrip;
-    tile_n = c0 + in_strip % kStrip;
+  const int width = WIDTH ? WIDTH : g.width, s = tile_div(tile, g.strip), c0 = s * width, in_strip = tile - s * (int)g.strip.d;
+  if (WIDTH && c0 + width <= g.n) {
+    tile_m = in_strip / (WIDTH ? WIDTH : 1);
+    tile_n = c0 + in_strip % (WIDTH ? WIDTH : 1);
   } else {
-    tile_m = tile_div(in_strip, g.last);
-    tile_n = c0 + in_strip - tile_m * (int)g.last.d;
+    const TileDiv by = c0 + width <= g.n ? g.across : g.last;
+    tile_m = tile_div(in_strip, by);
+    tile_n = c0 + in_strip - tile_m * (int)by.d;
   }
 }
 

@@ -102,7 +102,7 @@ __device__ __forceinline__ void seq_grad_stream_body(const StreamParams& p) {
       tile = xcd_contiguous(blockIdx.x, p.n_blocks);
     }
     int tile_m, tile_n;
-    tile_coords(tile, p.grid, tile_m, tile_n);
+    tile_coords<kStrip>(tile, p.grid, tile_m, tile_n);
     const int m0 = p.row0 + tile_m * BT, n0 = tile_n * BT;
     const int t0 = split ? item * p.chunk_tokens : 0;
     const int t1 = split ? min(p.n_tokens, t0 + p.chunk_tokens) : p.n_tokens;
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(256) void apply_beta_tiles_kernel(float* __restrict
                                                                int out_row0, TileGrid grid, int first_tile,
                                                                float beta) {
   int tile_m, tile_n;
-  tile_coords(first_tile + (int)(blockIdx.x >> 4), grid, tile_m, tile_n);
+  tile_coords<kStrip>(first_tile + (int)(blockIdx.x >> 4), grid, tile_m, tile_n);
   const int n = tile_n * 256 + (threadIdx.x & 63) * 4;
   if (n >= d_in) return;
 #pragma unroll

@@ -98,7 +98,7 @@ __device__ __forceinline__ void seq_grad_walk_body(const Params& p_) {
   asm volatile("" : "+s"(p.X), "+s"(p.Delta), "+s"(p.d_in), "+s"(p.d_out), "+s"(p.n_seq), "+s"(p.row0), "+s"(p.per_xcd));
   if constexpr (SEQ)
     asm volatile("" : "+s"(p.grid.m), "+s"(p.grid.n), "+s"(p.grid.strip.d), "+s"(p.grid.strip.mul), "+s"(p.grid.last.d),
-                      "+s"(p.grid.last.mul));
+                      "+s"(p.grid.last.mul), "+s"(p.grid.width), "+s"(p.grid.across.d), "+s"(p.grid.across.mul));
   if constexpr (SEQ)
     asm volatile("" : "+s"(p.by_tiles.d), "+s"(p.by_tiles.mul), "+s"(first), "+s"(end), "+s"(alone));
 
@@ -208,7 +208,7 @@ __device__ __forceinline__ void seq_grad_walk_body(const Params& p_) {
     rem = 0;                                                   // past the last pair: all-zero blocks
     if (ahead.more() && !(WTD && n_seg == 0)) {
       int tile_m, tile_n;
-      tile_coords(ahead.tile(), p.grid, tile_m, tile_n);
+      tile_coords<SEQ ? 0 : kStrip>(ahead.tile(), p.grid, tile_m, tile_n);
       cut_a = uniform(p.row0 + tile_m * T) * 2;
       cut_b = uniform(tile_n * T) * 2;
       const int k = SEQ ? ahead.i : 0;
@@ -461,7 +461,7 @@ __device__ __forceinline__ void seq_grad_walk_body(const Params& p_) {
     if constexpr (TABLE) seq = uniform(sh_seq[walk.i]);
     else if constexpr (SEQ) seq = walk.i;
     int tile_m, tile_n;
-    tile_coords(walk.tile(), p.grid, tile_m, tile_n);
+    tile_coords<SEQ ? 0 : kStrip>(walk.tile(), p.grid, tile_m, tile_n);
     tile_m = uniform(tile_m);
     tile_n = uniform(tile_n);
     const int m0 = p.row0 + tile_m * T, n0 = tile_n * T;
@@ -571,6 +571,16 @@ hipError_t launch_walk(const Params& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Columns of a strip of tiles.  An XCD's workgroups take neighbouring tiles, and what bounds a launch beside the power limit is
+// what they read from beyond their L2: with 32 tiles of an item at a time, eight columns by four rows are 12 operand panels; of the
+// fewer that an XCD takes of a sequence of up to 160 tiles, four columns make the more compact block.  Per-sequence launches, 8
+// against 4 columns, 256x256 tiles: 4x16 tiles, 32 sequences of 512 .. 4096 tokens 484 / 468 us; 11x7, 92 of 86 175 / 167; 8x8, 40 of
+// 87 69 / 66; 6x17, 12 of 481 86 / 83; 30 random ones 0.988x on average, the slowest 1.02x (2x17, 76 of 3568).  Sums and more tiles:
+// level or slower with 4 (35x6, 256 sequences: 2535 / 2580), few columns (up to 6): level or slower cut.
+int strip_width(const ContractionPlan& pl, bool per_sequence) {
+  return per_sequence && pl.tiles_n >= 7 && (long long)pl.tiles_m * pl.tiles_n <= 160 ? 4 : kStrip;
+}
+
 // False: nothing to do, or (status) too much of it.
 bool fill_params(const SeqGradArgs& a, const ContractionPlan& pl, WalkParams& p, hipError_t& status) {
   const long long tiles = (long long)pl.tiles_m * pl.tiles_n, pairs = tiles * (a.per_sequence ? a.n_seq : 1);
@@ -580,7 +590,7 @@ bool fill_params(const SeqGradArgs& a, const ContractionPlan& pl, WalkParams& p,
   p.d_in = a.d_in; p.d_out = a.d_out; p.n_seq = a.n_seq; p.n_tokens = a.n_tokens;
   p.row0 = a.row0; p.row_end = a.row0 + a.rows; p.out_row0 = a.out_row0;
   p.out_seq_stride = a.out_seq_stride; p.beta = a.beta;
-  p.grid = tile_grid(pl.tiles_m, pl.tiles_n);
+  p.grid = tile_grid(pl.tiles_m, pl.tiles_n, strip_width(pl, a.per_sequence));
   p.by_tiles = tile_div_by((unsigned)tiles);
   p.queue = nullptr;
   return true;

@@ -117,3 +117,18 @@ def test_arrangements(gpu_device, d_in, d_out, lens, budget, kind):
         tiled = isopo.seq_grads(layer, torch.full_like(S, float("nan")), layout=layout)
         c = torch.randn(len(lens), generator=torch.Generator().manual_seed(1)).to(gpu_device)
         assert torch.equal(isopo.weighted_grad(layer, c, S), isopo.weighted_grad(layer, c, tiled, layout=layout))
+
+
+@pytest.mark.parametrize("d_in,d_out,lens", [
+    (1800, 2568, [300, 33, 700] * 4), (2312, 1032, [90, 0, 400, 64] * 5), (2304, 768, [33, 500, 0] * 4),     # 8, 10 and 9 columns
+    (1792, 5632, [40, 200] * 2), (1792, 5888, [40, 200] * 2)])               # 154 tiles; 161: strips of eight
+def test_narrow_strips(gpu_device, d_in, d_out, lens):
+    """Tiles in strips of four columns, of which the last may be narrower, and on either side of where strips are of eight."""
+    layer = _layer(d_in, d_out, lens, gpu_device)
+    layout, _ = isopo.stash_layout(layer)
+    rows = isopo.seq_grads(layer, torch.full((len(lens), d_out, d_in), float("nan"), dtype=torch.bfloat16, device=gpu_device))
+    _check_stash(layer, rows, lens)
+    if layout == isopo.STASH_TILE_ORDER:
+        tiled = isopo.seq_grads(layer, torch.full_like(rows, float("nan")), layout=layout)
+        c = torch.randn(len(lens), generator=torch.Generator().manual_seed(1)).to(gpu_device)
+        assert torch.equal(isopo.weighted_grad(layer, c, rows), isopo.weighted_grad(layer, c, tiled, layout=layout))
