@@ -279,6 +279,15 @@ isopo_status isopo_weighted_grad(const isopo_layer* layer, const float* c, const
 isopo_status isopo_weighted_grad_stash(const isopo_layer* layer, const float* c, const void* stash,
                                        isopo_stash_layout layout, float beta, float* dW, void* stream);
 
+/* isopo_layer_gram, isopo_transform and isopo_weighted_grad_stash (keep_stash = 2: the stash stays in the workspace, in the layout
+ * that *layout then names) or isopo_weighted_grad without a stash (keep_stash = 0) as one call, on one stream, with the same results
+ * bit for bit and the same conditions on each argument.  Up to 128 sequences the coefficients are formed by the launch that finishes
+ * K, with info_dev as its counter: give one.  A transform's bad argument is reported before anything is enqueued. */
+isopo_status isopo_layer_step(const isopo_layer* layer, isopo_gram_path path, const float* A, isopo_variant variant, float lambda,
+                              isopo_reg_mode reg_mode, float beta, float* K, float* c, int32_t* info_dev, float* dW,
+                              void* workspace, size_t ws_bytes, int keep_stash, isopo_stash_layout* layout,
+                              void* transform_workspace, size_t transform_ws_bytes, void* stream);
+
 /* isopo_weighted_grad_stash with dW [d_out, d_in] in bf16, the gradient buffer of a bf16 model's parameter
  * (`mod.grad += ...` of both listings where `mod.weight` is bf16): the sums run in fp32 as before and
  * dW = bf16(beta * dW + sum_i c_i G_i) is rounded once, to nearest even; with beta = 0 the result is the

@@ -7,6 +7,7 @@
 
 #include <cmath>
 #include <mutex>
+#include "gram_finish.h"
 #include "kernels.h"
 
 // Scratch of isopo_transform_noalloc: the fp64 work matrices and right-hand sides that isopo_transform takes
@@ -219,8 +220,9 @@ isopo_status isopo_layer_gram_plan(const isopo_layer* layer, isopo_gram_path req
   return ISOPO_OK;
 }
 
-isopo_status isopo_layer_gram(const isopo_layer* layer, isopo_gram_path path, float* K, void* workspace,
-                              size_t ws_bytes, int keep_stash, void* stream) {
+// isopo_layer_gram.  `then`: the transform of K, launched with the Gram matrix's last step where that can be (true in *fused).
+static isopo_status layer_gram(const isopo_layer* layer, isopo_gram_path path, float* K, void* workspace, size_t ws_bytes,
+                               int keep_stash, void* stream, const TransformArgs* then, bool* fused) {
   isopo_status st = check_layer(layer, true);
   if (st != ISOPO_OK) return st;
   if (!K || !workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1))) return ISOPO_ERR_INVALID_ARG;
@@ -280,6 +282,7 @@ isopo_status isopo_layer_gram(const isopo_layer* layer, isopo_gram_path path, fl
   if (reinterpret_cast<char*>(partials) + pbytes > ws + ws_bytes) return ISOPO_ERR_WORKSPACE_TOO_SMALL;
 
   const int slots = stash_gram_slots(layer->n_seq, bf16, (long long)chunk_rows * layer->d_in);
+  const bool fuse = then && then->info && layer->n_seq <= kTransformFinishMax;
   for (int r0 = 0; r0 < layer->d_out; r0 += (int)chunk_rows) {
     const int rows = (layer->d_out - r0) < (int)chunk_rows ? (layer->d_out - r0) : (int)chunk_rows;
     SeqGradArgs a;
@@ -293,9 +296,19 @@ isopo_status isopo_layer_gram(const isopo_layer* layer, isopo_gram_path path, fl
     g.p0 = whole ? (long long)r0 * layer->d_in : 0;
     g.p1 = g.p0 + (long long)rows * layer->d_in;
     g.n_seq = layer->n_seq; g.bf16 = bf16; g.first = (r0 == 0); g.slots = slots; g.partials = partials;
+    if (fuse) g.clear = then->info;
     if (launch_stash_gram(g, s) != hipSuccess) return ISOPO_ERR_HIP;
   }
+  if (fuse) {
+    *fused = true;
+    return launch_finish_transform(gram_finish_of(partials, bf16, slots, layer->n_seq, K), *then, s) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
+  }
   return launch_stash_gram_finish(partials, bf16, slots, layer->n_seq, K, s) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
+}
+
+isopo_status isopo_layer_gram(const isopo_layer* layer, isopo_gram_path path, float* K, void* workspace,
+                              size_t ws_bytes, int keep_stash, void* stream) {
+  return layer_gram(layer, path, K, workspace, ws_bytes, keep_stash, stream, nullptr, nullptr);
 }
 
 isopo_status isopo_seq_grads(const isopo_layer* layer, void* stash, void* stream) {
@@ -361,9 +374,10 @@ size_t isopo_transform_workspace(int32_t n_seq, int32_t batch) {
   return (size_t)batch * ((size_t)n_seq * n_seq + n_seq) * sizeof(double);
 }
 
-isopo_status isopo_transform(const float* K, const float* A, int32_t n_seq, int32_t batch, isopo_variant variant,
-                             float lambda, isopo_reg_mode reg_mode, float* c, int32_t* info_dev, void* workspace,
-                             size_t ws_bytes, void* stream) {
+// The arguments of isopo_transform, checked.
+static isopo_status transform_args(const float* K, const float* A, int32_t n_seq, int32_t batch, isopo_variant variant, float lambda,
+                                   isopo_reg_mode reg_mode, float* c, int32_t* info_dev, void* workspace, size_t ws_bytes,
+                                   TransformArgs& t) {
   if (!K || !A || !c || n_seq <= 0 || batch <= 0) return ISOPO_ERR_INVALID_ARG;
   if (n_seq > ISOPO_MAX_SEQ) return ISOPO_ERR_UNSUPPORTED;
   if (!enum_in(variant, ISOPO_VARIANT_FISHER, ISOPO_VARIANT_INTERACTING)) return ISOPO_ERR_INVALID_ARG;
@@ -374,10 +388,40 @@ isopo_status isopo_transform(const float* K, const float* A, int32_t n_seq, int3
     if (need && (!workspace || ws_bytes < need)) return ISOPO_ERR_WORKSPACE_TOO_SMALL;
     if (need && (reinterpret_cast<uintptr_t>(workspace) & 15u)) return ISOPO_ERR_INVALID_ARG;
   }
-  TransformArgs t;
   t.K = K; t.A = A; t.n_seq = n_seq; t.batch = batch; t.variant = (int)variant; t.reg_mode = (int)reg_mode;
   t.lambda = lambda; t.c = c; t.info = info_dev; t.workspace = static_cast<double*>(workspace);
+  return ISOPO_OK;
+}
+
+isopo_status isopo_transform(const float* K, const float* A, int32_t n_seq, int32_t batch, isopo_variant variant,
+                             float lambda, isopo_reg_mode reg_mode, float* c, int32_t* info_dev, void* workspace,
+                             size_t ws_bytes, void* stream) {
+  TransformArgs t;
+  const isopo_status st = transform_args(K, A, n_seq, batch, variant, lambda, reg_mode, c, info_dev, workspace, ws_bytes, t);
+  if (st != ISOPO_OK) return st;
   return launch_transform(t, static_cast<hipStream_t>(stream)) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
+}
+
+isopo_status isopo_layer_step(const isopo_layer* layer, isopo_gram_path path, const float* A, isopo_variant variant, float lambda,
+                              isopo_reg_mode reg_mode, float beta, float* K, float* c, int32_t* info_dev, float* dW,
+                              void* workspace, size_t ws_bytes, int keep_stash, isopo_stash_layout* layout,
+                              void* transform_workspace, size_t transform_ws_bytes, void* stream) {
+  isopo_status st = check_layer(layer, true);
+  if (st != ISOPO_OK) return st;
+  if (keep_stash != 0 && keep_stash != 2) return ISOPO_ERR_INVALID_ARG;
+  TransformArgs t;
+  st = transform_args(K, A, layer->n_seq, 1, variant, lambda, reg_mode, c, info_dev, transform_workspace, transform_ws_bytes, t);
+  if (st != ISOPO_OK) return st;
+  bool fused = false;
+  st = layer_gram(layer, path, K, workspace, ws_bytes, keep_stash, stream, &t, &fused);
+  if (st != ISOPO_OK) return st;
+  if (!fused && launch_transform(t, static_cast<hipStream_t>(stream)) != hipSuccess) return ISOPO_ERR_HIP;
+  if (!keep_stash) return isopo_weighted_grad(layer, c, nullptr, beta, dW, stream);
+  isopo_stash_layout have;
+  st = isopo_stash_layout_of(layer, &have, nullptr);
+  if (st != ISOPO_OK) return st;
+  if (layout) *layout = have;
+  return isopo_weighted_grad_stash(layer, c, workspace, have, beta, dW, stream);
 }
 
 isopo_status isopo_transform_noalloc(const float* K, const float* A, int32_t n_seq, int32_t batch,

@@ -95,6 +95,7 @@ struct StashGramArgs {
   bool first;                // overwrite the partial slots instead of adding to them
   int slots;                 // stash_gram_slots of the first chunk's element count; the same for all chunks
   float* partials;           // [slots][stash_gram_slot_floats(n_seq, bf16)]
+  int32_t* clear = nullptr;  // up to 128 sequences: a word that the launch sets to zero
 };
 // partial slots a reduction over n_elem elements of each sequence uses
 int stash_gram_slots(int n_seq, bool bf16, long long n_elem);
@@ -109,6 +110,8 @@ size_t stash_gram_slot_floats(int n_seq, bool bf16);
 hipError_t launch_stash_gram(const StashGramArgs& a, hipStream_t s);
 // K[i][j] = K[j][i] = sum over slots (fixed order) of the (i<=j) entry.
 hipError_t launch_stash_gram_finish(const float* partials, bool bf16, int slots, int n_seq, float* K, hipStream_t s);
+struct GramFinish;
+GramFinish gram_finish_of(const float* partials, bool bf16, int slots, int n_seq, float* K);
 // n_seq <= 128: row-contiguous DMA into an LDS ring (launch_stash_gram routes to it).
 int stash_gram_stream_slots(int n_seq, bool bf16, long long n_elem);
 hipError_t launch_stash_gram_stream(const StashGramArgs& a, hipStream_t s);
@@ -226,6 +229,10 @@ constexpr int kTransformLdsMax = 128;         // more sequences: the interacting
 constexpr int kTransformRegsMax = 256;        // ... and from here on uses it; up to here the matrix is in registers
 constexpr int kTransformWidePanelMax = 512;   // larger problems factor panels of 16 columns instead of 32 (the panel has to fit in LDS)
 hipError_t launch_transform(const TransformArgs& a, hipStream_t s);
+// launch_stash_gram_finish and launch_transform of its K (batch 1, info given and cleared by the Gram pass) as one launch, for up to
+// kTransformFinishMax sequences
+constexpr int kTransformFinishMax = 128;
+hipError_t launch_finish_transform(const GramFinish& f, const TransformArgs& a, hipStream_t s);
 
 // Generalised (p, q, r) re-scaling of the per-sequence coefficients.
 struct RescaleArgs {

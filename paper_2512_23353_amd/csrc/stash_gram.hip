@@ -8,6 +8,7 @@
 // stash_gram_stream.hip, which leave partial sums in fixed slots; here are the finishing kernel, which adds the slots
 // in a fixed tree (K is bit-reproducible and exactly symmetric), and the weighted sum.
 #include "common.h"
+#include "gram_finish.h"
 #include "kernels.h"
 
 namespace isopo {
@@ -17,37 +18,7 @@ constexpr int kGramSlots = 256;             // at most: one partial slot per wor
 
 constexpr int tri(int nb) { return nb * (nb + 1) / 2; }
 
-// One 1024-thread block per 64 consecutive slot elements: wave w adds slots w, w+16, ... in order (eight loads in flight:
-// a load per turn of the loop cost 0.4 us each), the 16 waves are added in wave order, in 64 bits; only entries with
-// i <= j are written, mirrored.  256 slots of 32 sequences: 6.5 us before, 4.9 us now;
-// an fp32 stash's 1024 slots: 20.7 us before, its 256 slots 5.0 us, 2.3 us where it has 16 stages.
-__global__ __launch_bounds__(1024) void stash_gram_finish_kernel(const float* __restrict__ partials, int n_slots,
-                                                                 long long slot_floats, int n_seq, int mb,
-                                                                 float* __restrict__ K) {
-  __shared__ double red[16][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long long e = (long long)blockIdx.x * 64 + lane;      // element of the slot layout [pair][v][lane]
-  double s = 0.0;
-#pragma unroll 8
-  for (int w = wave; w < n_slots; w += 16) s += (double)partials[(long long)w * slot_floats + e];
-  red[wave][lane] = s;
-  __syncthreads();
-  if (wave != 0) return;
-  s = 0.0;
-#pragma unroll
-  for (int w = 0; w < 16; ++w) s += red[w][lane];
-  // blocks of mb x mb above the diagonal, row by row, each [v][lane] as the MFMA's accumulators hold it
-  const int per = mb * mb, nb = (n_seq + mb - 1) / mb;
-  const int v = (int)(e % per) >> 6;
-  int bi = 0, rem = (int)(e / per);
-  while (rem >= nb - bi) { rem -= nb - bi; ++bi; }
-  const int i = bi * mb + (mb == 16 ? 4 * (lane >> 4) + v : 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3));
-  const int j = (bi + rem) * mb + lane % mb;
-  if (i < n_seq && j < n_seq && i <= j) {
-    K[(size_t)i * n_seq + j] = (float)s;
-    K[(size_t)j * n_seq + i] = (float)s;
-  }
-}
+__global__ __launch_bounds__(kFinishThreads) void stash_gram_finish_kernel(GramFinish f) { gram_finish<false>(f); }
 
 // The weighted sum: a thread takes VPT 16-byte vectors of every sequence, kSumThreads apart, so a workgroup reads VPT runs of 4 KiB
 // side by side and VPT * 8 loads of a thread are in flight.  Bound by HBM; which VPT where: launch_stash_weighted_sum's rule.
@@ -227,10 +198,13 @@ hipError_t launch_stash_gram(const StashGramArgs& a, hipStream_t s) {
 
 hipError_t launch_stash_gram_finish(const float* partials, bool bf16, int slots, int n_seq, float* K, hipStream_t s) {
   if (n_seq > 128) return bf16 ? launch_stash_gram_large_finish(partials, n_seq, K, s) : hipErrorInvalidValue;
-  const long long slot_floats = (long long)stash_gram_slot_floats(n_seq, bf16);
-  hipLaunchKernelGGL(stash_gram_finish_kernel, dim3((unsigned)(slot_floats / 64)), dim3(1024), 0, s, partials, slots,
-                     slot_floats, n_seq, block_side(n_seq, bf16), K);
+  const GramFinish f = gram_finish_of(partials, bf16, slots, n_seq, K);
+  hipLaunchKernelGGL(stash_gram_finish_kernel, dim3((unsigned)(f.slot_floats / 64)), dim3(kFinishThreads), 0, s, f);
   return hipGetLastError();
+}
+
+GramFinish gram_finish_of(const float* partials, bool bf16, int slots, int n_seq, float* K) {
+  return {partials, slots, (long long)stash_gram_slot_floats(n_seq, bf16), n_seq, block_side(n_seq, bf16), K};
 }
 
 // Vectors per thread.  Four (and non-temporal stores) over stashes of 2 GiB and up of wide sequences: in tile order 4096x14336, 32

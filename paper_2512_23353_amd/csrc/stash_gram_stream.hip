@@ -46,6 +46,7 @@ struct Params {
   int n_seq, first;
   float* partials;
   long long slot_floats;
+  int32_t* clear;
 };
 
 // 16 bytes per lane, global -> LDS (lane l lands at lds_addr + 16*l).  Inline asm keeps the compiler's
@@ -83,6 +84,8 @@ __global__ __launch_bounds__(256, 1) void stash_gram_stream_kernel(Params p) {
   const unsigned smem_base = (unsigned)(size_t)(lds_void_ptr)smem;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+
+  if (p.clear && blockIdx.x == 0 && threadIdx.x == 0) *p.clear = 0;
 
   const long long n_elems = p.p1 - p.p0;
   const long long n_super = (n_elems + KW - 1) / KW;
@@ -679,7 +682,7 @@ hipError_t launch_stash_gram_stream(const StashGramArgs& a, hipStream_t s) {
   if (a.n_seq < 1 || a.n_seq > 128) return hipErrorInvalidValue;
   Params p;
   p.stash = a.stash; p.seq_stride = a.seq_stride; p.p0 = a.p0; p.p1 = a.p1;
-  p.n_seq = a.n_seq; p.first = a.first ? 1 : 0; p.partials = a.partials;
+  p.n_seq = a.n_seq; p.first = a.first ? 1 : 0; p.partials = a.partials; p.clear = a.clear;
   p.slot_floats = (long long)stash_gram_slot_floats(a.n_seq, a.bf16);
   const bool once = read_once(a.p1 - a.p0, a.n_seq, a.bf16);
   if (a.bf16) return once ? launch_bf16<true>(p, a.slots, s) : launch_bf16<false>(p, a.slots, s);

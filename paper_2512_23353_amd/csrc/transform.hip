@@ -19,6 +19,7 @@
 // (transform_kernel).  The result is the unique solution; the eigendecomposition the interacting listing uses reaches the same
 // vector.  A non-positive pivot is reported, never clamped.
 #include "common.h"
+#include "gram_finish.h"
 #include "kernels.h"
 
 namespace isopo {
@@ -346,19 +347,14 @@ constexpr size_t transform_regs_lds(int m) {
   return ((size_t)(nb + 1) * kBlk * kBlk + (size_t)nb * kBlk * kBlkPitch + nb * kBlk) * sizeof(double);
 }
 
-// W waves; S blocks off the diagonal and DN on it per wave.
-template <int W, int S, int DN>
-__global__ __launch_bounds__(64 * W) void transform_regs_kernel(const float* __restrict__ Kb, const float* __restrict__ Ab, int m,
-                                                                Regulariser prm, float* __restrict__ cb,
-                                                                int32_t* __restrict__ info) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+// W waves, the workgroup's first ones (the others have returned); S blocks off the diagonal and DN on it per wave.
+template <int W, int S, int DN, bool SHARED>
+__device__ __forceinline__ void transform_regs(const float* K, const float* A, int m, const Regulariser& prm, int prob, float* c,
+                                               int32_t* info, unsigned char* smem) {
   __shared__ double red[W];
   __shared__ int fail;
-  const int prob = blockIdx.x, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, l4 = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, l4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const float* const K = Kb + (size_t)prob * m * m;
-  const float* const A = Ab + (size_t)prob * m;
-  float* const c = cb + (size_t)prob * m;
   const int nb = transform_blocks(m);
   double* const ubuf = reinterpret_cast<double*>(smem);  // [block column][value pair][lane][2]
   double* const xbuf = ubuf + (nb + 1) * kBlk * kBlk;    // [block row][i][kBlkPitch]: -(L^-1)^T
@@ -386,7 +382,7 @@ __global__ __launch_bounds__(64 * W) void transform_regs_kernel(const float* __r
     for (int v = 0; v < 4; ++v) {
       const int r = kBlk * k + 4 * v + l4, q = kBlk * k + l16, lo = r < q ? r : q, hi = r < q ? q : r;
       const bool there = k < nb && hi < m;
-      const float x = K[there ? (size_t)hi * m + lo : 0];
+      const float x = get_shared<SHARED>(K + (there ? (size_t)hi * m + lo : 0));
       diag_in[d][v] = there ? x : 0.f;
     }
   }
@@ -398,13 +394,13 @@ __global__ __launch_bounds__(64 * W) void transform_regs_kernel(const float* __r
       const int r = kBlk * bk[s] + 4 * v + l4, q = rhs ? m : kBlk * bj[s] + l16;
       const bool there = bk[s] >= 0 && r < m && (rhs ? l16 == 0 : q < m);
       const float* const from = rhs ? A + r : K + (size_t)q * m + r;
-      const float x = *(there ? from : K);
+      const float x = get_shared<SHARED>(there ? from : K);
       in[s][v] = there ? x : 0.f;
     }
   }
   double reg = (double)prm.lambda;
   if (prm.mode != 0) {
-    const double part = wave_sum(tid < m ? (double)K[(size_t)tid * m + tid] : 0.0);   // m <= 64 W
+    const double part = wave_sum(tid < m ? (double)get_shared<SHARED>(K + (size_t)tid * m + tid) : 0.0);   // m <= 64 W
     if (lane == 0) red[wave] = part;
     __syncthreads();
     double sum = 0.0;
@@ -509,10 +505,10 @@ __global__ __launch_bounds__(64 * W) void transform_regs_kernel(const float* __r
   const int failed = fail;                               // read after a barrier: the last block row has no factor behind it
   if (failed >= 0) {
     for (int i = tid; i < m; i += 64 * W) c[i] = __builtin_nanf("");
-    if (info && tid == 0) info[prob] = failed + 1;
+    if (info && tid == 0) *info = failed + 1;
     return;
   }
-  if (info && tid == 0) info[prob] = 0;
+  if (info && tid == 0) *info = 0;
 
   // backward: v starts as y
 #pragma unroll
@@ -544,16 +540,13 @@ __global__ __launch_bounds__(64 * W) void transform_regs_kernel(const float* __r
 }
 
 // FISHER: the norms first; the relative regulariser is measured against their mean.
-template <int THREADS, int ROWS>
-__global__ __launch_bounds__(THREADS) void fisher_transform_kernel(const float* __restrict__ Kb, const float* __restrict__ Ab, int m,
-                                                                   Regulariser prm, float* __restrict__ cb, int32_t* __restrict__ info) {
+template <int THREADS, int ROWS, bool SHARED>
+__device__ __forceinline__ void fisher_transform(const float* K, const float* A, int m, const Regulariser& prm, int prob, float* c,
+                                                 int32_t* info) {
   constexpr int kWaves = THREADS / kWave;
   __shared__ double red[kWaves];
   __shared__ double f2s[ISOPO_MAX_SEQ_TRANSFORM];
-  const int prob = blockIdx.x, tid = threadIdx.x;
-  const float* K = Kb + (size_t)prob * m * m;
-  const float* A = Ab + (size_t)prob * m;
-  float* c = cb + (size_t)prob * m;
+  const int tid = threadIdx.x;
   // a wave takes ROWS rows at a time
   for (int i = tid / kWave * ROWS; i < m; i += kWaves * ROWS) {
     double s[ROWS] = {};
@@ -561,7 +554,7 @@ __global__ __launch_bounds__(THREADS) void fisher_transform_kernel(const float* 
     for (int j = tid % kWave; j < m; j += kWave)
 #pragma unroll
       for (int r = 0; r < ROWS; ++r) {
-        const double k = (double)K[(size_t)(i + r < m ? i + r : m - 1) * m + j];
+        const double k = (double)get_shared<SHARED>(K + (size_t)(i + r < m ? i + r : m - 1) * m + j);
         s[r] += k * k;
       }
 #pragma unroll
@@ -579,7 +572,49 @@ __global__ __launch_bounds__(THREADS) void fisher_transform_kernel(const float* 
     const double den = f2s[i] + reg;
     c[i] = den > 0.0 ? (float)((double)A[i] / sqrt(den)) : 0.f;
   }
-  if (info && tid == 0) info[prob] = 0;
+  if (info && tid == 0) *info = 0;
+}
+
+template <int W, int S, int DN>
+__global__ __launch_bounds__(64 * W) void transform_regs_kernel(const float* __restrict__ K, const float* __restrict__ A, int m,
+                                                                Regulariser prm, float* __restrict__ c, int32_t* __restrict__ info) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int prob = blockIdx.x;
+  transform_regs<W, S, DN, false>(K + (size_t)prob * m * m, A + (size_t)prob * m, m, prm, prob, c + (size_t)prob * m,
+                           info ? info + prob : nullptr, smem);
+}
+
+template <int THREADS, int ROWS>
+__global__ __launch_bounds__(THREADS) void fisher_transform_kernel(const float* __restrict__ K, const float* __restrict__ A, int m,
+                                                                   Regulariser prm, float* __restrict__ c, int32_t* __restrict__ info) {
+  const int prob = blockIdx.x;
+  fisher_transform<THREADS, ROWS, false>(K + (size_t)prob * m * m, A + (size_t)prob * m, m, prm, prob, c + (size_t)prob * m,
+                                  info ? info + prob : nullptr);
+}
+
+// The Gram matrix from its slots, and by the workgroup that finds itself the last one to have written its part of it the
+// coefficients: a launch and the wait between two fewer.  `info` counts the workgroups, from zero, until it says how the solve went.
+// 16 sequences 8.9 us against 4.8 and 6.1 in two launches.  K's entries pass the L2s on their way out and back in, so that no
+// workgroup has to write its L2 back or to drop it: with such fences the two launches were the faster ones (whole calls of 94 us
+// 2 us slower).
+template <int W, int S>
+__global__ __launch_bounds__(kFinishThreads) void finish_transform_kernel(GramFinish f, const float* __restrict__ A, int variant,
+                                                                          Regulariser prm, float* __restrict__ c, int32_t* info) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ int last;
+  gram_finish<true>(f);
+  if (threadIdx.x < kWave) {                             // the wave that has written: its part is there before it counts
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (threadIdx.x == 0) last = __hip_atomic_fetch_add(info, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  if (variant == 0) {
+    fisher_transform<kFinishThreads, 1, true>(f.K, A, f.n_seq, prm, 0, c, info);
+    return;
+  }
+  if (threadIdx.x >= 64 * W) return;
+  transform_regs<W, S, 1, true>(f.K, A, f.n_seq, prm, 0, c, info, smem);
 }
 
 // INTERACTING, the matrix in global memory.
@@ -646,7 +681,21 @@ hipError_t launch_regs(const TransformArgs& a, const Regulariser& reg, hipStream
   return hipGetLastError();
 }
 
+template <int W, int S>
+hipError_t launch_finish(const GramFinish& f, const TransformArgs& a, const Regulariser& reg, hipStream_t s) {
+  static_assert(transform_regs_lds(16 * W) + sizeof(double) * (1024 + ISOPO_MAX_SEQ_TRANSFORM) <= 60 * 1024, "LDS without a limit raised");
+  hipLaunchKernelGGL((finish_transform_kernel<W, S>), dim3((unsigned)(f.slot_floats / 64)), dim3(kFinishThreads),
+                     transform_regs_lds(f.n_seq), s, f, a.A, a.variant, reg, a.c, a.info);
+  return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_finish_transform(const GramFinish& f, const TransformArgs& a, hipStream_t s) {
+  const Regulariser reg{a.reg_mode, a.lambda, a.ema_state, a.ema_decay};
+  if (f.n_seq > kTransformFinishMax || !a.info || a.batch != 1) return hipErrorInvalidValue;
+  return f.n_seq <= 64 ? launch_finish<4, 3>(f, a, reg, s) : launch_finish<8, 5>(f, a, reg, s);
+}
 
 hipError_t launch_transform(const TransformArgs& a, hipStream_t s) {
   const Regulariser reg{a.reg_mode, a.lambda, a.ema_state, a.ema_decay};

@@ -29,7 +29,7 @@ _VARIANTS = {"fisher": VARIANT_FISHER, "interacting": VARIANT_INTERACTING}
 _PATHS = {"auto": GRAM_AUTO, "ghost": GRAM_GHOST, "materialised": GRAM_MATERIALISED}
 _PATH_NAMES = {v: k for k, v in _PATHS.items()}
 
-EXPORTS = ("isopo_layer_gram_plan", "isopo_gram_cost_model", "isopo_contraction_plan", "isopo_layer_gram",
+EXPORTS = ("isopo_layer_step", "isopo_layer_gram_plan", "isopo_gram_cost_model", "isopo_contraction_plan", "isopo_layer_gram",
            "isopo_stash_layout_of", "isopo_weighted_grad_stash", "isopo_weighted_grad_stash_bf16", "isopo_seq_grads_stash",
            "isopo_transform_ema", "isopo_seq_grads_limited", "isopo_seq_grads",
            "isopo_stash_gram_workspace", "isopo_stash_gram", "isopo_transform_workspace",
@@ -83,6 +83,9 @@ def load() -> ctypes.CDLL:
     lib.isopo_contraction_plan.restype = ctypes.c_int
     lib.isopo_layer_gram.argtypes = [lp, ctypes.c_int, vp, vp, sz, ctypes.c_int, vp]
     lib.isopo_layer_gram.restype = ctypes.c_int
+    lib.isopo_layer_step.argtypes = [lp, ctypes.c_int, vp, ctypes.c_int, f32, ctypes.c_int, f32, vp, vp, vp, vp, vp, sz,
+                                     ctypes.c_int, ctypes.POINTER(ctypes.c_int), vp, sz, vp]
+    lib.isopo_layer_step.restype = ctypes.c_int
     lib.isopo_seq_grads.argtypes = [lp, vp, vp]
     lib.isopo_seq_grads.restype = ctypes.c_int
     lib.isopo_seq_grads_limited.argtypes = [lp, vp, i32, vp, vp]
@@ -617,20 +620,31 @@ def probe_contraction_waves(layer: Layer, waves: int, dW: Optional[torch.Tensor]
 def layer_step(layer: Layer, A: torch.Tensor, variant="interacting", lam: float = 0.0,
                reg_mode: int = REG_ABSOLUTE, path="auto", beta: float = 0.0, dW: Optional[torch.Tensor] = None,
                workspace: Optional[torch.Tensor] = None, stream=None) -> dict:
-    """The three calls chained on one stream with no host synchronisation.  The returned workspace holds
-    the stash in layout `stash_layout` (None: no stash was kept)."""
+    """layer_gram, transform and weighted_grad on one stream with no host synchronisation, as one call of the library.  The
+    returned workspace holds the stash in layout `stash_layout` (None: no stash was kept)."""
     chosen, full, least = gram_plan(layer, path)
     if workspace is None:
         workspace = alloc_workspace(full, layer.device)
-    if path == "auto" and workspace.numel() < least:
+    have = workspace.numel()
+    if path == "auto" and have < least:
         chosen = "ghost"                # what isopo_layer_gram then takes, or it raises
-    stream = _stream(stream)
-    keep = chosen == "materialised" and workspace.numel() >= full
-    K, workspace = layer_gram(layer, path, workspace=workspace, keep_stash=KEEP_FAST if keep else 0, stream=stream)
-    c, info = transform(K, A, variant, lam, reg_mode, stream=stream)
-    layout = stash_layout(layer)[0] if keep else None
-    if keep:
-        dW = weighted_grad(layer, c, workspace, beta, dW, stream=stream, layout=layout)
-    else:
-        dW = weighted_grad(layer, c, None, beta, dW, stream=stream)
-    return {"K": K, "c": c, "info": info, "dW": dW, "path": chosen, "workspace": workspace, "stash_layout": layout}
+    if A.dtype != torch.float32 or not A.is_contiguous():
+        raise ValueError("K and A must be contiguous fp32")
+    m = layer.n_seq
+    if dW is None:
+        if beta != 0.0:
+            raise ValueError("beta != 0 needs an existing dW")
+        dW = torch.empty((layer.d_out, layer.d_in), dtype=torch.float32, device=layer.device)
+    K = torch.empty((m, m), dtype=torch.float32, device=layer.device)
+    c = torch.empty_like(A)
+    info = torch.empty(1, dtype=torch.int32, device=layer.device)      # written by every launch: no fill
+    keep = chosen == "materialised" and have >= full
+    need = transform_workspace(m, 1) if m > 128 else 0
+    tws = alloc_workspace(need, layer.device) if need else None
+    layout = ctypes.c_int()
+    _check(load().isopo_layer_step(layer.ref(), _PATHS[path], A.data_ptr(), _VARIANTS[variant], float(lam), int(reg_mode),
+                                   float(beta), K.data_ptr(), c.data_ptr(), info.data_ptr(), dW.data_ptr(),
+                                   workspace.data_ptr(), have, KEEP_FAST if keep else 0, layout, _ptr(tws), need,
+                                   _stream(stream)), "isopo_layer_step")
+    return {"K": K, "c": c, "info": info, "dW": dW, "path": chosen, "workspace": workspace,
+            "stash_layout": layout.value if keep else None}

@@ -1,0 +1,65 @@
+"""The layer step as one call, whose coefficients up to 128 sequences come from the launch that finishes K, against the three calls:
+the same bits on either side of the sizes where the launches change, for either Gram path, and when replayed from a graph."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_23353_amd import isopo
+from paper_2512_23353_amd import workloads as wl
+
+from helpers import to_device
+
+pytestmark = pytest.mark.gpu
+
+
+def _three_calls(layer, A, variant, lam, path):
+    chosen = isopo.gram_plan(layer, path)[0]
+    keep = isopo.KEEP_FAST if chosen == "materialised" else 0
+    K, ws = isopo.layer_gram(layer, path, keep_stash=keep)
+    c, info = isopo.transform(K, A, variant, lam, isopo.REG_REL_TRACE)
+    dW = isopo.weighted_grad(layer, c, ws, layout=isopo.stash_layout(layer)[0]) if keep else isopo.weighted_grad(layer, c)
+    return dict(K=K, c=c, info=info, dW=dW, path=chosen)
+
+
+@pytest.mark.parametrize("dtype,m", [("f32", 1), ("f32", 16), ("f32", 17), ("f32", 33), ("f32", 80), ("f32", 128), ("bf16", 2), ("bf16", 16),
+                                     ("bf16", 17), ("bf16", 64), ("bf16", 65), ("bf16", 127), ("bf16", 129)])
+@pytest.mark.parametrize("variant", ["interacting", "fisher"])
+def test_one_call_is_three(gpu_device, dtype, m, variant):
+    lens = [(7 * i) % 40 + 1 for i in range(m)]
+    layer, A = to_device(wl.custom_layer(264, 328, lens, dtype=dtype, seed=m, sigma_delta=1e-2, rho=0.3), gpu_device)
+    want = _three_calls(layer, A, variant, 0.1, "materialised")
+    for _ in range(3):                       # whatever the allocator hands out
+        got = isopo.layer_step(layer, A, variant, 0.1, isopo.REG_REL_TRACE, "materialised")
+        assert got["path"] == "materialised" and got["stash_layout"] == isopo.stash_layout(layer)[0]
+        for key in ("K", "c", "info", "dW"):
+            assert torch.equal(got[key], want[key]), key
+
+
+@pytest.mark.parametrize("m", [3, 70])
+def test_not_positive_definite(gpu_device, m):
+    """A sequence without tokens and no regulariser: the pivot is named and c is NaN, as from the call by itself."""
+    lens = [8] * m
+    lens[m // 2] = 0
+    layer, A = to_device(wl.custom_layer(256, 256, lens, dtype="bf16", seed=m, sigma_delta=1e-2), gpu_device)
+    got = isopo.layer_step(layer, A, "interacting", 0.0, isopo.REG_ABSOLUTE, "materialised")
+    want = isopo.transform(got["K"], A, "interacting", 0.0, isopo.REG_ABSOLUTE)
+    assert got["info"].item() == want[1].item() > 0 and torch.isnan(got["c"]).all()
+
+
+def test_replayed(gpu_device):
+    layer, A = to_device(wl.custom_layer(256, 512, [40, 7, 0, 90, 33] * 5, dtype="bf16", seed=5, sigma_delta=1e-2, rho=0.3), gpu_device)
+    want = isopo.layer_step(layer, A, "interacting", 0.1, isopo.REG_REL_TRACE, "materialised")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = isopo.layer_step(layer, A, "interacting", 0.1, isopo.REG_REL_TRACE, "materialised")
+    for _ in range(4):
+        for key in ("K", "c", "dW"):
+            got[key].fill_(float("nan"))
+        got["info"].fill_(77)
+        graph.replay()
+        other = isopo.layer_step(layer, A, "fisher", 0.1, isopo.REG_REL_TRACE, "materialised")
+        torch.cuda.synchronize()
+        assert not torch.equal(other["c"], want["c"])
+        for key in ("K", "c", "info", "dW"):
+            assert torch.equal(got[key], want[key]), key
