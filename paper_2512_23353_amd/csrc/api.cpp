@@ -253,7 +253,11 @@ static isopo_status layer_gram(const isopo_layer* layer, isopo_gram_path path, f
     g.parts = reinterpret_cast<float*>(reinterpret_cast<char*>(g.tok_seq) +
                                        align_up((size_t)layer->n_tokens * sizeof(int32_t)));
     g.K = K;
-    return launch_ghost_gram(g, s) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
+    g.sums_only = then && layer->n_seq <= kTransformFinishMax;
+    if (launch_ghost_gram(g, s) != hipSuccess) return ISOPO_ERR_HIP;
+    if (!g.sums_only) return ISOPO_OK;
+    *fused = true;
+    return launch_ghost_finish_transform(g.K64, K, *then, s) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
   }
 
   if (keep_stash < 0 || keep_stash > 2) return ISOPO_ERR_INVALID_ARG;

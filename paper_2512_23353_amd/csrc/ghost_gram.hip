@@ -21,21 +21,23 @@
 namespace isopo {
 namespace {
 
-__global__ void token_seq_kernel(const int32_t* __restrict__ off, int n_seq, int n_tokens,
-                                 int32_t* __restrict__ tok_seq) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_tokens) return;
-  int lo = 0, hi = n_seq;   // largest i with off[i] <= t (empty sequences are skipped by the <=)
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (off[mid] <= t) lo = mid; else hi = mid;
+// What the segment sums start from: the sequence of every token, and K64 cleared.  Thread `first` of `step`.
+__device__ __forceinline__ void ghost_prepare(const int32_t* __restrict__ off, int n_seq, int n_tokens, int32_t* __restrict__ tok_seq,
+                                              double* __restrict__ K64, int first, int step) {
+  for (int t = first; t < n_tokens; t += step) {
+    int lo = 0, hi = n_seq;   // largest i with off[i] <= t (empty sequences are skipped by the <=)
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (off[mid] <= t) lo = mid; else hi = mid;
+    }
+    tok_seq[t] = lo;
   }
-  tok_seq[t] = lo;
+  for (int i = first; i < n_seq * n_seq; i += step) K64[i] = 0.0;
 }
 
-__global__ void fill_f64_kernel(double* p, long long n) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.0;
+__global__ __launch_bounds__(256) void ghost_prepare_kernel(const int32_t* __restrict__ off, int n_seq, int n_tokens,
+                                                            int32_t* __restrict__ tok_seq, double* __restrict__ K64) {
+  ghost_prepare(off, n_seq, n_tokens, tok_seq, K64, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
 }
 
 // One 32x32 block of the token-pair matrix: rows t0.., columns s0.. .  False when the block lies past the last
@@ -344,14 +346,17 @@ constexpr int kGTileFloats = 16 * kGBlockFloats;  // the 16 blocks of a 128x128 
 // SPLIT = true (few tile pairs, a short microbatch): the 64-feature slices of both operands are cut into
 // `count` ranges and workgroup (pair, a) forms the parts P_a, Q_a of the two products over range a only; the
 // parts go to `parts` [pair][a][P, Q][block][lane][v] in fp32, and ghost_gram_parts_kernel sums them before
-// the Hadamard product, which is not linear in the ranges.
+// the Hadamard product, which is not linear in the ranges.  The first kPrepareBlocks workgroups prepare that kernel's token map and
+// sums meanwhile: a launch of its own costs the chain 3 us.
+constexpr int kPrepareBlocks = 16;                // a multiple of eight: the others keep their XCDs
 template <bool SPLIT>
 __global__ __launch_bounds__(256, 2) void ghost_gram_tiled_kernel(const unsigned short* __restrict__ X,
                                                                const unsigned short* __restrict__ Delta,
                                                                const int32_t* __restrict__ tok_seq, int n_tokens,
                                                                int d_in, int d_out, int n_seq, int n_tiles,
                                                                int count, float* __restrict__ parts,
-                                                               double* __restrict__ K64) {
+                                                               double* __restrict__ K64, const int32_t* __restrict__ off,
+                                                               int32_t* __restrict__ tok_out) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int split = SPLIT ? count : 1;
   const unsigned smem_base = (unsigned)(size_t)(lds_void_ptr)smem;
@@ -360,7 +365,11 @@ __global__ __launch_bounds__(256, 2) void ghost_gram_tiled_kernel(const unsigned
     // Workgroups go to the eight XCDs round robin.  XCD x takes the x-th eighth of the range-major list of
     // (range, tile pair): the columns of X and Delta that a range covers then pass through one or two L2s,
     // not all eight.
-    const int x = blockIdx.x & 7, e = blockIdx.x >> 3;
+    if (blockIdx.x < kPrepareBlocks) {
+      ghost_prepare(off, n_seq, n_tokens, tok_out, K64, blockIdx.x * 256 + threadIdx.x, kPrepareBlocks * 256);
+      return;
+    }
+    const int x = blockIdx.x & 7, e = (blockIdx.x - kPrepareBlocks) >> 3;
     const int n_pairs = n_tiles * (n_tiles + 1) / 2, total = n_pairs * split;       // at most 512
     const int first = x * total / 8;
     if (e >= (x + 1) * total / 8 - first) return;                    // the grid is padded to 8 * ceil(total / 8)
@@ -479,10 +488,13 @@ __global__ void ghost_finish_kernel(const double* __restrict__ K64, int n_seq, f
 
 hipError_t launch_ghost_gram(const GhostArgs& a, hipStream_t s) {
   const long long kk = (long long)a.n_seq * a.n_seq;
-  hipLaunchKernelGGL(fill_f64_kernel, dim3((unsigned)((kk + 255) / 256)), dim3(256), 0, s, a.K64, kk);
+  const int split = a.bf16 && a.n_tokens > 0 ? ghost_feature_split(a.n_tokens, a.d_in, a.d_out) : 1;
+  if (split == 1) {
+    const long long most = kk > a.n_tokens ? kk : a.n_tokens;
+    hipLaunchKernelGGL(ghost_prepare_kernel, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, s, a.off, a.n_seq, a.n_tokens,
+                       a.tok_seq, a.K64);
+  }
   if (a.n_tokens > 0) {
-    hipLaunchKernelGGL(token_seq_kernel, dim3((a.n_tokens + 255) / 256), dim3(256), 0, s, a.off, a.n_seq, a.n_tokens,
-                       a.tok_seq);
     const long long n_tiles = (a.n_tokens + 63) / 64;
     const long long pairs = n_tiles * (n_tiles + 1) / 2;
     if (pairs > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -498,15 +510,14 @@ hipError_t launch_ghost_gram(const GhostArgs& a, hipStream_t s) {
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
       }();
       if (attr != hipSuccess) return attr;
-      const int split = ghost_feature_split(a.n_tokens, a.d_in, a.d_out);
       const unsigned n_pairs = (unsigned)((long long)nt * (nt + 1) / 2);
       const unsigned short* Xb = static_cast<const unsigned short*>(a.X);
       const unsigned short* Db = static_cast<const unsigned short*>(a.Delta);
       if (split > 1) {
         if (!a.parts) return hipErrorInvalidValue;
-        const unsigned grid = 8 * ((n_pairs * split + 7) / 8);
+        const unsigned grid = kPrepareBlocks + 8 * ((n_pairs * split + 7) / 8);
         hipLaunchKernelGGL(ghost_gram_tiled_kernel<true>, dim3(grid), dim3(256), smem, s, Xb, Db, a.tok_seq,
-                           a.n_tokens, a.d_in, a.d_out, a.n_seq, nt, split, a.parts, a.K64);
+                           a.n_tokens, a.d_in, a.d_out, a.n_seq, nt, split, a.parts, a.K64, a.off, a.tok_seq);
         hipLaunchKernelGGL(ghost_gram_parts_kernel, dim3(n_pairs * 16), dim3(256), 0, s, a.parts, a.tok_seq, a.n_tokens,
                            a.n_seq, nt, split, a.K64);
       } else {
@@ -514,12 +525,14 @@ hipError_t launch_ghost_gram(const GhostArgs& a, hipStream_t s) {
         const unsigned n_runs = 8 * ((n_pairs + 8 * kGRun - 1) / (8 * kGRun));
         const unsigned run = (n_pairs + n_runs - 1) / n_runs;
         hipLaunchKernelGGL(ghost_gram_tiled_kernel<false>, dim3(n_runs * run), dim3(256), smem, s, Xb, Db, a.tok_seq,
-                           a.n_tokens, a.d_in, a.d_out, a.n_seq, nt, (int)run, static_cast<float*>(nullptr), a.K64);
+                           a.n_tokens, a.d_in, a.d_out, a.n_seq, nt, (int)run, static_cast<float*>(nullptr), a.K64, a.off,
+                           static_cast<int32_t*>(nullptr));
       }
     } else
       hipLaunchKernelGGL((ghost_gram_kernel<false>), dim3((unsigned)pairs), dim3(256), 0, s, a.X, a.Delta, a.tok_seq,
                          a.n_tokens, a.d_in, a.d_out, a.n_seq, (int)n_tiles, a.K64);
   }
+  if (a.sums_only) return hipGetLastError();
   hipLaunchKernelGGL(ghost_finish_kernel, dim3((unsigned)((kk + 255) / 256)), dim3(256), 0, s, a.K64, a.n_seq, a.K);
   return hipGetLastError();
 }

@@ -135,6 +135,7 @@ struct GhostArgs {
   double* K64;               // workspace [n_seq*n_seq]
   float* parts;              // workspace [ghost_parts_bytes / 4], bf16 with ghost_feature_split > 1 only
   float* K;
+  bool sums_only = false;    // K64 is what the caller goes on from (launch_ghost_finish_transform)
 };
 hipError_t launch_ghost_gram(const GhostArgs& a, hipStream_t s);
 // bf16 ghost kernel: ranges the 64-feature slices of X and Delta are cut into when the microbatch has too few
@@ -233,6 +234,8 @@ hipError_t launch_transform(const TransformArgs& a, hipStream_t s);
 // kTransformFinishMax sequences
 constexpr int kTransformFinishMax = 128;
 hipError_t launch_finish_transform(const GramFinish& f, const TransformArgs& a, hipStream_t s);
+// the same after launch_ghost_gram's K64: K, then its transform
+hipError_t launch_ghost_finish_transform(const double* K64, float* K, const TransformArgs& a, hipStream_t s);
 
 // Generalised (p, q, r) re-scaling of the per-sequence coefficients.
 struct RescaleArgs {

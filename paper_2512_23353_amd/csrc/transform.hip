@@ -681,6 +681,30 @@ hipError_t launch_regs(const TransformArgs& a, const Regulariser& reg, hipStream
   return hipGetLastError();
 }
 
+// K from the token products' 64-bit sums, and the coefficients, in one workgroup: a launch less.  With the chain's preparation in the
+// launch of the products (ghost_gram.hip) 5120x27648, 8 sequences of 64 to 256 tokens 514 -> 504 us a layer step.
+template <int W, int S>
+__global__ __launch_bounds__(kFinishThreads) void ghost_finish_transform_kernel(const double* __restrict__ K64, float* K, int m,
+                                                                                const float* __restrict__ A, int variant,
+                                                                                Regulariser prm, float* __restrict__ c, int32_t* info) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  for (int e = threadIdx.x; e < m * m; e += kFinishThreads) {
+    const int i = e / m, j = e % m;
+    if (i <= j) {
+      const float v = (float)K64[e];
+      K[(size_t)i * m + j] = v;
+      K[(size_t)j * m + i] = v;
+    }
+  }
+  __syncthreads();
+  if (variant == 0) {
+    fisher_transform<kFinishThreads, 1, false>(K, A, m, prm, 0, c, info);
+    return;
+  }
+  if (threadIdx.x >= 64 * W) return;
+  transform_regs<W, S, 1, false>(K, A, m, prm, 0, c, info, smem);
+}
+
 template <int W, int S>
 hipError_t launch_finish(const GramFinish& f, const TransformArgs& a, const Regulariser& reg, hipStream_t s) {
   static_assert(transform_regs_lds(16 * W) + sizeof(double) * (1024 + ISOPO_MAX_SEQ_TRANSFORM) <= 60 * 1024, "LDS without a limit raised");
@@ -689,7 +713,20 @@ hipError_t launch_finish(const GramFinish& f, const TransformArgs& a, const Regu
   return hipGetLastError();
 }
 
+template <int W, int S>
+hipError_t launch_ghost_finish(const double* K64, float* K, const TransformArgs& a, const Regulariser& reg, hipStream_t s) {
+  hipLaunchKernelGGL((ghost_finish_transform_kernel<W, S>), dim3(1), dim3(kFinishThreads), transform_regs_lds(a.n_seq), s, K64, K, a.n_seq,
+                     a.A, a.variant, reg, a.c, a.info);
+  return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_ghost_finish_transform(const double* K64, float* K, const TransformArgs& a, hipStream_t s) {
+  const Regulariser reg{a.reg_mode, a.lambda, a.ema_state, a.ema_decay};
+  if (a.n_seq > kTransformFinishMax || a.batch != 1) return hipErrorInvalidValue;
+  return a.n_seq <= 64 ? launch_ghost_finish<4, 3>(K64, K, a, reg, s) : launch_ghost_finish<8, 5>(K64, K, a, reg, s);
+}
 
 hipError_t launch_finish_transform(const GramFinish& f, const TransformArgs& a, hipStream_t s) {
   const Regulariser reg{a.reg_mode, a.lambda, a.ema_state, a.ema_decay};

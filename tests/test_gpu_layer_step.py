@@ -35,6 +35,24 @@ def test_one_call_is_three(gpu_device, dtype, m, variant):
             assert torch.equal(got[key], want[key]), key
 
 
+@pytest.mark.parametrize("dtype,d_out,lens", [("bf16", 4096, [33, 0, 128, 1]), ("bf16", 520, [5] * 16), ("bf16", 1032, [3, 40] * 32),
+                                              ("bf16", 1032, [9] * 65), ("bf16", 264, [5, 30] * 64), ("bf16", 264, [4] * 130),
+                                              ("f32", 328, [20, 0, 31]), ("f32", 328, [7] * 66)])
+@pytest.mark.parametrize("variant", ["interacting", "fisher"])
+def test_token_products(gpu_device, dtype, d_out, lens, variant):
+    """K twice (its 64-bit sums come in any order, so to one rounding), and from the step's own K the same coefficients."""
+    layer, A = to_device(wl.custom_layer(512, d_out, lens, dtype=dtype, seed=len(lens), sigma_delta=1e-2, rho=0.3), gpu_device)
+    want = _three_calls(layer, A, variant, 0.1, "ghost")
+    for _ in range(2):
+        got = isopo.layer_step(layer, A, variant, 0.1, isopo.REG_REL_TRACE, "ghost")
+        K, ref = got["K"].double(), want["K"].double()
+        scale = ref.diagonal().sqrt()
+        assert torch.equal(got["K"], got["K"].t()) and got["stash_layout"] is None
+        assert ((K - ref).abs() <= 2.0 ** -23 * ref.abs() + 2.0 ** -40 * scale[:, None] * scale[None, :]).all()
+        c, info = isopo.transform(got["K"], A, variant, 0.1, isopo.REG_REL_TRACE)
+        assert torch.equal(got["c"], c) and torch.equal(got["info"], info)
+
+
 @pytest.mark.parametrize("m", [3, 70])
 def test_not_positive_definite(gpu_device, m):
     """A sequence without tokens and no regulariser: the pivot is named and c is NaN, as from the call by itself."""
