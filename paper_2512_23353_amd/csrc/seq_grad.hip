@@ -315,17 +315,32 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
     bool have0 = fetch(r[0], s0, n0), have1 = fetch(r[1], s1, n1);
     if (have0) { sstore(split, r[0], 0, s0, n0); in0 = n0; }
     __syncthreads();
+    // The step in LDS buffer `buf` multiplied and the next one, `d`, split and stored in the other: one straight run of code, five
+    // of the splitting's instructions behind each MFMA.  (A step that is none any more arrives as zeros and is read by nobody; a wave
+    // without outputs multiplies zeros.)  One after the other, each behind a branch, the two took 3 % more: 2048x2048, 16 sequences,
+    // 9345 tokens 435 -> 421 us; 36x1400, 20 of 480 35.8 -> 33.1; the weighted sum 3072x768, 4394 tokens 135 -> 131.  Four or six and
+    // more between: 1 to 2 % of that lost.
+    auto step = [&](int buf, int tokens, float (&d)[8][FPL], float scale, int rows) __attribute__((always_inline)) {
+      compute(split, buf, tokens);
+      sstore(split, d, buf ^ 1, scale, rows);
+      if constexpr (split) {
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 * NB * kParts, 0);         // LDS reads
+#pragma unroll
+        for (int q = 0; q < 6 * NB * NB; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);                       // MFMA
+          __builtin_amdgcn_sched_group_barrier(0x2, 5, 0);                       // VALU
+        }
+      }
+    };
     while (have0) {
       const bool have2 = fetch(r[0], s0, n0);
-      if (live) compute(split, 0, in0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (have1) { sstore(split, r[1], 1, s1, n1); in1 = n1; }
+      step(0, in0, r[1], s1, n1);
+      in1 = n1;
       __syncthreads();
       if (!have1) break;
       have1 = fetch(r[1], s1, n1);
-      if (live) compute(split, 1, in1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (have2) { sstore(split, r[0], 0, s0, n0); in0 = n0; }
+      step(1, in1, r[0], s0, n0);
+      in0 = n0;
       __syncthreads();
       have0 = have2;
     }
