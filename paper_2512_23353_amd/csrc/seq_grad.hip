@@ -150,8 +150,8 @@ __device__ __forceinline__ int sequence_by_length(const int32_t* off, int n_seq,
 }
 
 // WT: side of a wave's square of outputs (64 or 32); a tile is 2 WT on a side.  KG groups of four waves share a
-// tile: group g takes every KG-th block of tokens, the groups' sums meet in LDS.
-template <int WT, int KG, bool WEIGHTED>
+// tile: group g takes every KG-th block of tokens, the groups' sums meet in LDS.  THROUGH: the stash goes past the L2s at once.
+template <int WT, int KG, bool WEIGHTED, bool THROUGH>
 __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void seq_grad_kernel(SeqGradParams p) {
   constexpr int BT = 2 * WT, NB = WT / 32;           // NB x NB MFMA blocks of 32x32 per wave
   constexpr int FPL = BT / 64;                       // features a lane stages
@@ -408,14 +408,16 @@ __global__ __launch_bounds__(256 * KG, WT == 64 ? 3 : (KG == 1 ? 6 : KG)) void s
           if (p.atomic) atomicAdd(o, acc[i][j][v]);
           else *o = (p.beta != 0.f ? p.beta * *o : 0.f) + acc[i][j][v];
         } else {
-          p.out[(size_t)item * p.out_seq_stride + idx] = acc[i][j][v];
+          float* const o = p.out + (size_t)item * p.out_seq_stride + idx;
+          if constexpr (THROUGH) __hip_atomic_store(o, (float)acc[i][j][v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       // sc1
+          else *o = acc[i][j][v];
         }
       }
     }
   }
 }
 
-template <int WT, int KG, bool WEIGHTED>
+template <int WT, int KG, bool WEIGHTED, bool THROUGH>
 hipError_t launch_cfg(SeqGradParams p, int rows, long long items, hipStream_t s) {
   constexpr int BT = 2 * WT;
   p.tiles_n = (p.d_in + BT - 1) / BT;
@@ -425,7 +427,7 @@ hipError_t launch_cfg(SeqGradParams p, int rows, long long items, hipStream_t s)
   p.tiles = (int)tiles;
   constexpr size_t smem = (size_t)KG * group_lds(BT);
   static_assert(smem >= (size_t)(KG - 1) * WT * WT * 4 * sizeof(float), "the groups' sums meet in LDS");
-  auto kern = seq_grad_kernel<WT, KG, WEIGHTED>;
+  auto kern = seq_grad_kernel<WT, KG, WEIGHTED, THROUGH>;
   // once per process and instantiation (static initialisation is thread-safe); a failure is returned by every call
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -434,11 +436,11 @@ hipError_t launch_cfg(SeqGradParams p, int rows, long long items, hipStream_t s)
   return hipGetLastError();
 }
 
-template <bool WEIGHTED>
+template <bool WEIGHTED, bool THROUGH>
 hipError_t launch_plan(const SeqGradParams& p, const SplitContractionPlan& pl, int rows, long long items, hipStream_t s) {
-  if (pl.tile == 128) return launch_cfg<64, 1, WEIGHTED>(p, rows, items, s);
-  if (pl.groups == 1) return launch_cfg<32, 1, WEIGHTED>(p, rows, items, s);
-  return pl.groups == 2 ? launch_cfg<32, 2, WEIGHTED>(p, rows, items, s) : launch_cfg<32, 4, WEIGHTED>(p, rows, items, s);
+  if (pl.tile == 128) return launch_cfg<64, 1, WEIGHTED, THROUGH>(p, rows, items, s);
+  if (pl.groups == 1) return launch_cfg<32, 1, WEIGHTED, THROUGH>(p, rows, items, s);
+  return pl.groups == 2 ? launch_cfg<32, 2, WEIGHTED, THROUGH>(p, rows, items, s) : launch_cfg<32, 4, WEIGHTED, THROUGH>(p, rows, items, s);
 }
 
 }  // namespace
@@ -461,14 +463,21 @@ hipError_t launch_seq_grad(const SeqGradArgs& a, hipStream_t s) {
   p.few_tokens = a.n_tokens <= kFewTokens * blocks;
   const SplitContractionPlan pl = plan_split_contraction(a.rows, a.d_in, a.n_tokens, a.n_seq, a.off_host, a.per_sequence);
   p.longest_first = pl.longest_first;
-  if (a.per_sequence) return launch_plan<false>(p, pl, a.rows, a.n_seq, s);
+  if (a.per_sequence) {
+    // Stores past the L2s leave nothing to be written back behind the launch: whole calls 892x256, 19 sequences of 57 tokens 37.3 -> 35.3
+    // us; 336x512, 7 of 28 23.1 -> 21.8; 1536x1536, 16 of 668 328 -> 325.  A row that does not start at a line leaves pieces of lines,
+    // which then go to memory one by one instead of meeting in the L2: 1220x300, 40 of 147 (58 MB) 87.5 -> 89.8, so those only where the
+    // L2s (32 MiB) hold the stash (2652x440, 6 of 41 45.2 -> 44.1; 768x468, 3 of 39 24.1 -> 23.3).
+    if (a.d_in % 32 == 0 || (long long)a.n_seq * a.rows * a.d_in * 4 <= 32LL << 20) return launch_plan<false, true>(p, pl, a.rows, a.n_seq, s);
+    return launch_plan<false, false>(p, pl, a.rows, a.n_seq, s);
+  }
   p.chunk_tokens = pl.chunk_tokens;
   if (pl.n_chunks > 1) {
     p.atomic = 1;
     const hipError_t e = launch_apply_beta(p.out + (size_t)(a.row0 - a.out_row0) * a.d_in, (long long)a.rows * a.d_in, a.beta, s);
     if (e != hipSuccess) return e;
   }
-  return launch_plan<true>(p, pl, a.rows, pl.n_chunks, s);
+  return launch_plan<true, false>(p, pl, a.rows, pl.n_chunks, s);
 }
 
 }  // namespace isopo
