@@ -58,8 +58,8 @@ struct OrderedWalkParams : WalkParams {
 
 // T: side of the output tile.  NW: waves per workgroup, a 2 x NW/2 arrangement of wave tiles; four on the per-sequence launch
 // (on the 256x256 tile one wave per SIMD with its 256 accumulators per lane pinned to the AGPRs), eight on the sums (two waves
-// per SIMD, 128 accumulators per lane in VGPRs), as in seq_grad_stream.hip.
-template <int T, int KIND, int WALK, bool TILED, int NW, class Params>
+// per SIMD, 128 accumulators per lane in VGPRs), as in seq_grad_stream.hip.  THROUGH: a row-major stash goes past the L2s at once.
+template <int T, int KIND, int WALK, bool TILED, int NW, bool THROUGH, class Params>
 __device__ __forceinline__ void seq_grad_walk_body(const Params& p_) {
   static_assert(KIND == kSeq || !TILED, "tile order is a layout of the per-sequence stash");
   static_assert(NW == 4 || NW == 8, "waves per workgroup");
@@ -520,7 +520,8 @@ __device__ __forceinline__ void seq_grad_walk_body(const Params& p_) {
             // non-temporally each goes to memory by itself: 2216x632, 83 sequences of 41 tokens: 57 us against 158;
             // 3256x2560, 28 of 346: 291 against 367; 568x1104, 79 of 213: 46 against 64.  Widths whose rows start at lines
             // are level on average (256x1536, 85 of 750: 83 against 74; 512x3328, 40 of 24: 40 against 50).
-            __builtin_amdgcn_raw_buffer_store_b128(pk, rs, voff[j], 0, 0);
+            constexpr int kSc1 = 16;
+            __builtin_amdgcn_raw_buffer_store_b128(pk, rs, voff[j], 0, THROUGH ? kSc1 : 0);
           }
         } else {
           f32x4v old[FN];
@@ -549,22 +550,22 @@ __device__ __forceinline__ void seq_grad_walk_body(const Params& p_) {
   __builtin_amdgcn_s_waitcnt(0x0f70);                          // loads into the LDS of a workgroup that is gone
 }
 
-template <int T, int OCC, int WALK, bool TILED, class Params>
+template <int T, int OCC, int WALK, bool TILED, bool THROUGH, class Params>
 __global__ __launch_bounds__(256, OCC) void seq_grad_walk_kernel(Params p) {
-  seq_grad_walk_body<T, kSeq, WALK, TILED, 4>(p);
+  seq_grad_walk_body<T, kSeq, WALK, TILED, 4, THROUGH>(p);
 }
 
 template <int T, int OCC, int KIND>
 __global__ __launch_bounds__(512, OCC) void seq_grad_walk_waves8_kernel(WalkParams p) {
-  seq_grad_walk_body<T, KIND, kDealt, false, 8>(p);
+  seq_grad_walk_body<T, KIND, kDealt, false, 8, false>(p);
 }
 
-template <int T, int OCC, int KIND, int WALK, bool TILED, int NW, class Params>
+template <int T, int OCC, int KIND, int WALK, bool TILED, int NW, bool THROUGH, class Params>
 hipError_t launch_walk(const Params& p, hipStream_t s) {
   constexpr size_t smem = (size_t)NSTAGE * BK * T * 2 * 2;
   auto kern = [] {
     if constexpr (NW == 8) return &seq_grad_walk_waves8_kernel<T, OCC, KIND>;
-    else return &seq_grad_walk_kernel<T, OCC, WALK, TILED, Params>;
+    else return &seq_grad_walk_kernel<T, OCC, WALK, TILED, THROUGH, Params>;
   }();
   // once per process (static initialisation is thread-safe); a failure is returned by every call
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -605,10 +606,10 @@ hipError_t launch_sum(const SeqGradArgs& a, const ContractionPlan& pl, hipStream
   hipError_t status;
   if (!fill_params(a, pl, p, status)) return status;
   p.per_xcd = std::min((pl.tiles_m * pl.tiles_n + 7) / 8, 32);
-  return launch_walk<256, 1, KIND, kDealt, false, 8>(p, s);
+  return launch_walk<256, 1, KIND, kDealt, false, 8, false>(p, s);
 }
 
-template <int T, int OCC, bool TILED>
+template <int T, int OCC, bool TILED, bool THROUGH>
 hipError_t launch_sequences(const SeqGradArgs& a, const ContractionPlan& pl, hipStream_t s) {
   OrderedWalkParams p;
   hipError_t status;
@@ -619,8 +620,9 @@ hipError_t launch_sequences(const SeqGradArgs& a, const ContractionPlan& pl, hip
   if (budget > 0) p.queue = a.queue;
   for (int x = 0; x < 8; ++x) p.xcd[x] = {w.first[x], w.first[x + 1], w.alone[x], 0};
   if constexpr (T == 128)
-    if (w.kind == kSingle) return launch_walk<T, OCC, kSeq, kSingle, TILED, 4>(static_cast<const WalkParams&>(p), s);
-  return w.kind == kRanges ? launch_walk<T, OCC, kSeq, kRanges, TILED, 4>(p, s) : launch_walk<T, OCC, kSeq, kDealt, TILED, 4>(p, s);
+    if (w.kind == kSingle) return launch_walk<T, OCC, kSeq, kSingle, TILED, 4, THROUGH>(static_cast<const WalkParams&>(p), s);
+  return w.kind == kRanges ? launch_walk<T, OCC, kSeq, kRanges, TILED, 4, THROUGH>(p, s)
+                           : launch_walk<T, OCC, kSeq, kDealt, TILED, 4, THROUGH>(p, s);
 }
 
 }  // namespace
@@ -631,9 +633,15 @@ hipError_t launch_seq_grad_walk(const SeqGradArgs& a, const ContractionPlan& pl,
     if (a.tile_order) {
       // the caller has checked stash_tile_order_ok; anything else would scatter the stores
       if (a.rows % pl.tile || a.d_in % pl.tile || a.row0 % pl.tile || a.out_row0 % pl.tile) return hipErrorInvalidValue;
-      return big ? launch_sequences<256, 1, true>(a, pl, s) : launch_sequences<128, 2, true>(a, pl, s);
+      return big ? launch_sequences<256, 1, true, false>(a, pl, s) : launch_sequences<128, 2, true, false>(a, pl, s);
     }
-    return big ? launch_sequences<256, 1, false>(a, pl, s) : launch_sequences<128, 2, false>(a, pl, s);
+    // Row by row, where rows start at lines and the last-level cache (256 MiB) takes the stash: past the L2s at once, as in tile order.
+    // Whole steps, us through the L2 and past it: 1448x256, 7 sequences of 512 tokens 26.9 / 25.5; 248x4800, 10 of 24 38.0 / 36.4;
+    // 1488x1792, 9 of 745 61.2 / 59.9; 24 random ones 0.985x, the slowest 1.003x.  Larger stashes lose (1280x2944, 126 of 126, 950 MB
+    // 634 / 668), and rows that start within lines up to a third (264x824, 201 of 88 90 / 119).
+    if (a.d_in % 64 == 0 && 2LL * a.n_seq * a.rows * a.d_in <= 256LL << 20)
+      return big ? launch_sequences<256, 1, false, true>(a, pl, s) : launch_sequences<128, 2, false, true>(a, pl, s);
+    return big ? launch_sequences<256, 1, false, false>(a, pl, s) : launch_sequences<128, 2, false, false>(a, pl, s);
   }
   if (!big || pl.n_chunks > 1) return hipErrorInvalidValue;
   return a.c != nullptr ? launch_sum<kWeighted>(a, pl, s) : launch_sum<kSum>(a, pl, s);
