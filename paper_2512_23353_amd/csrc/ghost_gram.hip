@@ -21,10 +21,11 @@
 namespace isopo {
 namespace {
 
-// What the segment sums start from: the sequence of every token, and K64 cleared.  Thread `first` of `step`.
+// What the segment sums start from: the sequence of every token, and K64 cleared.  Thread `first` of `step`; in 64 bits, for the sum
+// of the two may pass 2^31.
 __device__ __forceinline__ void ghost_prepare(const int32_t* __restrict__ off, int n_seq, int n_tokens, int32_t* __restrict__ tok_seq,
-                                              double* __restrict__ K64, int first, int step) {
-  for (int t = first; t < n_tokens; t += step) {
+                                              double* __restrict__ K64, long long first, long long step) {
+  for (long long t = first; t < n_tokens; t += step) {
     int lo = 0, hi = n_seq;   // largest i with off[i] <= t (empty sequences are skipped by the <=)
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
@@ -32,12 +33,12 @@ __device__ __forceinline__ void ghost_prepare(const int32_t* __restrict__ off, i
     }
     tok_seq[t] = lo;
   }
-  for (int i = first; i < n_seq * n_seq; i += step) K64[i] = 0.0;
+  for (long long i = first; i < n_seq * n_seq; i += step) K64[i] = 0.0;
 }
 
 __global__ __launch_bounds__(256) void ghost_prepare_kernel(const int32_t* __restrict__ off, int n_seq, int n_tokens,
                                                             int32_t* __restrict__ tok_seq, double* __restrict__ K64) {
-  ghost_prepare(off, n_seq, n_tokens, tok_seq, K64, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
+  ghost_prepare(off, n_seq, n_tokens, tok_seq, K64, blockIdx.x * 256LL + threadIdx.x, gridDim.x * 256LL);
 }
 
 // One 32x32 block of the token-pair matrix: rows t0.., columns s0.. .  False when the block lies past the last
@@ -488,6 +489,8 @@ __global__ void ghost_finish_kernel(const double* __restrict__ K64, int n_seq, f
 
 hipError_t launch_ghost_gram(const GhostArgs& a, hipStream_t s) {
   const long long kk = (long long)a.n_seq * a.n_seq;
+  const long long n_tiles = (a.n_tokens + 63LL) / 64, pairs = n_tiles * (n_tiles + 1) / 2;
+  if (pairs > 0x7fffffffLL) return hipErrorInvalidValue;               // before anything is launched
   const int split = a.bf16 && a.n_tokens > 0 ? ghost_feature_split(a.n_tokens, a.d_in, a.d_out) : 1;
   if (split == 1) {
     const long long most = kk > a.n_tokens ? kk : a.n_tokens;
@@ -495,9 +498,6 @@ hipError_t launch_ghost_gram(const GhostArgs& a, hipStream_t s) {
                        a.tok_seq, a.K64);
   }
   if (a.n_tokens > 0) {
-    const long long n_tiles = (a.n_tokens + 63) / 64;
-    const long long pairs = n_tiles * (n_tiles + 1) / 2;
-    if (pairs > 0x7fffffffLL) return hipErrorInvalidValue;
     if (a.bf16) {
       const int nt = (a.n_tokens + kGT - 1) / kGT;
       constexpr size_t smem = (size_t)kGStages * kGStageBytes;

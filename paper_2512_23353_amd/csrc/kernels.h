@@ -161,7 +161,7 @@ inline double ghost_walk_time(long long pairs, int d_in, int d_out, int split) {
   return split > 1 ? walk + kGhostParts + (double)pairs * split * kGhostPartBytes / kRateGhostParts : walk;
 }
 inline int ghost_feature_split(int n_tokens, int d_in, int d_out) {
-  const long long nt = (n_tokens + 127) / 128, pairs = nt * (nt + 1) / 2;
+  const long long nt = (n_tokens + 127LL) / 128, pairs = nt * (nt + 1) / 2;
   if (pairs <= 0) return 1;
   const long long slices = (d_in + 63) / 64 + (d_out + 63) / 64;
   long long most = 512 / pairs;                        // two workgroups per compute unit (LDS ring: 64 KiB)

@@ -8,6 +8,8 @@
 #include <cstdlib>
 #include <vector>
 
+#include <hip/hip_runtime.h>
+
 #include "../include/isopo.h"
 
 static std::vector<int32_t> offsets(const std::vector<int32_t>& lengths) {
@@ -20,6 +22,13 @@ static unsigned long long rng_state = 88172645463325252ULL;
 static unsigned rnd(unsigned lo, unsigned hi) {            // xorshift64: fixed, portable sequence
   rng_state ^= rng_state << 13; rng_state ^= rng_state >> 7; rng_state ^= rng_state << 17;
   return lo + (unsigned)(rng_state % (hi - lo + 1));
+}
+
+// Every kernel launch of the library's host code begins with this call of the runtime: counted here, and nothing is launched.
+static int launches = 0;
+extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) {
+  ++launches;
+  return hipErrorNotSupported;
 }
 
 static int failures = 0;
@@ -151,6 +160,23 @@ int main() {
     EXPECT(isopo_ntk_eigh_workspace(0, 1) == 0 && isopo_ntk_eigh_workspace(300, 2) > 0);
     for (int s = 0; s <= 6; ++s) EXPECT(isopo_status_string((isopo_status)s) != nullptr);
   }
+  // Token products of more tokens than a launch has pairs of tiles for (65535 tiles of 64): refused before anything is launched, on
+  // either type, also next to 2^31.  The addresses are only checked for alignment.
+  for (const int64_t n : {(int64_t)65535 * 64 + 1, (int64_t)1 << 30, (int64_t)1200000000, ((int64_t)1 << 31) - 1})
+    for (const isopo_dtype dtype : {ISOPO_F32, ISOPO_BF16}) {
+      const std::vector<int32_t> off = {0, (int32_t)(n / 2), (int32_t)n};
+      void* const there = reinterpret_cast<void*>((uintptr_t)1 << 20);
+      isopo_layer l{};
+      l.dtype = dtype; l.n_tokens = n; l.d_in = 64; l.d_out = 64; l.n_seq = 2; l.seq_offsets_host = off.data();
+      l.seq_offsets_dev = static_cast<int32_t*>(there); l.X = there; l.Delta = there;
+      launches = 0;
+      EXPECT(isopo_layer_gram(&l, ISOPO_GRAM_GHOST, static_cast<float*>(there), there, (size_t)1 << 40, 0, nullptr) == ISOPO_ERR_HIP);
+      EXPECT(launches == 0);
+      float* const f = static_cast<float*>(there);
+      EXPECT(isopo_layer_step(&l, ISOPO_GRAM_GHOST, f, ISOPO_VARIANT_FISHER, 0.f, ISOPO_REG_ABSOLUTE, 0.f, f, f, nullptr, f, there,
+                              (size_t)1 << 40, 0, nullptr, nullptr, 0, nullptr) == ISOPO_ERR_HIP);
+      EXPECT(launches == 0);
+    }
   std::printf("done failures=%d\n", failures);
   return failures ? 1 : 0;
 }
