@@ -211,7 +211,7 @@ size_t isopo_transform_workspace(int32_t n_seq, int32_t batch);
  *   info_dev  device int32 [batch] or NULL.  0: ok.  k > 0 (INTERACTING only):
  *             the k-th pivot of K + reg I was not positive; c of that problem
  *             is then filled with NaN.  FISHER: a zero denominator gives
- *             c_i = 0. */
+ *             c_i = 0.  Either: an infinite K_ii gives c_i = 0. */
 isopo_status isopo_transform(const float* K, const float* A, int32_t n_seq, int32_t batch,
                              isopo_variant variant, float lambda, isopo_reg_mode reg_mode,
                              float* c, int32_t* info_dev, void* workspace, size_t ws_bytes,

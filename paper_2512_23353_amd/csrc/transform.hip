@@ -334,11 +334,16 @@ __device__ __forceinline__ void four_rows(double x, double (&r)[4]) {
 }
 
 // 1 / sqrt(p), p a positive number: the instruction's estimate y, and one third-order step, y (1 + e / 2 + 3 e^2 / 8) with
-// e = 1 - p y^2.  NaN for zero and infinity.
+// e = 1 - p y^2.  NaN for zero and infinity (no pivot is infinite: kInfinite).
 __device__ __forceinline__ double inverse_root(double p) {
   const double y = __builtin_amdgcn_rsq(p), e = fma(-p * y, y, 1.0);
   return fma(y * e, fma(e, 0.375, 0.5), y);
 }
+
+// An infinite diagonal entry as the factorisation holds it (K's finite ones are below 2^128, reg below 2^257): the root of its pivot
+// divides that sequence's coefficient, and its part in the others', down to nothing.  (Infinity itself would be inf * 0 in
+// inverse_root; a comparison there cost 2 % of the solve.)
+constexpr double kInfinite = 0x1p1000;
 
 // Doubles of dynamic LDS: the blocks of a row of U, every block row's -L^-1, transposed, and v.
 __host__ __device__ constexpr int transform_blocks(int m) { return (m + kBlk - 1) / kBlk; }
@@ -415,7 +420,8 @@ __device__ __forceinline__ void transform_regs(const float* K, const float* A, i
     for (int v = 0; v < 4; ++v) {
       const int r = 4 * v + l4;
       const bool padded = kBlk * (wave + d * W) + r >= m;           // the identity's rows
-      D[d][v] = -((double)diag_in[d][v] + (r == l16 ? (padded ? 1.0 : reg) : 0.0));
+      const double x = (double)diag_in[d][v] + (r == l16 ? (padded ? 1.0 : reg) : 0.0);
+      D[d][v] = r == l16 && x > kInfinite ? -kInfinite : -x;
     }
 #pragma unroll
   for (int s = 0; s < S; ++s)
