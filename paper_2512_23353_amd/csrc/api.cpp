@@ -112,7 +112,7 @@ size_t stash_bytes(const isopo_layer* l, int rows) {
   return (size_t)l->n_seq * (size_t)rows * (size_t)l->d_in * elem_size(l->dtype);
 }
 
-// Gram partial sums, then one aligned block that no kernel uses any more: the sizes that callers were told stay.
+// Gram partial sums, then one aligned block whose first word counts the workgroups that have finished their part of K (layer step).
 size_t gram_partial_bytes(const isopo_layer* l) {
   return align_up(stash_gram_partial_bytes(l->n_seq, l->dtype == ISOPO_BF16));
 }
@@ -286,7 +286,8 @@ static isopo_status layer_gram(const isopo_layer* layer, isopo_gram_path path, f
   if (reinterpret_cast<char*>(partials) + pbytes > ws + ws_bytes) return ISOPO_ERR_WORKSPACE_TOO_SMALL;
 
   const int slots = stash_gram_slots(layer->n_seq, bf16, (long long)chunk_rows * layer->d_in);
-  const bool fuse = then && then->info && layer->n_seq <= kTransformFinishMax;
+  const bool fuse = then && layer->n_seq <= kTransformFinishMax;
+  int32_t* const arrived = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(partials) + gram_partial_bytes(layer));
   for (int r0 = 0; r0 < layer->d_out; r0 += (int)chunk_rows) {
     const int rows = (layer->d_out - r0) < (int)chunk_rows ? (layer->d_out - r0) : (int)chunk_rows;
     SeqGradArgs a;
@@ -300,12 +301,13 @@ static isopo_status layer_gram(const isopo_layer* layer, isopo_gram_path path, f
     g.p0 = whole ? (long long)r0 * layer->d_in : 0;
     g.p1 = g.p0 + (long long)rows * layer->d_in;
     g.n_seq = layer->n_seq; g.bf16 = bf16; g.first = (r0 == 0); g.slots = slots; g.partials = partials;
-    if (fuse) g.clear = then->info;
+    if (fuse) g.clear = arrived;
     if (launch_stash_gram(g, s) != hipSuccess) return ISOPO_ERR_HIP;
   }
   if (fuse) {
     *fused = true;
-    return launch_finish_transform(gram_finish_of(partials, bf16, slots, layer->n_seq, K), *then, s) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
+    return launch_finish_transform(gram_finish_of(partials, bf16, slots, layer->n_seq, K), arrived, *then, s) == hipSuccess
+               ? ISOPO_OK : ISOPO_ERR_HIP;
   }
   return launch_stash_gram_finish(partials, bf16, slots, layer->n_seq, K, s) == hipSuccess ? ISOPO_OK : ISOPO_ERR_HIP;
 }

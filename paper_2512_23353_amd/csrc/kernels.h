@@ -230,10 +230,10 @@ constexpr int kTransformLdsMax = 128;         // more sequences: the interacting
 constexpr int kTransformRegsMax = 256;        // ... and from here on uses it; up to here the matrix is in registers
 constexpr int kTransformWidePanelMax = 512;   // larger problems factor panels of 16 columns instead of 32 (the panel has to fit in LDS)
 hipError_t launch_transform(const TransformArgs& a, hipStream_t s);
-// launch_stash_gram_finish and launch_transform of its K (batch 1, info given and cleared by the Gram pass) as one launch, for up to
-// kTransformFinishMax sequences
+// launch_stash_gram_finish and launch_transform of its K (batch 1) as one launch, for up to kTransformFinishMax sequences.  `arrived`: a
+// word of the call's own workspace, cleared by the Gram pass
 constexpr int kTransformFinishMax = 128;
-hipError_t launch_finish_transform(const GramFinish& f, const TransformArgs& a, hipStream_t s);
+hipError_t launch_finish_transform(const GramFinish& f, int32_t* arrived, const TransformArgs& a, hipStream_t s);
 // the same after launch_ghost_gram's K64: K, then its transform
 hipError_t launch_ghost_finish_transform(const double* K64, float* K, const TransformArgs& a, hipStream_t s);
 

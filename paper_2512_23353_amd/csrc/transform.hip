@@ -599,19 +599,20 @@ __global__ __launch_bounds__(THREADS) void fisher_transform_kernel(const float* 
 }
 
 // The Gram matrix from its slots, and by the workgroup that finds itself the last one to have written its part of it the
-// coefficients: a launch and the wait between two fewer.  `info` counts the workgroups, from zero, until it says how the solve went.
+// coefficients: a launch and the wait between two fewer.  `arrived` counts the workgroups, from zero.
 // 16 sequences 8.9 us against 4.8 and 6.1 in two launches.  K's entries pass the L2s on their way out and back in, so that no
 // workgroup has to write its L2 back or to drop it: with such fences the two launches were the faster ones (whole calls of 94 us
 // 2 us slower).
 template <int W, int S>
-__global__ __launch_bounds__(kFinishThreads) void finish_transform_kernel(GramFinish f, const float* __restrict__ A, int variant,
-                                                                          Regulariser prm, float* __restrict__ c, int32_t* info) {
+__global__ __launch_bounds__(kFinishThreads) void finish_transform_kernel(GramFinish f, int32_t* arrived, const float* __restrict__ A,
+                                                                          int variant, Regulariser prm, float* __restrict__ c,
+                                                                          int32_t* info) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ int last;
   gram_finish<true>(f);
   if (threadIdx.x < kWave) {                             // the wave that has written: its part is there before it counts
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (threadIdx.x == 0) last = __hip_atomic_fetch_add(info, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    if (threadIdx.x == 0) last = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
   }
   __syncthreads();
   if (!last) return;
@@ -712,10 +713,10 @@ __global__ __launch_bounds__(kFinishThreads) void ghost_finish_transform_kernel(
 }
 
 template <int W, int S>
-hipError_t launch_finish(const GramFinish& f, const TransformArgs& a, const Regulariser& reg, hipStream_t s) {
+hipError_t launch_finish(const GramFinish& f, int32_t* arrived, const TransformArgs& a, const Regulariser& reg, hipStream_t s) {
   static_assert(transform_regs_lds(16 * W) + sizeof(double) * (1024 + ISOPO_MAX_SEQ_TRANSFORM) <= 60 * 1024, "LDS without a limit raised");
   hipLaunchKernelGGL((finish_transform_kernel<W, S>), dim3((unsigned)(f.slot_floats / 64)), dim3(kFinishThreads),
-                     transform_regs_lds(f.n_seq), s, f, a.A, a.variant, reg, a.c, a.info);
+                     transform_regs_lds(f.n_seq), s, f, arrived, a.A, a.variant, reg, a.c, a.info);
   return hipGetLastError();
 }
 
@@ -734,10 +735,10 @@ hipError_t launch_ghost_finish_transform(const double* K64, float* K, const Tran
   return a.n_seq <= 64 ? launch_ghost_finish<4, 3>(K64, K, a, reg, s) : launch_ghost_finish<8, 5>(K64, K, a, reg, s);
 }
 
-hipError_t launch_finish_transform(const GramFinish& f, const TransformArgs& a, hipStream_t s) {
+hipError_t launch_finish_transform(const GramFinish& f, int32_t* arrived, const TransformArgs& a, hipStream_t s) {
   const Regulariser reg{a.reg_mode, a.lambda, a.ema_state, a.ema_decay};
-  if (f.n_seq > kTransformFinishMax || !a.info || a.batch != 1) return hipErrorInvalidValue;
-  return f.n_seq <= 64 ? launch_finish<4, 3>(f, a, reg, s) : launch_finish<8, 5>(f, a, reg, s);
+  if (f.n_seq > kTransformFinishMax || !arrived || a.batch != 1) return hipErrorInvalidValue;
+  return f.n_seq <= 64 ? launch_finish<4, 3>(f, arrived, a, reg, s) : launch_finish<8, 5>(f, arrived, a, reg, s);
 }
 
 hipError_t launch_transform(const TransformArgs& a, hipStream_t s) {

@@ -81,3 +81,43 @@ def test_replayed(gpu_device):
         assert not torch.equal(other["c"], want["c"])
         for key in ("K", "c", "info", "dW"):
             assert torch.equal(got[key], want[key]), key
+
+
+def _step(layer, A, path, info, workspace, stream=None):
+    """isopo_layer_step as the header has it: the buffers are the caller's, info may be none or shared."""
+    full = isopo.gram_plan(layer, path)[1]
+    keep = isopo.KEEP_FAST if path == "materialised" and workspace.numel() >= full else 0
+    out = dict(K=torch.empty((layer.n_seq, layer.n_seq), device=layer.device), c=torch.full_like(A, float("nan")),
+               dW=torch.empty((layer.d_out, layer.d_in), device=layer.device))
+    paths = {"ghost": isopo.GRAM_GHOST, "materialised": isopo.GRAM_MATERIALISED}
+    status = isopo.load().isopo_layer_step(
+        layer.ref(), paths[path], A.data_ptr(), isopo.VARIANT_INTERACTING, 0.1, isopo.REG_REL_TRACE, 0.0, out["K"].data_ptr(),
+        out["c"].data_ptr(), None if info is None else info.data_ptr(), out["dW"].data_ptr(), workspace.data_ptr(), workspace.numel(),
+        keep, None, None, 0, (stream or torch.cuda.current_stream()).cuda_stream)
+    assert status == 0
+    return out
+
+
+@pytest.mark.parametrize("path", ["materialised", "ghost"])
+@pytest.mark.parametrize("m", [5, 90])
+def test_steps_in_flight(gpu_device, path, m):
+    """Two streams, a step on each, one word for the status of both: what a step counts with is in its own workspace.  And none."""
+    cases, want = [], []
+    for seed in (1, 2):
+        layer, A = to_device(wl.custom_layer(256 * seed, 512, [9 * seed] * m, dtype="bf16", seed=seed, sigma_delta=1e-2, rho=0.3), gpu_device)
+        workspace = isopo.alloc_workspace(isopo.gram_plan(layer, path)[1], gpu_device)
+        cases.append((layer, A, workspace, torch.cuda.Stream()))
+        want.append(_three_calls(layer, A, "interacting", 0.1, path))
+    info = torch.full((1,), 77, dtype=torch.int32, device=gpu_device)
+    torch.cuda.synchronize()
+    for word in (info, info, None):
+        got = []
+        for layer, A, workspace, stream in cases:
+            with torch.cuda.stream(stream):
+                got.append(_step(layer, A, path, word, workspace, stream))
+        torch.cuda.synchronize()
+        assert info.item() == 0
+        for g, w, (layer, A, _, _) in zip(got, want, cases):
+            if path == "materialised":                         # token products: 64-bit sums in any order
+                assert torch.equal(g["K"], w["K"]) and torch.equal(g["dW"], w["dW"])
+            assert torch.equal(g["c"], isopo.transform(g["K"], A, "interacting", 0.1, isopo.REG_REL_TRACE)[0])
