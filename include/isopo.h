@@ -282,7 +282,7 @@ isopo_status isopo_weighted_grad_stash(const isopo_layer* layer, const float* c,
 /* isopo_layer_gram, isopo_transform and isopo_weighted_grad_stash (keep_stash = 2: the stash stays in the workspace, in the layout
  * that *layout then names) or isopo_weighted_grad without a stash (keep_stash = 0) as one call, on one stream, with the same results
  * bit for bit and the same conditions on each argument.  Up to 128 sequences the coefficients are formed by the launch that finishes
- * K.  A transform's bad argument is reported before anything is enqueued. */
+ * K.  A bad argument of any of the three is reported before anything is enqueued. */
 isopo_status isopo_layer_step(const isopo_layer* layer, isopo_gram_path path, const float* A, isopo_variant variant, float lambda,
                               isopo_reg_mode reg_mode, float beta, float* K, float* c, int32_t* info_dev, float* dW,
                               void* workspace, size_t ws_bytes, int keep_stash, isopo_stash_layout* layout,

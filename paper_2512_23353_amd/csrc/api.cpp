@@ -415,6 +415,7 @@ isopo_status isopo_layer_step(const isopo_layer* layer, isopo_gram_path path, co
   isopo_status st = check_layer(layer, true);
   if (st != ISOPO_OK) return st;
   if (keep_stash != 0 && keep_stash != 2) return ISOPO_ERR_INVALID_ARG;
+  if (!dW || !aligned16(dW)) return ISOPO_ERR_INVALID_ARG;             // what the last of the three would say, before the first
   TransformArgs t;
   st = transform_args(K, A, layer->n_seq, 1, variant, lambda, reg_mode, c, info_dev, transform_workspace, transform_ws_bytes, t);
   if (st != ISOPO_OK) return st;

@@ -160,6 +160,24 @@ int main() {
     EXPECT(isopo_ntk_eigh_workspace(0, 1) == 0 && isopo_ntk_eigh_workspace(300, 2) > 0);
     for (int s = 0; s <= 6; ++s) EXPECT(isopo_status_string((isopo_status)s) != nullptr);
   }
+  // the layer step looks at every argument before it enqueues anything
+  {
+    const std::vector<int32_t> off = {0, 300, 700};
+    char* const there = reinterpret_cast<char*>((uintptr_t)1 << 20);               // never followed
+    float* const f = reinterpret_cast<float*>(there);
+    isopo_layer l{};
+    l.dtype = ISOPO_BF16; l.n_tokens = 700; l.d_in = 256; l.d_out = 256; l.n_seq = 2; l.seq_offsets_host = off.data();
+    l.seq_offsets_dev = reinterpret_cast<int32_t*>(there); l.X = there; l.Delta = there;
+    for (const isopo_gram_path path : {ISOPO_GRAM_GHOST, ISOPO_GRAM_MATERIALISED})
+      for (float* const dW : {static_cast<float*>(nullptr), f + 1})
+        for (const int keep : {0, 2}) {
+          if (path == ISOPO_GRAM_GHOST && keep) continue;
+          launches = 0;
+          EXPECT(isopo_layer_step(&l, path, f, ISOPO_VARIANT_FISHER, 0.f, ISOPO_REG_ABSOLUTE, 0.f, f, f, nullptr, dW, there,
+                                  (size_t)1 << 40, keep, nullptr, nullptr, 0, nullptr) == ISOPO_ERR_INVALID_ARG);
+          EXPECT(launches == 0);
+        }
+  }
   // Token products of more tokens than a launch has pairs of tiles for (65535 tiles of 64): refused before anything is launched, on
   // either type, also next to 2^31.  The addresses are only checked for alignment.
   for (const int64_t n : {(int64_t)65535 * 64 + 1, (int64_t)1 << 30, (int64_t)1200000000, ((int64_t)1 << 31) - 1})
