@@ -31,7 +31,8 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 size_t elem_size(isopo_dtype t) { return t == ISOPO_BF16 ? 2 : 4; }
 
 // An enum argument arrives through a C ABI and may hold any int.  Its bytes are read as an int before
-// anything touches it as the enum type (for which a value outside the enumerators' range is undefined).
+// anything touches it as the enum type (for which a value outside the enumerators' range is undefined): helpers that check one take
+// it by reference.
 template <class E>
 bool enum_in(const E& e, int lo, int hi) {
   static_assert(sizeof(E) == sizeof(int), "C enums of this header are ints");
@@ -221,7 +222,7 @@ isopo_status isopo_layer_gram_plan(const isopo_layer* layer, isopo_gram_path req
 }
 
 // isopo_layer_gram.  `then`: the transform of K, launched with the Gram matrix's last step where that can be (true in *fused).
-static isopo_status layer_gram(const isopo_layer* layer, isopo_gram_path path, float* K, void* workspace, size_t ws_bytes,
+static isopo_status layer_gram(const isopo_layer* layer, const isopo_gram_path& path, float* K, void* workspace, size_t ws_bytes,
                                int keep_stash, void* stream, const TransformArgs* then, bool* fused) {
   isopo_status st = check_layer(layer, true);
   if (st != ISOPO_OK) return st;
@@ -381,8 +382,8 @@ size_t isopo_transform_workspace(int32_t n_seq, int32_t batch) {
 }
 
 // The arguments of isopo_transform, checked.
-static isopo_status transform_args(const float* K, const float* A, int32_t n_seq, int32_t batch, isopo_variant variant, float lambda,
-                                   isopo_reg_mode reg_mode, float* c, int32_t* info_dev, void* workspace, size_t ws_bytes,
+static isopo_status transform_args(const float* K, const float* A, int32_t n_seq, int32_t batch, const isopo_variant& variant, float lambda,
+                                   const isopo_reg_mode& reg_mode, float* c, int32_t* info_dev, void* workspace, size_t ws_bytes,
                                    TransformArgs& t) {
   if (!K || !A || !c || n_seq <= 0 || batch <= 0) return ISOPO_ERR_INVALID_ARG;
   if (n_seq > ISOPO_MAX_SEQ) return ISOPO_ERR_UNSUPPORTED;

@@ -160,6 +160,28 @@ int main() {
     EXPECT(isopo_ntk_eigh_workspace(0, 1) == 0 && isopo_ntk_eigh_workspace(300, 2) > 0);
     for (int s = 0; s <= 6; ++s) EXPECT(isopo_status_string((isopo_status)s) != nullptr);
   }
+  // values that are none of an enum's, through every entry point that takes one: refused, never loaded as the enum
+  {
+    const std::vector<int32_t> off = {0, 3, 7};
+    char* const there = reinterpret_cast<char*>((uintptr_t)1 << 20);               // never followed
+    float* const f = reinterpret_cast<float*>(there);
+    isopo_layer l{};
+    l.dtype = ISOPO_BF16; l.n_tokens = 7; l.d_in = 64; l.d_out = 64; l.n_seq = 2; l.seq_offsets_host = off.data();
+    l.seq_offsets_dev = reinterpret_cast<int32_t*>(there); l.X = there; l.Delta = there;
+    const size_t much = (size_t)1 << 40;
+    auto step = [&](int path, int variant, int mode) {
+      return isopo_layer_step(&l, (isopo_gram_path)path, f, (isopo_variant)variant, 0.f, (isopo_reg_mode)mode, 0.f, f, f, nullptr, f,
+                              there, much, 0, nullptr, nullptr, 0, nullptr);
+    };
+    launches = 0;
+    for (const int v : {-1, 4, 1 << 30}) {
+      EXPECT(isopo_layer_gram(&l, (isopo_gram_path)v, f, there, much, 0, nullptr) == ISOPO_ERR_INVALID_ARG);
+      EXPECT(isopo_transform(f, f, 2, 1, (isopo_variant)v, 0.f, ISOPO_REG_ABSOLUTE, f, nullptr, nullptr, 0, nullptr) == ISOPO_ERR_INVALID_ARG);
+      EXPECT(isopo_transform(f, f, 2, 1, ISOPO_VARIANT_FISHER, 0.f, (isopo_reg_mode)v, f, nullptr, nullptr, 0, nullptr) == ISOPO_ERR_INVALID_ARG);
+      EXPECT(step(v, 0, 0) == ISOPO_ERR_INVALID_ARG && step(1, v, 0) == ISOPO_ERR_INVALID_ARG && step(1, 0, v) == ISOPO_ERR_INVALID_ARG);
+    }
+    EXPECT(launches == 0);
+  }
   // the layer step looks at every argument before it enqueues anything
   {
     const std::vector<int32_t> off = {0, 300, 700};
