@@ -199,6 +199,47 @@ int main() {
                                   (size_t)1 << 40, keep, nullptr, nullptr, 0, nullptr) == ISOPO_ERR_INVALID_ARG);
           EXPECT(launches == 0);
         }
+    auto step = [&](const isopo_layer* layer, int path, const float* A, int variant, float lambda, int reg_mode, float* K, float* c,
+                    void* workspace, size_t bytes, int keep, void* transform_workspace, size_t transform_bytes) {
+      launches = 0;
+      const isopo_status st = isopo_layer_step(layer, (isopo_gram_path)path, A, (isopo_variant)variant, lambda, (isopo_reg_mode)reg_mode,
+                                               0.f, K, c, nullptr, f, workspace, bytes, keep, nullptr, transform_workspace,
+                                               transform_bytes, nullptr);
+      EXPECT(launches == 0);
+      return st;
+    };
+    const size_t much = (size_t)1 << 40;
+    size_t full = 0, least = 0;
+    EXPECT(isopo_layer_gram_plan(&l, ISOPO_GRAM_MATERIALISED, nullptr, &full, &least) == ISOPO_OK);
+    EXPECT(step(nullptr, 2, f, 0, 0.f, 0, f, f, there, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    for (const int keep : {-1, 1, 3}) EXPECT(step(&l, 2, f, 0, 0.f, 0, f, f, there, much, keep, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    EXPECT(step(&l, 1, f, 0, 0.f, 0, f, f, there, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);     // token products keep no stash
+    for (const int path : {-1, 3}) EXPECT(step(&l, path, f, 0, 0.f, 0, f, f, there, much, 0, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    EXPECT(step(&l, 2, nullptr, 0, 0.f, 0, f, f, there, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    EXPECT(step(&l, 2, f, 0, 0.f, 0, nullptr, f, there, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    EXPECT(step(&l, 2, f, 0, 0.f, 0, f, nullptr, there, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    for (const int variant : {-1, 2}) EXPECT(step(&l, 2, f, variant, 0.f, 0, f, f, there, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    for (const float lambda : {-1.f, __builtin_nanf("")})
+      EXPECT(step(&l, 2, f, 1, lambda, 0, f, f, there, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    for (const int mode : {-1, 2}) EXPECT(step(&l, 2, f, 1, 0.f, mode, f, f, there, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    EXPECT(step(&l, 2, f, 1, 0.f, 0, f, f, nullptr, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    EXPECT(step(&l, 2, f, 1, 0.f, 0, f, f, there + 16, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    EXPECT(step(&l, 2, f, 1, 0.f, 0, f, f, there, full - 1, 2, nullptr, 0) == ISOPO_ERR_WORKSPACE_TOO_SMALL);
+    EXPECT(step(&l, 2, f, 1, 0.f, 0, f, f, there, least - 1, 0, nullptr, 0) == ISOPO_ERR_WORKSPACE_TOO_SMALL);
+    l.seq_offsets_dev = nullptr;
+    EXPECT(step(&l, 2, f, 1, 0.f, 0, f, f, there, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    l.seq_offsets_dev = reinterpret_cast<int32_t*>(there);
+    l.X = there + 8;
+    EXPECT(step(&l, 2, f, 1, 0.f, 0, f, f, there, much, 2, nullptr, 0) == ISOPO_ERR_INVALID_ARG);
+    // from 129 sequences on the interacting solve asks for a workspace
+    const std::vector<int32_t> many = offsets(std::vector<int32_t>(129, 3));
+    l.X = there; l.n_seq = 129; l.n_tokens = many.back(); l.seq_offsets_host = many.data();
+    const size_t need = isopo_transform_workspace(129, 1);
+    EXPECT(step(&l, 2, f, 1, 0.f, 0, f, f, there, much, 2, nullptr, need) == ISOPO_ERR_WORKSPACE_TOO_SMALL);
+    EXPECT(step(&l, 2, f, 1, 0.f, 0, f, f, there, much, 2, there, need - 1) == ISOPO_ERR_WORKSPACE_TOO_SMALL);
+    EXPECT(step(&l, 2, f, 1, 0.f, 0, f, f, there, much, 2, there + 8, need) == ISOPO_ERR_INVALID_ARG);
+    l.dtype = ISOPO_F32;                                                                // no stash of more than 128 fp32 sequences
+    EXPECT(step(&l, 2, f, 1, 0.f, 0, f, f, there, much, 2, there, need) == ISOPO_ERR_UNSUPPORTED);
   }
   // Token products of more tokens than a launch has pairs of tiles for (65535 tiles of 64): refused before anything is launched, on
   // either type, also next to 2^31.  The addresses are only checked for alignment.

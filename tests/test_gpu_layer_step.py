@@ -1,5 +1,6 @@
 """The layer step as one call, whose coefficients up to 128 sequences come from the launch that finishes K, against the three calls:
-the same bits on either side of the sizes where the launches change, for either Gram path, and when replayed from a graph."""
+the same bits on either side of the sizes where the launches change, for either Gram path (token products: K to one rounding, and the
+coefficients of that K), with a workspace of fewer rows, when replayed from a graph, and with two steps in flight."""
 import numpy as np
 import pytest
 import torch
@@ -81,6 +82,29 @@ def test_replayed(gpu_device):
         assert not torch.equal(other["c"], want["c"])
         for key in ("K", "c", "info", "dW"):
             assert torch.equal(got[key], want[key]), key
+
+
+@pytest.mark.parametrize("dtype,m,d_out", [("bf16", 5, 776), ("bf16", 90, 1032), ("bf16", 130, 520), ("f32", 7, 520), ("f32", 70, 776)])
+@pytest.mark.parametrize("variant", ["interacting", "fisher"])
+def test_workspace_of_fewer_rows(gpu_device, dtype, m, d_out, variant):
+    """A workspace below the full one, whatever it holds: K in several passes over rows, of which each clears the word that the
+    workgroups that finish K count in, and dW from X and Delta (few tokens: no atomics).  The three calls on the same workspace, bit for
+    bit."""
+    layer, A = to_device(wl.custom_layer(264, d_out, [i % 3 // 2 + (m < 20) for i in range(m)], dtype=dtype, seed=m, sigma_delta=1e-2, rho=0.3),
+                         gpu_device)
+    _, full, least = isopo.gram_plan(layer, "materialised")
+    workspace = isopo.alloc_workspace(least, gpu_device)
+    assert least < full
+    workspace.fill_(0xff)
+    K, _ = isopo.layer_gram(layer, "materialised", workspace=workspace)
+    c, info = isopo.transform(K, A, variant, 0.1, isopo.REG_REL_TRACE)
+    dW = isopo.weighted_grad(layer, c)
+    for _ in range(2):
+        workspace.fill_(0xff)
+        got = isopo.layer_step(layer, A, variant, 0.1, isopo.REG_REL_TRACE, "materialised", workspace=workspace)
+        assert got["path"] == "materialised" and got["stash_layout"] is None
+        for key, want in (("K", K), ("c", c), ("info", info), ("dW", dW)):
+            assert torch.equal(got[key], want), key
 
 
 def _step(layer, A, path, info, workspace, stream=None):

@@ -119,11 +119,23 @@ def test_arrangements(gpu_device, d_in, d_out, lens, budget, kind):
         assert torch.equal(isopo.weighted_grad(layer, c, S), isopo.weighted_grad(layer, c, tiled, layout=layout))
 
 
-@pytest.mark.parametrize("d_in,d_out,lens", [
-    (1800, 2568, [300, 33, 700] * 4), (2312, 1032, [90, 0, 400, 64] * 5), (2304, 768, [33, 500, 0] * 4),     # 8, 10 and 9 columns
-    (1792, 5632, [40, 200] * 2), (1792, 5888, [40, 200] * 2)])               # 154 tiles; 161: strips of eight
-def test_narrow_strips(gpu_device, d_in, d_out, lens):
-    """Tiles in strips of four columns, of which the last may be narrower, and on either side of where strips are of eight."""
+@pytest.mark.parametrize("d_in,d_out,lens,tile,rows,columns,kind", [
+    (1000, 1032, [90, 0, 400, 64] * 5, 128, 9, 8, "dealt"), (1032, 1288, [33, 500, 0] * 4, 128, 11, 9, "dealt"),
+    (1160, 1032, [90, 0, 400, 64] * 5, 128, 9, 10, "dealt"), (1288, 1288, [33, 500, 0] * 4, 128, 11, 11, "dealt"),
+    (1000, 264, [20] * 200, 128, 3, 8, "ranges"), (1160, 264, [20] * 200, 128, 3, 10, "ranges"),
+    (1160, 1288, [40, 7], 128, 11, 10, "single"), (1160, 1032, [2000, 3] * 3, 128, 9, 10, "alone"),
+    (1024, 512, [90, 0, 400, 64] * 5, 128, 4, 8, "alone"), (1280, 512, [2000, 3] * 3, 128, 4, 10, "single"),       # tile order
+    (2304, 768, [33, 500, 0] * 4, 256, 3, 9, "alone"), (2560, 1024, [33, 500, 0] * 8, 256, 4, 10, "dealt"),
+    (2048, 2048, [90, 0, 400, 64] * 9, 256, 8, 8, "dealt"), (1792, 5632, [40, 200] * 2, 256, 22, 7, "dealt"),
+    (2560, 2568, [90, 0, 400, 64] * 9, 256, 11, 10, "dealt"), (2600, 2568, [90, 0, 400, 64] * 9, 256, 11, 11, "dealt"),      # row by row
+    (1792, 5888, [40, 200] * 2, 256, 23, 7, "dealt"), (2312, 4104, [300, 33, 700] * 4, 256, 17, 10, "dealt"),    # 161 tiles and more
+    (1800, 2568, [300, 33, 700] * 4, 128, 21, 15, "dealt"), (2312, 1032, [90, 0, 400, 64] * 5, 128, 9, 19, "dealt")])
+def test_narrow_strips(gpu_device, d_in, d_out, lens, tile, rows, columns, kind):
+    """Tiles in strips of four columns (launches of up to 160 tiles), the last of one to four, on both tiles, in either layout and
+    every way of dealing the pairs out; and launches of more tiles, in strips of eight."""
+    plan, (walk, _) = bf16_plan(d_in, d_out, lens, True), walk_plan(d_in, d_out, lens)
+    assert (plan.tile, plan.tiles_m, plan.tiles_n) == (tile, rows, columns)
+    assert kind == ("alone" if any(walk.alone) else ("dealt", "ranges", "single")[walk.kind])
     layer = _layer(d_in, d_out, lens, gpu_device)
     layout, _ = isopo.stash_layout(layer)
     rows = isopo.seq_grads(layer, torch.full((len(lens), d_out, d_in), float("nan"), dtype=torch.bfloat16, device=gpu_device))
