@@ -1,5 +1,5 @@
-"""The Cholesky transform's trailing update at the edges of its 16 x 16 blocks (the row of the advantages opens a block row of its
-own, or shares the last one), against a 64-bit solve."""
+"""The Cholesky transform's trailing update at the edges of its 16 x 16 blocks, against a 64-bit solve: up to 256 sequences the
+advantages are a block column of their own, in memory above their row opens a block row or shares the last one."""
 import numpy as np
 import pytest
 import torch
@@ -9,7 +9,8 @@ from paper_2512_23353_amd import isopo
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m", [18, 31, 32, 33, 80, 81, 95, 96, 97, 129, 130, 143, 144, 145, 159, 160, 255, 256, 272, 273])
+@pytest.mark.parametrize("m", [18, 31, 32, 33, 80, 81, 95, 96, 97, 129, 130, 143, 144, 145, 159, 160, 255, 256, 257, 271, 272, 273,
+                               287, 288, 400, 401])
 def test_trailing_block_edges(gpu_device, m):
     rng = np.random.default_rng(m)
     J = rng.standard_normal((3, m, m + 8))

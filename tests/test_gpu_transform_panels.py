@@ -1,5 +1,6 @@
-"""The Cholesky transform at the edges of what one wave holds of a panel (48 or 32 rows below its diagonal block), of one
-pass of the workgroup's waves over the rows, and of the last, partial panel: against a 64-bit solve."""
+"""The Cholesky transform at the edges of what one wave holds of a panel (above 256 sequences: 32 rows below its diagonal block, above
+512 48), of one pass of the workgroup's waves over the rows, and of the last, partial panel, and around the same numbers of sequences
+where the matrix is in registers: against a 64-bit solve."""
 import numpy as np
 import pytest
 import torch

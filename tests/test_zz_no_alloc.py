@@ -1,10 +1,10 @@
 """isopo_transform_noalloc: the transform for callers that cannot allocate.
 
-Its scratch is an array the library holds on the GPU; every buffer the call
-touches besides it comes from the caller.  Checked against isopo_transform
-(same kernels, caller-provided workspace) on two calls in a row, the second
-on a smaller problem, so that what the first call left in the shared array
-is shown not to matter.  This file sorts last on purpose.
+Its scratch, which problems of more than 256 sequences use, is an array the
+library holds on the GPU; every buffer the call touches besides it comes from
+the caller.  Checked against isopo_transform (same kernels, caller-provided
+workspace) on calls in a row, each on a smaller problem, so that what the one
+before left in the shared array is shown not to matter.  This file sorts last on purpose.
 """
 import numpy as np
 import pytest
@@ -36,9 +36,9 @@ def _problem(rng, m, batch, dev, singular=None):
 def test_two_calls_in_a_row_match_the_workspace_entry_point(gpu_device):
     lib = isopo.load()
     rng = np.random.default_rng(777)
-    # both sizes are above 128 sequences, where the scratch is used; the second is smaller and has one problem
-    # that is not positive definite
-    for m, batch, singular in ((256, 3, None), (160, 2, 1)):
+    # the first two use the scratch, and the second is the smaller one and has a problem that is not positive definite; up to 256
+    # sequences the matrix is in registers
+    for m, batch, singular in ((400, 3, None), (272, 2, 1), (256, 3, None), (160, 2, 1)):
         K, A, Kd, Ad = _problem(rng, m, batch, gpu_device, singular)
         for variant, lam, mode in (("interacting", 1e-2, isopo.REG_REL_TRACE), ("interacting", 0.0, isopo.REG_ABSOLUTE),
                                    ("fisher", 1e-2, isopo.REG_REL_TRACE)):
@@ -75,11 +75,12 @@ def test_two_calls_in_a_row_match_the_workspace_entry_point(gpu_device):
     assert torch.equal(c, c_ws)
 
 
-def test_replays_from_a_hip_graph(gpu_device):
+@pytest.mark.parametrize("m", [200, 300])
+def test_replays_from_a_hip_graph(gpu_device, m):
     """The callers this entry point is for: captured once, replayed on the buffers' current contents, with
     eager calls of the workspace entry point in between (they do not touch the library's array)."""
     rng = np.random.default_rng(778)
-    m, batch = 200, 2
+    batch = 2
     K, A, Kd, Ad = _problem(rng, m, batch, gpu_device)
     c = torch.empty_like(Ad)
     info = torch.zeros(batch, dtype=torch.int32, device=gpu_device)
