@@ -203,7 +203,7 @@ size_t isopo_stash_gram_workspace(int32_t n_seq);
 isopo_status isopo_stash_gram(const void* stash, isopo_dtype dtype, int32_t n_seq, int64_t n_elem, float* K,
                               void* workspace, size_t ws_bytes, void* stream);
 
-/* Bytes of device workspace isopo_transform needs (0 for n_seq <= 128). */
+/* Bytes of device workspace isopo_transform asks for: 0 for n_seq <= 128.  (Up to 256 sequences it is asked for and not touched.) */
 size_t isopo_transform_workspace(int32_t n_seq, int32_t batch);
 
 /* Coefficients from K and A, for `batch` independent problems laid out
@@ -219,17 +219,17 @@ isopo_status isopo_transform(const float* K, const float* A, int32_t n_seq, int3
 
 /* isopo_transform for callers that cannot allocate or pass device scratch: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments without the workspace, same kernels,
- * same results bit for bit.  The fp64 work matrices that n_seq > 128 needs live in an array the library
+ * same results bit for bit.  The fp64 work matrices that n_seq > 256 needs live in an array the library
  * holds on each GPU it runs on (ISOPO_NOALLOC_SCRATCH_BYTES per GPU, until the process ends); the call
  * allocates and frees nothing.
  *   limit   isopo_transform_workspace(n_seq, batch) <= ISOPO_NOALLOC_SCRATCH_BYTES, e.g. a block's seven
  *           256-sequence problems, or one problem of 1024 sequences; beyond it ISOPO_ERR_SCRATCH_LIMIT,
- *           nothing enqueued
+ *           nothing enqueued (also up to 256 sequences, which do not touch the array)
  *   device  the array of the device that is current at the call is used: the stream must belong to it.  The
- *           first call on a device looks the array's address up (make it outside stream capture)
- *   races   all calls on one GPU share that GPU's array: calls that may overlap in time (two streams, two
- *           threads) race on it; order them, or use isopo_transform with workspaces of their own.  The
- *           array keeps the last call's contents; no call depends on them */
+ *           first call on a device with n_seq > 128 looks the array's address up (make it outside stream capture)
+ *   races   all calls on one GPU share that GPU's array: INTERACTING calls of more than 256 sequences that may
+ *           overlap in time (two streams, two threads) race on it; order them, or use isopo_transform with
+ *           workspaces of their own.  The array keeps the last such call's contents; no call depends on them */
 #define ISOPO_NOALLOC_SCRATCH_BYTES ((size_t)16 << 20)
 isopo_status isopo_transform_noalloc(const float* K, const float* A, int32_t n_seq, int32_t batch,
                                      isopo_variant variant, float lambda, isopo_reg_mode reg_mode,
@@ -280,9 +280,10 @@ isopo_status isopo_weighted_grad_stash(const isopo_layer* layer, const float* c,
                                        isopo_stash_layout layout, float beta, float* dW, void* stream);
 
 /* isopo_layer_gram, isopo_transform and isopo_weighted_grad_stash (keep_stash = 2: the stash stays in the workspace, in the layout
- * that *layout then names) or isopo_weighted_grad without a stash (keep_stash = 0) as one call, on one stream, with the same results
- * bit for bit and the same conditions on each argument.  Up to 128 sequences the coefficients are formed by the launch that finishes
- * K.  A bad argument of any of the three is reported before anything is enqueued. */
+ * that *layout then names) or isopo_weighted_grad without a stash (keep_stash = 0) as one call, on one stream, with the same
+ * conditions on each argument and the same results bit for bit, as far as the three calls repeat theirs: token products (GHOST) sum K
+ * in any order, so that K agrees to one rounding and c is the transform of the K returned, and dW without a stash may come from
+ * atomics (isopo_weighted_grad).  Up to 128 sequences the coefficients are formed by the launch that finishes K.  A bad argument of any of the three is reported before anything is enqueued. */
 isopo_status isopo_layer_step(const isopo_layer* layer, isopo_gram_path path, const float* A, isopo_variant variant, float lambda,
                               isopo_reg_mode reg_mode, float beta, float* K, float* c, int32_t* info_dev, float* dW,
                               void* workspace, size_t ws_bytes, int keep_stash, isopo_stash_layout* layout,

@@ -10,8 +10,8 @@
 #include "gram_finish.h"
 #include "kernels.h"
 
-// Scratch of isopo_transform_noalloc: the fp64 work matrices and right-hand sides that isopo_transform takes
-// from its workspace argument when n_seq > 128.  One copy per GPU, at its own address on each, resident
+// Scratch of isopo_transform_noalloc: the fp64 work matrices and right-hand sides that isopo_transform keeps
+// in its workspace argument when n_seq > 256.  One copy per GPU, at its own address on each, resident
 // until the process ends.  In host code this name is only a handle for hipGetSymbolAddress; the device
 // address it resolves to (static_scratch below) is what kernels and copies get.
 constexpr size_t kStaticScratchBytes = ISOPO_NOALLOC_SCRATCH_BYTES;
@@ -377,7 +377,7 @@ isopo_status isopo_stash_gram(const void* stash, isopo_dtype dtype, int32_t n_se
 }
 
 size_t isopo_transform_workspace(int32_t n_seq, int32_t batch) {
-  if (n_seq <= kTransformLdsMax || batch <= 0) return 0;
+  if (n_seq <= kTransformNoWorkspaceMax || batch <= 0) return 0;
   return (size_t)batch * ((size_t)n_seq * n_seq + n_seq) * sizeof(double);
 }
 

@@ -222,12 +222,12 @@ struct TransformArgs {
   float lambda;
   float* c;
   int32_t* info;
-  double* workspace;         // [batch][n_seq*n_seq + n_seq] when n_seq > kTransformLdsMax, else unused
+  double* workspace;         // [batch][n_seq*n_seq + n_seq] when n_seq > kTransformRegsMax, else not touched
   float* ema_state = nullptr;  // reg_mode 2: [batch][2] trailing mean of tr(K)/m, number of minibatches seen
   float ema_decay = 0.f;
 };
-constexpr int kTransformLdsMax = 128;         // more sequences: the interacting transform asks for a workspace
-constexpr int kTransformRegsMax = 256;        // ... and from here on uses it; up to here the matrix is in registers
+constexpr int kTransformNoWorkspaceMax = 128; // the entry points ask for a workspace from here on, as they did when these sizes used it
+constexpr int kTransformRegsMax = 256;        // up to here the matrix is in registers; larger ones use the workspace
 constexpr int kTransformWidePanelMax = 512;   // larger problems factor panels of 16 columns instead of 32 (the panel has to fit in LDS)
 hipError_t launch_transform(const TransformArgs& a, hipStream_t s);
 // launch_stash_gram_finish and launch_transform of its K (batch 1) as one launch, for up to kTransformFinishMax sequences.  `arrived`: a

@@ -10,7 +10,7 @@
 // token-position samples) and ||G_i||^2 = K_ii.  E[val^2] is the caller's
 // trailing mean, or this batch's mean when the caller passes none; the batch
 // means are returned so the caller can carry the trailing mean forward.
-// m values: one workgroup, fp64, fixed summation order; 64 sequences 4.1 -> 2.9 us with one pair of barriers and no pow.
+// m values: one workgroup, fp64, fixed summation order; 64 sequences 4.1 -> 2.9 us with one barrier and no pow.
 #include "common.h"
 #include "kernels.h"
 
@@ -20,7 +20,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr double kEps = 1e-8;
 
-// Sums over the workgroup, three at a time: one pair of barriers.
+// Sums over the workgroup, three at a time: one barrier (`red` is used once).
 __device__ void block_sums(double (&x)[3], double (*red)[3]) {
 #pragma unroll
   for (int q = 0; q < 3; ++q) x[q] = wave_sum(x[q]);

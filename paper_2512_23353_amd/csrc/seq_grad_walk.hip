@@ -579,8 +579,10 @@ hipError_t launch_walk(const Params& p, hipStream_t s) {
 // what they read from beyond their L2: with 32 tiles of an item at a time, eight columns by four rows are 12 operand panels; of the
 // fewer that an XCD takes of a sequence of up to 160 tiles, four columns make the more compact block.  Per-sequence launches, 8
 // against 4 columns, 256x256 tiles: 4x16 tiles, 32 sequences of 512 .. 4096 tokens 484 / 468 us; 11x7, 92 of 86 175 / 167; 8x8, 40 of
-// 87 69 / 66; 6x17, 12 of 481 86 / 83; 30 random ones 0.988x on average, the slowest 1.02x (2x17, 76 of 3568).  Sums and more tiles:
-// level or slower with 4 (35x6, 256 sequences: 2535 / 2580), few columns (up to 6): level or slower cut.
+// 87 69 / 66; 6x17, 12 of 481 86 / 83; 30 random ones 0.988x on average, the slowest 1.02x (2x17, 76 of 3568).  Per-sequence launches
+// of more tiles: level or slower with 4 (56x16, 32 sequences 0.997x; 35x6, 256 sequences 2535 / 2580), few columns (up to 6): level or
+// slower cut.  Sums are not part of the rule, their width is known to the compiler: of eleven uncut ones nine are level with 4,
+// two would gain (108x20 tiles, 1238 tokens 448 / 438; 16x56, 8000 tokens 785 / 755).
 int strip_width(const ContractionPlan& pl, bool per_sequence) {
   return per_sequence && pl.tiles_n >= 7 && (long long)pl.tiles_m * pl.tiles_n <= 160 ? 4 : kStrip;
 }

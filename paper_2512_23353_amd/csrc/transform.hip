@@ -70,8 +70,8 @@ __host__ __device__ constexpr int transform_front(int m) { return m + transform_
 // registers, and factors the NB columns by itself (the diagonal block again in every wave): the pivot and a column's entries
 // of the diagonal block's rows come from their lanes (v_readlane), so that a column is one reciprocal square root and a
 // chain of multiply-adds, without an LDS round trip or a barrier (one of each per column, and a 64-bit division and
-// square root in every thread, made a column 0.8 us).  1024 sequences: 8980 us before, 5080 now.  The kernel spills 10 scalar
-// registers, and at 1024 threads, whose cap is 128 vector registers, 8 and 16 vector ones.  The upper triangle of the diagonal
+// square root in every thread, made a column 0.8 us).  1024 sequences: 8980 us before, 5080 now.  The kernel spills 6 scalar
+// registers, and at 1024 threads, whose cap is 128 vector registers, 4 and 14 vector ones.  The upper triangle of the diagonal
 // block is carried along and never read.
 // The trailing matrix (rows up to and including the row of A) then takes the rank-NB update in
 // 16 x 16 blocks, a wave each, on the matrix cores, whose factors come from the panel in LDS: a lane reads two values for
@@ -112,8 +112,8 @@ __device__ bool cholesky_solve(const float* __restrict__ K, const float* __restr
     // lanes < NB: the diagonal block's rows, the others NB + base + lane - NB.  Rows and columns from nbk on are the
     // identity's, so that the columns are one straight run of code; what the row of A makes of them is never read.  A pivot
     // that is not positive leaves NaN or infinity in all that follows; the first one is found at the end.
-    constexpr int ROWSPerWave = kWave - NB, ROWSPerPass = ROWSPerWave * (kThreads / kWave);
-    for (int base = (tid / kWave) * ROWSPerWave; base == 0 || base < nrows - NB; base += ROWSPerPass) {
+    constexpr int kRowsPerWave = kWave - NB, kRowsPerPass = kRowsPerWave * (kThreads / kWave);
+    for (int base = (tid / kWave) * kRowsPerWave; base == 0 || base < nrows - NB; base += kRowsPerPass) {
       const int lr = lane < NB ? lane : base + lane;
       const bool has = lr < nrows;
       double row[NB], pivot = 1.0, inv = 0.0;
@@ -274,7 +274,8 @@ __device__ bool cholesky_solve(const float* __restrict__ K, const float* __restr
 // through memory once per panel: us before and now, 16 sequences 7.3 and 5.0; 32, 12.5 and 7.3; 64, 24.4 and 12.7; 128, 56.9 and
 // 27.9; 192, 113 and 58; 256, 187 and 89.  Tried: a row per lane for all sixteen columns, without the MFMA between (64: 15.3; 256:
 // 123); the four pivots from their 4 x 4 block alone, in every lane (64: 13.1); eight waves at 256 (95).  Sixteen waves have 128
-// registers each, of which the blocks take 80: ten a lane go to scratch.
+// registers each, of which the blocks take 80: ten words a lane go to scratch, and 85 scalar registers into lanes of vector ones (25 with
+// eight waves, 32 where K is finished first, none with four).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kBlk = 16, kBlkPitch = kBlk + 1;
 
@@ -689,7 +690,8 @@ hipError_t launch_regs(const TransformArgs& a, const Regulariser& reg, hipStream
 }
 
 // K from the token products' 64-bit sums, and the coefficients, in one workgroup: a launch less.  With the chain's preparation in the
-// launch of the products (ghost_gram.hip) 5120x27648, 8 sequences of 64 to 256 tokens 514 -> 504 us a layer step.
+// launch of the products (ghost_gram.hip) Gram matrix and transform of ten random layers 0.89x (1024x3072, 7 sequences, 504 tokens 35.7
+// -> 29.9 us); 5120x27648, 8 sequences of 64 to 256 tokens 517 -> 511 us a layer step.
 template <int W, int S>
 __global__ __launch_bounds__(kFinishThreads) void ghost_finish_transform_kernel(const double* __restrict__ K64, float* K, int m,
                                                                                 const float* __restrict__ A, int variant,
