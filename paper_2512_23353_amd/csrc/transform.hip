@@ -557,13 +557,28 @@ __device__ __forceinline__ void fisher_transform(const float* K, const float* A,
   // a wave takes ROWS rows at a time
   for (int i = tid / kWave * ROWS; i < m; i += kWaves * ROWS) {
     double s[ROWS] = {};
-#pragma unroll 2
-    for (int j = tid % kWave; j < m; j += kWave)
+    if constexpr (ROWS == 1) {
+      // 128 columns on their way together (below, the lanes whose trips are fewer wait for their last one by themselves: 96 sequences 6.7
+      // us, and 6.3 so; four rows at a time, 256 sequences 16.3, and 17.2 so)
+      for (int j0 = 0; j0 < m; j0 += 2 * kWave) {
+        float k[2] = {0.f, 0.f};
 #pragma unroll
-      for (int r = 0; r < ROWS; ++r) {
-        const double k = (double)get_shared<SHARED>(K + (size_t)(i + r < m ? i + r : m - 1) * m + j);
-        s[r] += k * k;
+        for (int u = 0; u < 2; ++u) {
+          const int j = j0 + u * kWave + tid % kWave;
+          if (j < m) k[u] = get_shared<SHARED>(K + (size_t)i * m + j);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) s[0] += (double)k[u] * (double)k[u];
       }
+    } else {
+#pragma unroll 2
+      for (int j = tid % kWave; j < m; j += kWave)
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+          const double k = (double)get_shared<SHARED>(K + (size_t)(i + r < m ? i + r : m - 1) * m + j);
+          s[r] += k * k;
+        }
+    }
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
       s[r] = wave_sum(s[r]);
@@ -748,12 +763,15 @@ hipError_t launch_transform(const TransformArgs& a, hipStream_t s) {
   if (a.variant == 0) {
     // What it waits for is memory, so as many rows are on their way as there are, but a wave more or a second sum costs too.  us with
     // 256 threads and a row per wave, 1024 and one, 1024 and four: 4 sequences 2.8, 3.1, 3.4; 16 3.9, 3.5, 3.7; 64 -, 5.3, 5.4;
-    // 128 -, 8.0, 8.0; 224 -, 15.5, 12.1; 1024 -, 92, 71 (220 with one load in flight).
+    // 128 -, 8.0, 8.0; 224 -, 15.5, 12.1; 1024 -, 92, 71 (220 with one load in flight).  More problems than compute units (256) wait for
+    // each other's waves, of which the smaller ones then take fewer: 16 sequences, 1000 problems 8.5 with 1024 threads, 6.2 with 512, 5.7
+    // with 256; 33, 400 6.6, 5.8, 7.0; 64, 1000 15.2, 13.4, 13.2; 97, 400 11.6, 10.9, -.
     auto launch = [&](auto kern, int threads) {
       hipLaunchKernelGGL(kern, dim3(a.batch), dim3(threads), 0, s, a.K, a.A, a.n_seq, reg, a.c, a.info);
       return hipGetLastError();
     };
-    if (a.n_seq <= 8) return launch(fisher_transform_kernel<256, 1>, 256);
+    if (a.n_seq <= 8 || (a.n_seq <= 48 && a.batch > 512)) return launch(fisher_transform_kernel<256, 1>, 256);
+    if (a.n_seq <= 104 && a.batch > 256) return launch(fisher_transform_kernel<512, 1>, 512);
     return a.n_seq <= 96 ? launch(fisher_transform_kernel<1024, 1>, 1024) : launch(fisher_transform_kernel<1024, 4>, 1024);
   }
   if (a.n_seq <= 64) return launch_regs<4, 3, 1>(a, reg, s);

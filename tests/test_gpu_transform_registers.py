@@ -40,3 +40,17 @@ def test_fisher_rows(gpu_device, m):
     want = A / np.sqrt(f2 + 0.5 * f2.mean(axis=1, keepdims=True))
     # 64-bit sums of positive terms, one rounding to fp32
     assert (np.abs(c.cpu().numpy() - want) <= 2.0 ** -23 * np.abs(want)).all()
+
+
+@pytest.mark.parametrize("m", [8, 9, 48, 49, 64, 65, 104, 105])
+@pytest.mark.parametrize("batch", [257, 513])
+def test_fisher_batches(gpu_device, m, batch):
+    """More problems than compute units: fewer waves for each of the smaller ones."""
+    rng = np.random.default_rng(m)
+    K = rng.standard_normal((batch, m, m)).astype(np.float32)
+    A = rng.standard_normal((batch, m)).astype(np.float32)
+    c, info = isopo.transform(torch.from_numpy(K).to(gpu_device), torch.from_numpy(A).to(gpu_device), "fisher", 0.5, isopo.REG_REL_TRACE)
+    f2 = (K.astype(np.float64) ** 2).mean(axis=2)
+    want = A / np.sqrt(f2 + 0.5 * f2.mean(axis=1, keepdims=True))
+    # as above
+    assert (np.abs(c.cpu().numpy() - want) <= 2.0 ** -23 * np.abs(want)).all() and not info.any()
